@@ -159,9 +159,9 @@ int moe_dispatch_slots(const void* x, int dtype, int64_t S, int M, int E, int k,
  *                        rows c >= min(row_counts[s,g], C) of X (and of dY in backward) are zero,
  *                        i.e. capacity padding (counts from moe_gate_topk qualify when all experts
  *                        are local).  Results are the same as without it -- FFN(0) = 0 and zero rows
- *                        add nothing to the weight gradients -- but row tiles that hold nothing
- *                        else are not multiplied (their outputs are stored as zeros), and with
- *                        n_src = 1 the weight-gradient reductions stop at the count.
+ *                        add nothing to the weight gradients -- but padding rows are not multiplied
+ *                        beyond the last row tile of an expert (their outputs are stored as zeros),
+ *                        and the weight-gradient reductions stop at each chunk's count.
  *
  * Backward (chain rule of the above), given dY [n_src,G,C,M] and the saved Z and A:
  *   dX  [n_src, G, C, M]  out
@@ -175,18 +175,18 @@ size_t moe_ffn_workspace_bytes(int dtype, int n_src, int G, int64_t C, int M, in
 /* Tile hint of the bf16 grouped GEMMs, an argument of every expert-FFN call.  It selects among
  * kernels that compute the same products and may change the fp32 summation order, nothing else:
  *   MOE_TILE_AUTO   per GEMM from its tile count (what a caller should pass)
- *   MOE_TILE_SMALL  128 x 128 output tiles, register-staged kernel (what AUTO picks for tiny GEMMs;
- *                   this kernel ignores row_counts)
- *   MOE_TILE_256    256 x 256 tiles, LDS-DMA kernel
- *   MOE_TILE_192    the same kernel with 192-row tiles wherever the operand layout allows (the
- *                   row-tiled GEMMs; AUTO picks it when it fills the chip's compute units better)
+ *   MOE_TILE_SMALL  128 x 128 output tiles, row_counts ignored
+ *   MOE_TILE_256    256 x 256 tiles
+ *   MOE_TILE_192    192-row tiles in the row-tiled GEMMs, 256 x 256 in the weight gradients
+ * AUTO chooses among these and smaller tiles (down to 32 x 64 for a few rows per expert).
  * Other values: MOE_EINVAL.  Ignored for fp32. */
 enum { MOE_TILE_AUTO = 0, MOE_TILE_SMALL = 1, MOE_TILE_256 = 2, MOE_TILE_192 = 3 };
 
 /* Floating-point operations the forward (backward = 0: 2 GEMMs) or backward (backward = 1: 4 GEMMs)
  * call multiplies out for this shape and tile hint: 2 * M * H_l per multiplied row
- * and GEMM, where a row counts if it lies in a row tile that is not skipped (row-tiled GEMMs) or
- * below the count (weight-gradient reductions, n_src = 1).  row_counts_host is a HOST copy of the
+ * and GEMM, where a row counts if it lies in a row tile that is not skipped (row-tiled GEMMs, tiles taken
+ * chunk by chunk) or below the count (weight-gradient reductions, n_src = 1; with several chunks every
+ * row counts).  With several chunks the calls multiply fewer rows than this: an upper bound there.  row_counts_host is a HOST copy of the
  * row_counts passed to the calls, or NULL (every row is multiplied).  Pure host arithmetic, used by
  * the benchmark to price the matrix pipes by executed work.  0 for invalid shapes. */
 double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C, int M, int H, int n_esp,

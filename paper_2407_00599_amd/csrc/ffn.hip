@@ -15,20 +15,19 @@
 // g at physical row ((r / C) * G + g) * C + r % C, so no permutation pass is needed and only
 // the last row tile of an expert is ragged.
 //
-// bf16 path: MFMA v_mfma_f32_32x32x16_bf16, fp32 accumulation, two kernels.
-//   ffn_gemm_dma  (every problem with at least 64 tiles of 256 x 256): global memory goes straight to
-//       LDS (buffer_load ... lds), a ring of five 32 KiB stages of k tile 32, 8 waves; operands whose
-//       memory layout has k as the slow index stay in that layout in LDS and are read with the
-//       transposing LDS load, so no transpose pass exists.  Described in front of gemm_dma_tile.
-//   ffn_gemm_bf16 (small problems, 128 x 128 tiles): global -> registers -> LDS tiles [row][k] with
-//       k contiguous (row pitch 64 + 8 bf16: conflict-free 16-byte fragment reads); operands with k as
-//       the slow index are transposed in registers (8x8 blocks, v_perm) on their way to LDS; the loads
-//       of k tile kt+1 are issued before the MFMAs of tile kt (LDS double buffer, one barrier per tile).
-// Both issue the MFMA with the operands swapped (D^T = B^T A^T) so that a lane ends up with 4
-// consecutive output columns.  Workgroup ids are remapped so that each XCD (ids are dealt round-robin
-// to the 8 XCDs) works on one contiguous range of tiles and its L2 sees the same operand panels.
+// bf16 path: one kernel, MFMA v_mfma_f32_32x32x16_bf16 with fp32 accumulation, over a family of tiles from 256 x 256
+// down to 32 x 64 (described in front of gemm_dma_tile; plan_tiles chooses).  Global memory goes straight to LDS
+// (buffer_load ... lds) in k tiles of 64; operands whose memory layout has k as the slow index stay in that layout in
+// LDS and are read with the transposing LDS load, so no transpose pass exists.  The MFMA is issued with the operands
+// swapped (D^T = B^T A^T) so that a lane ends up with 4 consecutive output columns.
+//
+// Row counts (capacity padding): the row-tiled GEMMs take an expert's rows in compacted order, the occupied rows of
+// all its chunks first, so that only ceil(occupied / tile) row tiles are multiplied however the occupancy is spread
+// over the chunks; the weight gradients skip the k tiles of a chunk that lie behind its count.
 //
 // fp32 path: a plain LDS-tiled kernel with fp64 accumulation, for the small fp32 configuration.
+#include <math.h>
+
 #include <type_traits>
 
 #include "common.h"
@@ -61,7 +60,6 @@ struct GemmArgs {
   int64_t b_goff, c_goff;            // per-expert stride of weight-type operands, elements
   int64_t b_off, c_off;              // constant offset of the ESP slice, elements
   int tiles_m, tiles_n, total_tiles;
-  int kchunks;                       // TN: k tiles per chunk = ceil(Cc / 64)
   uint64_t a_bytes, b_bytes;         // bf16 path: byte sizes of the A and B tensors (buffer descriptors)
 };
 
@@ -86,56 +84,6 @@ __device__ __forceinline__ int64_t a_src_row(const GemmArgs& p, int r, int g) {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int KT = 64;          // k tile
-constexpr int PITCH = KT + 8;   // LDS row pitch in bf16 elements (144 bytes)
-
-// 8x8 transpose of 16-bit elements: in[i] holds 8 consecutive n for k = i; out[n] holds 8
-// consecutive k for that n.
-__device__ __forceinline__ void transpose8x8(const uint4* in, uint4* out) {
-  const uint32_t* I = reinterpret_cast<const uint32_t*>(in);
-  uint32_t* O = reinterpret_cast<uint32_t*>(out);
-#pragma unroll
-  for (int n = 0; n < 8; ++n) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      const uint32_t a = I[(2 * d) * 4 + n / 2];      // k = 2d
-      const uint32_t b = I[(2 * d + 1) * 4 + n / 2];  // k = 2d+1
-      O[n * 4 + d] = (n & 1) ? __builtin_amdgcn_perm(b, a, 0x07060302u) : __builtin_amdgcn_perm(b, a, 0x05040100u);
-    }
-  }
-}
-
-// 4(k) x 8(n) -> 8 rows of 4 consecutive k (8 bytes each)
-__device__ __forceinline__ void transpose4x8(const uint4* in, uint2* out) {
-  const uint32_t* I = reinterpret_cast<const uint32_t*>(in);
-#pragma unroll
-  for (int n = 0; n < 8; ++n) {
-    const uint32_t a0 = I[0 * 4 + n / 2], b0 = I[1 * 4 + n / 2];
-    const uint32_t a1 = I[2 * 4 + n / 2], b1 = I[3 * 4 + n / 2];
-    if (n & 1) {
-      out[n].x = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
-      out[n].y = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
-    } else {
-      out[n].x = __builtin_amdgcn_perm(b0, a0, 0x05040100u);
-      out[n].y = __builtin_amdgcn_perm(b1, a1, 0x05040100u);
-    }
-  }
-}
-
-// Staging of one operand tile [ROWS x KT] (rows = output-dim index, k contiguous in LDS).
-// DIRECT: memory has k contiguous.  Thread handles chunks c = tid + i*NT, row = c/8, kc = c%8.
-// TRANSPOSED: memory has the row index contiguous and k as the slow index.  Thread handles
-// 8(k) x 8(row) blocks (or 4 x 8 half blocks when there are fewer blocks than threads).
-template <int ROWS, int NT>
-struct Stage {
-  static constexpr int NCH = ROWS * 8 / NT;            // direct: 16-byte chunks per thread
-  static constexpr int NBLK = ROWS;                    // transposed: number of 8x8 blocks (ROWS/8 * 8)
-  static constexpr bool HALF = NBLK < NT;              // 4x8 half blocks
-  static constexpr int NB = HALF ? 1 : NBLK / NT;      // blocks per thread
-  static_assert(NCH >= 1 && (HALF ? NBLK * 2 == NT : NBLK % NT == 0), "tile/thread mismatch");
-  uint4 reg[NCH];                                      // NCH == 8*NB (full) or 4 (half)
-};
-
 // Guarded 16-byte loads go through buffer descriptors: a lane that must not load passes an
 // offset beyond num_records and receives zeros, without a branch, so the whole k loop body is
 // one basic block whose loads, LDS traffic and MFMAs can be interleaved.
@@ -143,9 +91,6 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 constexpr uint32_t OOB = 0xFFFFFFF0u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-}
-__device__ __forceinline__ void pin(uint4& v) {
-  asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
 }
 template <bool STREAM = false>   // STREAM: non-temporal hint, for data read here for the last time
 __device__ __forceinline__ uint4 ldb16(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
@@ -185,371 +130,7 @@ __device__ __forceinline__ float gelu_grad_poly(float z) {
   return fmaf(zc, q, 0.5f);
 }
 
-// Epilogue shared by the bf16 kernels.  A lane holds, for each 32x32 block (i, j) of its wave
-// tile, output row m = mbase + 32 i + lane%32 and columns n = nbase + 32 j + 8 (q/4) + 4 (lane/32)
-// + q%4 for q = 0..15, i.e. four runs of 4 consecutive columns: 8-byte stores.
-template <int MB, int NBK, int KIND, int EPI>
-__device__ __forceinline__ void store_tile(const GemmArgs& p, f32x16_t (&acc)[MB][NBK], int g, int mbase, int nbase,
-                                           int lane) {
-  bf16_t* __restrict__ Cb = reinterpret_cast<bf16_t*>(p.C);
-  bf16_t* __restrict__ C2b = reinterpret_cast<bf16_t*>(p.C2);
-  const bf16_t* __restrict__ Zb = reinterpret_cast<const bf16_t*>(p.Zin);
-#pragma unroll
-  for (int i = 0; i < MB; ++i) {
-    const int m = mbase + i * 32 + (lane & 31);
-    if (m >= p.Mdim) continue;
-    int64_t crow;
-    if (KIND == KIND_TN) crow = (int64_t)g * p.c_goff + p.c_off + (int64_t)m * p.ldc;
-    else crow = phys_row(m, g, p.G, p.Cc) * p.ldc;
-#pragma unroll
-    for (int j = 0; j < NBK; ++j) {
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int n = nbase + j * 32 + q4 * 8 + (lane >> 5) * 4;
-        if (n >= p.Ndim) continue;
-        float v[4] = {acc[i][j][q4 * 4 + 0], acc[i][j][q4 * 4 + 1], acc[i][j][q4 * 4 + 2], acc[i][j][q4 * 4 + 3]};
-        if (EPI == EPI_STORE) {
-          *reinterpret_cast<uint2*>(Cb + crow + n) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-        } else if (EPI == EPI_GELU) {
-          *reinterpret_cast<uint2*>(Cb + crow + n) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-          float a[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) a[e] = gelu_poly(v[e]);
-          *reinterpret_cast<uint2*>(C2b + crow + n) = make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
-        } else {
-          const uint2 zq = *reinterpret_cast<const uint2*>(Zb + crow + n);
-          const float z[4] = {__uint_as_float(zq.x << 16), __uint_as_float(zq.x & 0xFFFF0000u),
-                              __uint_as_float(zq.y << 16), __uint_as_float(zq.y & 0xFFFF0000u)};
-          float d[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) d[e] = v[e] * gelu_grad_poly(z[e]);
-          *reinterpret_cast<uint2*>(Cb + crow + n) = make_uint2(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]));
-        }
-      }
-    }
-  }
-}
-
-// Workgroup -> output tile.  Workgroup ids are dealt round-robin to the 8 XCDs, so id % 8 names
-// the XCD; each XCD is given one contiguous range of a linear tile order in which 32 consecutive
-// tiles (what its 32 CUs run at the same time) form an 8 (rows) x 4 (columns) patch of one expert:
-// per k step they share 8 + 4 operand slices in that XCD's L2 instead of 1 + 32.
-// (vb = index of the workgroup within its problem; problems of a merged launch start at multiples of 8,
-// so vb % 8 is still the XCD)
-__device__ __forceinline__ bool map_tile(const GemmArgs& p, int vb, int& g, int& tm, int& tn) {
-  constexpr int SW = 4;
-  const int per_xcd = (p.total_tiles + 7) / 8;
-  const int tile = (vb & 7) * per_xcd + (vb >> 3);
-  if (tile >= p.total_tiles) return false;
-  const int tiles_per_g = p.tiles_m * p.tiles_n;
-  g = tile / tiles_per_g;
-  const int t = tile - g * tiles_per_g;
-  const int full = p.tiles_n / SW;
-  const int strip = p.tiles_m * SW;
-  if (t < full * strip) {
-    const int sn = t / strip, r = t - sn * strip;
-    tm = r / SW;
-    tn = sn * SW + (r - tm * SW);
-  } else {
-    const int w = p.tiles_n - full * SW;
-    const int r = t - full * strip;
-    tm = r / w;
-    tn = full * SW + (r - tm * w);
-  }
-  return true;
-}
-
-// Instruction-order hints for the scheduler (sched_group_barrier): "N instructions of this
-// class next".  Recipe interleaves NM MFMAs with NA instructions of class MA and NB of class MB.
-enum { SG_MFMA = 0x008, SG_VMEM_READ = 0x020, SG_DS_READ = 0x100, SG_DS_WRITE = 0x200 };
-template <int MASK, int N>
-__device__ __forceinline__ void sched_group() {
-  if constexpr (N > 0) __builtin_amdgcn_sched_group_barrier(MASK, N, 0);
-}
-template <int I, int NM, int NA, int MA, int NB, int MB_>
-struct Recipe {
-  static __device__ __forceinline__ void run() {
-    if constexpr (I < NM) {
-      sched_group<MA, (I + 1) * NA / NM - I * NA / NM>();
-      sched_group<MB_, (I + 1) * NB / NM - I * NB / NM>();
-      sched_group<SG_MFMA, 1>();
-      Recipe<I + 1, NM, NA, MA, NB, MB_>::run();
-    }
-  }
-};
-
-template <int TM, int TN, int WM, int WN, int KIND, int EPI>
-__global__ __launch_bounds__(WM * WN * 64) void ffn_gemm_bf16(const GemmArgs p) {
-  constexpr int NT = WM * WN * 64;
-  constexpr int TMW = TM / WM, TNW = TN / WN;  // per-wave tile
-  constexpr int MB = TMW / 32, NBK = TNW / 32;
-  constexpr bool A_TR = (KIND == KIND_TN);
-  constexpr bool B_TR = (KIND == KIND_NN || KIND == KIND_TN);
-  using SA = Stage<TM, NT>;
-  using SB = Stage<TN, NT>;
-
-  __shared__ __attribute__((aligned(16))) bf16_t smem[2 * (TM + TN) * PITCH];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-
-  int g, tm, tn;
-  if (!map_tile(p, (int)blockIdx.x, g, tm, tn)) return;
-  const int m0 = tm * TM, n0 = tn * TN;
-
-  const int64_t b_base = (int64_t)g * p.b_goff + p.b_off;   // weight-type B: start of expert g's slice
-  // descriptors: activation tensors whole (host guarantees < 4 GiB); weights from expert g's slice on
-  const __amdgpu_buffer_rsrc_t rA = make_rsrc(p.A, (uint32_t)p.a_bytes);
-  const uint64_t b_rem = p.b_bytes - (uint64_t)b_base * 2;
-  const __amdgpu_buffer_rsrc_t rB =
-      (KIND == KIND_TN) ? make_rsrc(p.B, (uint32_t)p.b_bytes)
-                        : make_rsrc(reinterpret_cast<const bf16_t*>(p.B) + b_base,
-                                    b_rem > OOB ? OOB : (uint32_t)b_rem);
-
-  // ---- per-thread staging coordinates (fixed over the k loop), byte offsets ----
-  // direct:      chunk i -> row = tid/8 + i*(NT/8), k chunk = tid%8
-  // transposed:  full 8x8 blocks: bi = tid + b*NT, kb = bi%8, r8 = bi/8;  half blocks: kb4 = tid%16, r8 = tid/16
-  uint32_t a_off[A_TR ? 1 : SA::NCH];
-  if (!A_TR) {
-#pragma unroll
-    for (int i = 0; i < SA::NCH; ++i) {
-      const int r = m0 + (tid >> 3) + i * (NT / 8);
-      const int64_t row = (r < p.Mdim) ? a_src_row(p, r, g) : -1;
-      a_off[i] = (row >= 0) ? (uint32_t)((row * p.lda + (tid & 7) * 8) * 2) : OOB;
-    }
-  }
-  uint32_t b_off[B_TR ? 1 : SB::NCH];
-  if (!B_TR) {
-#pragma unroll
-    for (int i = 0; i < SB::NCH; ++i) {
-      const int n = n0 + (tid >> 3) + i * (NT / 8);
-      b_off[i] = (n < p.Ndim) ? (uint32_t)(((int64_t)n * p.ldb + (tid & 7) * 8) * 2) : OOB;
-    }
-  }
-  const int nk = (KIND == KIND_TN) ? p.n_src * p.kchunks : (p.Kdim + KT - 1) / KT;
-  const uint32_t lda2 = (uint32_t)(p.lda * 2), ldb2 = (uint32_t)(p.ldb * 2);
-
-  SA sa;
-  SB sb;
-
-  // global -> registers for k tile kt; kt >= nk loads nothing (all lanes out of range)
-  auto load_tiles = [&](int kt) {
-    const bool live = kt < nk;
-    // ---------------- A ----------------
-    if (!A_TR) {
-      const int k0 = kt * KT;
-      const bool kok = live && k0 + (tid & 7) * 8 < p.Kdim;
-#pragma unroll
-      for (int i = 0; i < SA::NCH; ++i)
-        sa.reg[i] = ldb16(rA, (kok && a_off[i] != OOB) ? a_off[i] + (uint32_t)k0 * 2u : OOB);
-    } else {
-      const int s = kt / p.kchunks;
-      const int c0 = (kt - s * p.kchunks) * KT;
-      const int64_t chunk_row = ((int64_t)s * p.G + g) * p.Cc + c0;
-      const int klim = live ? p.Cc - c0 : 0;
-      if (!SA::HALF) {
-#pragma unroll
-        for (int b = 0; b < SA::NB; ++b) {
-          const int bi = tid + b * NT;
-          const int kb = bi & 7, r8 = bi >> 3;
-          const int col = m0 + r8 * 8;
-          const uint32_t off0 = (uint32_t)(((chunk_row + kb * 8) * p.lda + col) * 2);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            uint32_t o = off0 + i * lda2;
-            bool ok = kb * 8 + i < klim && col < p.Mdim;
-            if (p.gather != nullptr && ok) {   // fused dispatch: the row is a token looked up through the slot map
-              const int64_t row = a_src_row(p, c0 + kb * 8 + i, g);
-              ok = row >= 0;
-              o = (uint32_t)((row * p.lda + col) * 2);
-            }
-            sa.reg[b * 8 + i] = ldb16(rA, ok ? o : OOB);
-          }
-        }
-      } else {
-        const int kb4 = tid & 15, r8 = tid >> 4;
-        const int col = m0 + r8 * 8;
-        const uint32_t off0 = (uint32_t)(((chunk_row + kb4 * 4) * p.lda + col) * 2);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          uint32_t o = off0 + i * lda2;
-          bool ok = kb4 * 4 + i < klim && col < p.Mdim;
-          if (p.gather != nullptr && ok) {
-            const int64_t row = a_src_row(p, c0 + kb4 * 4 + i, g);
-            ok = row >= 0;
-            o = (uint32_t)((row * p.lda + col) * 2);
-          }
-          sa.reg[i] = ldb16(rA, ok ? o : OOB);
-        }
-      }
-    }
-    // ---------------- B ----------------
-    if (!B_TR) {  // NT: weight rows n, k contiguous
-      const int k0 = kt * KT;
-      const bool kok = live && k0 + (tid & 7) * 8 < p.Kdim;
-#pragma unroll
-      for (int i = 0; i < SB::NCH; ++i)
-        sb.reg[i] = ldb16(rB, (kok && b_off[i] != OOB) ? b_off[i] + (uint32_t)k0 * 2u : OOB);
-    } else {
-      uint32_t krow0;  // byte offset of k row 0 of this tile (relative to the descriptor base)
-      int klim;        // number of valid k rows in this tile
-      if (KIND == KIND_NN) {
-        krow0 = (uint32_t)((int64_t)kt * KT * p.ldb * 2);
-        klim = live ? p.Kdim - kt * KT : 0;
-      } else {
-        const int s = kt / p.kchunks;
-        const int c0 = (kt - s * p.kchunks) * KT;
-        krow0 = (uint32_t)((((int64_t)s * p.G + g) * p.Cc + c0) * p.ldb * 2);
-        klim = live ? p.Cc - c0 : 0;
-      }
-      if (!SB::HALF) {
-#pragma unroll
-        for (int b = 0; b < SB::NB; ++b) {
-          const int bi = tid + b * NT;
-          const int kb = bi & 7, r8 = bi >> 3;
-          const int col = n0 + r8 * 8;
-          const uint32_t off0 = krow0 + (uint32_t)(kb * 8) * ldb2 + (uint32_t)col * 2u;
-#pragma unroll
-          for (int i = 0; i < 8; ++i)
-            sb.reg[b * 8 + i] = ldb16(rB, (kb * 8 + i < klim && col < p.Ndim) ? off0 + i * ldb2 : OOB);
-        }
-      } else {
-        const int kb4 = tid & 15, r8 = tid >> 4;
-        const int col = n0 + r8 * 8;
-        const uint32_t off0 = krow0 + (uint32_t)(kb4 * 4) * ldb2 + (uint32_t)col * 2u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          sb.reg[i] = ldb16(rB, (kb4 * 4 + i < klim && col < p.Ndim) ? off0 + i * ldb2 : OOB);
-      }
-    }
-  };
-
-  auto store_A = [&](int buf) {
-    bf16_t* As = smem + buf * (TM + TN) * PITCH;
-    if (!A_TR) {
-#pragma unroll
-      for (int i = 0; i < SA::NCH; ++i) {
-        const int row = (tid >> 3) + i * (NT / 8);
-        *reinterpret_cast<uint4*>(As + row * PITCH + (tid & 7) * 8) = sa.reg[i];
-      }
-    } else if (!SA::HALF) {
-#pragma unroll
-      for (int b = 0; b < SA::NB; ++b) {
-        const int bi = tid + b * NT;
-        const int kb = bi & 7, r8 = bi >> 3;
-        uint4 t[8];
-        transpose8x8(&sa.reg[b * 8], t);
-#pragma unroll
-        for (int n = 0; n < 8; ++n) *reinterpret_cast<uint4*>(As + (r8 * 8 + n) * PITCH + kb * 8) = t[n];
-      }
-    } else {
-      const int kb4 = tid & 15, r8 = tid >> 4;
-      uint2 t[8];
-      transpose4x8(sa.reg, t);
-#pragma unroll
-      for (int n = 0; n < 8; ++n) *reinterpret_cast<uint2*>(As + (r8 * 8 + n) * PITCH + kb4 * 4) = t[n];
-    }
-  };
-  auto store_B = [&](int buf) {
-    bf16_t* Bs = smem + buf * (TM + TN) * PITCH + TM * PITCH;
-    if (!B_TR) {
-#pragma unroll
-      for (int i = 0; i < SB::NCH; ++i) {
-        const int row = (tid >> 3) + i * (NT / 8);
-        *reinterpret_cast<uint4*>(Bs + row * PITCH + (tid & 7) * 8) = sb.reg[i];
-      }
-    } else if (!SB::HALF) {
-#pragma unroll
-      for (int b = 0; b < SB::NB; ++b) {
-        const int bi = tid + b * NT;
-        const int kb = bi & 7, r8 = bi >> 3;
-        uint4 t[8];
-        transpose8x8(&sb.reg[b * 8], t);
-#pragma unroll
-        for (int n = 0; n < 8; ++n) *reinterpret_cast<uint4*>(Bs + (r8 * 8 + n) * PITCH + kb * 8) = t[n];
-      }
-    } else {
-      const int kb4 = tid & 15, r8 = tid >> 4;
-      uint2 t[8];
-      transpose4x8(sb.reg, t);
-#pragma unroll
-      for (int n = 0; n < 8; ++n) *reinterpret_cast<uint2*>(Bs + (r8 * 8 + n) * PITCH + kb4 * 4) = t[n];
-    }
-  };
-
-  f32x16_t acc[MB][NBK];
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NBK; ++j)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-
-  // fragment addresses of this lane inside a stage
-  const int a_frag = (wm * TMW + (lane & 31)) * PITCH + (lane >> 5) * 8;
-  const int b_frag = TM * PITCH + (wn * TNW + (lane & 31)) * PITCH + (lane >> 5) * 8;
-  bf16x8_t fa[2][MB], fb[2][NBK];
-  auto load_frags = [&](int buf, int kk, int set) {
-    const bf16_t* st = smem + buf * (TM + TN) * PITCH + kk * 16;
-#pragma unroll
-    for (int i = 0; i < MB; ++i) fa[set][i] = *reinterpret_cast<const bf16x8_t*>(st + a_frag + i * 32 * PITCH);
-#pragma unroll
-    for (int j = 0; j < NBK; ++j) fb[set][j] = *reinterpret_cast<const bf16x8_t*>(st + b_frag + j * 32 * PITCH);
-  };
-
-  constexpr int NWA = A_TR ? 8 * (SA::HALF ? 1 : SA::NB) : SA::NCH;   // LDS writes per tile, A / B
-  constexpr int NWB = B_TR ? 8 * (SB::HALF ? 1 : SB::NB) : SB::NCH;
-  load_tiles(0);
-  store_A(0);
-  store_B(0);
-  __syncthreads();
-  load_frags(0, 0, 0);
-
-  // One k tile per iteration; the body is branch-free.  sched_barrier(0) fences keep the order
-  // written here: global loads of the next tile first (a whole tile of MFMAs hides their
-  // latency), fragment reads of step kk+1 issued before the MFMAs of step kk, LDS writes of the
-  // next tile riding on the last two MFMA groups.
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-#pragma unroll
-    for (int kk = 0; kk < KT / 16; ++kk) {
-      const int cur = kk & 1;
-      if (kk + 1 < KT / 16) load_frags(buf, kk + 1, cur ^ 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (kk == 0) load_tiles(kt + 1);
-      // the empty asm pins the staged registers here, so the transposes that consume them are
-      // not hoisted up to the loads (where they would wait for memory)
-      if (kk == KT / 16 - 2) {
-#pragma unroll
-        for (int i = 0; i < SA::NCH; ++i) pin(sa.reg[i]);
-        store_A(buf ^ 1);
-      }
-      if (kk == KT / 16 - 1) {
-#pragma unroll
-        for (int i = 0; i < SB::NCH; ++i) pin(sb.reg[i]);
-        store_B(buf ^ 1);
-      }
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NBK; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
-      // inside the fenced group: one memory instruction per MFMA, so that issuing the loads /
-      // LDS writes never holds up the matrix pipe
-      constexpr int NM = MB * NBK;
-      if (kk == 0) Recipe<0, NM, SA::NCH + SB::NCH, SG_VMEM_READ, 0, SG_DS_READ>::run();
-      if (kk == KT / 16 - 2) Recipe<0, NM, NWA, SG_DS_WRITE, 0, SG_DS_READ>::run();
-      if (kk == KT / 16 - 1) Recipe<0, NM, NWB, SG_DS_WRITE, 0, SG_DS_READ>::run();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __syncthreads();
-    load_frags(buf ^ 1, 0, 0);
-  }
-
-  store_tile<MB, NBK, KIND, EPI>(p, acc, g, m0 + wm * TMW, n0 + wn * TNW, lane);
-}
-
-// Epilogue of the DMA kernel, staged through LDS so that global memory sees 16-byte accesses in
+// Epilogue, staged through LDS so that global memory sees 16-byte accesses in
 // which consecutive lanes cover a contiguous run of a row (the MFMA result layout alone gives
 // 8-byte pieces strided across 32 rows).  Each wave owns a private slice of the (now idle) stage
 // memory: per 32-row block it writes bf16 results in [32][CW] row-major form (CW = columns of the
@@ -568,7 +149,8 @@ __device__ __forceinline__ void stb16(__amdgpu_buffer_rsrc_t r, uint32_t byte_of
 }
 template <int KIND, int EPI, int MB, int NBK>
 __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc)[MB][NBK], char* wave_lds, int g,
-                                               int mbase, int nbase, int lane, bool zero_fill = false) {
+                                               int mwave, int mshift, int nbase, const uint32_t (&out_off)[2],
+                                               int lane, bool zero_fill = false) {
   constexpr int CW = 32 * NBK;            // columns of the wave tile
   constexpr int PITCH_B = 2 * CW + 16;    // staged row pitch, bytes
   constexpr int BUF = 32 * PITCH_B;
@@ -595,47 +177,29 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc
     rC2 = make_rsrc(EPI == EPI_GELU ? p.C2 : p.C, bytes);
     rZ = make_rsrc(EPI == EPI_DGELU ? p.Zin : p.C, bytes);
   }
-  // byte offset of (row, ncol) for the rows this lane touches in the row-wise phase, or OOB.  One
-  // multiplication per lane; the rows of a wave tile are then a constant number of leading dimensions apart.
+  // byte offset of (row, ncol) for the rows this lane touches in the row-wise phase, or OOB: rows of a weight
+  // gradient are a constant number of leading dimensions apart; for activations the lanes hold the offsets of the
+  // wave tile's rows (lane, lane + 64), which are handed round
   uint32_t off[MB][NT_];
-  const uint32_t ldc2 = (uint32_t)p.ldc * 2u;
   if (KIND == KIND_TN) {
-    const uint32_t base = ((uint32_t)(mbase + rl) * (uint32_t)p.ldc + (uint32_t)ncol) * 2u;
+    const uint32_t ldc2 = (uint32_t)p.ldc * 2u;
+    const uint32_t base = ((uint32_t)(mwave + mshift + rl) * (uint32_t)p.ldc + (uint32_t)ncol) * 2u;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int t = 0; t < NT_; ++t) {
         const int d = i * 32 + RPI * t;
-        off[i][t] = (mbase + d + rl < p.Mdim && col_ok) ? base + (uint32_t)d * ldc2 : OOB;
+        off[i][t] = (mwave + mshift + d + rl < p.Mdim && col_ok) ? base + (uint32_t)d * ldc2 : OOB;
       }
   } else {
-    // virtual row r of expert g is physical row ((r / C) G + g) C + r % C; one division for the
-    // wave tile (a wave tile crosses at most one chunk boundary if C is not smaller than its
-    // height: rows past it lie (G - 1) C physical rows further on)
-    const int q0 = mbase / p.Cc, r0 = mbase - q0 * p.Cc;
-    if (p.Cc >= 32 * MB) {
-      const uint32_t row0 = (uint32_t)((q0 * p.G + g) * p.Cc + r0 + rl);
-      const uint32_t base = (row0 * (uint32_t)p.ldc + (uint32_t)ncol) * 2u;
-      const uint32_t wrap_add = (uint32_t)(p.G - 1) * (uint32_t)p.Cc * ldc2;
-      const int to_wrap = p.Cc - r0 - rl;     // rows at or beyond this distance are in the next chunk
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int t = 0; t < NT_; ++t) {
-          const int d = i * 32 + RPI * t;
-          const uint32_t o = base + (uint32_t)d * ldc2 + (d >= to_wrap ? wrap_add : 0u);
-          off[i][t] = (mbase + d + rl < p.Mdim && col_ok) ? o : OOB;
-        }
-    } else {
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int t = 0; t < NT_; ++t) {
-          const int m = mbase + i * 32 + RPI * t + rl;
-          const uint32_t row = (uint32_t)phys_row(m < p.Mdim ? m : 0, g, p.G, p.Cc);
-          off[i][t] = (m < p.Mdim && col_ok) ? (row * (uint32_t)p.ldc + (uint32_t)ncol) * 2u : OOB;
-        }
-    }
+      for (int t = 0; t < NT_; ++t) {
+        const int d = mshift + i * 32 + RPI * t;   // multiple of RPI: d + rl stays within one half of the wave tile
+        const uint32_t o = (uint32_t)__shfl((int)(d < 64 ? out_off[0] : out_off[1]), (d & 63) + rl, 64);
+        off[i][t] = (o != OOB && col_ok) ? o + (uint32_t)ncol * 2u : OOB;   // even: bit 0 marks a row of zeros
+      }
   }
   if (zero_fill) {   // a tile of padding rows: every result is zero
     const uint4 z = make_uint4(0, 0, 0, 0);
@@ -643,19 +207,27 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int t = 0; t < NT_; ++t) {
-        stb16(rC, off[i][t], z);
-        if (EPI == EPI_GELU) stb16(rC2, off[i][t], z);
+        stb16(rC, off[i][t] & ~1u, z);
+        if (EPI == EPI_GELU) stb16(rC2, off[i][t] & ~1u, z);
       }
     return;
+  }
+  uint4 zq_next[EPI == EPI_DGELU ? NT_ : 1];
+  if (EPI == EPI_DGELU) {
+#pragma unroll
+    for (int t = 0; t < NT_; ++t) zq_next[t] = ldb16<true>(rZ, off[0][t] & ~1u);
   }
   // accumulator phase: row lane % 32, for block j and q4: 4 columns at 32 j + 8 q4 + 4 (lane / 32)
   const int acc_off = (lane & 31) * PITCH_B + (lane >> 5) * 8;
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
-    if (EPI == EPI_DGELU) {  // bring in the saved pre-activation, row-wise
+    if (EPI == EPI_DGELU) {  // bring in the saved pre-activation, row-wise; the next block's is requested first
 #pragma unroll
-      for (int t = 0; t < NT_; ++t)
-        *reinterpret_cast<uint4*>(buf0 + (RPI * t + rl) * PITCH_B + cc * 16) = ldb16<true>(rZ, off[i][t]);
+      for (int t = 0; t < NT_; ++t) *reinterpret_cast<uint4*>(buf0 + (RPI * t + rl) * PITCH_B + cc * 16) = zq_next[t];
+      if (i + 1 < MB) {
+#pragma unroll
+        for (int t = 0; t < NT_; ++t) zq_next[t] = ldb16<true>(rZ, off[i + 1][t] & ~1u);
+      }
     }
 #pragma unroll
     for (int j = 0; j < NBK; ++j) {
@@ -686,49 +258,70 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc
     // row-wise read-back and store (LDS operations of one wave complete in program order)
 #pragma unroll
     for (int t = 0; t < NT_; ++t) {
-      stb16<(EPI == EPI_GELU || KIND == KIND_TN)>(rC, off[i][t],
-                                                   *reinterpret_cast<const uint4*>(buf0 + (RPI * t + rl) * PITCH_B + cc * 16));
-      if (EPI == EPI_GELU)
-        stb16(rC2, off[i][t], *reinterpret_cast<const uint4*>(buf1 + (RPI * t + rl) * PITCH_B + cc * 16));
+      const bool zero = KIND != KIND_TN && (off[i][t] & 1u);
+      const uint4 none = make_uint4(0, 0, 0, 0);
+      const uint4 v = *reinterpret_cast<const uint4*>(buf0 + (RPI * t + rl) * PITCH_B + cc * 16);
+      stb16<(EPI == EPI_GELU || KIND == KIND_TN)>(rC, off[i][t] & ~1u, zero ? none : v);
+      if (EPI == EPI_GELU) {
+        const uint4 v2 = *reinterpret_cast<const uint4*>(buf1 + (RPI * t + rl) * PITCH_B + cc * 16);
+        stb16(rC2, off[i][t] & ~1u, zero ? none : v2);
+      }
     }
   }
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16 MFMA kernel with an LDS-DMA pipeline (the fast path for large GEMMs).
+// bf16 MFMA tile with an LDS-DMA pipeline.
 //
-// 256x256 (or 192x256) output tile, 8 waves (2 along the rows x 4 along the columns, two per SIMD: 128x64 or
-// 96x64 per wave), k tile 32, a ring of DSTAGES = 5 LDS stages of 32 KiB (all of a compute unit's LDS).
-// Global memory goes straight to LDS (buffer_load ... lds, 16 bytes per lane, no VGPR staging, no
-// ds_write): a wave instruction fills 1 KiB of consecutive 16-byte slots in lane order, so the
-// tile is stored unpadded and bank conflicts are avoided by permuting WHICH 16-byte chunk of a
-// row each lane fetches (an XOR swizzle that the fragment reads undo).  Lanes whose row / column
-// / k index is out of range pass an out-of-range buffer offset; the hardware then writes zeros.
-//   operand with k contiguous in memory : stage holds [row][32 k] (64 B rows, 4 chunks), chunk c
-//       of row r sits in slot c ^ ((r >> 2) & 3); fragments are read with ds_read_b128.
-//   operand with k as the slow index    : stage holds [32 k][256 cols] (512 B rows, 32 chunks),
-//       chunk c of k-row k sits in slot c ^ (4 (k & 3)); fragments are read with the transposing
-//       LDS load ds_read_b64_tr_b16: a 16-lane group reads a 4(k) x 16(col) patch (lane s: k-row
-//       s/4, 8-byte piece s%4) and lane i receives the 4 k-values of column i.
-// Pipeline: while tile t is multiplied, the B-operand requests of tile t+3 go out during its first
-// 16-wide MFMA step and the A-operand requests of tile t+4 during its second.  Once per k tile, between
-// the two steps, each wave waits until its own requests for tile t+1 have landed (s_waitcnt vmcnt),
-// all waves meet at a barrier, and the stage freed by tile t-1 (the one tile t+4 goes to) may be
-// refilled.  Because the barrier sits in the middle, the first fragments of tile t+1 are fetched under
-// the second MFMA step and no LDS latency is exposed at the tile boundary.
+// TM x TN output tile, k tile 64, WM x WN waves over the tile times WK waves over the four 16-wide MFMA
+// steps of a k tile (their sums are added through LDS at the end).  Global memory goes straight to LDS
+// (buffer_load ... lds, 16 bytes per lane, no VGPR staging, no ds_write) into two rings of whole k tiles, SA
+// tiles of the A operand and SB of the B operand.  A k tile is 64 wide so that every request of a k-contiguous
+// operand covers whole 128-byte lines.  A wave instruction fills 1 KiB of consecutive 16-byte slots in lane
+// order, so a tile is stored unpadded and bank conflicts are avoided by permuting WHICH 16-byte chunk of a row
+// each lane fetches (an XOR swizzle that the fragment reads undo).  Every lane of a request fetches from inside the
+// tensor: the zero fill of an out-of-range request can reach LDS after the wait for it is over, and would then
+// destroy what the slot was refilled with.  Rows and columns outside the problem and padding rows are fetched
+// from another row / column (what they yield is not stored, or stored as zeros), k indexes behind the end of a k tile
+// from its first one (the A fragments are masked).
+//   operand with k contiguous in memory : [row][64 k] (128-byte rows, 8 chunks), chunk c of row r in slot
+//       c ^ ((r >> 1) & 7); fragments are read with ds_read_b128.
+//   operand with k as the slow index    : [64 k][T cols], chunk c of k-row k in slot c ^ 4 (k & 3) (T = 64:
+//       c ^ 4 ((k >> 1) & 1)); fragments are read with the transposing LDS load ds_read_b64_tr_b16: a
+//       16-lane group reads a 4(k) x 16(col) patch (lane s: k-row s/4, 8-byte piece s%4) and lane i receives
+//       the 4 k-values of column i.
+// Pipeline: the fragments of MFMA step s+1 are read under step s.  Once per k tile, inside its last step (when
+// the fragments of that step are in registers, so nobody needs the tile's LDS any more), each wave waits until
+// its own requests for the next tile have landed, all waves meet at a barrier, the fragments of the next tile's
+// first step are read, and the freed slots are refilled: tile t+SB of B, then tile t+SA of A, one request
+// between MFMA rows.  The last SA tiles have nothing to request behind them; they are a loop of their own, in which a
+// wave waits for all of its requests instead of for the older ones by count.
+// What bounds it: with every compute unit busy, the power limit (the clock falls to 1.7 - 1.8 GHz) and the delivery
+// of tiles from L2; with few tiles, the latency of a k tile.  k tiles of 64 instead of 32 (64-byte pieces of
+// k-contiguous rows fetch half a cache line and look every line up twice): 8 experts of 16384 x 4096 x 7168, per
+// GEMM, 6.83 / 6.44 (forward) and 6.90 / 7.59 (backward) -> 6.3 / 5.9 and 6.1 / 6.1 ms, 1.1 - 1.2 -> 1.2 - 1.35
+// PFLOP/s.  A finer wait per MFMA row, four waves of 128 x 128 and rows padded off a power of two measured no better.
 // ------------------------------------------------------------------------------------------
 #define LDS_AS __attribute__((address_space(3)))
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-
-constexpr int DT = 256;                    // tile edge
-constexpr int DK = 32;                     // k tile
-constexpr int DSTAGES = 5;                 // 160 KiB: all of a compute unit's LDS
+constexpr int DK = 64;   // k tile
 // s_waitcnt immediate that waits until at most n vector-memory operations are outstanding (gfx9 encoding)
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
-constexpr int DREGION = DT * DK * 2;       // bytes per operand per stage (16 KiB)
-constexpr int DSTAGE = 2 * DREGION;
 
-__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, bf16_t* lds_wave_base, uint32_t byte_off) {
+template <int TM_, int TN_, int WM_, int WN_, int WK_, int SA_, int SB_>
+struct TileCfg {
+  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, WK = WK_, SA = SA_, SB = SB_;
+  static constexpr int NW = WM * WN * WK;             // waves
+  static constexpr int MB = TM / WM / 32, NB = TN / WN / 32;   // 32 x 32 blocks per wave
+  static constexpr int RA = TM / 8 / NW, RB = TN / 8 / NW;     // requests (1 KiB) per wave and k tile
+  static constexpr int SPT = 4 / WK;                  // MFMA steps per wave and k tile
+  static constexpr int A_UNIT = TM * DK * 2, B_UNIT = TN * DK * 2;
+  static constexpr int LDS = SA * A_UNIT + SB * B_UNIT;
+  static_assert(SPT == 2 || SPT == 4, "one or two wave groups over k");
+  static_assert(TM / 8 % NW == 0 && TN / 8 % NW == 0, "requests are dealt evenly");
+  static_assert(SA == SB || SA == SB + 1, "ring depths");
+};
+
+__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, char* lds_wave_base, uint32_t byte_off) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (LDS_AS void*)lds_wave_base, 16, (int)byte_off, 0, 0, 0);
 }
 // Fragment reads are issued as volatile asm: the compiler then neither reorders them nor guards
@@ -744,35 +337,186 @@ template <int OFF>
 __device__ __forceinline__ void lds_read_kc(Frag& f, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.q) : "v"(addr), "n"(OFF));
 }
-template <int OFF>
-__device__ __forceinline__ void lds_read_nc(Frag& f, uint32_t addr_lo, uint32_t addr_hi) {
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.h[0]) : "v"(addr_lo), "n"(OFF));
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.h[1]) : "v"(addr_hi), "n"(OFF));
+template <int OFF, int HOFF>   // HOFF: distance of the second half's k-rows
+__device__ __forceinline__ void lds_read_nc(Frag& f, uint32_t addr) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.h[0]) : "v"(addr), "n"(OFF));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.h[1]) : "v"(addr), "n"(OFF + HOFF));
 }
 __device__ __forceinline__ void ready(Frag& f) { asm volatile("" : "+v"(f.q)); }
 
-// WN = waves along n: 4 (8 waves, 128x64 per wave, two per SIMD) is what is launched; the template also
-// allows 2 (4 waves, 128x128 per wave).
-// TMR = rows of the output tile: 256, or 192 (three 32-row blocks per wave; only for operands A
-// with k contiguous) for problems whose 256-row tiling would leave many compute units idle.
-template <int KIND, int EPI, int WN, int TMR, bool GATHER = false>
+__device__ __forceinline__ int clamp_count(int c, int Cc) { return min(max(c, 0), Cc); }
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unrolled<I + 1, N>(f);
+  }
+}
+
+// Workgroup -> output tile.  Workgroup ids are dealt round-robin to the 8 XCDs, so id % 8 names the XCD (problems
+// of a merged launch start at multiples of 8); each XCD works on one contiguous range of a linear tile order in
+// which 32 consecutive tiles (what its 32 CUs run at the same time) form an 8 (rows) x 4 (columns) patch of one
+// expert: per k step they share 8 + 4 operand slices in that XCD's L2 instead of 1 + 32.
+// t = index within an expert of tm_n row tiles.
+__device__ __forceinline__ void patch_order(int t, int tm_n, int tiles_n, int& tm, int& tn) {
+  constexpr int SW = 4;
+  const int full = tiles_n / SW;
+  const int strip = tm_n * SW;
+  if (t < full * strip) {
+    const int sn = t / strip, r = t - sn * strip;
+    tm = r / SW;
+    tn = sn * SW + (r - tm * SW);
+  } else {
+    const int w = tiles_n - full * SW;
+    const int r = t - full * strip;
+    tm = r / w;
+    tn = full * SW + (r - tm * w);
+  }
+}
+// With row counts the order holds the row tiles that have occupied rows first (compacted: an expert with n
+// occupied rows has ceil(n / TM) of them) and then the tiles that only have to be filled with zeros; each XCD gets an
+// equal share of both, whatever the routing.  Returns 0: no tile, 1: a tile to multiply, 2: a tile of zeros.
+template <int TM>
+__device__ __forceinline__ int map_tile(const GemmArgs& p, int vb, bool counted, int& g, int& tm, int& tn) {
+  const int x = vb & 7, i = vb >> 3;
+  if (!counted) {
+    const int per_xcd = (p.total_tiles + 7) / 8;
+    const int tile = x * per_xcd + i;
+    if (i >= per_xcd || tile >= p.total_tiles) return 0;
+    const int tiles_per_g = p.tiles_m * p.tiles_n;
+    g = tile / tiles_per_g;
+    patch_order(tile - g * tiles_per_g, p.tiles_m, p.tiles_n, tm, tn);
+    return 1;
+  }
+  if (p.n_src == 1 && p.G <= 16) {   // few counts: scalar loads, which hit the scalar cache from a compute unit's second tile on
+    int o[16], occ_all = 0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[e] = p.cnt[min(e, p.G - 1)];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      o[e] = e < p.G ? (clamp_count(o[e], p.Cc) + TM - 1) / TM : 0;
+      occ_all += o[e];
+    }
+    const int T = occ_all * p.tiles_n, Z = p.total_tiles - T;
+    const int per_t = (T + 7) / 8, per_z = (Z + 7) / 8;
+    const bool zero = i >= per_t;
+    const int tile = zero ? x * per_z + (i - per_t) : x * per_t + i;
+    if (zero ? (i - per_t >= per_z || tile >= Z) : tile >= T) return 0;
+    int first = 0, mine = 0, og = 0, run = 0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int m = e < p.G ? (zero ? p.tiles_m - o[e] : o[e]) : 0;
+      if (run * p.tiles_n <= tile && m > 0) { g = e; first = run; mine = m; og = o[e]; }
+      run += m;
+    }
+    patch_order(tile - first * p.tiles_n, mine, p.tiles_n, tm, tn);
+    if (zero) tm += og;
+    return zero ? 2 : 1;
+  }
+  const int lane = threadIdx.x & 63;
+  auto occupied = [&](int e) {   // row tiles of expert e that hold occupied rows
+    int n = 0;
+    if (e < p.G) {
+#pragma unroll 8
+      for (int s = 0; s < p.n_src; ++s) n += clamp_count(p.cnt[s * p.G + e], p.Cc);
+    }
+    return (n + TM - 1) / TM;
+  };
+  const int o0 = occupied(lane);
+  int occ_all = 0;
+  for (int e0 = 0; e0 < p.G; e0 += 64) {
+    int o = e0 == 0 ? o0 : occupied(e0 + lane);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) o += __shfl_xor(o, d, 64);
+    occ_all += o;
+  }
+  occ_all = __builtin_amdgcn_readfirstlane(occ_all);
+  const int T = occ_all * p.tiles_n, Z = p.total_tiles - T;
+  const int per_t = (T + 7) / 8, per_z = (Z + 7) / 8;
+  const bool zero = i >= per_t;
+  const int tile = zero ? x * per_z + (i - per_t) : x * per_t + i;
+  if (zero ? (i - per_t >= per_z || tile >= Z) : tile >= T) return 0;
+  int run = 0;   // tiles of the experts before e0
+  for (int e0 = 0; e0 < p.G; e0 += 64) {
+    const int o = e0 == 0 ? o0 : occupied(e0 + lane);
+    const int mine = e0 + lane < p.G ? (zero ? p.tiles_m - o : o) : 0;
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int v = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += v;
+    }
+    const unsigned long long hit = __ballot((run + incl) * p.tiles_n > tile);
+    if (hit) {
+      const int l = __ffsll((long long)hit) - 1;
+      const int before = __shfl(incl - mine, l, 64), og = __shfl(o, l, 64), mg = __shfl(mine, l, 64);
+      g = __builtin_amdgcn_readfirstlane(e0 + l);
+      patch_order(tile - (run + before) * p.tiles_n, mg, p.tiles_n, tm, tn);
+      tm = __builtin_amdgcn_readfirstlane(tm + (zero ? og : 0));
+      tn = __builtin_amdgcn_readfirstlane(tn);
+      return zero ? 2 : 1;
+    }
+    run += __shfl(incl, 63, 64);
+  }
+  return 0;
+}
+
+// Compacted row order of an expert that receives several chunks with row counts: its occupied rows first, chunk by
+// chunk, then the padding rows, chunk by chunk.  Finds the physical rows of N positions; occ = an occupied row.
+template <int N>
+__device__ __forceinline__ void compact_rows(const GemmArgs& p, int g, const int (&r)[N], int (&row)[N], bool (&occ)[N]) {
+  const int lane = threadIdx.x & 63;
+  int total = 0;
+  for (int s0 = 0; s0 < p.n_src; s0 += 64) {
+    int c = s0 + lane < p.n_src ? clamp_count(p.cnt[(s0 + lane) * p.G + g], p.Cc) : 0;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+    total += c;
+  }
+  total = __builtin_amdgcn_readfirstlane(total);
+#pragma unroll
+  for (int n = 0; n < N; ++n) { row[n] = 0; occ[n] = r[n] < total; }
+  int pre = 0, pad = total;   // positions of this chunk's first occupied / padding row
+  for (int s0 = 0; s0 < p.n_src; s0 += 64) {
+    const int cl = s0 + lane < p.n_src ? clamp_count(p.cnt[(s0 + lane) * p.G + g], p.Cc) : 0;
+    const int ns = min(64, p.n_src - s0);
+    for (int s = 0; s < ns; ++s) {
+      const int c = __builtin_amdgcn_readlane(cl, s);
+      const int base = ((s0 + s) * p.G + g) * p.Cc;
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        const int at = occ[n] ? pre : pad;
+        if (r[n] >= at) row[n] = base + (occ[n] ? 0 : c) + (r[n] - at);
+      }
+      pre += c;
+      pad += p.Cc - c;
+    }
+  }
+}
+
+// GATHER: the k-slow A operand of a weight-gradient GEMM (X^T dZ) is the token matrix read through the
+// inverse slot map (row r of the chunk is token gather[g C + r] / gather_k); n_src = 1.
+template <int KIND, int EPI, typename CF, bool GATHER = false>
 __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int vb) {
   constexpr bool A_NC = (KIND == KIND_TN);                     // A has k as the slow index
   constexpr bool B_NC = (KIND == KIND_NN || KIND == KIND_TN);  // B has k as the slow index
-  static_assert(TMR == 256 || (TMR == 192 && !A_NC && WN == 4), "unsupported tile height");
-  // GATHER: the k-slow A operand of a weight-gradient GEMM (X^T dZ) is the token matrix read through the
-  // inverse slot map (row r of the chunk is token gather[g C + r] / gather_k); n_src = 1.
-  static_assert(!GATHER || (KIND == KIND_TN && WN == 4), "row gather in the reduction: the 8-wave weight-gradient kernel only");
-  constexpr int MB = TMR / 64, NBK = 8 / WN;     // 32x32 blocks per wave tile
-  constexpr int RPW = 8 / WN;             // requests per wave per operand per k tile (16 in all)
+  constexpr int TM = CF::TM, TN = CF::TN, WM = CF::WM, WN = CF::WN, WK = CF::WK, SA = CF::SA, SB = CF::SB;
+  constexpr int MB = CF::MB, NB = CF::NB, RA = CF::RA, RB = CF::RB, SPT = CF::SPT;
+  static_assert(!A_NC || TM == 64 || TM == 128 || TM == 256, "k-slow tiles are a power of two wide");
+  static_assert(!GATHER || (KIND == KIND_TN && CF::NW == 8), "row gather in the reduction: eight k-rows per wave");
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps LDS bases in SGPRs
-  const int wm = wave / WN, wn = wave % WN;
+  const int wk = WK == 1 ? 0 : wave / (WM * WN);
+  const int wm = (wave / WN) % WM, wn = wave % WN;
 
   int g, tm, tn;
-  if (!map_tile(p, vb, g, tm, tn)) return;
-  const int m0 = tm * TMR, n0 = tn * DT;
+  const bool counted = KIND != KIND_TN && p.cnt != nullptr;
+  const int what = map_tile<TM>(p, vb, counted, g, tm, tn);
+  if (what == 0) return;
+  const int m0 = tm * TM, n0 = tn * TN;
+  const bool compact = counted && p.n_src > 1;
 
   const int64_t b_base = (int64_t)g * p.b_goff + p.b_off;
   const __amdgpu_buffer_rsrc_t rA = make_rsrc(p.A, (uint32_t)p.a_bytes);
@@ -781,180 +525,216 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
       (KIND == KIND_TN) ? make_rsrc(p.B, (uint32_t)p.b_bytes)
                         : make_rsrc(reinterpret_cast<const bf16_t*>(p.B) + b_base, b_rem > OOB ? OOB : (uint32_t)b_rem);
 
-  // Rows at or beyond a chunk's count are padding (zero inputs, zero results).  A row tile made of
-  // nothing else stores zeros and leaves; a reduction over the rows (the weight gradients) stops at
-  // the count when there is a single chunk.
-  int kvalid = p.Cc;   // TN: rows of a chunk that are multiplied
-  if (KIND == KIND_TN && p.cnt != nullptr && p.n_src == 1) kvalid = min(max(p.cnt[g], 0), p.Cc);
-  const int kpc = max((kvalid + DK - 1) / DK, 1);  // TN: k tiles per chunk
-  const int nk = (KIND == KIND_TN) ? (kvalid > 0 ? p.n_src * kpc : 0) : (p.Kdim + DK - 1) / DK;
-
-  // ---- per-lane request coordinates: each wave issues RPW requests per operand per k tile ----
-  // k-contiguous operand, request q = RPW wave + j: rows 16 q + lane/4, slot lane%4 holds logical chunk kc_c
-  const int kc_c = (lane & 3) ^ ((lane >> 4) & 3);
-  // k-slow operand, request q: k-rows 2 q + lane/32, slot lane%32 holds logical chunk nc_c[j]
-  uint32_t a_req[RPW], b_req[RPW];   // byte offset of the lane's 16 bytes at k tile 0, or OOB
-  int a_k[RPW], b_k[RPW];            // k index (within the k tile) this request covers (k-slow), or first k (k-contig)
+  // physical rows of the requests' A rows (row-tiled GEMMs) and of rows lane, lane + 64 of the wave tile
+  int q_row[RA];
+  uint32_t out_off[2] = {OOB, OOB};   // byte offset of the row in the output (+ 1: a row of zeros), or OOB
+  if (KIND != KIND_TN) {
+    int r[RA + 2], row[RA + 2];
+    bool occ[RA + 2];
 #pragma unroll
-  for (int j = 0; j < RPW; ++j) {
-    const int q = wave * RPW + j;
-    if (!A_NC) {
-      const int rt = q * 16 + (lane >> 2);   // rows past a 192-row tile are never fetched
-      const int r = m0 + rt;
-      a_k[j] = kc_c * 8;
-      const int64_t row = (rt < TMR && r < p.Mdim) ? a_src_row(p, r, g) : -1;
-      a_req[j] = (row >= 0) ? (uint32_t)((row * p.lda + kc_c * 8) * 2) : OOB;
+    for (int j = 0; j < RA; ++j) r[j] = m0 + (wave * RA + j) * 8 + (lane >> 3);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) r[RA + j] = m0 + wm * (32 * MB) + 64 * j + lane;
+    if (compact) {
+      compact_rows<RA + 2>(p, g, r, row, occ);
     } else {
-      const int k = 2 * q + (lane >> 5);
-      const int col = m0 + (((lane & 31) ^ (4 * (k & 3))) * 8);
-      a_k[j] = k;
-      a_req[j] = (col < p.Mdim) ? (uint32_t)(((int64_t)(GATHER ? 0 : k) * p.lda + col) * 2) : OOB;
+      const int cnt_g = counted ? clamp_count(p.cnt[g], p.Cc) : p.Mdim;
+#pragma unroll
+      for (int j = 0; j < RA + 2; ++j) {
+        occ[j] = r[j] < cnt_g;
+        row[j] = p.n_src == 1 ? g * p.Cc + r[j] : (int)phys_row(min(r[j], p.Mdim - 1), g, p.G, p.Cc);
+      }
+      if (p.gather != nullptr) {   // rows are the tokens that the slots hold; an empty slot is a row of zeros
+        int iv[RA + 2];
+#pragma unroll
+        for (int j = 0; j < RA + 2; ++j) iv[j] = p.gather[(int64_t)g * p.Cc + min(r[j], p.Mdim - 1)];
+#pragma unroll
+        for (int j = 0; j < RA + 2; ++j) {
+          const uint32_t tok = p.gather_k == 1 ? (uint32_t)iv[j] : __umulhi((uint32_t)iv[j], p.gather_magic);
+          occ[j] = occ[j] && iv[j] >= 0 && (int64_t)tok < p.gather_rows;
+          if (j < RA) row[j] = (int)tok;
+        }
+      }
     }
-    if (!B_NC) {
-      const int n = n0 + q * 16 + (lane >> 2);
-      b_k[j] = kc_c * 8;
-      b_req[j] = (n < p.Ndim) ? (uint32_t)(((int64_t)n * p.ldb + kc_c * 8) * 2) : OOB;
+#pragma unroll
+    for (int j = 0; j < RA; ++j) q_row[j] = (r[j] < p.Mdim && occ[j]) ? row[j] : 0;   // no row: any row of the tensor
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (r[RA + j] < p.Mdim) out_off[j] = (uint32_t)row[RA + j] * (uint32_t)p.ldc * 2u + (occ[RA + j] ? 0u : 1u);
+  }
+  constexpr int EMB = (WK == 2 && MB >= 2) ? MB / 2 : MB;      // row and column blocks a wave finishes
+  constexpr int ENB = (WK == 2 && MB < 2 && NB >= 2) ? NB / 2 : NB;
+  constexpr bool ONE = WK == 2 && MB < 2 && NB < 2;            // a single block: the second group's waves finish nothing
+  const int e_i = (WK == 2 && MB >= 2) ? wk * EMB : 0, e_j = (WK == 2 && MB < 2 && NB >= 2) ? wk * ENB : 0;
+  const int e_n = n0 + wn * (32 * NB) + 32 * e_j;
+  char* e_lds = smem + wave * (CF::LDS / CF::NW / 64 * 64);
+  if (KIND != KIND_TN && what == 2) {   // padding rows only: every result is zero (dZ of a padding row is never read)
+    if (EPI != EPI_DGELU) {
+      f32x16_t none[EMB][ENB] = {};
+      store_tile_lds<KIND, EPI, EMB, ENB>(p, none, e_lds, g, m0 + wm * (32 * MB), 32 * e_i, e_n, out_off, lane, true);
+    }
+    return;
+  }
+
+  // ---- k tiles.  Row-tiled GEMMs: Kdim / 64.  Weight gradients: the reduction runs over the expert's rows, chunk by
+  // chunk (a k tile never crosses a chunk), and a chunk's k tiles end at its row count. ----
+  int nk;
+  int ch_cnt = 0, ch_s0 = 0, ch_c0 = 0, ch_row = 0, ch_lim = 0, ch_left = 0;   // TN: walk over the chunks
+  unsigned long long ch_mask = 0;
+  auto load_chunks = [&]() {     // counts of chunks ch_s0 .. ch_s0 + 63, one per lane
+    const int s = ch_s0 + lane;
+    ch_cnt = s < p.n_src ? (p.cnt != nullptr ? clamp_count(p.cnt[s * p.G + g], p.Cc) : p.Cc) : 0;
+    ch_mask = __ballot(ch_cnt > 0);
+  };
+  if (KIND == KIND_TN) {
+    nk = 0;
+    for (ch_s0 = 0; ch_s0 < p.n_src; ch_s0 += 64) {
+      load_chunks();
+      int n = (ch_cnt + DK - 1) / DK;
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
+      nk += __builtin_amdgcn_readfirstlane(n);
+    }
+    if (p.n_src > 64) { ch_s0 = 0; load_chunks(); } else ch_s0 = 0;
+  } else {
+    nk = (p.Kdim + DK - 1) / DK;
+  }
+  struct KTile { int row0, lim; };   // first row of the k tile in the operand, rows (k values) that exist
+  auto next_ktile = [&]() -> KTile {   // TN: the next k tile of the walk; past the end: no rows
+    if (ch_left <= 0) {
+      while (ch_mask == 0 && ch_s0 + 64 < p.n_src) { ch_s0 += 64; load_chunks(); }
+      if (ch_mask == 0) return KTile{0, 0};
+      const int l = __ffsll((long long)ch_mask) - 1;
+      ch_mask &= ch_mask - 1;
+      ch_left = __builtin_amdgcn_readlane(ch_cnt, l);
+      ch_row = ((ch_s0 + l) * p.G + g) * p.Cc;
+    }
+    const KTile t{ch_row, min(ch_left, DK)};
+    ch_row += DK;
+    ch_left -= DK;
+    return t;
+  };
+
+  // ---- per-lane request coordinates: byte offset of the lane's row / column, the k index within the tile that the
+  // request covers (k-slow) or starts at (k-contiguous), and the byte offset of that k index ----
+  uint32_t a_req[RA], b_req[RB], a_ko[RA], b_ko[RB];
+  int a_k[RA], b_k[RB];
+  constexpr int ACPR = TM / 8, BCPR = TN / 8;   // k-slow: 16-byte chunks per k-row
+  const uint32_t lda2 = (uint32_t)p.lda * 2u, ldb2 = (uint32_t)p.ldb * 2u;
+  auto swz_nc = [](int k, int cpr) { return cpr >= 16 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); };
+#pragma unroll
+  for (int j = 0; j < RA; ++j) {
+    const int q = wave * RA + j;
+    if (!A_NC) {
+      a_k[j] = ((lane & 7) ^ ((4 * q + (lane >> 4)) & 7)) * 8;
+      a_req[j] = (uint32_t)q_row[j] * lda2;
+      a_ko[j] = (uint32_t)a_k[j] * 2u;
     } else {
-      const int k = 2 * q + (lane >> 5);
-      const int col = n0 + (((lane & 31) ^ (4 * (k & 3))) * 8);
-      b_k[j] = k;
-      b_req[j] = (col < p.Ndim) ? (uint32_t)(((int64_t)k * p.ldb + col) * 2) : OOB;
+      a_k[j] = q * (64 / ACPR) + lane / ACPR;
+      const int col = m0 + (((lane % ACPR) ^ swz_nc(a_k[j], ACPR)) * 8);
+      a_req[j] = (uint32_t)(col < p.Mdim ? col : m0) * 2u;
+      a_ko[j] = GATHER ? 0u : (uint32_t)a_k[j] * lda2;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < RB; ++j) {
+    const int q = wave * RB + j;
+    if (!B_NC) {
+      b_k[j] = ((lane & 7) ^ ((4 * q + (lane >> 4)) & 7)) * 8;
+      b_req[j] = (uint32_t)min(n0 + q * 8 + (lane >> 3), p.Ndim - 1) * ldb2;
+      b_ko[j] = (uint32_t)b_k[j] * 2u;
+    } else {
+      b_k[j] = q * (64 / BCPR) + lane / BCPR;
+      const int col = n0 + (((lane % BCPR) ^ swz_nc(b_k[j], BCPR)) * 8);
+      b_req[j] = (uint32_t)(col < p.Ndim ? col : n0) * 2u;
+      b_ko[j] = (uint32_t)b_k[j] * ldb2;
     }
   }
 
-  // GATHER: the four k-rows a wave requests per k tile (4 wave .. 4 wave + 3: requests j = 0, 1, lane halves)
-  // are the same for all its lanes, so their slot-map entries are read with scalar loads (issued as asm so
-  // that they stay scalar: nothing is added to the vector-memory queue whose length the waits below count).
-  // They are issued at the start of a k tile, have arrived at its second fragment wait (lgkmcnt(0)), and are
-  // turned into per-lane row offsets after the barrier, just before the A request that uses them.
-  uint32_t g_now[RPW];   // byte offset of the token row behind this lane's k-row of the next A request, or OOB
-  auto gather_fetch = [&](int kt, int (&dst)[4]) {
-    const int64_t last = (int64_t)p.G * p.Cc - 1;
-    const int64_t i0 = (int64_t)g * p.Cc + kt * DK + 4 * wave;   // rows past the count are never used
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t i = i0 + u < last ? i0 + u : last;
-      const uint32_t off = (uint32_t)__builtin_amdgcn_readfirstlane((int)(i * 4));
-      asm volatile("s_load_dword %0, %1, %2" : "=s"(dst[u]) : "s"(p.gather), "s"(off));
-    }
+  // GATHER: the k-rows of a k tile are token rows.  Lane l loads the slot-map entry of k-row l, one request set ahead of
+  // the A requests that use it and before that set's own requests: the wait for tile t+1 at the next barrier then covers
+  // the entries as well, and nothing waits for them by itself.  The eight rows a wave requests are the same for all
+  // its lanes.  An empty slot is fetched as token 0 and masked.
+  uint32_t g_now[RA];   // byte offset of the token row behind this lane's k-row of the next A request
+  const __amdgpu_buffer_rsrc_t rG = make_rsrc(p.gather, GATHER ? (uint32_t)((int64_t)p.G * p.Cc * 4) : 0u);
+  auto gather_fetch = [&](int row0) -> int {   // entries past the map read as zero; rows past the row count are masked
+    return (int)__builtin_amdgcn_raw_buffer_load_b32(rG, (row0 + lane) * 4, 0, 0);
   };
-  auto gather_rows = [&](int (&src)[4]) {   // after an lgkmcnt(0) wait that follows the fetch
+  auto gather_rows = [&](int entry) -> uint64_t {   // returns which of the 64 slots are occupied
+    constexpr int RPR = A_NC ? 64 / ACPR : 1;   // k-rows per request
+    const uint32_t tok = p.gather_k == 1 ? (uint32_t)entry : __umulhi((uint32_t)entry, p.gather_magic);
+    const bool full = entry >= 0 && (int64_t)tok < p.gather_rows;
+    const uint32_t off = full ? tok * (uint32_t)(p.lda * 2) : 0u;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) asm volatile("" : "+s"(src[u]));
+    for (int j = 0; j < RA; ++j) {
+      uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)off, (wave * RA + j) * RPR);
 #pragma unroll
-    for (int j = 0; j < RPW; ++j) {
-      const int iv = (lane >> 5) ? src[2 * j + 1] : src[2 * j];
-      const uint32_t tok = p.gather_k == 1 ? (uint32_t)iv : __umulhi((uint32_t)iv, p.gather_magic);
-      g_now[j] = (iv >= 0 && (int64_t)tok < p.gather_rows) ? tok * (uint32_t)(p.lda * 2) : OOB;
+      for (int u = 1; u < RPR; ++u) {
+        const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)off, (wave * RA + j) * RPR + u);
+        o = lane / ACPR == u ? v : o;
+      }
+      g_now[j] = o;
     }
+    return __ballot(full);
   };
-  // Requests of k tile kt into its stage, one instruction (1 KiB) at a time: which = 0 (A) / 1 (B),
-  // j = 0..RPW-1.  Tiles past the end still issue (all lanes out of range, zeros are written) so that
-  // the number of outstanding requests per wave is the same in every iteration.
-  auto request1 = [&](int kt, int stage, int which, int j) {
-    char* st = smem + stage * DSTAGE;
-    const bool live = kt < nk;
-    uint32_t add;   // byte offset of the k tile
-    int lim;        // valid k count in this tile
-    if (KIND == KIND_TN) {
-      const int s = kt / kpc;
-      const int c0 = (kt - s * kpc) * DK;
-      const int64_t row0 = ((int64_t)s * p.G + g) * p.Cc + c0;
-      add = (uint32_t)(row0 * (which ? p.ldb : p.lda) * 2);
-      lim = live ? kvalid - c0 : 0;
-    } else {
-      add = (which && B_NC) ? (uint32_t)((int64_t)kt * DK * p.ldb * 2) : (uint32_t)kt * (DK * 2);
-      lim = live ? p.Kdim - kt * DK : 0;
-    }
-    const int q = wave * RPW + j;
-    if (which == 0) {
-      if (GATHER)
-        dma16(rA, reinterpret_cast<bf16_t*>(st + q * 1024),
-              (a_req[j] != OOB && g_now[j] != OOB && a_k[j] < lim) ? a_req[j] + g_now[j] : OOB);
-      else
-        dma16(rA, reinterpret_cast<bf16_t*>(st + q * 1024), (a_req[j] != OOB && a_k[j] < lim) ? a_req[j] + add : OOB);
-    }
-    else
-      dma16(rB, reinterpret_cast<bf16_t*>(st + DREGION + q * 1024),
-            (b_req[j] != OOB && b_k[j] < lim) ? b_req[j] + add : OOB);
+  // One request (1 KiB) of k tile kt into ring slot `slot`.
+  auto request_a = [&](const KTile& kt, int slot, int j) {
+    const uint32_t add = GATHER ? g_now[j] : A_NC ? (uint32_t)kt.row0 * lda2 : (uint32_t)kt.row0 * 2u;
+    dma16(rA, smem + slot * CF::A_UNIT + (wave * RA + j) * 1024, a_req[j] + add + (a_k[j] < kt.lim ? a_ko[j] : 0u));
   };
-  auto request_half = [&](int kt, int which) {   // prologue only: kt < DSTAGES
-#pragma unroll
-    for (int j = 0; j < RPW; ++j) request1(kt, kt, which, j);
+  auto request_b = [&](const KTile& kt, int slot, int j) {
+    const uint32_t add = B_NC ? (uint32_t)kt.row0 * ldb2 : (uint32_t)kt.row0 * 2u;
+    dma16(rB, smem + SA * CF::A_UNIT + slot * CF::B_UNIT + (wave * RB + j) * 1024,
+          b_req[j] + add + (b_k[j] < kt.lim ? b_ko[j] : 0u));
   };
+  auto ktile_at = [&](int t) -> KTile { return KTile{t * DK, p.Kdim - t * DK}; };   // row-tiled GEMMs
 
-  // ---- per-lane fragment addresses inside a stage (bytes), for k step kk = 0; kk = 1 adds a constant ----
-  // k-contiguous: row = base + 32 i + lane%32, logical chunk 2 kk + lane/32  -> slot ^ ((row >> 2) & 3)
-  // k-slow: 16-lane group b = lane/16, s = lane%16: k = 16 kk + 8 (b/2) + 4 h + s/4,
-  //         col = base + 32 j + 16 (b%2) + 4 (s%4); chunk = col/8 ^ 2 (s/4), piece = (s%4)&1
-  // k-contiguous: x_fr[kk][0] (blocks add a constant); k-slow: x_fr[h][block] (the swizzle touches the
-  // chunk-index bits that the block offset sets, so every 32-column block has its own base address)
-  uint32_t a_fr[2][4], b_fr[2][NBK];
+  // ---- per-lane fragment addresses (bytes); see the layout above ----
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS char*)smem;
+  uint32_t a_fr[A_NC ? MB : 1], b_fr[B_NC ? NB : 1];
   {
     const int b = lane >> 4, s = lane & 15;
+    const int chunk = ((2 * wk * SPT + (lane >> 5)) ^ ((lane >> 1) & 7)) * 16;
+    const int knc = 16 * wk * SPT + 8 * (b >> 1) + (s >> 2);
     if (!A_NC) {
-      const int row = wm * (32 * MB) + (lane & 31);
-      for (int kk = 0; kk < 2; ++kk)
-        a_fr[kk][0] = a_fr[kk][1] = a_fr[kk][2] = a_fr[kk][3] =
-            row * 64 + (((2 * kk + (lane >> 5)) ^ ((lane >> 2) & 3)) * 16);
+      a_fr[0] = lds0 + (wm * (32 * MB) + (lane & 31)) * 128 + chunk;
     } else {
-      for (int h = 0; h < 2; ++h)
-        for (int blk = 0; blk < 4; ++blk) {
-          const int col = wm * 128 + 32 * blk + 16 * (b & 1) + 4 * (s & 3);
-          const int k = 8 * (b >> 1) + 4 * h + (s >> 2);
-          a_fr[h][blk] = k * 512 + (((col >> 3) ^ (4 * (s >> 2))) * 16) + ((s & 1) * 8);
-        }
+#pragma unroll
+      for (int i = 0; i < (A_NC ? MB : 1); ++i) {
+        const int col = wm * (32 * MB) + 32 * i + 16 * (b & 1) + 4 * (s & 3);
+        a_fr[i] = lds0 + knc * (2 * TM) + (((col >> 3) ^ swz_nc(s >> 2, ACPR)) * 16) + ((s & 1) * 8);
+      }
     }
     if (!B_NC) {
-      const int row = wn * (32 * NBK) + (lane & 31);
-      for (int kk = 0; kk < 2; ++kk)
-        for (int blk = 0; blk < NBK; ++blk)
-          b_fr[kk][blk] = DREGION + row * 64 + (((2 * kk + (lane >> 5)) ^ ((lane >> 2) & 3)) * 16);
+      b_fr[0] = lds0 + SA * CF::A_UNIT + (wn * (32 * NB) + (lane & 31)) * 128 + chunk;
     } else {
-      for (int h = 0; h < 2; ++h)
-        for (int blk = 0; blk < NBK; ++blk) {
-          const int col = wn * (32 * NBK) + 32 * blk + 16 * (b & 1) + 4 * (s & 3);
-          const int k = 8 * (b >> 1) + 4 * h + (s >> 2);
-          b_fr[h][blk] = DREGION + k * 512 + (((col >> 3) ^ (4 * (s >> 2))) * 16) + ((s & 1) * 8);
-        }
+#pragma unroll
+      for (int j = 0; j < (B_NC ? NB : 1); ++j) {
+        const int col = wn * (32 * NB) + 32 * j + 16 * (b & 1) + 4 * (s & 3);
+        b_fr[j] = lds0 + SA * CF::A_UNIT + knc * (2 * TN) + (((col >> 3) ^ swz_nc(s >> 2, BCPR)) * 16) + ((s & 1) * 8);
+      }
     }
   }
-  Frag fa[2][MB], fb[2][NBK];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS char*)smem;
-  // fragments of k step kk of tile kt go to register set kk; part 0 = the four B fragments,
-  // part 1 = A fragments 0,1, part 2 = A fragments 2,3 (so the reads can be spread between MFMAs)
-  auto load_frags = [&](int stage, auto kk_tag, int part) {
-    constexpr int kk = decltype(kk_tag)::value;
-    const uint32_t st = lds0 + (uint32_t)stage * DSTAGE;
-    if (part == 0) {
-      if (!B_NC) {
-        lds_read_kc<0 * 2048>(fb[kk][0], st + b_fr[kk][0]); lds_read_kc<1 * 2048>(fb[kk][1], st + b_fr[kk][0]);
-        if (NBK == 4) {
-          lds_read_kc<2 * 2048>(fb[kk][NBK - 2], st + b_fr[kk][0]); lds_read_kc<3 * 2048>(fb[kk][NBK - 1], st + b_fr[kk][0]);
-        }
-      } else {
-        lds_read_nc<kk * 8192>(fb[kk][0], st + b_fr[0][0], st + b_fr[1][0]);
-        lds_read_nc<kk * 8192>(fb[kk][1], st + b_fr[0][1], st + b_fr[1][1]);
-        if (NBK == 4) {
-          lds_read_nc<kk * 8192>(fb[kk][NBK - 2], st + b_fr[0][NBK - 2], st + b_fr[1][NBK - 2]);
-          lds_read_nc<kk * 8192>(fb[kk][NBK - 1], st + b_fr[0][NBK - 1], st + b_fr[1][NBK - 1]);
-        }
-      }
-    } else if (part == 1) {
-      if (!A_NC) {
-        lds_read_kc<0 * 2048>(fa[kk][0], st + a_fr[kk][0]); lds_read_kc<1 * 2048>(fa[kk][1], st + a_fr[kk][0]);
-      } else {
-        lds_read_nc<kk * 8192>(fa[kk][0], st + a_fr[0][0], st + a_fr[1][0]);
-        lds_read_nc<kk * 8192>(fa[kk][1], st + a_fr[0][1], st + a_fr[1][1]);
-      }
+  Frag fa[2][MB], fb[2][NB];
+  // fragments of this wave's step ST in the ring slots go to register set ST & 1; piece 0 = B, piece 1 + n = A blocks
+  // 2 n, 2 n + 1 (so the reads can be spread between MFMAs)
+  constexpr int NPIECE = 1 + (MB + 1) / 2;
+  auto read_piece = [&](int slot_a, int slot_b, auto st_tag, auto piece_tag) {
+    constexpr int ST = decltype(st_tag)::value, P = decltype(piece_tag)::value, set = ST & 1;
+    if constexpr (P == 0) {
+      const uint32_t so = (uint32_t)slot_b * CF::B_UNIT;
+      unrolled<0, NB>([&](auto j) {
+        constexpr int J = decltype(j)::value;
+        if constexpr (!B_NC) lds_read_kc<J * 4096>(fb[set][J], (b_fr[0] + so) ^ (32u * ST));
+        else lds_read_nc<ST * 32 * TN, 8 * TN>(fb[set][J], b_fr[B_NC ? J : 0] + so);
+      });
     } else {
-      if (!A_NC) {
-        lds_read_kc<2 * 2048>(fa[kk][2], st + a_fr[kk][0]);
-        if (MB == 4) lds_read_kc<3 * 2048>(fa[kk][MB - 1], st + a_fr[kk][0]);
-      } else {
-        lds_read_nc<kk * 8192>(fa[kk][2], st + a_fr[0][2], st + a_fr[1][2]);
-        lds_read_nc<kk * 8192>(fa[kk][MB - 1], st + a_fr[0][3], st + a_fr[1][3]);
-      }
+      const uint32_t so = (uint32_t)slot_a * CF::A_UNIT;
+      unrolled<2 * (P - 1), (2 * P < MB ? 2 * P : MB)>([&](auto i) {
+        constexpr int I = decltype(i)::value;
+        if constexpr (!A_NC) lds_read_kc<I * 4096>(fa[set][I], (a_fr[0] + so) ^ (32u * ST));
+        else lds_read_nc<ST * 32 * TM, 8 * TM>(fa[set][I], a_fr[A_NC ? I : 0] + so);
+      });
     }
   };
   auto frags_ready = [&](int set) {
@@ -962,127 +742,235 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
 #pragma unroll
     for (int i = 0; i < MB; ++i) ready(fa[set][i]);
 #pragma unroll
-    for (int j = 0; j < NBK; ++j) ready(fb[set][j]);
+    for (int j = 0; j < NB; ++j) ready(fb[set][j]);
   };
-  using K0 = std::integral_constant<int, 0>;
-  using K1 = std::integral_constant<int, 1>;
 
-  f32x16_t acc[MB][NBK];
+  f32x16_t acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int j = 0; j < NBK; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
 
-  if (GATHER) {
-    int g_pro[4][4];
+  // Refill set t (issued after the barrier of tile t): tile t+SB of B, then tile t+SA of A.  kb, ka: its tiles.
+  constexpr int NREQ = RA + RB;
+  constexpr int PT_LAST = MB > 1 ? MB - 1 : 1;                       // issue points behind the barrier, in the last step
+  constexpr int PTS = PT_LAST + (SPT - 1) * MB;                      // ... and in the steps before the next barrier
+  constexpr int PER = (NREQ + PTS - 1) / PTS;
+  constexpr int N_LAST = PT_LAST * PER < NREQ ? PT_LAST * PER : NREQ;   // requests issued in the last step
+  constexpr int IN_FLIGHT = (SA > SB ? RA : 0) + (SB - 2) * (NREQ + (GATHER ? 1 : 0));    // newer requests than those of tile t+1, at barrier t
+  KTile ka{0, 0}, kb{0, 0};
+  int g_entry = 0;        // GATHER: slot-map entries of g_next, the tile after ka
+  KTile g_next{0, 0};
+  uint64_t k_mask[SA];    // TN: which k-rows of tiles t .. t + SA - 1 exist
+  auto mask_of = [&](const KTile& kt, uint64_t full) -> uint64_t {
+    return kt.lim >= DK ? full : kt.lim <= 0 ? 0ull : full & ((1ull << kt.lim) - 1ull);
+  };
+  // prologue: the refills that would have gone before the first tile, and the last-step part of set -1
+  {
+    KTile pro[SA];
 #pragma unroll
-    for (int t4 = 0; t4 < 4; ++t4) gather_fetch(t4, g_pro[t4]);
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    for (int t = 0; t < SA; ++t) pro[t] = KIND == KIND_TN ? next_ktile() : ktile_at(t);
+    int g_pro[SA];
+    if (GATHER) {
 #pragma unroll
-    for (int t4 = 0; t4 < 4; ++t4) {
-      gather_rows(g_pro[t4]);
-      request_half(t4, 0);
-      if (t4 < 3) request_half(t4, 1);
+      for (int t = 0; t < SA; ++t) g_pro[t] = gather_fetch(pro[t].row0);
+      g_next = next_ktile();
+      g_entry = gather_fetch(g_next.row0);
     }
-  } else {
-    request_half(0, 0); request_half(0, 1);
-    request_half(1, 0); request_half(1, 1);
-    request_half(2, 0); request_half(2, 1);
-    request_half(3, 0);
+    auto pro_a = [&](int t) {
+      const uint64_t full = GATHER ? gather_rows(g_pro[t]) : ~0ull;
+      k_mask[t] = mask_of(pro[t], full);
+    };
+#pragma unroll
+    for (int st = -SA; st <= -2; ++st) {
+      if (st + SB >= 0) {
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+          if (pro[st + SB].lim > 0) request_b(pro[st + SB], st + SB, j);
+      }
+      pro_a(st + SA);
+#pragma unroll
+      for (int j = 0; j < RA; ++j)
+        if (pro[st + SA].lim > 0) request_a(pro[st + SA], st + SA, j);
+    }
+    ka = pro[SA - 1];
+    kb = pro[SB - 1];
+    pro_a(SA - 1);
+    unrolled<0, N_LAST>([&](auto r) {
+      constexpr int R = decltype(r)::value;
+      if constexpr (R < RB) { if (kb.lim > 0) request_b(kb, SB - 1, R); }
+      else { if (ka.lim > 0) request_a(ka, SA - 1, R - RB); }
+    });
+    // this wave's requests for tile 0 have landed
+    if (nk >= SA) __builtin_amdgcn_s_waitcnt(vmcnt_imm(IN_FLIGHT + N_LAST));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    __builtin_amdgcn_s_barrier();
   }
-  // The padding test comes after the first requests are on their way, so that reading the counts
-  // delays no tile that has work (a padding tile has fetched a few zeros for nothing).
-  if (KIND != KIND_TN && p.cnt != nullptr) {
-    const int r_end = min(m0 + TMR, p.Mdim);
-    bool pad = true;
-    for (int sc = m0 / p.Cc; sc * p.Cc < r_end; ++sc) {
-      const int c_lo = max(m0 - sc * p.Cc, 0);
-      if (c_lo < p.cnt[sc * p.G + g]) { pad = false; break; }
-    }
-    if (pad) {
-      __builtin_amdgcn_s_waitcnt(0x0070);   // the requests in flight write LDS: let them land before leaving
-      f32x16_t none[MB][NBK] = {};
-      store_tile_lds<KIND, EPI, MB, NBK>(p, none, smem, g, m0 + wm * (32 * MB), n0 + wn * (32 * NBK), lane, true);
-      return;
-    }
-  }
-  // this wave's requests for tile 0 have landed (the 5 RPW issued after them may be in flight)
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(5 * RPW));
-  __builtin_amdgcn_s_barrier();
-  load_frags(0, K0{}, 0); load_frags(0, K0{}, 1); load_frags(0, K0{}, 2);
+  using K0 = std::integral_constant<int, 0>;
+  unrolled<0, NPIECE>([&](auto pc) { read_piece(0, 0, K0{}, pc); });
 
   auto mfma_row = [&](int set, int i) {
 #pragma unroll
-    for (int j = 0; j < NBK; ++j)
+    for (int j = 0; j < NB; ++j)
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j].v, fa[set][i].v, acc[i][j], 0, 0, 0);
   };
-  auto next_stage = [](int s_) { return s_ + 1 == DSTAGES ? 0 : s_ + 1; };
-  // Each k tile is two MFMA steps of MB rows (NBK MFMAs each).  Between the rows go, one piece at
-  // a time, the fragment reads of the next step and the tile requests, so that neither the LDS nor
-  // the address path sees a burst and the matrix pipe always has work queued.
-  //   step 0: B-operand requests of tile kt+3;  step 1: barrier, then A-operand requests of tile kt+4
-  // (stage of tile t = t mod 5: s0 holds tile kt, s1 tile kt+1, s3 tile kt+3, s4 tile kt+4 = the stage of kt-1)
-  int s0 = 0, s1 = 1, s3 = 3, s4 = 4;
-  for (int kt = 0; kt < nk; ++kt) {
-    frags_ready(0);
-    int g_idx[4];
-    if (GATHER) gather_fetch(kt + 4, g_idx);   // arrives by frags_ready(1)
-    __builtin_amdgcn_sched_barrier(0);
+  int sa = 0, sb = 0;                 // ring slots of the current tile
+  int wa = SA - 1, wb = SB - 1;       // ring slots that the refill set in progress goes to
+  auto issue = [&](auto from_tag, auto last_tag) {    // the next PER requests; LAST: the tile may be past the end
+    constexpr int F = decltype(from_tag)::value, N = PER;
+    constexpr bool LAST = decltype(last_tag)::value;
+    unrolled<F, (F + N < NREQ ? F + N : NREQ)>([&](auto r) {
+      constexpr int R = decltype(r)::value;
+      if constexpr (R < RB) { if (!LAST || kb.lim > 0) request_b(kb, wb, R); }
+      else { if (!LAST || ka.lim > 0) request_a(ka, wa, R - RB); }
+    });
+  };
+  // zeroes the k-rows of set `set` (step ST of a tile) that do not exist, in the A fragments
+  auto mask_frags = [&](uint64_t mask, auto st_tag, int set) {
+    constexpr int ST = decltype(st_tag)::value;
+    const uint32_t bits = (uint32_t)(mask >> (16 * (wk * SPT + ST))) >> (8 * (lane >> 5));
+    u32x4_t m;
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
-      mfma_row(0, i);
-      __builtin_amdgcn_sched_barrier(0);
-      if (i < 3) load_frags(s0, K1{}, i);
-      if (i < RPW) request1(kt + 3, s3, 1, i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    frags_ready(1);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_row(1, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    // tile kt+1 has landed (the 4 RPW requests of tiles kt+2, kt+3 issued after it may still be in flight)
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * RPW));
-    __builtin_amdgcn_s_barrier();        // everyone is past tile kt-1, and tile kt+1 is complete
-    __builtin_amdgcn_sched_barrier(0);
-    if (GATHER) gather_rows(g_idx);    // rows of tile kt+4
+    for (int d = 0; d < 4; ++d) m[d] = ((bits >> (2 * d)) & 1u) * 0x0000FFFFu + ((bits >> (2 * d + 1)) & 1u) * 0xFFFF0000u;
 #pragma unroll
-    for (int i = 1; i < MB; ++i) {
-      load_frags(s1, K0{}, i - 1);
-      if (MB == 3 && i == 2) load_frags(s1, K0{}, 2);
-      if (i - 1 < RPW) request1(kt + 4, s4, 0, i - 1);
+    for (int i = 0; i < MB; ++i) fa[set][i].q &= m;
+  };
+  // one k tile; LAST: one of the last SA tiles, whose refills may be past the end
+  auto k_tile = [&](int t, auto last_tag) {
+    constexpr bool LAST = decltype(last_tag)::value;
+    const int na = sa + 1 == SA ? 0 : sa + 1, nb = sb + 1 == SB ? 0 : sb + 1;   // slots of tile t+1
+    const uint64_t mask = KIND == KIND_TN ? k_mask[0] : LAST ? mask_of(ktile_at(t), ~0ull) : ~0ull;
+    unrolled<0, SPT>([&](auto st) {
+      constexpr int ST = decltype(st)::value, set = ST & 1;
+      using NEXT = std::integral_constant<int, (ST + 1) % SPT>;
+      frags_ready(set);
+      if constexpr (KIND == KIND_TN || LAST) {
+        if (mask != ~0ull) mask_frags(mask, st, set);
+      }
       __builtin_amdgcn_sched_barrier(0);
-      mfma_row(1, i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (RPW == 4) request1(kt + 4, s4, 0, 3);
-    s0 = s1; s1 = next_stage(s1); s3 = next_stage(s3); s4 = next_stage(s4);
+      if constexpr (ST < SPT - 1) {
+        unrolled<0, MB>([&](auto i) {
+          constexpr int I = decltype(i)::value;
+          mfma_row(set, I);
+          __builtin_amdgcn_sched_barrier(0);
+          unrolled<0, NPIECE>([&](auto pc) {
+            if constexpr (decltype(pc)::value * MB / NPIECE == I) read_piece(sa, sb, NEXT{}, pc);
+          });
+          issue(std::integral_constant<int, (PT_LAST + ST * MB + I) * PER>{}, last_tag);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      } else {
+        mfma_row(set, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(LAST ? 0 : IN_FLIGHT));   // this wave's requests for tile t+1 have landed
+        __builtin_amdgcn_s_barrier();                        // everyone is done with tile t, and tile t+1 is complete
+        __builtin_amdgcn_sched_barrier(0);
+        wa = sa; wb = sb;
+        if (KIND == KIND_TN) {
+          const KTile nx = GATHER ? g_next : next_ktile();
+          if constexpr (SA > SB) kb = ka; else kb = nx;
+          ka = nx;
+          uint64_t full = ~0ull;
+          if (GATHER) {
+            full = gather_rows(g_entry);
+            g_next = next_ktile();
+            g_entry = gather_fetch(g_next.row0);
+          }
+#pragma unroll
+          for (int u = 0; u + 1 < SA; ++u) k_mask[u] = k_mask[u + 1];
+          k_mask[SA - 1] = mask_of(ka, full);
+        } else {
+          ka = ktile_at(t + SA);
+          kb = ktile_at(t + SB);
+        }
+        unrolled<0, PT_LAST>([&](auto i1) {
+          constexpr int I1 = decltype(i1)::value;
+          unrolled<0, NPIECE>([&](auto pc) {
+            if constexpr (decltype(pc)::value * PT_LAST / NPIECE == I1) read_piece(na, nb, NEXT{}, pc);
+          });
+          issue(std::integral_constant<int, I1 * PER>{}, last_tag);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (I1 + 1 < MB) mfma_row(set, I1 + 1);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      }
+    });
+    sa = na; sb = nb;
+  };
+  const int n_main = nk - SA;    // every refill of these tiles exists
+  int t = 0;
+  for (; t < n_main; ++t) k_tile(t, std::false_type{});
+  for (; t < nk; ++t) k_tile(t, std::true_type{});
+  __builtin_amdgcn_s_waitcnt(0x0070);  // every request and fragment read is done before LDS is reused
+  __syncthreads();
+
+  if constexpr (WK == 2) {   // each of the two wave groups finishes half of the blocks: exchange the other halves
+    f32x16_t mine[EMB][ENB];
+    float4* xch = reinterpret_cast<float4*>(smem) + (size_t)wave * (EMB * ENB * 4 * 64);
+    const float4* oth = reinterpret_cast<const float4*>(smem) + (size_t)(wave ^ (WM * WN)) * (EMB * ENB * 4 * 64);
+#pragma unroll
+    for (int i = 0; i < EMB; ++i)
+#pragma unroll
+      for (int j = 0; j < ENB; ++j)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          float own[4], snd[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float lo = acc[i][j][q4 * 4 + e];
+            const float hi = ONE ? lo : acc[MB >= 2 ? EMB + i : i][MB >= 2 ? j : (ONE ? 0 : ENB) + j][q4 * 4 + e];
+            own[e] = wk ? hi : lo;
+            snd[e] = wk ? lo : hi;
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) mine[i][j][q4 * 4 + e] = own[e];
+          xch[((i * ENB + j) * 4 + q4) * 64 + lane] = make_float4(snd[0], snd[1], snd[2], snd[3]);
+        }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < EMB; ++i)
+#pragma unroll
+      for (int j = 0; j < ENB; ++j)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const float4 v = oth[((i * ENB + j) * 4 + q4) * 64 + lane];
+          mine[i][j][q4 * 4 + 0] += v.x; mine[i][j][q4 * 4 + 1] += v.y;
+          mine[i][j][q4 * 4 + 2] += v.z; mine[i][j][q4 * 4 + 3] += v.w;
+        }
+    __syncthreads();
+    if (ONE && wk != 0) return;
+    store_tile_lds<KIND, EPI, EMB, ENB>(p, mine, e_lds, g, m0 + wm * (32 * MB), 32 * e_i, e_n, out_off, lane);
+  } else {
+    store_tile_lds<KIND, EPI, MB, NB>(p, acc, e_lds, g, m0 + wm * (32 * MB), 0, e_n, out_off, lane);
   }
-  __builtin_amdgcn_s_waitcnt(0x0070);  // drain trailing (empty) requests and fragment reads before LDS is released
-
-  __syncthreads();  // every wave is done reading fragments: the stage memory can be reused
-  store_tile_lds<KIND, EPI, MB, NBK>(p, acc, smem + wave * (DSTAGES * DSTAGE / (2 * WN)), g, m0 + wm * (32 * MB),
-                                 n0 + wn * (32 * NBK), lane);
 }
 
-template <int KIND, int EPI, int WN, int TMR = 256, bool GATHER = false>
-__global__ __launch_bounds__(128 * WN) void ffn_gemm_dma(const GemmArgs p) {
-  __shared__ __attribute__((aligned(1024))) char smem[DSTAGES * DSTAGE];
-  gemm_dma_tile<KIND, EPI, WN, TMR, GATHER>(p, smem, (int)blockIdx.x);
+template <int KIND, int EPI, typename CF, bool GATHER = false>
+__global__ __launch_bounds__(64 * CF::NW) void ffn_gemm_dma(const GemmArgs p) {
+  __shared__ __attribute__((aligned(1024))) char smem[CF::LDS];
+  gemm_dma_tile<KIND, EPI, CF, GATHER>(p, smem, (int)blockIdx.x);
 }
+
+using Tile256 = TileCfg<256, 256, 2, 4, 1, 3, 2>;
+using Tile192 = TileCfg<192, 256, 2, 4, 1, 3, 2>;
+using Tile128 = TileCfg<128, 128, 2, 2, 2, 3, 2>;
+using Tile64x128 = TileCfg<64, 128, 1, 4, 2, 3, 3>;
+using Tile64 = TileCfg<64, 64, 1, 2, 2, 5, 5>;
+using Tile32x64 = TileCfg<32, 64, 1, 2, 2, 6, 6>;
 
 // The three GEMMs of the backward pass that only depend on dZ, in one launch: dX = dZ W1^T (row-tiled,
 // the long tiles, first in the grid) and the two weight gradients.  nbx and nbw are the (multiple-of-8)
 // workgroup counts of the first two problems.
-template <int TMR_X, bool GATHER_W1 = false>   // GATHER_W1: the third problem reads its A operand through a slot map
+template <typename CFX, bool GATHER_W1 = false>   // GATHER_W1: the third problem reads its A operand through a slot map
 __global__ __launch_bounds__(512) void ffn_bwd_trio(const GemmArgs px, const GemmArgs pw2, const GemmArgs pw1, int nbx,
                                                     int nbw) {
-  __shared__ __attribute__((aligned(1024))) char smem[DSTAGES * DSTAGE];
+  __shared__ __attribute__((aligned(1024))) char smem[Tile256::LDS];
   const int b = (int)blockIdx.x;
-  if (b < nbx) gemm_dma_tile<KIND_NT, EPI_STORE, 4, TMR_X>(px, smem, b);
-  else if (b < nbx + nbw) gemm_dma_tile<KIND_TN, EPI_STORE, 4, 256>(pw2, smem, b - nbx);
-  else gemm_dma_tile<KIND_TN, EPI_STORE, 4, 256, GATHER_W1>(pw1, smem, b - nbx - nbw);
+  if (b < nbx) gemm_dma_tile<KIND_NT, EPI_STORE, CFX>(px, smem, b);
+  else if (b < nbx + nbw) gemm_dma_tile<KIND_TN, EPI_STORE, Tile256>(pw2, smem, b - nbx);
+  else gemm_dma_tile<KIND_TN, EPI_STORE, Tile256, GATHER_W1>(pw1, smem, b - nbx - nbw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1199,41 +1087,62 @@ int num_cus() {
   return n;
 }
 
-// Which bf16 kernel and tile a grouped GEMM gets: tile_m x tile_n output tiles; dma = the LDS-DMA
-// kernel (the only one that skips padding rows).  `tile` is the caller's hint (MOE_TILE_*).
+// Tile of a bf16 grouped GEMM, tile_m x tile_n.
 struct TilePlan {
-  bool dma;
   int tile_m, tile_n;
 };
-TilePlan plan_tiles(int tile, bool tn, int G, int Mdim, int Ndim) {
-  TilePlan t;
-  const int64_t big_tiles = (int64_t)G * ((Mdim + 255) / 256) * ((Ndim + 255) / 256);
-  t.dma = tile == MOE_TILE_AUTO ? big_tiles >= 64 : tile != MOE_TILE_SMALL;
-  t.tile_n = t.dma ? 256 : 128;
-  t.tile_m = t.tile_n;
-  // 192-row tiles when they need no more rounds of the chip's compute units (weighted by tile height)
-  if (t.dma && !tn && tile != MOE_TILE_256) {
-    const int64_t tiles_n = (Ndim + 255) / 256;
-    const int64_t t256 = (int64_t)G * ((Mdim + 255) / 256) * tiles_n;
-    const int64_t t192 = (int64_t)G * ((Mdim + 191) / 192) * tiles_n;
-    const int64_t cu = num_cus();
-    if (tile == MOE_TILE_192 || ((t192 + cu - 1) / cu) * 192 <= ((t256 + cu - 1) / cu) * 256) t.tile_m = 192;
+// The tiles a row-tiled GEMM may take, and what one costs (microseconds, measured): a k tile of 64 with few and with all
+// compute units busy (a compute unit holds one workgroup of the first two, two of the others), and everything
+// outside the k loop.  Large tiles move the fewest bytes per flop; small ones fill the chip when there are few
+// rows, and their k tile is short when a long reduction is what a launch waits for.
+struct TileCost {
+  TilePlan tile;
+  int per_cu;
+  float k_few, k_all, fixed;
+};
+constexpr TileCost ROW_TILES[] = {{{256, 256}, 1, 0.95f, 1.50f, 10.f}, {{192, 256}, 1, 0.72f, 1.22f, 9.f},
+                                  {{128, 128}, 2, 0.50f, 1.05f, 7.f},  {{64, 128}, 2, 0.31f, 0.66f, 6.f},
+                                  {{64, 64}, 2, 0.24f, 0.42f, 6.f},    {{32, 64}, 2, 0.20f, 0.30f, 5.f}};
+// `tile` is the caller's hint (MOE_TILE_*); wide = only tiles that the merged backward launch can take (eight waves).
+TilePlan plan_tiles(int tile, bool tn, int G, int Mdim, int Ndim, int Kdim, bool wide = false) {
+  auto tiles = [&](TilePlan t) { return (int64_t)G * ((Mdim + t.tile_m - 1) / t.tile_m) * ((Ndim + t.tile_n - 1) / t.tile_n); };
+  if (tile == MOE_TILE_SMALL) return {128, 128};
+  if (tile == MOE_TILE_256) return {256, 256};
+  if (tn) return tile == MOE_TILE_AUTO && tiles({256, 256}) < 64 ? TilePlan{128, 128} : TilePlan{256, 256};
+  if (tile == MOE_TILE_192) return {192, 256};
+  const float nk = (float)((Kdim + 63) / 64), cu = (float)num_cus();
+  TilePlan best{256, 256};
+  float best_t = 0.f;
+  for (const TileCost& c : ROW_TILES) {
+    if (wide && c.tile.tile_n == 64) continue;
+    const float n = (float)tiles(c.tile);
+    const float busy = c.per_cu == 1 ? n / cu : (n - cu) / cu;
+    const float k = c.k_few + (c.k_all - c.k_few) * fminf(fmaxf(busy, 0.f), 1.f);
+    const float t = ceilf(n / (cu * c.per_cu)) * (nk * k + c.fixed);
+    if (best_t == 0.f || t < best_t) { best_t = t; best = c.tile; }
   }
-  return t;
+  return best;
 }
 
 // fills the tile counts and buffer sizes of a bf16 problem
-TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile) {
-  a.kchunks = (a.Cc + KT - 1) / KT;
+TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile, bool wide = false) {
   const uint64_t act_rows = (uint64_t)a.n_src * a.G * a.Cc;
   a.a_bytes = (a.gather ? (uint64_t)a.gather_rows : act_rows) * (uint64_t)a.lda * 2;
   a.b_bytes = tn ? act_rows * (uint64_t)a.ldb * 2 : (uint64_t)a.G * (uint64_t)a.b_goff * 2;
-  const TilePlan t = plan_tiles(tile, tn, a.G, a.Mdim, a.Ndim);
+  // Rows of capacity padding are not multiplied; how many there are is not known here.  Where counts are passed the
+  // plan is priced for nine rows in ten (capacity factors are 1 to 1.25), so that a last row tile that will mostly be
+  // padding does not decide the height.
+  const int rows = !tn && a.cnt ? (int)(((int64_t)a.Mdim * 9 + 9) / 10) : a.Mdim;
+  const TilePlan t = plan_tiles(tile, tn, a.G, rows, a.Ndim, a.Kdim, wide);
   a.tiles_n = (a.Ndim + t.tile_n - 1) / t.tile_n;
   a.tiles_m = (a.Mdim + t.tile_m - 1) / t.tile_m;
   a.total_tiles = a.G * a.tiles_m * a.tiles_n;
   return t;
 }
+
+// Workgroups of a problem, a multiple of 8: every XCD takes an equal share of the tiles to multiply and, with row
+// counts, an equal share of the tiles of zeros, each share rounded up.
+int grid_of(const GemmArgs& a) { return (a.total_tiles + (a.cnt ? 14 : 7)) / 8 * 8; }
 
 template <int KIND, int EPI>
 void launch_gemm(GemmArgs a, int dtype, int tile, hipStream_t st) {
@@ -1245,15 +1154,23 @@ void launch_gemm(GemmArgs a, int dtype, int tile, hipStream_t st) {
     return;
   }
   const TilePlan t = prepare_bf16(a, KIND == KIND_TN, tile);
-  const dim3 grid((unsigned)(((a.total_tiles + 7) / 8) * 8));
-  if (!t.dma) {
-    hipLaunchKernelGGL((ffn_gemm_bf16<128, 128, 2, 2, KIND, EPI>), grid, dim3(256), 0, st, a);
-  } else if (t.tile_m == 192) {
-    if constexpr (KIND != KIND_TN) hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, 4, 192>), grid, dim3(512), 0, st, a);
-  } else if (KIND == KIND_TN && a.gather != nullptr) {
-    if constexpr (KIND == KIND_TN) hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, 4, 256, true>), grid, dim3(512), 0, st, a);
-  } else {
-    hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, 4>), grid, dim3(512), 0, st, a);
+  const dim3 grid((unsigned)grid_of(a));
+  auto launch = [&](auto cfg) {
+    using CF = decltype(cfg);
+    if constexpr (KIND == KIND_TN) {
+      if (a.gather != nullptr) hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF, true>), grid, dim3(64 * CF::NW), 0, st, a);
+      else hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF>), grid, dim3(64 * CF::NW), 0, st, a);
+    } else {
+      hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF>), grid, dim3(64 * CF::NW), 0, st, a);
+    }
+  };
+  if (t.tile_m == 128) return launch(Tile128{});
+  if (t.tile_m == 256) return launch(Tile256{});
+  if constexpr (KIND != KIND_TN) {
+    if (t.tile_m == 192) launch(Tile192{});
+    else if (t.tile_m == 64 && t.tile_n == 128) launch(Tile64x128{});
+    else if (t.tile_m == 64) launch(Tile64{});
+    else launch(Tile32x64{});
   }
 }
 
@@ -1278,11 +1195,11 @@ int check_ffn_shape(int dtype, int n_src, int G, int64_t C, int M, int H, int es
 
 // multiplied rows of a row-tiled GEMM (outputs [R rows per expert] x N), or of the reduction of a
 // weight-gradient GEMM, given host-side row counts
-static double rows_multiplied(int tile, bool tn, int dtype, int n_src, int G, int64_t C, int Mdim, int Ndim,
+static double rows_multiplied(int tile, bool tn, int dtype, int n_src, int G, int64_t C, int Mdim, int Ndim, int Kdim,
                               const int32_t* cnt) {
   const int64_t R = (int64_t)n_src * C;
-  const TilePlan t = plan_tiles(tile, tn, G, Mdim, Ndim);
-  if (cnt == nullptr || dtype != MOE_BF16 || !t.dma) return (double)G * (double)R;
+  const TilePlan t = plan_tiles(tile, tn, G, !tn && cnt ? (int)(((int64_t)Mdim * 9 + 9) / 10) : Mdim, Ndim, Kdim);
+  if (cnt == nullptr || dtype != MOE_BF16 || tile == MOE_TILE_SMALL) return (double)G * (double)R;
   double rows = 0;
   for (int g = 0; g < G; ++g) {
     if (tn) {
@@ -1311,11 +1228,11 @@ extern "C" double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C,
   const int R = (int)(n_src * C);
   const int32_t* c = row_counts_host;
   const double mh = 2.0 * (double)M * (double)Hl;
+  auto rows = [&](bool tn, int Mdim, int Ndim, int Kdim) { return rows_multiplied(tile, tn, dtype, n_src, G, C, Mdim, Ndim, Kdim, c); };
   if (!backward)   // Z = X W1 (rows x Hl), Y = A W2 (rows x M)
-    return mh * (rows_multiplied(tile, false, dtype, n_src, G, C, R, Hl, c) + rows_multiplied(tile, false, dtype, n_src, G, C, R, M, c));
+    return mh * (rows(false, R, Hl, M) + rows(false, R, M, Hl));
   // dA = dY W2^T (rows x Hl), dW2 (Hl x M over the rows), dW1 (M x Hl over the rows), dX = dZ W1^T (rows x M)
-  return mh * (rows_multiplied(tile, false, dtype, n_src, G, C, R, Hl, c) + rows_multiplied(tile, true, dtype, n_src, G, C, Hl, M, c) +
-               rows_multiplied(tile, true, dtype, n_src, G, C, M, Hl, c) + rows_multiplied(tile, false, dtype, n_src, G, C, R, M, c));
+  return mh * (rows(false, R, Hl, M) + rows(true, Hl, M, R) + rows(true, M, Hl, R) + rows(false, R, M, Hl));
 }
 
 extern "C" size_t moe_ffn_workspace_bytes(int dtype, int n_src, int G, int64_t C, int M, int H, int n_esp) {
@@ -1323,6 +1240,8 @@ extern "C" size_t moe_ffn_workspace_bytes(int dtype, int n_src, int G, int64_t C
   const size_t esz = dtype == MOE_BF16 ? 2 : 4;
   return moe::align_up((size_t)n_src * G * C * (size_t)(H / n_esp) * esz, 256);   // dZ
 }
+
+static uint32_t magic_of(int k) { return k > 1 ? (uint32_t)((0x100000000ull + (uint64_t)k - 1) / (uint64_t)k) : 0u; }
 
 static int ffn_fwd_impl(const void* X, const int32_t* gather, int gather_k, int64_t gather_rows, int dtype,
                         const void* W1, const void* W2, int n_src, int G, int64_t C, int M, int H, int esp_idx,
@@ -1337,17 +1256,18 @@ static int ffn_fwd_impl(const void* X, const int32_t* gather, int gather_k, int6
   const int64_t h0 = (int64_t)esp_idx * Hl;
 
   GemmArgs a{};
-  a.G = G; a.n_src = n_src; a.Cc = (int)C; a.R = (int)(n_src * C); a.cnt = row_counts;
+  a.G = G; a.n_src = n_src; a.Cc = (int)C; a.R = (int)(n_src * C);
+  a.cnt = tile == MOE_TILE_SMALL ? nullptr : row_counts;
   // Z = X * W1[:, h0:h0+Hl] ; A = GeLU(Z)
   a.A = X; a.lda = M;
-  a.gather = gather; a.gather_k = gather_k; a.gather_rows = gather_rows;
+  a.gather = gather; a.gather_k = gather_k; a.gather_rows = gather_rows; a.gather_magic = magic_of(gather_k);
   a.B = W1; a.ldb = H; a.b_goff = (int64_t)M * H; a.b_off = h0;
   a.C = Z; a.C2 = A; a.ldc = Hl;
   a.Mdim = a.R; a.Ndim = Hl; a.Kdim = M;
   launch_gemm<KIND_NN, EPI_GELU>(a, dtype, tile, st);
   // Y = A * W2[h0:h0+Hl, :]
   a.A = A; a.lda = Hl;
-  a.gather = nullptr; a.gather_k = 0; a.gather_rows = 0;
+  a.gather = nullptr; a.gather_k = 0; a.gather_rows = 0; a.gather_magic = 0;
   a.B = W2; a.ldb = M; a.b_goff = (int64_t)H * M; a.b_off = h0 * M;
   a.C = Y; a.C2 = nullptr; a.ldc = M;
   a.Mdim = a.R; a.Ndim = M; a.Kdim = Hl;
@@ -1396,7 +1316,8 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
   void* dZ = ws;
 
   GemmArgs a{};
-  a.G = G; a.n_src = n_src; a.Cc = (int)C; a.R = (int)(n_src * C); a.cnt = row_counts;
+  a.G = G; a.n_src = n_src; a.Cc = (int)C; a.R = (int)(n_src * C);
+  a.cnt = tile == MOE_TILE_SMALL ? nullptr : row_counts;
   // dA = dY * W2[h0:h0+Hl, :]^T ; dZ = dA * GeLU'(Z)
   a.A = dY; a.lda = M;
   a.B = W2; a.ldb = M; a.b_goff = (int64_t)H * M; a.b_off = h0 * M;
@@ -1413,7 +1334,7 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
   GemmArgs w1 = w2;
   w1.A = X; w1.lda = M;
   w1.gather = gather; w1.gather_k = gather_k; w1.gather_rows = gather_rows;
-  w1.gather_magic = gather_k > 1 ? (uint32_t)((0x100000000ull + (uint64_t)gather_k - 1) / (uint64_t)gather_k) : 0u;
+  w1.gather_magic = magic_of(gather_k);
   w1.B = dZ; w1.ldb = Hl;
   w1.C = dW1; w1.ldc = H; w1.c_goff = (int64_t)M * H; w1.c_off = h0;
   w1.Mdim = M; w1.Ndim = Hl; w1.Kdim = a.R;
@@ -1427,17 +1348,19 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
   if (dtype == MOE_BF16) {
     // the three are independent: one launch, long row tiles first, if all of them take the LDS-DMA kernel
     GemmArgs px = dx, p2 = w2, p1 = w1;
-    const TilePlan tx = prepare_bf16(px, false, tile), t2 = prepare_bf16(p2, true, tile), t1 = prepare_bf16(p1, true, tile);
-    if (tx.dma && t2.dma && t1.dma) {
-      const int nbx = (px.total_tiles + 7) / 8 * 8, nb2 = (p2.total_tiles + 7) / 8 * 8, nb1 = (p1.total_tiles + 7) / 8 * 8;
+    const TilePlan tx = prepare_bf16(px, false, tile, true), t2 = prepare_bf16(p2, true, tile), t1 = prepare_bf16(p1, true, tile);
+    if (t2.tile_m == 256 && t1.tile_m == 256) {
+      const int nbx = grid_of(px), nb2 = grid_of(p2), nb1 = grid_of(p1);
       const dim3 grid((unsigned)(nbx + nb2 + nb1));
-      if (gather) {
-        if (tx.tile_m == 192) hipLaunchKernelGGL((ffn_bwd_trio<192, true>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-        else hipLaunchKernelGGL((ffn_bwd_trio<256, true>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-      } else {
-        if (tx.tile_m == 192) hipLaunchKernelGGL((ffn_bwd_trio<192>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-        else hipLaunchKernelGGL((ffn_bwd_trio<256>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-      }
+      auto launch = [&](auto cfg) {
+        using CF = decltype(cfg);
+        if (gather) hipLaunchKernelGGL((ffn_bwd_trio<CF, true>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
+        else hipLaunchKernelGGL((ffn_bwd_trio<CF>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
+      };
+      if (tx.tile_m == 256) launch(Tile256{});
+      else if (tx.tile_m == 192) launch(Tile192{});
+      else if (tx.tile_m == 128) launch(Tile128{});
+      else launch(Tile64x128{});
       return moe::check_launch();
     }
   }
