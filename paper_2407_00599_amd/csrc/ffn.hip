@@ -25,7 +25,7 @@
 // all its chunks first, so that only ceil(occupied / tile) row tiles are multiplied however the occupancy is spread
 // over the chunks; the weight gradients skip the k tiles of a chunk that lie behind its count.
 //
-// fp32 path: a plain LDS-tiled kernel with fp64 accumulation, for the small fp32 configuration.
+// fp32 path: a kernel on the fp64 matrix cores (fp64 accumulation), row counts used the same way.
 #include <math.h>
 
 #include <type_traits>
@@ -495,6 +495,50 @@ __device__ __forceinline__ void compact_rows(const GemmArgs& p, int g, const int
   }
 }
 
+struct KTile {
+  int row0, lim;   // first row of the k tile in the operand (row-tiled GEMMs: first k), rows (k values) that exist
+};
+// The reduction of a weight gradient runs over the expert's rows chunk by chunk (a k tile never crosses a chunk), and a
+// chunk's k tiles end at its row count; empty chunks are passed over.
+struct ChunkWalk {
+  const GemmArgs& p;
+  int g, cnt = 0, s0 = 0, row = 0, left = 0;   // cnt: rows of chunk s0 + lane
+  unsigned long long mask = 0;
+  __device__ __forceinline__ ChunkWalk(const GemmArgs& p_, int g_) : p(p_), g(g_) {}
+  __device__ __forceinline__ void load() {     // counts of chunks s0 .. s0 + 63, one per lane
+    const int s = s0 + (threadIdx.x & 63);
+    cnt = s < p.n_src ? (p.cnt != nullptr ? clamp_count(p.cnt[s * p.G + g], p.Cc) : p.Cc) : 0;
+    mask = __ballot(cnt > 0);
+  }
+  __device__ __forceinline__ int start(int step) {   // returns the number of k tiles
+    int nk = 0;
+    for (s0 = 0; s0 < p.n_src; s0 += 64) {
+      load();
+      int n = (cnt + step - 1) / step;
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
+      nk += __builtin_amdgcn_readfirstlane(n);
+    }
+    s0 = 0;
+    if (p.n_src > 64) load();
+    return nk;
+  }
+  __device__ __forceinline__ KTile next(int step) {   // past the end: no rows
+    if (left <= 0) {
+      while (mask == 0 && s0 + 64 < p.n_src) { s0 += 64; load(); }
+      if (mask == 0) return KTile{0, 0};
+      const int l = __ffsll((long long)mask) - 1;
+      mask &= mask - 1;
+      left = __builtin_amdgcn_readlane(cnt, l);
+      row = ((s0 + l) * p.G + g) * p.Cc;
+    }
+    const KTile t{row, min(left, step)};
+    row += step;
+    left -= step;
+    return t;
+  }
+};
+
 // GATHER: the k-slow A operand of a weight-gradient GEMM (X^T dZ) is the token matrix read through the
 // inverse slot map (row r of the chunk is token gather[g C + r] / gather_k); n_src = 1.
 template <int KIND, int EPI, typename CF, bool GATHER = false>
@@ -576,44 +620,10 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     return;
   }
 
-  // ---- k tiles.  Row-tiled GEMMs: Kdim / 64.  Weight gradients: the reduction runs over the expert's rows, chunk by
-  // chunk (a k tile never crosses a chunk), and a chunk's k tiles end at its row count. ----
-  int nk;
-  int ch_cnt = 0, ch_s0 = 0, ch_c0 = 0, ch_row = 0, ch_lim = 0, ch_left = 0;   // TN: walk over the chunks
-  unsigned long long ch_mask = 0;
-  auto load_chunks = [&]() {     // counts of chunks ch_s0 .. ch_s0 + 63, one per lane
-    const int s = ch_s0 + lane;
-    ch_cnt = s < p.n_src ? (p.cnt != nullptr ? clamp_count(p.cnt[s * p.G + g], p.Cc) : p.Cc) : 0;
-    ch_mask = __ballot(ch_cnt > 0);
-  };
-  if (KIND == KIND_TN) {
-    nk = 0;
-    for (ch_s0 = 0; ch_s0 < p.n_src; ch_s0 += 64) {
-      load_chunks();
-      int n = (ch_cnt + DK - 1) / DK;
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
-      nk += __builtin_amdgcn_readfirstlane(n);
-    }
-    if (p.n_src > 64) { ch_s0 = 0; load_chunks(); } else ch_s0 = 0;
-  } else {
-    nk = (p.Kdim + DK - 1) / DK;
-  }
-  struct KTile { int row0, lim; };   // first row of the k tile in the operand, rows (k values) that exist
-  auto next_ktile = [&]() -> KTile {   // TN: the next k tile of the walk; past the end: no rows
-    if (ch_left <= 0) {
-      while (ch_mask == 0 && ch_s0 + 64 < p.n_src) { ch_s0 += 64; load_chunks(); }
-      if (ch_mask == 0) return KTile{0, 0};
-      const int l = __ffsll((long long)ch_mask) - 1;
-      ch_mask &= ch_mask - 1;
-      ch_left = __builtin_amdgcn_readlane(ch_cnt, l);
-      ch_row = ((ch_s0 + l) * p.G + g) * p.Cc;
-    }
-    const KTile t{ch_row, min(ch_left, DK)};
-    ch_row += DK;
-    ch_left -= DK;
-    return t;
-  };
+  // ---- k tiles: Kdim / 64 of a row-tiled GEMM, the walk over the expert's chunks for a weight gradient ----
+  ChunkWalk walk(p, g);
+  const int nk = KIND == KIND_TN ? walk.start(DK) : (p.Kdim + DK - 1) / DK;
+  auto next_ktile = [&]() { return walk.next(DK); };
 
   // ---- per-lane request coordinates: byte offset of the lane's row / column, the k index within the tile that the
   // request covers (k-slow) or starts at (k-contiguous), and the byte offset of that k index ----
@@ -974,103 +984,226 @@ __global__ __launch_bounds__(512) void ffn_bwd_trio(const GemmArgs px, const Gem
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 kernel: 64x64 tile, 256 threads, 4x4 outputs per thread, fp64 accumulation.
+// fp32 kernel: fp64 matrix cores (v_mfma_f64_16x16x4_f64: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and
+// receives D[4 r + l / 16][l % 16], r = 0..3), fp64 accumulation.
+//
+// TM x 64 tile, four waves (2 x 2), k chunks of 32: both operands are converted to fp64 once per workgroup on their way
+// into LDS ([k][row], pitch T + 16 doubles: the two k planes of a 32-lane read fall into different halves of the
+// banks; row r of k is at r ^ 8 (k / 4), so that the eight k groups that a wave writes for k-contiguous operands do too);
+// the next chunk is requested into registers before the current one is multiplied.
+// Bound by the fp64 matrix rate (70 TFLOP/s measured for the bare instruction), less the conversions (16 cycles per wave
+// and 64 values, during which the matrix unit waits: an eighth of a 64 x 64 tile) and, with few rows, the fill and
+// drain of a workgroup.  The tiles are small because the fp32 problems are.  8 experts x 4096 rows x 512 x 2048: 55 to 59
+// TFLOP/s; x 256 rows: 37 to 49, where fp64 vector FMAs on 64 x 64 tiles reached 11 to 25 and multiplied all padding.
 // ------------------------------------------------------------------------------------------
-template <int KIND, int EPI>
-__global__ __launch_bounds__(256) void ffn_gemm_f32(const GemmArgs p) {
-  constexpr int T = 64, KS = 16;
-  __shared__ float As[KS][T + 4];
-  __shared__ float Bs[KS][T + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int tile = blockIdx.x;
-  const int tiles_per_g = p.tiles_m * p.tiles_n;
-  const int g = tile / tiles_per_g;
-  const int tr = tile - g * tiles_per_g;
-  const int m0 = (tr / p.tiles_n) * T, n0 = (tr % p.tiles_n) * T;
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+constexpr int FK = 32;   // k chunk
+template <int TM, int TN>
+constexpr int f32_lds() { return FK * (TM + 16 + TN + 16) * 8; }
+template <int KIND, int EPI, int TM, int TN>
+__device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int vb) {
+  constexpr int PA = TM + 16, PB = TN + 16;
+  constexpr bool A_NC = KIND == KIND_TN, B_NC = KIND != KIND_NT;   // k is the slow index in memory
+  constexpr int MB = TM / 32, NB = TN / 32;                         // 16 x 16 blocks per wave
+  constexpr int UA = TM * FK / 4 / 256, UB = TN * FK / 4 / 256;     // 16-byte pieces per thread and chunk
+  double* Bs = As + FK * PA;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  int g, tm, tn;
+  const bool counted = KIND != KIND_TN && p.cnt != nullptr;
+  const int what = map_tile<TM>(p, vb, counted, g, tm, tn);
+  if (what == 0) return;
+  const int m0 = tm * TM, n0 = tn * TN;
   const float* __restrict__ A = reinterpret_cast<const float*>(p.A);
-  const float* __restrict__ B = reinterpret_cast<const float*>(p.B);
-  const int Kd = (KIND == KIND_TN) ? p.R : p.Kdim;
-  double acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
+  const float* __restrict__ B = reinterpret_cast<const float*>(p.B) + (KIND == KIND_TN ? 0 : (int64_t)g * p.b_goff + p.b_off);
 
-  for (int k0 = 0; k0 < Kd; k0 += KS) {
+  // rows: of this thread's A pieces (row-tiled GEMMs) and, lane l, of output row l of the tile
+  int a_row[UA], o_row = 0;
+  bool o_zero = false;
+  if (KIND != KIND_TN) {
+    int r[UA + 1], row[UA + 1];
+    bool occ[UA + 1];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = tid + q * 256;  // 1024 elements per operand tile
-      {
-        // A tile element (i, k)
-        int i, k;
-        if (KIND == KIND_TN) { i = c & 63; k = c >> 6; } else { k = c & 15; i = c >> 4; }
-        float v = 0.f;
-        if (m0 + i < p.Mdim && k0 + k < Kd) {
-          if (KIND == KIND_TN) {
-            const int64_t row = a_src_row(p, k0 + k, g);
-            if (row >= 0) v = A[row * p.lda + m0 + i];
-          }
-          else {
-            const int64_t row = a_src_row(p, m0 + i, g);
-            if (row >= 0) v = A[row * p.lda + k0 + k];
-          }
+    for (int u = 0; u < UA; ++u) r[u] = m0 + (tid + 256 * u) / (FK / 4);
+    r[UA] = m0 + lane;
+    if (counted && p.n_src > 1) {
+      compact_rows<UA + 1>(p, g, r, row, occ);
+    } else {
+      const int cnt_g = counted ? clamp_count(p.cnt[g], p.Cc) : p.Mdim;
+#pragma unroll
+      for (int u = 0; u <= UA; ++u) {
+        occ[u] = r[u] < cnt_g;
+        row[u] = (int)phys_row(min(r[u], p.Mdim - 1), g, p.G, p.Cc);
+        if (p.gather != nullptr) {
+          const int64_t tok = a_src_row(p, min(r[u], p.Mdim - 1), g);
+          occ[u] = occ[u] && tok >= 0;
+          if (u < UA) row[u] = (int)tok;
         }
-        As[k][i] = v;
-      }
-      {
-        // B tile element (k, j)
-        int j, k;
-        if (KIND == KIND_NT) { k = c & 15; j = c >> 4; } else { j = c & 63; k = c >> 6; }
-        float v = 0.f;
-        if (n0 + j < p.Ndim && k0 + k < Kd) {
-          if (KIND == KIND_NN) v = B[(int64_t)g * p.b_goff + p.b_off + (int64_t)(k0 + k) * p.ldb + n0 + j];
-          else if (KIND == KIND_NT) v = B[(int64_t)g * p.b_goff + p.b_off + (int64_t)(n0 + j) * p.ldb + k0 + k];
-          else v = B[phys_row(k0 + k, g, p.G, p.Cc) * p.ldb + n0 + j];
-        }
-        Bs[k][j] = v;
       }
     }
-    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const float4 a = *reinterpret_cast<const float4*>(&As[k][ty * 4]);
-      const float4 b = *reinterpret_cast<const float4*>(&Bs[k][tx * 4]);
-      const double ad[4] = {(double)a.x, (double)a.y, (double)a.z, (double)a.w};
-      const double bd[4] = {(double)b.x, (double)b.y, (double)b.z, (double)b.w};
+    for (int u = 0; u < UA; ++u) a_row[u] = (r[u] < p.Mdim && occ[u]) ? row[u] : 0;   // no row: any row, its results are not stored
+    o_row = r[UA] < p.Mdim ? row[UA] : -1;
+    o_zero = !occ[UA];
+  }
+  ChunkWalk walk(p, g);
+  const int nk = what == 2 ? 0 : KIND == KIND_TN ? walk.start(FK) : (p.Kdim + FK - 1) / FK;
+
+  auto swz = [](int k, int T) constexpr { return ((k >> 2) & (T / 8 - 1)) * 8; };   // see the layout above
+  // This thread's pieces: where they start at k = 0 (k-contiguous: row and k offset; k-slow: column), and their k.  A
+  // column outside the problem is fetched from the tile's first one; only a partial chunk looks at k at all.
+  const float *pa[UA], *pb[UB];
+  int a_k[UA], b_k[UB];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(ad[i], bd[j], acc[i][j]);
+  for (int u = 0; u < UA; ++u) {
+    const int i = tid + 256 * u;
+    if (!A_NC) {
+      a_k[u] = (i % (FK / 4)) * 4;
+      pa[u] = A + (int64_t)a_row[u] * p.lda + a_k[u];
+    } else {
+      a_k[u] = i / (TM / 4);
+      const int m = m0 + (i % (TM / 4)) * 4;
+      pa[u] = A + (m < p.Mdim ? m : m0);
     }
+  }
+#pragma unroll
+  for (int u = 0; u < UB; ++u) {
+    const int i = tid + 256 * u;
+    if (!B_NC) {
+      b_k[u] = (i % (FK / 4)) * 4;
+      pb[u] = B + (int64_t)min(n0 + i / (FK / 4), p.Ndim - 1) * p.ldb + b_k[u];
+    } else {
+      b_k[u] = i / (TN / 4);
+      const int n = n0 + (i % (TN / 4)) * 4;
+      pb[u] = B + (n < p.Ndim ? n : n0);
+    }
+  }
+  float4 ra[UA], rb[UB];
+  auto fetch = [&](const KTile& kt) {
+    const bool part = kt.lim < FK;
+#pragma unroll
+    for (int u = 0; u < UA; ++u) {
+      const int k = part && a_k[u] >= kt.lim ? 0 : a_k[u];
+      const float* src = pa[u];
+      if (!A_NC) {
+        src += kt.row0 + (k - a_k[u]);
+      } else {
+        int64_t row = kt.row0 + k;
+        if (p.gather != nullptr) row = a_src_row(p, kt.row0 + k - g * p.Cc, g);
+        src += max(row, (int64_t)0) * p.lda;
+        if (p.gather != nullptr && row < 0) { ra[u] = make_float4(0.f, 0.f, 0.f, 0.f); continue; }
+      }
+      ra[u] = *reinterpret_cast<const float4*>(src);
+      if (part && a_k[u] >= kt.lim) ra[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int k = part && b_k[u] >= kt.lim ? 0 : b_k[u];
+      const float* src = B_NC ? pb[u] + (int64_t)(kt.row0 + k) * p.ldb : pb[u] + kt.row0 + (k - b_k[u]);
+      rb[u] = *reinterpret_cast<const float4*>(src);
+      if (part && b_k[u] >= kt.lim) rb[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  auto stage1 = [&](double* dst, int T, int pitch, bool nc, int i, const float4& v) {
+    if (nc) {     // 4 consecutive rows / columns of one k
+      const int k = i / (T / 4);
+      double* d = dst + k * pitch + (((i % (T / 4)) * 4) ^ swz(k, T));
+      d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+    } else {      // 4 consecutive k of one row
+      const int k = (i % (FK / 4)) * 4;
+      double* d = dst + k * pitch + ((i / (FK / 4)) ^ swz(k, T));
+      d[0] = v.x; d[pitch] = v.y; d[2 * pitch] = v.z; d[3 * pitch] = v.w;
+    }
+  };
+  // where the lane reads its operands: the layout's XOR is a constant of a k group; its lowest bit turns over a bit of
+  // the lane's row, its highest the half of the tile the wave owns, the others an address constant
+  const double *fa[2][2], *fb[2][2];
+#pragma unroll
+  for (int lo = 0; lo < 2; ++lo)
+#pragma unroll
+    for (int hi = 0; hi < 2; ++hi) {
+      fa[lo][hi] = As + (lane >> 4) * PA + (wm ^ hi) * (TM / 2) + ((lane & 15) ^ (8 * lo));
+      fb[lo][hi] = Bs + (lane >> 4) * PB + (wn ^ hi) * (TN / 2) + ((lane & 15) ^ (8 * lo));
+    }
+  f64x4_t acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  auto ktile = [&](int t) { return KIND == KIND_TN ? walk.next(FK) : KTile{t * FK, p.Kdim - t * FK}; };
+  if (nk > 0) fetch(ktile(0));
+  for (int t = 0; t < nk; ++t) {
+    __syncthreads();   // the previous chunk is consumed
+#pragma unroll
+    for (int u = 0; u < UA; ++u) stage1(As, TM, PA, A_NC, tid + 256 * u, ra[u]);
+#pragma unroll
+    for (int u = 0; u < UB; ++u) stage1(Bs, TN, PB, B_NC, tid + 256 * u, rb[u]);
     __syncthreads();
+    if (t + 1 < nk) fetch(ktile(t + 1));
+    unrolled<0, FK / 4>([&](auto k4_tag) {
+      constexpr int k4 = decltype(k4_tag)::value, xa = swz(4 * k4, TM), xb = swz(4 * k4, TN);
+      double a[MB], b[NB];
+#pragma unroll
+      for (int i = 0; i < MB; ++i) a[i] = fa[(xa >> 3) & 1][xa / (TM / 2)][4 * k4 * PA + ((16 * i) ^ (xa & (TM / 2 - 16)))];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) b[j] = fb[(xb >> 3) & 1][xb / (TN / 2)][4 * k4 * PB + ((16 * j) ^ (xb & (TN / 2 - 16)))];
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    });
   }
   float* __restrict__ C = reinterpret_cast<float*>(p.C);
   float* __restrict__ C2 = reinterpret_cast<float*>(p.C2);
   const float* __restrict__ Z = reinterpret_cast<const float*>(p.Zin);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= p.Mdim) continue;
-    int64_t crow;
-    if (KIND == KIND_TN) crow = (int64_t)g * p.c_goff + p.c_off + (int64_t)m * p.ldc;
-    else crow = phys_row(m, g, p.G, p.Cc) * p.ldc;
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= p.Ndim) continue;
-      const float v = (float)acc[i][j];
-      if (EPI == EPI_STORE) {
-        C[crow + n] = v;
-      } else if (EPI == EPI_GELU) {
-        C[crow + n] = v;
-        C2[crow + n] = gelu_f(v);
+    for (int r = 0; r < 4; ++r) {
+      const int ml = wm * (TM / 2) + 16 * i + 4 * r + (lane >> 4);   // row within the tile
+      int64_t crow;
+      bool zero = false;
+      if (KIND == KIND_TN) {
+        if (m0 + ml >= p.Mdim) continue;
+        crow = (int64_t)g * p.c_goff + p.c_off + (int64_t)(m0 + ml) * p.ldc;
       } else {
-        float ge, dg;
-        gelu_and_grad(Z[crow + n], ge, dg);
-        C[crow + n] = v * dg;
+        const int row = __shfl(o_row, ml, 64);
+        zero = __shfl((int)o_zero, ml, 64) != 0;
+        if (row < 0) continue;
+        crow = (int64_t)row * p.ldc;
+      }
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int n = n0 + wn * (TN / 2) + 16 * j + (lane & 15);
+        if (n >= p.Ndim) continue;
+        const float v = zero ? 0.f : (float)acc[i][j][r];
+        if (EPI == EPI_STORE) {
+          C[crow + n] = v;
+        } else if (EPI == EPI_GELU) {
+          C[crow + n] = v;
+          C2[crow + n] = gelu_f(v);
+        } else {
+          float ge, dg;
+          gelu_and_grad(Z[crow + n], ge, dg);
+          C[crow + n] = v * dg;
+        }
       }
     }
-  }
+}
+
+template <int KIND, int EPI, int TM, int TN>
+__global__ __launch_bounds__(256, 4) void ffn_gemm_f32(const GemmArgs p) {   // (the second bound keeps the accumulators out of the AGPRs)
+  __shared__ __attribute__((aligned(16))) double smem[f32_lds<TM, TN>() / 8];
+  gemm_f32_tile<KIND, EPI, TM, TN>(p, smem, (int)blockIdx.x);
+}
+// the three backward GEMMs that only depend on dZ, as in ffn_bwd_trio
+template <int TM, int TN>
+__global__ __launch_bounds__(256, 4) void ffn_bwd_trio_f32(const GemmArgs px, const GemmArgs pw2, const GemmArgs pw1, int nbx,
+                                                           int nbw) {
+  __shared__ __attribute__((aligned(16))) double smem[f32_lds<TM, TN>() / 8];
+  const int b = (int)blockIdx.x;
+  if (b < nbx) gemm_f32_tile<KIND_NT, EPI_STORE, TM, TN>(px, smem, b);
+  else gemm_f32_tile<KIND_TN, EPI_STORE, TM, TN>(b < nbx + nbw ? pw2 : pw1, smem, b < nbx + nbw ? b - nbx : b - nbx - nbw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1144,13 +1277,35 @@ TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile, bool wide = false) {
 // counts, an equal share of the tiles of zeros, each share rounded up.
 int grid_of(const GemmArgs& a) { return (a.total_tiles + (a.cnt ? 14 : 7)) / 8 * 8; }
 
+// fp32 tiles: the largest (fewest conversions per product) that gives every compute unit enough workgroups to even out
+using I32 = std::integral_constant<int, 32>;
+using I64 = std::integral_constant<int, 64>;
+int64_t tiles_f32(const GemmArgs& a, bool tn, int tile_m, int tile_n) {
+  const int64_t rows = tn || a.cnt == nullptr ? a.Mdim : ((int64_t)a.Mdim * 9 + 9) / 10;   // as in prepare_bf16
+  return (int64_t)a.G * ((rows + tile_m - 1) / tile_m) * ((a.Ndim + tile_n - 1) / tile_n);
+}
+int plan_f32(int64_t tiles_64x64, int64_t tiles_32x64) {   // 2: 64 x 64, 1: 32 x 64, 0: 32 x 32
+  const int64_t enough = 4 * (int64_t)num_cus();
+  return tiles_64x64 >= enough ? 2 : tiles_32x64 >= enough ? 1 : 0;
+}
+void prepare_f32(GemmArgs& a, int tile_m, int tile_n) {
+  a.tiles_m = (a.Mdim + tile_m - 1) / tile_m;
+  a.tiles_n = (a.Ndim + tile_n - 1) / tile_n;
+  a.total_tiles = a.G * a.tiles_m * a.tiles_n;
+}
+
 template <int KIND, int EPI>
 void launch_gemm(GemmArgs a, int dtype, int tile, hipStream_t st) {
   if (dtype == MOE_F32) {
-    a.tiles_m = (a.Mdim + 63) / 64;
-    a.tiles_n = (a.Ndim + 63) / 64;
-    a.total_tiles = a.G * a.tiles_m * a.tiles_n;
-    hipLaunchKernelGGL((ffn_gemm_f32<KIND, EPI>), dim3(a.total_tiles), dim3(256), 0, st, a);
+    const int size = plan_f32(tiles_f32(a, KIND == KIND_TN, 64, 64), tiles_f32(a, KIND == KIND_TN, 32, 64));
+    auto launch = [&](auto tm_tag, auto tn_tag) {
+      constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
+      prepare_f32(a, TM, TN);
+      hipLaunchKernelGGL((ffn_gemm_f32<KIND, EPI, TM, TN>), dim3((unsigned)grid_of(a)), dim3(256), 0, st, a);
+    };
+    if (size == 2) launch(I64{}, I64{});
+    else if (size == 1) launch(I32{}, I64{});
+    else launch(I32{}, I32{});
     return;
   }
   const TilePlan t = prepare_bf16(a, KIND == KIND_TN, tile);
@@ -1363,6 +1518,20 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
       else launch(Tile64x128{});
       return moe::check_launch();
     }
+  }
+  if (dtype == MOE_F32) {   // one launch here too
+    const int size = plan_f32(tiles_f32(dx, false, 64, 64) + tiles_f32(w2, true, 64, 64) + tiles_f32(w1, true, 64, 64),
+                              tiles_f32(dx, false, 32, 64) + tiles_f32(w2, true, 32, 64) + tiles_f32(w1, true, 32, 64));
+    auto launch = [&](auto tm_tag, auto tn_tag) {
+      constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
+      prepare_f32(dx, TM, TN); prepare_f32(w2, TM, TN); prepare_f32(w1, TM, TN);
+      const int nbx = grid_of(dx), nb2 = grid_of(w2), nb1 = grid_of(w1);
+      hipLaunchKernelGGL((ffn_bwd_trio_f32<TM, TN>), dim3((unsigned)(nbx + nb2 + nb1)), dim3(256), 0, st, dx, w2, w1, nbx, nb2);
+    };
+    if (size == 2) launch(I64{}, I64{});
+    else if (size == 1) launch(I32{}, I64{});
+    else launch(I32{}, I32{});
+    return moe::check_launch();
   }
   launch_gemm<KIND_TN, EPI_STORE>(w2, dtype, tile, st);
   launch_gemm<KIND_TN, EPI_STORE>(w1, dtype, tile, st);

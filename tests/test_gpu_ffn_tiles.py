@@ -1,4 +1,4 @@
-"""GPU parity of the bf16 expert FFN over the tiles that the plan picks by itself (few to some hundred rows per
+"""GPU parity of the expert FFN over the tiles that the plan picks by itself (few to some hundred rows per
 expert, ragged in every dimension) and over the compacted row order: several source chunks with row counts,
 more than 64 of them, more than 16 and more than 64 experts, empty and overfull chunks."""
 import numpy as np
@@ -8,7 +8,7 @@ import torch
 from oracle import moe_oracle as O
 from paper_2407_00599_amd import synth
 from test_gpu_ffn import gpu_ffn
-from util import DEV, TOL, ROWS, EXPERT, to_dev, to_host, assert_close
+from util import DEV, TOL, ROWS, EXPERT, to_dev, to_host, assert_close, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
@@ -25,10 +25,17 @@ CASES = [
     (1, 80, 6, 64, 64),        # more than 64 experts
     (70, 2, 9, 136, 264),      # more than 64 chunks
 ]
+CASES_F32 = [
+    (1, 8, 200, 72, 2056),     # enough tiles for 64 x 64 in the wide GEMMs, 32 x 32 in the narrow ones
+    (2, 6, 150, 200, 1544),
+    (1, 3, 33, 40, 72),
+    (3, 20, 40, 72, 136),
+    (70, 2, 9, 136, 264),
+]
 
 
-@pytest.mark.parametrize("n_src,G,C,M,H", CASES)
-def test_auto_tiles_and_compacted_rows(n_src, G, C, M, H):
+@pytest.mark.parametrize("n_src,G,C,M,H,dtype", [c + ("bf16",) for c in CASES] + [c + ("f32",) for c in CASES_F32])
+def test_auto_tiles_and_compacted_rows(n_src, G, C, M, H, dtype):
     rng = np.random.default_rng(n_src * 7919 + C)
     occ = rng.integers(-C // 2, C + 2, size=(n_src, G)).clip(0)          # a third of the chunks empty, some at or above C
     Xn = rng.standard_normal((n_src, G, C, M)).astype(np.float32)
@@ -36,15 +43,15 @@ def test_auto_tiles_and_compacted_rows(n_src, G, C, M, H):
     for s in range(n_src):
         for g in range(G):
             Xn[s, g, occ[s, g]:] = 0; dYn[s, g, occ[s, g]:] = 0
-    X, dY = synth.store(Xn, "bf16"), synth.store(dYn, "bf16")
-    W1 = synth.store((rng.standard_normal((G, M, H)) / np.sqrt(M)).astype(np.float32), "bf16")
-    W2 = synth.store((rng.standard_normal((G, H, M)) / np.sqrt(H)).astype(np.float32), "bf16")
+    X, dY = synth.store(Xn, dtype), synth.store(dYn, dtype)
+    W1 = synth.store((rng.standard_normal((G, M, H)) / np.sqrt(M)).astype(np.float32), dtype)
+    W2 = synth.store((rng.standard_normal((G, H, M)) / np.sqrt(H)).astype(np.float32), dtype)
     cnt = torch.tensor(occ.astype(np.int32), device=DEV)
     args = [to_dev(t) for t in (X, dY, W1, W2)]
-    got = gpu_ffn(*args, n_src, G, C, M, H, 0, 1, torch.bfloat16, cnt)
+    got = gpu_ffn(*args, n_src, G, C, M, H, 0, 1, torch_dtype(dtype), cnt)
     rZ, rY = O.expert_ffn_fwd(X.val, W1.val, W2.val, 0, 1)
     rdX, rdW1, rdW2 = O.expert_ffn_bwd(dY.val, X.val, W1.val, W2.val, 0, 1)
-    tol = TOL["bf16"]
+    tol = TOL[dtype]
     for name, t, ref, group in (("Z", got[0], rZ, ROWS), ("A", got[1], O.gelu(rZ), ROWS), ("Y", got[2], rY, ROWS),
                                 ("dX", got[3], rdX, ROWS), ("dW1", got[4], rdW1, EXPERT), ("dW2", got[5], rdW2, EXPERT)):
         assert_close(to_host(t), ref, tol, name, group)
@@ -52,5 +59,5 @@ def test_auto_tiles_and_compacted_rows(n_src, G, C, M, H):
     for t in got[:4]:
         assert np.all(to_host(t)[pad] == 0.0)
     for _ in range(4):         # the pipeline's requests race with nothing: every run gives the same bits
-        for a, b in zip(got, gpu_ffn(*args, n_src, G, C, M, H, 0, 1, torch.bfloat16, cnt)):
+        for a, b in zip(got, gpu_ffn(*args, n_src, G, C, M, H, 0, 1, torch_dtype(dtype), cnt)):
             assert torch.equal(a, b)
