@@ -2,15 +2,16 @@
 // (Section III-B): logits = x Wg (+bias), top-k, combine weights, capacity slots.
 //
 // Kernels (wave64 throughout):
-//   gate_logits_small_e : E <= 16.  One wave owns 64/EC tokens; lanes split M, so x is read
+//   gate_logits_small_e : E <= 16, many tokens, fp32 activations.  One wave owns 64/EC tokens; lanes split M, so x is read
 //                         once, coalesced, 16 B per lane; Wg goes through LDS as fp64, shared
 //                         by the 8 waves of a block.  fp64 accumulation, then a halving
 //                         cross-lane reduction that leaves lane i with output i.
 //   gate_logits_mfma    : E > 16.  64 tokens x 64 experts per block on the fp64 matrix cores
 //                         (v_mfma_f64_16x16x4_f64), K chunks converted to fp64 on their way into LDS.
-//   gate_topk           : a group of W = pow2 >= E lanes per token; k rounds of an arg-max
-//                         butterfly (ties -> lower expert index); softmax weights; per-block
-//                         (choice, expert) histogram for the slot scan.
+//   gate_logits_split   : E <= 16, few tokens.  A block owns 2 or 4 tokens, its waves split M.
+//   gate_topk           : W lanes per token, k arg-max rounds (ties -> lower expert index); softmax weights;
+//                         per-block (choice, expert) histogram for the slot scan.  With a single token block it
+//                         assigns the slots as well.
 //   gate_scan           : one wave per expert; exclusive scan of the histograms over token blocks and
 //                         over choices (choice-major priority), per-expert demand counts.
 //   gate_slots          : rank of each (token, choice) inside its block via wave ballots,
@@ -163,28 +164,124 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 1) void gate_logits_small_e(
   }
 }
 
+// E <= 16 and few tokens, where the latency of one block's walk along M is the time of the call: a block owns T
+// tokens and its waves split M (pieces of 128, 2 consecutive m per lane).  A lane's weights are 2 E consecutive floats,
+// read from L2 (with E = EC as 16-byte pieces) and converted once for the T tokens; the waves' sums are added through
+// LDS.  Pieces of 4 m per lane need fewer requests, but a request then touches twice the lines, which several waves'
+// requests push out of L1 before their other halves are read.  256 tokens x 4096, 8 experts: 13 us, where a walk in
+// chunks staged through LDS with a barrier each took 49; 4096 x 1024, 8 experts: 14 -> 10 us; 2048 x 768, 16
+// experts: 23 -> 10 us.
+constexpr int LS_MAXW = 8;
+template <int EC, bool BF16, int T, bool FULL>   // FULL: E = EC
+__global__ __launch_bounds__(64 * LS_MAXW) void gate_logits_split(const void* __restrict__ x, const float* __restrict__ Wg,
+                                                                  const float* __restrict__ bias, float* __restrict__ logits,
+                                                                  int64_t S, int M, int E) {
+  constexpr int NOUT = T * EC;
+  static_assert(NOUT == 32 || NOUT == 64, "the reduction below leaves an output in every lane or every second one");
+  __shared__ double red[LS_MAXW][NOUT];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int64_t t0 = (int64_t)blockIdx.x * T;
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wg), 0, (uint32_t)((uint64_t)M * E * 4), 0x00020000);
+  double acc[NOUT];
+#pragma unroll
+  for (int i = 0; i < NOUT; ++i) acc[i] = 0.0;
+#pragma unroll 2
+  for (int m = (wave * 64 + lane) * 2; m < M; m += nw * 128) {   // M % 8 == 0: both elements are in or out
+    float xv[T][2];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int64_t off = (t0 + t < S ? t0 + t : S - 1) * (int64_t)M + m;   // a token past the end: any row, not stored
+      if (BF16) {
+        const uint32_t v = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const bf16_t*>(x) + off);
+        xv[t][0] = __uint_as_float(v << 16); xv[t][1] = __uint_as_float(v & 0xFFFF0000u);
+      } else {
+        const float2 v = *reinterpret_cast<const float2*>(reinterpret_cast<const float*>(x) + off);
+        xv[t][0] = v.x; xv[t][1] = v.y;
+      }
+    }
+    float wv[2][EC];
+    if (FULL) {
+      const float4* wp = reinterpret_cast<const float4*>(Wg + (int64_t)m * EC);
+#pragma unroll
+      for (int i = 0; i < EC / 2; ++i) {
+        const float4 v = wp[i];
+        float* d = &wv[4 * i / EC][(4 * i) % EC];
+        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+      }
+    } else {   // an expert past the end: the next row's weights (behind the last row: zeros, from the descriptor), not stored
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int e = 0; e < EC; ++e)
+          wv[q][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, (m + q) * E * 4 + e * 4, 0, 0));
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      double wd[EC];
+#pragma unroll
+      for (int e = 0; e < EC; ++e) wd[e] = (double)wv[q][e];
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const double xd = (double)xv[t][q];
+#pragma unroll
+        for (int e = 0; e < EC; ++e) acc[t * EC + e] = fma(xd, wd[e], acc[t * EC + e]);
+      }
+    }
+  }
+  // halving reduction over the lanes, as in gate_logits_small_e
+#pragma unroll
+  for (int st = 0; st < 6; ++st) {
+    const int lm = 32 >> st;
+    if ((NOUT >> st) > 1) {
+      const int h = NOUT >> (st + 1);
+      const bool up = (lane & lm) != 0;
+#pragma unroll
+      for (int i = 0; i < h; ++i) {
+        const double keep = up ? acc[i + h] : acc[i];
+        const double send = up ? acc[i] : acc[i + h];
+        acc[i] = keep + shfl_xor_f64(send, lm);
+      }
+    } else {
+      acc[0] += shfl_xor_f64(acc[0], lm);
+    }
+  }
+  constexpr int REP = 64 / NOUT;
+  if (lane % REP == 0) red[wave][lane / REP] = acc[0];
+  __syncthreads();
+  if (threadIdx.x < NOUT) {
+    const int64_t t = t0 + threadIdx.x / EC;
+    const int e = threadIdx.x % EC;
+    double v = 0.0;
+    for (int q = 0; q < nw; ++q) v += red[q][threadIdx.x];
+    if (t < S && e < E) logits[t * E + e] = (float)(bias ? v + (double)bias[e] : v);
+  }
+}
+
 // E > 16: fp64 matrix cores.  v_mfma_f64_16x16x4_f64 multiplies a 16 x 4 by a 4 x 16 tile of doubles (lane l
 // supplies A[l % 16][l / 16] and B[l / 16][l % 16], and receives D[4 r + l / 16][l % 16], r = 0..3).  A block of
 // 4 waves owns 64 tokens x 64 experts (grid.y walks the expert blocks), a wave 16 tokens x 64 experts (four
 // accumulator tiles).  M is walked in chunks of 32: x and Wg are converted to fp64 once on their way into LDS
 // ([k][token] and [k][expert], pitch 80 doubles so that the two k planes of a 32-lane access fall into
-// different banks), the next chunk's raw data being requested before the current one is multiplied.
+// different banks), in two buffers: the next chunk is converted and stored between the current one's products, and the
+// one after it requested.
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 constexpr int LM_KC = 32, LM_PITCH = 80;
-template <bool BF16>
-__global__ __launch_bounds__(256) void gate_logits_mfma(const void* __restrict__ x, const float* __restrict__ Wg,
+// KW = 2: two such groups of four waves take alternate chunks and add their sums through LDS at the end, so that a
+// compute unit that gets one block still has two waves per SIMD, one's conversions and fetches under the other's matrix
+// instructions (256 blocks: 128 -> 102 us for 16384 x 2048 x 64).
+template <bool BF16, int KW>
+__global__ __launch_bounds__(256 * KW) void gate_logits_mfma(const void* __restrict__ x, const float* __restrict__ Wg,
                                                         const float* __restrict__ bias, float* __restrict__ logits,
                                                         int64_t S, int M, int E) {
-  __shared__ double xs[LM_KC * LM_PITCH];
-  __shared__ double ws[LM_KC * LM_PITCH];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ double stage_s[KW][2][2][LM_KC * LM_PITCH];   // two chunks of x and Wg per group
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6, kw = KW == 1 ? 0 : threadIdx.x >> 8;
   const int64_t tb = (int64_t)blockIdx.x * 64;
   const int e0 = blockIdx.y * 64;
-  // staging roles: x -> token tid / 4, k offset 8 (tid % 4); Wg -> k row tid / 8, experts 8 (tid % 8)
+  // staging roles: x -> token tid / 4, k offset 8 (tid % 4); Wg -> expert tid % 64, k rows tid / 64 + 4 u
   const int xt = tid >> 2, xk = (tid & 3) * 8;
-  const int wk = tid >> 3, we = (tid & 7) * 8;
+  const int wk = tid >> 6, we = tid & 63;
   uint4 xraw[BF16 ? 1 : 2];
-  float4 wraw[2];
+  float wraw[8];
   auto fetch = [&](int k0) {
     const bool xok = (tb + xt < S) && (k0 + xk < M);     // M % 8 == 0: the 8 elements are in or out together
     const int64_t xo = (tb + xt) * (int64_t)M + k0 + xk;
@@ -195,15 +292,13 @@ __global__ __launch_bounds__(256) void gate_logits_mfma(const void* __restrict__
       xraw[0] = xok ? p[0] : make_uint4(0, 0, 0, 0);
       xraw[BF16 ? 0 : 1] = xok ? p[1] : make_uint4(0, 0, 0, 0);
     }
-    const bool kok = k0 + wk < M;
     const float* wp = Wg + (int64_t)(k0 + wk) * E + e0 + we;
-    float wv[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) wv[u] = (kok && e0 + we + u < E) ? wp[u] : 0.f;   // E need not be a multiple of 4
-    wraw[0] = make_float4(wv[0], wv[1], wv[2], wv[3]);
-    wraw[1] = make_float4(wv[4], wv[5], wv[6], wv[7]);
+    for (int u = 0; u < 8; ++u) wraw[u] = (k0 + wk + 4 * u < M && e0 + we < E) ? wp[(int64_t)(4 * u) * E] : 0.f;
   };
-  auto stage = [&]() {
+  auto stage = [&](int buf) {
+    double* xs = stage_s[kw][buf][0];
+    double* ws = stage_s[kw][buf][1];
     float xf[8];
     if (BF16) {
       unpack_bf16x8(xraw[0], xf);
@@ -214,30 +309,51 @@ __global__ __launch_bounds__(256) void gate_logits_mfma(const void* __restrict__
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) xs[(xk + u) * LM_PITCH + xt] = (double)xf[u];
-    const float wv[8] = {wraw[0].x, wraw[0].y, wraw[0].z, wraw[0].w, wraw[1].x, wraw[1].y, wraw[1].z, wraw[1].w};
 #pragma unroll
-    for (int u = 0; u < 8; ++u) ws[wk * LM_PITCH + we + u] = (double)wv[u];
+    for (int u = 0; u < 8; ++u) ws[(wk + 4 * u) * LM_PITCH + we] = (double)wraw[u];
   };
   f64x4_t acc[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) acc[j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
 
-  fetch(0);
-  for (int k0 = 0; k0 < M; k0 += LM_KC) {
-    __syncthreads();   // the previous chunk is consumed
-    stage();
-    __syncthreads();
-    if (k0 + LM_KC < M) fetch(k0 + LM_KC);
+  const int nch = (M + LM_KC * KW - 1) / (LM_KC * KW);   // chunks of this group (one past the end is zeros)
+  auto chunk = [&](int c) { return (c * KW + kw) * LM_KC; };
+  fetch(chunk(0));
+  stage(0);
+  if (nch > 1) fetch(chunk(1));
+  for (int c = 0; c < nch; ++c) {
+    __syncthreads();   // chunk c is staged, and the other buffer is consumed
+    const double* xs = stage_s[kw][c & 1][0] + (lane >> 4) * LM_PITCH + wave * 16 + (lane & 15);
+    const double* ws = stage_s[kw][c & 1][1] + (lane >> 4) * LM_PITCH + (lane & 15);
+    auto products = [&](int s0) {
 #pragma unroll
-    for (int s4 = 0; s4 < LM_KC / 4; ++s4) {
-      const int kr = (4 * s4 + (lane >> 4)) * LM_PITCH;
-      const double a = xs[kr + wave * 16 + (lane & 15)];
+      for (int s4 = s0; s4 < s0 + LM_KC / 8; ++s4) {
+        const double a = xs[4 * s4 * LM_PITCH];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const double bv = ws[kr + j * 16 + (lane & 15)];
-        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv, acc[j], 0, 0, 0);
+        for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, ws[4 * s4 * LM_PITCH + j * 16], acc[j], 0, 0, 0);
       }
+    };
+    products(0);
+    if (c + 1 < nch) stage((c + 1) & 1);
+    if (c + 2 < nch) fetch(chunk(c + 2));
+    products(LM_KC / 8);
+  }
+  if constexpr (KW == 2) {
+    __syncthreads();
+    double* red = &stage_s[0][0][0][0] + (wave * 64 + lane) * 17;   // 17: lanes on different banks
+    static_assert(256 * 17 <= KW * 4 * LM_KC * LM_PITCH, "the sums fit in the staging buffers");
+    if (kw == 1) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[4 * j + r] = acc[j][r];
     }
+    __syncthreads();
+    if (kw == 1) return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[j][r] += red[4 * j + r];
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -461,104 +577,122 @@ __device__ __forceinline__ Cand better(Cand a, Cand b) {
   return a;
 }
 
-// W lanes per token (W = pow2, W*EPL >= E).  Lane r of a group holds experts r, r+W, ...
-// One block per GATE_TB tokens, min(W, 8) waves: the W passes (GATE_TB / W tokens each) are dealt to the waves.
-template <int W, int EPL>
-__global__ __launch_bounds__(GATE_TB * (W < 8 ? W : 8)) void gate_topk(const float* __restrict__ logits, int64_t S, int E, int k,
-                                                      int norm_topk, int32_t* __restrict__ idx, float* __restrict__ w,
-                                                      int32_t* __restrict__ blockhist) {
-  __shared__ int hist[MOE_MAX_K * MOE_MAX_E];
-  constexpr int NWV = W < 8 ? W : 8;   // waves per block
-  constexpr int PPW = W / NWV;         // passes per wave
-  const int tid = threadIdx.x & (GATE_TB - 1), wave = threadIdx.x / GATE_TB;
-  for (int i = threadIdx.x; i < k * E; i += GATE_TB * NWV) hist[i] = 0;
+// Rank of each lane's expert among the lanes before it with the same expert (live lanes only).
+__device__ __forceinline__ int match_rank(int e, bool live, int E, int lane) {
+  unsigned long long same = __ballot(live);
+  for (int bit = 1; bit < E; bit <<= 1) {
+    const unsigned long long has = __ballot((e & bit) != 0);
+    same &= (e & bit) ? has : ~has;
+  }
+  return __popcll(same & ((1ull << lane) - 1ull));
+}
+
+// Top-k of TB tokens.  W lanes hold a token's logits (lane r of a group the experts r, r + W, ...; W EPL >= E): the
+// arg-max rounds compare within a lane first and need log2(W) cross-lane steps, none up to 16 experts.  The rounds are
+// a loop and the code is small: every launch fetches its instructions anew, and at a few hundred tokens that fetch is
+// a good part of its time.
+// ONE (all tokens fit in one block): the slots are assigned here, and neither histograms nor a second launch are
+// needed.  32 tokens, 8 experts: 4 + 9 us in two launches -> 4 us.
+constexpr int topk_tokens(int W, bool one) { return !one ? GATE_TB : 1024 / W < 256 ? 1024 / W : 256; }
+template <int W, int EPL, bool ONE>
+__global__ __launch_bounds__(topk_tokens(W, ONE) * W) void gate_topk(const float* __restrict__ logits, int64_t S, int E, int k,
+                                                                     int norm_topk, int32_t* __restrict__ idx, float* __restrict__ w,
+                                                                     int32_t* __restrict__ blockhist, int pair_major, int64_t C,
+                                                                     int32_t* __restrict__ slot, int32_t* __restrict__ inv,
+                                                                     int32_t* __restrict__ counts) {
+  constexpr int TB = topk_tokens(W, ONE), NT = TB * W, NSUB = TB / 64;   // ONE: demand is counted per 64 tokens
+  constexpr int EP = W * EPL;
+  __shared__ int hist[(ONE ? NSUB : 1) * MOE_MAX_K * EP];
+  __shared__ float selv[MOE_MAX_K * TB];
+  __shared__ int sele[ONE ? MOE_MAX_K * TB : 1];
+  __shared__ int count_s[ONE ? EP : 1];
+  const int tid = threadIdx.x, lane = tid & 63, r = tid % W, tl = tid / W;
+  const int npair = k * E;
+  for (int i = tid; i < (ONE ? NSUB : 1) * npair; i += NT) hist[i] = 0;
+  const int64_t t = (int64_t)blockIdx.x * TB + tl;
+  const bool live = t < S;
+  float v[EPL];
+  unsigned taken = 0;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int e = r + i * W;
+    v[i] = logits[min(t, S - 1) * E + min(e, E - 1)];
+    if (!(live && e < E)) taken |= 1u << i;
+  }
+  const unsigned absent = taken;
   __syncthreads();
-  const int r = tid % W;
-  const int64_t tb0 = (int64_t)blockIdx.x * GATE_TB;
-  constexpr int TPP = GATE_TB / W;  // tokens per pass
-  constexpr int PG = PPW < 4 ? PPW : 4;  // passes whose logits are requested together
-  float vv[PG][EPL];
-  for (int pi = 0; pi < PPW; ++pi) {
-    const int pass = wave * PPW + pi;
-    if (pi % PG == 0) {
+  float mx = 0.f, den = 0.f;
+  for (int j = 0; j < k; ++j) {
+    Cand c{0.f, 0x7fffffff};
 #pragma unroll
-      for (int u = 0; u < PG; ++u) {
-        const int64_t tu = tb0 + (pass + u) * TPP + tid / W;
+    for (int i = 0; i < EPL; ++i)
+      if (!(taken & (1u << i)) && (c.e == 0x7fffffff || v[i] > c.v)) c = Cand{v[i], r + i * W};
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-          const int e = r + i * W;
-          vv[u][i] = (tu < S && e < E) ? logits[tu * E + e] : 0.f;
-        }
-      }
+    for (int m = 1; m < W; m <<= 1) {
+      Cand o;
+      o.v = __shfl_xor(c.v, m, 64);
+      o.e = __shfl_xor(c.e, m, 64);
+      c = better(c, o);
     }
-    const int64_t t = tb0 + pass * TPP + tid / W;
-    const bool live = t < S;
-    float v[EPL];
-    unsigned taken = 0;
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      const int e = r + i * W;
-      float val = 0.f;
-#pragma unroll
-      for (int u = 0; u < PG; ++u)
-        if (u == pi % PG) val = vv[u][i];
-      v[i] = val;
-      if (!(live && e < E)) taken |= 1u << i;
-    }
-    float selv[MOE_MAX_K];
-    int sele[MOE_MAX_K];
-#pragma unroll
-    for (int j = 0; j < MOE_MAX_K; ++j) {
-      selv[j] = 0.f; sele[j] = 0;
-      if (j < k) {
-        Cand c{0.f, 0x7fffffff};
-#pragma unroll
-        for (int i = 0; i < EPL; ++i)
-          if (!(taken & (1u << i))) c = better(c, Cand{v[i], r + i * W});
-#pragma unroll
-        for (int m = 1; m < W; m <<= 1) {
-          Cand o;
-          o.v = __shfl_xor(c.v, m, 64);
-          o.e = __shfl_xor(c.e, m, 64);
-          c = better(c, o);
-        }
-        selv[j] = c.v; sele[j] = c.e;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i)
-          if (c.e == r + i * W) taken |= 1u << i;
-      }
-    }
-    // weights: exp(l - max) over the selected k, or over all experts
-    const float mx = selv[0];
-    float den = 0.f;
-    if (norm_topk) {
-#pragma unroll
-      for (int j = 0; j < MOE_MAX_K; ++j)
-        if (j < k) den += expf(selv[j] - mx);
-    } else {
-      float part = 0.f;
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        const int e = r + i * W;
-        if (live && e < E) part += expf(v[i] - mx);
-      }
-#pragma unroll
-      for (int m = 1; m < W; m <<= 1) part += __shfl_xor(part, m, 64);
-      den = part;
-    }
-    if (live && r < k) {
-      float lv = 0.f; int le = 0;
-#pragma unroll
-      for (int j = 0; j < MOE_MAX_K; ++j)
-        if (j == r) { lv = selv[j]; le = sele[j]; }
-      idx[t * k + r] = le;
-      w[t * k + r] = expf(lv - mx) / den;
-      atomicAdd(&hist[r * E + le], 1);
+    if (c.e % W == r) taken |= 1u << (c.e / W & 31);
+    if (j == 0) mx = c.v;
+    den += expf(c.v - mx);
+    if (live && r == 0) {
+      const int e = min(c.e, E - 1);   // (logits that are not numbers can leave a group's lanes of different minds)
+      selv[j * TB + tl] = c.v;
+      if (ONE) sele[j * TB + tl] = e;
+      idx[t * k + j] = e;
+      atomicAdd(&hist[(ONE ? (tl >> 6) * npair : 0) + j * E + e], 1);
     }
   }
+  if (!norm_topk) {   // weights over all experts instead of the selected ones
+    den = 0.f;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i)
+      if (!(absent & (1u << i))) den += expf(v[i] - mx);
+#pragma unroll
+    for (int m = 1; m < W; m <<= 1) den += __shfl_xor(den, m, 64);
+  }
+  if (live) {   // a group's lanes are in one wave, whose LDS operations complete in order
+    for (int j = r; j < k; j += W) w[t * k + j] = expf(selv[j * TB + tl] - mx) / den;
+  }
   __syncthreads();
-  // stored [choice][expert][block] so the scan reads one (choice, expert) row contiguously
-  for (int i = threadIdx.x; i < k * E; i += GATE_TB * NWV) blockhist[(int64_t)i * gridDim.x + blockIdx.x] = hist[i];
+  if constexpr (!ONE) {
+    // [choice][expert][block] for gate_scan, which reads a (choice, expert) row, or [block][choice][expert]
+    for (int i = tid; i < npair; i += NT)
+      blockhist[pair_major ? (int64_t)i * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * npair + i] = hist[i];
+  } else {
+    // choice-major queues: positions of the first token of every (64 tokens, choice, expert)
+    for (int e = tid; e < E; e += NT) {
+      int run = 0;
+      for (int j = 0; j < k; ++j)
+        for (int q = 0; q < NSUB; ++q) {
+          const int h = hist[q * npair + j * E + e];
+          hist[q * npair + j * E + e] = run;
+          run += h;
+        }
+      count_s[e] = run;
+      counts[e] = run;
+    }
+    __syncthreads();
+    for (int u = tid >> 6; u < NSUB * k; u += NT / 64) {   // one wave per (choice, 64 tokens)
+      const int j = u / NSUB, q = u - j * NSUB, tq = q * 64 + lane;
+      const bool ok = tq < S;
+      const int e = ok ? sele[j * TB + tq] : 0;
+      const int rank = match_rank(e, ok, E, lane);
+      if (ok) {
+        const int pos = hist[q * npair + j * E + e] + rank;
+        const bool keep = pos < C;
+        slot[(int64_t)tq * k + j] = keep ? pos : -1;
+        if (keep) inv[(int64_t)e * C + pos] = tq * k + j;
+      }
+    }
+    const uint32_t total = (uint32_t)((int64_t)E * C);   // below 2^31
+    for (uint32_t i = tid; i < total; i += NT) {
+      const uint32_t e = i / (uint32_t)C;
+      if (i - e * (uint32_t)C >= (uint32_t)count_s[e]) inv[i] = -1;
+    }
+  }
 }
 
 // blockhist[j][e][b] -> blockbase[j][e][b] = queue position of the first (token, choice j) of
@@ -588,100 +722,78 @@ __global__ __launch_bounds__(256) void gate_scan(const int32_t* __restrict__ blo
   if (lane == 0) counts[e] = run;
 }
 
-// SCAN = false: queue positions of the block's first tokens come from gate_scan (blockbase, counts).
-// SCAN = true (few token blocks): every block works them out itself from the per-block histograms --
-// for each (choice j, expert e) the demand of the earlier blocks, plus all demand of the earlier
-// choices -- which saves the scan launch; block 0 also writes counts.  Same integers either way.
-template <bool SCAN>
-__global__ __launch_bounds__(GATE_TB) void gate_slots(const int32_t* __restrict__ idx, const int32_t* __restrict__ blockbase,
-                                                       int32_t* __restrict__ counts, int64_t S, int E, int k,
-                                                       int64_t C, int32_t* __restrict__ slot, int32_t* __restrict__ inv) {
-  static_assert(GATE_TB == 64, "one wave per block");
-  __shared__ int wavecnt[GATE_TB / 64][MOE_MAX_E];
-  __shared__ int base_s[SCAN ? MOE_MAX_K * MOE_MAX_E : 1];   // queue position of this block's first (j, e) token
-  __shared__ int tot_s[SCAN ? MOE_MAX_K * MOE_MAX_E : 1];    // demand of (j, e) over all blocks
-  __shared__ int count_s[SCAN ? MOE_MAX_E : 1];              // total demand of expert e
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t t = (int64_t)blockIdx.x * GATE_TB + tid;
-  const bool live = t < S;
-  if (SCAN) {
-    // here blockbase holds the histograms [j][e][b].  Lanes run over b; sixteen (j, e) rows at a time, so that
-    // sixteen loads are in flight per lane; the wave-wide sums of a row: its total and the part of the
-    // blocks before this one.
+// One block per GATE_TB tokens, wave j ranks choice j.
+// SELF = false: queue positions of the block's first tokens come from gate_scan (base, counts).
+// SELF = true: every block works them out itself from the histograms [block][choice][expert] -- for each
+// (choice j, expert e) the demand of the earlier blocks, plus all demand of the earlier choices -- which saves the
+// scan launch; block 0 also writes counts.  Same integers either way.  The histogram rows are read four pairs at a time
+// by groups of threads that share the blocks between them, and the groups' sums meet in LDS.
+constexpr int SLOT_NT = 512;
+template <bool SELF>
+__global__ __launch_bounds__(SLOT_NT) void gate_slots(const int32_t* __restrict__ idx, const int32_t* __restrict__ base,
+                                                      int32_t* __restrict__ counts, int64_t S, int E, int k,
+                                                      int64_t C, int32_t* __restrict__ slot, int32_t* __restrict__ inv) {
+  static_assert(GATE_TB == 64 && SLOT_NT / 64 >= MOE_MAX_K, "a wave per choice, a lane per token");
+  __shared__ __attribute__((aligned(16))) int base_s[SELF ? MOE_MAX_K * MOE_MAX_E : 1];   // queue position of this block's first (j, e) token
+  __shared__ __attribute__((aligned(16))) int tot_s[SELF ? MOE_MAX_K * MOE_MAX_E : 1];    // demand of (j, e) over all blocks
+  __shared__ int count_s[SELF ? MOE_MAX_E : 1];              // total demand of expert e
+  const int tid = threadIdx.x, lane = tid & 63, j = tid >> 6;
+  const int64_t t = (int64_t)blockIdx.x * GATE_TB + lane;
+  const bool live = t < S && j < k;
+  const int e = live ? idx[t * k + j] : 0;
+  if (SELF) {
     const int nblk = (int)gridDim.x, me = (int)blockIdx.x, npair = k * E;
-    for (int p0 = 0; p0 < npair; p0 += 16) {
-      int tot[16], pre[16];
+    for (int i = tid; i < npair; i += SLOT_NT) base_s[i] = tot_s[i] = 0;
+    __syncthreads();
+    auto sum_rows = [&](auto vec_tag) {   // V pairs per thread and step
+      constexpr int V = decltype(vec_tag)::value;
+      typedef int32_t vec_t __attribute__((ext_vector_type(V)));
+      const int nu = npair / V;
+      int lanes = 1;
+      while (lanes < nu && lanes < SLOT_NT) lanes <<= 1;
+      const int groups = SLOT_NT / lanes, gr = tid / lanes;
+      for (int u = tid % lanes; u < nu; u += lanes) {
+        int tot[V] = {}, pre[V] = {};
+#pragma unroll 8
+        for (int b = gr; b < nblk; b += groups) {
+          const vec_t h = *reinterpret_cast<const vec_t*>(base + (int64_t)b * npair + u * V);
 #pragma unroll
-      for (int u = 0; u < 16; ++u) tot[u] = pre[u] = 0;
-      for (int b0 = 0; b0 < nblk; b0 += 64) {
-        const int b = b0 + lane;
-        int h[16];
+          for (int q = 0; q < V; ++q) { tot[q] += h[q]; pre[q] += b < me ? h[q] : 0; }
+        }
 #pragma unroll
-        for (int u = 0; u < 16; ++u) h[u] = (b < nblk && p0 + u < npair) ? blockbase[(int64_t)(p0 + u) * nblk + b] : 0;
-#pragma unroll
-        for (int u = 0; u < 16; ++u) { tot[u] += h[u]; pre[u] += b < me ? h[u] : 0; }
+        for (int q = 0; q < V; ++q) { atomicAdd(&tot_s[u * V + q], tot[q]); atomicAdd(&base_s[u * V + q], pre[q]); }
       }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) { tot[u] += __shfl_xor(tot[u], o, 64); pre[u] += __shfl_xor(pre[u], o, 64); }
-        if (lane == 0 && p0 + u < npair) { base_s[p0 + u] = pre[u]; tot_s[p0 + u] = tot[u]; }
-      }
-    }
+    };
+    if (npair % 4 == 0) sum_rows(std::integral_constant<int, 4>{});
+    else sum_rows(std::integral_constant<int, 1>{});
     __syncthreads();
     // choice-major queues: all demand of the earlier choices at expert e comes first
-    for (int e = tid; e < E; e += GATE_TB) {
+    for (int ee = tid; ee < E; ee += SLOT_NT) {
       int run = 0;
-      for (int j = 0; j < k; ++j) {
-        const int i = j * E + e;
-        base_s[i] += run;
-        run += tot_s[i];
+      for (int c = 0; c < k; ++c) {
+        base_s[c * E + ee] += run;
+        run += tot_s[c * E + ee];
       }
-      count_s[e] = run;
-      if (me == 0) counts[e] = run;
+      count_s[ee] = run;
+      if (me == 0) counts[ee] = run;
     }
     __syncthreads();
   }
-  for (int j = 0; j < k; ++j) {
-    for (int i = tid; i < (GATE_TB / 64) * MOE_MAX_E; i += GATE_TB) (&wavecnt[0][0])[i] = 0;
-    __syncthreads();
-    const int e = live ? idx[t * k + j] : -1;
-    int rank = 0;
-    unsigned long long todo = __ballot(live);
-    while (todo) {
-      const int leader = __ffsll((long long)todo) - 1;
-      const int e0 = __shfl(e, leader, 64);
-      const unsigned long long same = __ballot(live && e == e0);
-      if (e == e0) {
-        rank = __popcll(same & ((1ull << lane) - 1ull));
-        if (lane == leader) wavecnt[wv][e0] = __popcll(same);
-      }
-      todo &= ~same;
-    }
-    __syncthreads();
+  if (j < k) {
+    const int rank = match_rank(e, live, E, lane);
     if (live) {
-      int pos = (SCAN ? base_s[j * E + e] : blockbase[((int64_t)j * E + e) * gridDim.x + blockIdx.x]) + rank;
-      for (int q = 0; q < wv; ++q) pos += wavecnt[q][e];
+      const int pos = (SELF ? base_s[j * E + e] : base[((int64_t)j * E + e) * gridDim.x + blockIdx.x]) + rank;
       const bool keep = pos < C;
       slot[t * k + j] = keep ? pos : -1;
       if (keep) inv[(int64_t)e * C + pos] = (int32_t)(t * k + j);
     }
-    __syncthreads();
   }
   // empty tail of every expert's block: slots [min(counts[e], C), C)
-  const int64_t total = (int64_t)E * C;
-  for (int64_t i = (int64_t)blockIdx.x * GATE_TB + tid; i < total; i += (int64_t)gridDim.x * GATE_TB) {
-    const int e = (int)(i / C);
-    const int64_t c = i - (int64_t)e * C;
-    if (c >= (SCAN ? count_s[e] : counts[e])) inv[i] = -1;
+  const int64_t total = (int64_t)E * C;   // below 2^31
+  for (int64_t i = (int64_t)blockIdx.x * SLOT_NT + tid; i < total; i += (int64_t)gridDim.x * SLOT_NT) {
+    const uint32_t ee = (uint32_t)i / (uint32_t)C, c = (uint32_t)i - ee * (uint32_t)C;
+    if (c >= (uint32_t)(SELF ? count_s[ee] : counts[ee])) inv[i] = -1;
   }
-}
-
-template <int W, int EPL>
-void launch_topk(const float* logits, int64_t S, int E, int k, int norm, int32_t* idx, float* w, int32_t* bh,
-                 int nblk, hipStream_t st) {
-  hipLaunchKernelGGL((gate_topk<W, EPL>), dim3(nblk), dim3(GATE_TB * (W < 8 ? W : 8)), 0, st, logits, S, E, k, norm,
-                     idx, w, bh);
 }
 
 }  // namespace
@@ -758,7 +870,28 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
       if (E <= 4) LAUNCH_M4_TW(1); else if (E <= 8) LAUNCH_M4_TW(2); else LAUNCH_M4_TW(4);
 #undef LAUNCH_M4_TW
 #undef LAUNCH_M4
+    } else if (E <= 16 && S < 8192 && (uint64_t)M * E * 4 < (1ull << 31)) {   // 32-bit offsets into Wg
+      // Few tokens: as many waves over M as it has pieces.  From a thousand tokens on, twice the tokens per block (half the
+      // weight traffic and conversions) and waves that walk several pieces, about 2048 of them in all, so that the
+      // reduction at a wave's end does not outweigh its products.
+      const bool many = S >= 1024;
+      const int T = (E <= 8 ? 4 : 2) * (many ? 2 : 1);
+      const int64_t blocks = (S + T - 1) / T;
+      int nw = (M + 127) / 128 < LS_MAXW ? (M + 127) / 128 : LS_MAXW;
+      if (many && nw > 2048 / blocks) nw = (int)(2048 / blocks); 
+      if (nw < 1) nw = 1;
+      const dim3 grid((unsigned)blocks), block(64 * nw);
+#define LAUNCH_SPLIT(ec, t, full) do { \
+    if (bf) hipLaunchKernelGGL((gate_logits_split<ec, true, t, full>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E); \
+    else hipLaunchKernelGGL((gate_logits_split<ec, false, t, full>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E); } while (0)
+#define LAUNCH_SPLIT_E(full8, full16) do { \
+    if (E <= 8) { if (many) LAUNCH_SPLIT(8, 8, full8); else LAUNCH_SPLIT(8, 4, full8); } \
+    else { if (many) LAUNCH_SPLIT(16, 4, full16); else LAUNCH_SPLIT(16, 2, full16); } } while (0)
+      if (E == 8 || E == 16) LAUNCH_SPLIT_E(true, true); else LAUNCH_SPLIT_E(false, false);
+#undef LAUNCH_SPLIT_E
+#undef LAUNCH_SPLIT
     } else if (E <= 16) {
+      // fp32 activations (or token rows past 32-bit offsets)
       const int EC = E <= 8 ? 8 : 16;
       const int T = E <= 8 ? 4 : 2;
       // many tokens: 8-wave blocks halve the Wg staging work per token; few tokens: 4-wave blocks fill the chip
@@ -771,25 +904,44 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
       if (EC == 8) LAUNCH_SMALL(8, 4); else LAUNCH_SMALL(16, 2);
 #undef LAUNCH_SMALL
     } else {
-      const dim3 grid((unsigned)((S + 63) / 64), (unsigned)((E + 63) / 64)), block(256);
-      if (bf) hipLaunchKernelGGL((gate_logits_mfma<true>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E);
-      else hipLaunchKernelGGL((gate_logits_mfma<false>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E);
+      const dim3 grid((unsigned)((S + 63) / 64), (unsigned)((E + 63) / 64));
+      const bool two = (uint64_t)grid.x * grid.y <= 256 && M > LM_KC;   // at most one block per compute unit
+#define LAUNCH_WIDE(bf_, kw_) hipLaunchKernelGGL((gate_logits_mfma<bf_, kw_>), grid, dim3(256 * kw_), 0, st, xs, Wg, gate_bias, logits, S, M, E)
+      if (bf) { if (two) LAUNCH_WIDE(true, 2); else LAUNCH_WIDE(true, 1); }
+      else { if (two) LAUNCH_WIDE(false, 2); else LAUNCH_WIDE(false, 1); }
+#undef LAUNCH_WIDE
     }
   }
-  if (E <= 1) launch_topk<1, 1>(logits, S, E, k, norm, idx, w, blockhist, nblk, st);
-  else if (E <= 2) launch_topk<2, 1>(logits, S, E, k, norm, idx, w, blockhist, nblk, st);
-  else if (E <= 4) launch_topk<4, 1>(logits, S, E, k, norm, idx, w, blockhist, nblk, st);
-  else if (E <= 8) launch_topk<8, 1>(logits, S, E, k, norm, idx, w, blockhist, nblk, st);
-  else if (E <= 16) launch_topk<16, 1>(logits, S, E, k, norm, idx, w, blockhist, nblk, st);
-  else if (E <= 32) launch_topk<32, 1>(logits, S, E, k, norm, idx, w, blockhist, nblk, st);
-  else if (E <= 64) launch_topk<64, 1>(logits, S, E, k, norm, idx, w, blockhist, nblk, st);
-  else if (E <= 128) launch_topk<64, 2>(logits, S, E, k, norm, idx, w, blockhist, nblk, st);
-  else launch_topk<64, 4>(logits, S, E, k, norm, idx, w, blockhist, nblk, st);
-  if ((int64_t)nblk * k * E <= 16384) {   // every block reads all histograms itself: at most 64 KiB each
-    hipLaunchKernelGGL(gate_slots<true>, dim3(nblk), dim3(GATE_TB), 0, st, idx, blockhist, counts, S, E, k, C, slot, inv);
+  // Every block reads all histograms itself up to 256 KiB of them and 64 MiB over all blocks (a few microseconds from L2,
+  // what the scan launch costs).
+  const int64_t npair = (int64_t)k * E;
+  const bool self = nblk * npair <= 65536 && (int64_t)nblk * nblk * npair <= (1 << 24);
+  auto route = [&](auto w_tag, auto epl_tag) {   // returns true: the slots are assigned too
+    constexpr int W = decltype(w_tag)::value, EPL = decltype(epl_tag)::value;
+    if (S <= topk_tokens(W, true)) {
+      hipLaunchKernelGGL((gate_topk<W, EPL, true>), dim3(1), dim3(topk_tokens(W, true) * W), 0, st, logits, S, E, k, norm, idx,
+                         w, blockhist, 0, C, slot, inv, counts);
+      return true;
+    }
+    hipLaunchKernelGGL((gate_topk<W, EPL, false>), dim3(nblk), dim3(GATE_TB * W), 0, st, logits, S, E, k, norm, idx, w, blockhist,
+                       self ? 0 : 1, C, slot, inv, counts);
+    return false;
+  };
+  using std::integral_constant;
+  bool done;
+  if (E <= 4) done = route(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+  else if (E <= 8) done = route(integral_constant<int, 1>{}, integral_constant<int, 8>{});
+  else if (E <= 16) done = route(integral_constant<int, 1>{}, integral_constant<int, 16>{});
+  else if (E <= 32) done = route(integral_constant<int, 4>{}, integral_constant<int, 8>{});
+  else if (E <= 64) done = route(integral_constant<int, 8>{}, integral_constant<int, 8>{});
+  else if (E <= 128) done = route(integral_constant<int, 8>{}, integral_constant<int, 16>{});
+  else done = route(integral_constant<int, 16>{}, integral_constant<int, 16>{});
+  if (done) return moe::check_launch();
+  if (self) {
+    hipLaunchKernelGGL(gate_slots<true>, dim3(nblk), dim3(SLOT_NT), 0, st, idx, blockhist, counts, S, E, k, C, slot, inv);
   } else {
     hipLaunchKernelGGL(gate_scan, dim3((E + 3) / 4), dim3(256), 0, st, blockhist, nblk, E, k, blockbase, counts);
-    hipLaunchKernelGGL(gate_slots<false>, dim3(nblk), dim3(GATE_TB), 0, st, idx, blockbase, counts, S, E, k, C, slot, inv);
+    hipLaunchKernelGGL(gate_slots<false>, dim3(nblk), dim3(SLOT_NT), 0, st, idx, blockbase, counts, S, E, k, C, slot, inv);
   }
   return moe::check_launch();
 }

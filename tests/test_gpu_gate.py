@@ -50,6 +50,11 @@ CASES = [
     (256, 8, 2, 77, True, 1), (257, 8, 3, 5, True, 0), (1000, 5, 2, 300, False, 1), (1000, 16, 4, 250, True, 1),
     (777, 17, 8, 400, False, 0), (513, 64, 2, 17, True, 1), (2049, 100, 6, 100, False, 1), (1500, 256, 8, 40, True, 0),
     (300, 3, 3, 300, False, 1), (4096, 8, 2, 1229, False, 1), (70000, 64, 2, 2000, True, 1),
+    # around the largest problem that one block takes (256 tokens up to 32 experts, 128 up to 128, 64 beyond)
+    (256, 32, 8, 60, True, 0), (257, 32, 2, 20, False, 1), (128, 33, 5, 9, False, 0), (129, 64, 1, 3, True, 1),
+    (128, 128, 8, 7, True, 1), (64, 256, 3, 2, False, 0), (65, 129, 8, 1, True, 0), (191, 16, 1, 10, True, 0),
+    # blocks that scan the histograms themselves, pairs in fours and not; the last size that does, and the first that does not
+    (4100, 9, 3, 900, True, 1), (8192, 128, 4, 300, False, 1), (8193, 128, 4, 300, True, 0), (8192, 1, 1, 8000, False, 0),
 ]
 
 
@@ -109,6 +114,22 @@ def test_gate_logits_odd_shapes(E, M, dtype):
     assert rel_err(got["logits"], ref) <= 1e-6
     if (got["logits"].astype(np.float32) == ref).all():
         check_routing(got, ref, k, 50, 1)
+
+
+@pytest.mark.parametrize("S,E,M,dtype", [(1, 8, 8, "bf16"), (33, 8, 4096, "f32"), (1023, 5, 136, "bf16"), (1024, 16, 1032, "f32"),
+                                         (1025, 11, 520, "bf16"), (4099, 8, 264, "bf16"), (8191, 16, 72, "bf16"),
+                                         (8191, 3, 128, "f32"), (2000, 1, 8, "f32"), (16448, 65, 40, "bf16")])
+def test_gate_logits_few_tokens(S, E, M, dtype):
+    """The kernel whose waves split M (E <= 16, fewer than 8192 tokens): both token counts per block, M below and off its
+    128-wide pieces, full and partial expert columns; and a wide gate whose M is not a multiple of its chunks."""
+    rng = np.random.default_rng(S + E + M)
+    x = synth.store(rng.standard_normal((S, M)).astype(np.float32), dtype)
+    Wg = (rng.standard_normal((M, E)) * 0.3).astype(np.float32)
+    bias = rng.standard_normal(E).astype(np.float32) if E % 2 else None
+    got = run_gate(None, 1, 50, 1, x=to_dev(x), Wg=to_dev(Wg), bias=to_dev(bias) if bias is not None else None, S_total=S, M=M)
+    ref = O.gate_logits(x.val, Wg, bias)
+    # fp64 sums in either order, rounded once: at most one unit in the last place apart
+    assert rel_err(got["logits"], ref) <= 1.2e-7
 
 
 @pytest.mark.parametrize("S,E,M,n_mp", [(9000, 12, 200, 1), (20001, 7, 1096, 1), (35000, 16, 520, 2), (70001, 3, 72, 1),
