@@ -2,7 +2,7 @@
 // top-k selection held fixed.
 //
 //   E <= 16 : gate_bwd_fused (dlogits, dx and the dWg partial sums in one kernel) + gate_dwg_reduce.
-//   E  > 16 : gate_dlogits (one thread per token; norm_topk: dl[e_j] = w_j (dw_j - sum_j' w_j' dw_j'),
+//   E  > 16 : gate_dlogits (one wave per token; norm_topk: dl[e_j] = w_j (dw_j - sum_j' w_j' dw_j'),
 //             otherwise dl[e] = sum_j dw_j p[e_j] (delta(e,e_j) - p[e]) with p = softmax(l)),
 //             gate_dx_wide (dx[t,m] (+)= sum_e dl[t,e] Wg[m,e]), gate_dwg_wide + gate_dwg_reduce.
 //   dWg[m,e] = sum_t x[t,m] dl[t,e] is formed as per-token-chunk fp32 partial sums followed by a
@@ -22,48 +22,66 @@ inline int dwg_chunk(int64_t S, int E) {
   return (int)(c < least ? least : (c + 7) / 8 * 8);
 }
 
+// The selected experts' weights and weight gradients of a token, all requested together.
+struct Picks {
+  float w[MOE_MAX_K], g[MOE_MAX_K];
+  int e[MOE_MAX_K];
+  float inner;   // sum_j w_j dw_j
+  __device__ __forceinline__ Picks(const float* dw, const float* wt, const int32_t* idx, int64_t t, int k) {
+#pragma unroll
+    for (int j = 0; j < MOE_MAX_K; ++j) {
+      const int64_t at = t * k + (j < k ? j : k - 1);
+      w[j] = wt[at]; g[j] = dw[at]; e[j] = idx[at];
+    }
+    inner = 0.f;
+#pragma unroll
+    for (int j = 0; j < MOE_MAX_K; ++j)
+      if (j < k) inner = fmaf(w[j], g[j], inner); else e[j] = -1;
+  }
+};
+
+// E > 16: one wave per token, a lane per expert (four passes at most), so that rows of logits and dlogits are read and
+// written whole.  8192 x 128: 36 us with a thread per token -> 5 us.
 __global__ __launch_bounds__(256) void gate_dlogits(const float* __restrict__ dw, const float* __restrict__ w,
                                                     const int32_t* __restrict__ idx, const float* __restrict__ logits,
                                                     int64_t S, int E, int k, int norm_topk, float* __restrict__ dl) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  constexpr int EPL = MOE_MAX_E / 64;
+  const int lane = threadIdx.x & 63;
+  const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= S) return;
-  float wj[MOE_MAX_K], gj[MOE_MAX_K];
-  int ej[MOE_MAX_K];
-  float inner = 0.f;
+  const Picks p(dw, w, idx, t, k);
+  float v[EPL];
 #pragma unroll
-  for (int j = 0; j < MOE_MAX_K; ++j) {
-    wj[j] = 0.f; gj[j] = 0.f; ej[j] = -1;
-    if (j < k) {
-      wj[j] = w[t * k + j]; gj[j] = dw[t * k + j]; ej[j] = idx[t * k + j];
-      inner = fmaf(wj[j], gj[j], inner);
-    }
-  }
-  float mx = 0.f, den = 1.f;
+  for (int i = 0; i < EPL; ++i) v[i] = 0.f;
   if (!norm_topk) {
-    mx = logits[t * E];
-    for (int e = 1; e < E; ++e) mx = fmaxf(mx, logits[t * E + e]);
-    den = 0.f;
-    for (int e = 0; e < E; ++e) den += expf(logits[t * E + e] - mx);
+    float l[EPL], mx = -__builtin_inff(), den = 0.f;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      l[i] = logits[t * E + min(lane + 64 * i, E - 1)];
+      mx = fmaxf(mx, l[i]);
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      v[i] = expf(l[i] - mx);
+      if (lane + 64 * i < E) den += v[i];
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) den += __shfl_xor(den, d, 64);
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) v[i] = -(v[i] / den) * p.inner;
   }
-  for (int e = 0; e < E; ++e) {
-    float v = norm_topk ? 0.f : -(expf(logits[t * E + e] - mx) / den) * inner;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int e = lane + 64 * i;
 #pragma unroll
     for (int j = 0; j < MOE_MAX_K; ++j)
-      if (ej[j] == e) v += norm_topk ? wj[j] * (gj[j] - inner) : wj[j] * gj[j];
-    dl[t * E + e] = v;
+      if (p.e[j] == e) v[i] += norm_topk ? p.w[j] * (p.g[j] - p.inner) : p.w[j] * p.g[j];
+    if (e < E) dl[t * E + e] = v[i];
   }
 }
 
-template <bool BF16>
-__device__ __forceinline__ void ld8g(const void* base, int64_t off, float* f) {
-  if (BF16) {
-    unpack_bf16x8(*reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(base) + off), f);
-  } else {
-    const float4* p = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + off);
-    const float4 a = p[0], b = p[1];
-    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-  }
-}
 template <bool BF16>
 __device__ __forceinline__ void st8g(void* base, int64_t off, const float* f) {
   if (BF16) {
@@ -114,32 +132,8 @@ __global__ __launch_bounds__(256) void gate_dwg_reduce(const float* __restrict__
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// E <= 16: the whole gate backward except the final reduction in ONE kernel.  A block owns one
-// chunk of tokens (the unit of a dWg partial sum) and NTHR * 4 columns of M (one wave, 256 columns,
-// for up to 8 experts: many small blocks hide each other's phases; two waves for up to 16); a
-// thread owns 4 consecutive columns, so that its slice of Wg and its dWg accumulators fit in registers.  Sixteen tokens at a time, sixteen threads compute the
-// dlogits rows into LDS (column block 0 also stores them); then every thread reads its x and old
-// dx pieces of those tokens once and uses them twice:
-//     dWg partial[e][q] += x[t, q] dl[t, e]        dx[t, q] (+)= sum_e dl[t, e] Wg[q, e]
-// The partial sums leave through LDS so that [m][e] rows are written contiguously.
-// ---------------------------------------------------------------------------------------------
-constexpr int FT = 16;   // tokens per dlogits stage
-template <bool BF16, int N>
-__device__ __forceinline__ void ldn(const void* base, int64_t off, float* f) {
-  if (N == 8) { ld8g<BF16>(base, off, f); return; }
-  if (BF16) {
-    const uint2 v = *reinterpret_cast<const uint2*>(reinterpret_cast<const bf16_t*>(base) + off);
-    f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xFFFF0000u);
-    f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xFFFF0000u);
-  } else {
-    const float4 a = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + off);
-    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
-  }
-}
-template <bool BF16, int N>
-__device__ __forceinline__ void stn(void* base, int64_t off, const float* f) {
-  if (N == 8) { st8g<BF16>(base, off, f); return; }
+template <bool BF16>
+__device__ __forceinline__ void st4g(void* base, int64_t off, const float* f) {
   if (BF16) {
     *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(base) + off) = make_uint2(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]));
   } else {
@@ -173,94 +167,129 @@ struct RawRow {
   }
 };
 
-template <bool BF16, int EC, int CPT, int NTHR>
-__global__ __launch_bounds__(NTHR) void gate_bwd_fused(const float* __restrict__ dw, const float* __restrict__ w,
-                                                       const int32_t* __restrict__ idx, const float* __restrict__ logits,
-                                                       const void* __restrict__ x, const float* __restrict__ Wg,
-                                                       int64_t S, int M, int E, int k, int norm_topk, int chunk,
-                                                       float* __restrict__ dl_out, void* __restrict__ dx, int accumulate,
-                                                       float* __restrict__ partial) {
-  constexpr int MT = NTHR * CPT, PITCH = MT + 8;
-  __shared__ __attribute__((aligned(16))) float outs[EC * PITCH];
-  __shared__ __attribute__((aligned(16))) float dls[FT * EC];
-  const int tid = threadIdx.x;
-  const int mb = blockIdx.x * MT, ml = tid * CPT, m0 = mb + ml;
+// ---------------------------------------------------------------------------------------------
+// E <= 16: the whole gate backward except the final reduction in ONE kernel.  A block of four waves owns one
+// chunk of tokens (the unit of a dWg partial sum) and 256 columns of M; a thread owns 4 consecutive columns of a quarter
+// of the tokens, so that its slice of Wg and its dWg accumulators fit in registers.  The chunk's dlogits rows go to
+// LDS first (one thread per token; column block 0 also stores them); then every wave reads the x and old dx pieces of its
+// tokens once, FT tokens at a time, and uses them twice:
+//     dWg partial[e][q] += x[t, q] dl[t, e]        dx[t, q] (+)= sum_e dl[t, e] Wg[q, e]
+// The four waves' sums are added in LDS in a fixed order and leave it so that [m][e] rows are written contiguously.
+// Memory-bound at large sizes; at small ones the time is a chain of latencies, the fetch of the instructions among
+// them: a version that unrolled 16 tokens was 17 to 34 KB of straight-line code and, with one wave per chunk, wrote
+// four times the partial sums.  2048 x 768, 16 experts: 27 -> 17 us; 4096 x 1024, 8 experts: 21 -> 18 us; 32768 x 4096, 8
+// experts: 208 -> 186 us.
+// ---------------------------------------------------------------------------------------------
+constexpr int FW = 4;                                    // waves per block
+constexpr int FT = 4;                                    // tokens per stage of a wave
+constexpr int FUSED_CHUNK = 256;                         // dlogits rows in LDS at a time
+// tokens per block: at most 256 partial sums (their number is at most that of dwg_chunk, which sizes the workspace)
+inline int64_t fused_chunk(int64_t S) {
+  const int64_t step = FW * FT, c = (S + 255) / 256;
+  return (c + step - 1) / step * step;
+}
+template <bool BF16, int EC>
+__global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_fused(const float* __restrict__ dw, const float* __restrict__ w,
+                                                          const int32_t* __restrict__ idx, const float* __restrict__ logits,
+                                                          const void* __restrict__ x, const float* __restrict__ Wg,
+                                                          int64_t S, int M, int E, int k, int norm_topk, int64_t chunk,
+                                                          float* __restrict__ dl_out, void* __restrict__ dx, int accumulate,
+                                                          float* __restrict__ partial) {
+  constexpr int CPT = 4, MT = 64 * CPT, PITCH = MT + 8, NTHR = 64 * FW;
+  static_assert(FUSED_CHUNK == NTHR, "a thread per dlogits row");
+  __shared__ __attribute__((aligned(16))) float outs[2][EC * PITCH];
+  __shared__ __attribute__((aligned(16))) float dls[FUSED_CHUNK * EC];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mb = blockIdx.x * MT, m0 = mb + lane * CPT;
   const bool mok = m0 < M;
+  const int mc = mok ? m0 : 0;     // a lane behind the last column works on the first ones and stores nothing
   const int64_t tb = (int64_t)blockIdx.y * chunk;
   const int64_t te = (tb + chunk < S) ? tb + chunk : S;
   float* out = partial + (int64_t)blockIdx.y * (M + 1) * E;
 
+  // The block's slab of Wg, contiguous in memory, goes through LDS once for the four waves: read directly, a lane's
+  // weights are strided pieces, and every request of a wave is 64 lines.
+  for (int i = tid; i < MT * E; i += NTHR) {
+    const int m = i / E, e = i - m * E;
+    outs[0][e * PITCH + m] = mb + m < M ? Wg[(int64_t)mb * E + i] : 0.f;
+  }
   float wr[CPT][EC], acc[EC][CPT];
 #pragma unroll
-  for (int q = 0; q < CPT; ++q)
+  for (int e = 0; e < EC; ++e)
 #pragma unroll
-    for (int e = 0; e < EC; ++e) {
-      wr[q][e] = (mok && e < E) ? Wg[(int64_t)(m0 + q) * E + e] : 0.f;
-      acc[e][q] = 0.f;
-    }
+    for (int q = 0; q < CPT; ++q) acc[e][q] = 0.f;
   float colsum = 0.f;   // thread e < E of column block 0 sums dl[:, e] for the bias row
 
-  for (int64_t t0 = tb; t0 < te; t0 += FT) {
-    const int nt = (int)((te - t0 < FT) ? te - t0 : FT);
-    // the stage's x and old dx pieces are requested before the dlogits rows are worked out
-    RawRow<BF16, CPT> xr[FT], dr[FT];
-#pragma unroll
-    for (int u = 0; u < FT; ++u) {
-      if (mok && u < nt) xr[u].load(x, (t0 + u) * (int64_t)M + m0); else xr[u].zero();
-      if (mok && u < nt && accumulate) dr[u].load(dx, (t0 + u) * (int64_t)M + m0); else dr[u].zero();
-    }
-    __syncthreads();   // the previous stage's dl rows are consumed
-    if (tid < FT) {
-      const int64_t t = t0 + tid;
+  for (int64_t c0 = tb; c0 < te; c0 += FUSED_CHUNK) {
+    const int nc = (int)(te - c0 < FUSED_CHUNK ? te - c0 : FUSED_CHUNK);
+    if (c0 != tb) __syncthreads();   // the previous dl rows are consumed
+    if (tid < nc) {
+      const int64_t t = c0 + tid;
+      const Picks p(dw, w, idx, t, k);
       float row[EC];
 #pragma unroll
       for (int e = 0; e < EC; ++e) row[e] = 0.f;
-      if (t < te) {
-        float wj[MOE_MAX_K], gj[MOE_MAX_K];
-        int ej[MOE_MAX_K];
-        float inner = 0.f;
+      if (!norm_topk) {
+        float mx = -__builtin_inff(), den = 0.f;
 #pragma unroll
-        for (int j = 0; j < MOE_MAX_K; ++j) {
-          wj[j] = 0.f; gj[j] = 0.f; ej[j] = -1;
-          if (j < k) {
-            wj[j] = w[t * k + j]; gj[j] = dw[t * k + j]; ej[j] = idx[t * k + j];
-            inner = fmaf(wj[j], gj[j], inner);
-          }
-        }
-        float mx = 0.f, den = 1.f;
-        if (!norm_topk) {
-          mx = logits[t * E];
-          for (int e = 1; e < E; ++e) mx = fmaxf(mx, logits[t * E + e]);
-          den = 0.f;
-          for (int e = 0; e < E; ++e) den += expf(logits[t * E + e] - mx);
+        for (int e = 0; e < EC; ++e) {
+          row[e] = logits[t * E + (e < E ? e : E - 1)];
+          mx = fmaxf(mx, row[e]);
         }
 #pragma unroll
         for (int e = 0; e < EC; ++e) {
-          if (e < E) {
-            float v = norm_topk ? 0.f : -(expf(logits[t * E + e] - mx) / den) * inner;
-#pragma unroll
-            for (int j = 0; j < MOE_MAX_K; ++j)
-              if (ej[j] == e) v += norm_topk ? wj[j] * (gj[j] - inner) : wj[j] * gj[j];
-            row[e] = v;
-            if (blockIdx.x == 0) dl_out[t * E + e] = v;
-          }
+          row[e] = expf(row[e] - mx);
+          if (e < E) den += row[e];
         }
+#pragma unroll
+        for (int e = 0; e < EC; ++e) row[e] = e < E ? -(row[e] / den) * p.inner : 0.f;
       }
 #pragma unroll
       for (int e = 0; e < EC; ++e) dls[tid * EC + e] = row[e];
+      for (int j = 0; j < k; ++j) {
+        const float wj = w[t * k + j], gj = dw[t * k + j];   // (in the cache by now; a register array would not be indexed)
+        const int ej = idx[t * k + j];
+        if ((unsigned)ej < (unsigned)E) dls[tid * EC + ej] += norm_topk ? wj * (gj - p.inner) : wj * gj;
+      }
+    } else {   // rows behind the chunk's end: zeros, which the last stage multiplies
+#pragma unroll
+      for (int e = 0; e < EC; ++e) dls[tid * EC + e] = 0.f;
     }
     __syncthreads();
-    if (blockIdx.x == 0 && tid < EC)
-      for (int t = 0; t < FT; ++t) colsum += dls[t * EC + tid];
-    if (mok) {
+    if (c0 == tb) {
+#pragma unroll
+      for (int e = 0; e < EC; ++e) {
+        const float4 v = e < E ? *reinterpret_cast<const float4*>(&outs[0][e * PITCH + lane * CPT]) : make_float4(0.f, 0.f, 0.f, 0.f);
+        wr[0][e] = v.x; wr[1][e] = v.y; wr[2][e] = v.z; wr[3][e] = v.w;
+      }
+    }
+    if (blockIdx.x == 0) {
+      for (int i = tid; i < nc * E; i += NTHR) {
+        const int t = i / E, e = i - t * E;
+        dl_out[c0 * E + i] = dls[t * EC + e];
+      }
+      if (tid < EC) {
+#pragma unroll 8
+        for (int t = 0; t < nc; ++t) colsum += dls[t * EC + tid];
+      }
+    }
+    for (int u0 = wave * FT; u0 < nc; u0 += FW * FT) {
+      RawRow<BF16, CPT> xr[FT], dr[FT];
+#pragma unroll
+      for (int u = 0; u < FT; ++u) {   // a row behind the end: the last one again, not stored, its dl row is zero
+        const int64_t at = (c0 + min(u0 + u, nc - 1)) * (int64_t)M + mc;
+        xr[u].load(x, at);
+        if (accumulate) dr[u].load(dx, at); else dr[u].zero();
+      }
 #pragma unroll
       for (int u = 0; u < FT; ++u) {
+        const bool in = u0 + u < nc;
         float xv[CPT], dv[CPT];
 #pragma unroll
-        for (int q = 0; q < CPT; ++q) { xv[q] = xr[u].get(q); dv[q] = dr[u].get(q); }
+        for (int q = 0; q < CPT; ++q) { xv[q] = in ? xr[u].get(q) : 0.f; dv[q] = dr[u].get(q); }
 #pragma unroll
         for (int e4 = 0; e4 < EC; e4 += 4) {
-          const float4 d4 = *reinterpret_cast<const float4*>(&dls[u * EC + e4]);
+          const float4 d4 = *reinterpret_cast<const float4*>(&dls[(u0 + u) * EC + e4]);
           const float d[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
           for (int v = 0; v < 4; ++v)
@@ -270,149 +299,180 @@ __global__ __launch_bounds__(NTHR) void gate_bwd_fused(const float* __restrict__
               dv[q] = fmaf(d[v], wr[q][e4 + v], dv[q]);
             }
         }
-        if (u < nt) stn<BF16, CPT>(dx, (t0 + u) * (int64_t)M + m0, dv);
+        if (in && mok) st4g<BF16>(dx, (c0 + u0 + u) * (int64_t)M + m0, dv);
       }
     }
   }
+  __syncthreads();   // every wave has its weights
+  // waves 2 and 3 hand their sums to 0 and 1, wave 1 to wave 0
+  auto put = [&](float* o) {
+#pragma unroll
+    for (int e = 0; e < EC; ++e)
+      *reinterpret_cast<float4*>(&o[e * PITCH + lane * CPT]) = make_float4(acc[e][0], acc[e][1], acc[e][2], acc[e][3]);
+  };
+  auto add = [&](const float* o) {
+#pragma unroll
+    for (int e = 0; e < EC; ++e) {
+      const float4 v = *reinterpret_cast<const float4*>(&o[e * PITCH + lane * CPT]);
+      acc[e][0] += v.x; acc[e][1] += v.y; acc[e][2] += v.z; acc[e][3] += v.w;
+    }
+  };
+  if (wave >= 2) put(outs[wave - 2]);
   __syncthreads();
-#pragma unroll
-  for (int e = 0; e < EC; ++e)
-#pragma unroll
-    for (int q = 0; q < CPT; q += 4)
-      *reinterpret_cast<float4*>(&outs[e * PITCH + ml + q]) = make_float4(acc[e][q], acc[e][q + 1], acc[e][q + 2], acc[e][q + 3]);
+  if (wave < 2) add(outs[wave]);
+  if (wave == 1) put(outs[1]);    // its own buffer, which it has just read
+  __syncthreads();
+  if (wave == 0) { add(outs[1]); put(outs[0]); }
   __syncthreads();
   for (int i = tid; i < MT * EC; i += NTHR) {
     const int m = i / EC, e = i - m * EC;
-    if (mb + m < M && e < E) out[(int64_t)(mb + m) * E + e] = outs[e * PITCH + m];
+    if (mb + m < M && e < E) out[(int64_t)(mb + m) * E + e] = outs[0][e * PITCH + m];
   }
   if (blockIdx.x == 0 && tid < E && tid < EC) out[(int64_t)M * E + tid] = colsum;
 }
 
 // ---------------------------------------------------------------------------------------------
-// E > 16.  The two products are small-K / small-N GEMMs on the vector ALUs with everything shared
-// through LDS, experts taken 32 (dx) or 64 (dWg) at a time.
-//
-// gate_dx_wide: a block owns 64 tokens x 256 columns; thread = 4 columns x 16 tokens (64 fp32
-// accumulators that stay in registers across the expert chunks).  Per chunk the Wg slab goes to LDS
-// transposed, [e][column] with pitch 260, so a thread reads its 4 columns of an expert with one 16-byte
-// access and consecutive lanes are contiguous; dl rows are read as wave-wide broadcasts.
+// E > 16.  The two products run on the fp32 matrix cores: v_mfma_f32_32x32x2_f32, lane l supplies A[l % 32][l / 32] and
+// B[l / 32][l % 32] and receives D[8 (i / 4) + 4 (l / 32) + i % 4][l % 32], i = 0..15.  Operands are read straight from
+// memory in the layout in which they lie: which k a lane's half feeds in which step, and which row or column of the
+// output a lane's index names, are free as long as both operands agree, so the lanes take 8 to 16 consecutive bytes and no
+// LDS and no barriers are needed; the reuse between waves comes from the caches.  8192 x 2048 x 128 experts (4.3 GFLOP
+// each; 27 us at the nominal matrix rate): dx 187 -> 67 us, dWg 132 -> 55 us against vector FMAs on operands
+// staged through LDS.
 // ---------------------------------------------------------------------------------------------
-constexpr int WX_EB = 32, WX_TOK = 64, WX_COLS = 256, WX_PITCH = WX_COLS + 4;
-template <bool BF16>
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+
+// gate_dx_wide: dx^T tiles (rows: columns of M, columns: tokens).  A wave owns 32 tokens, whose dl rows it holds in
+// registers (KG groups of 8 experts), and walks WX_COLS columns 32 at a time.  Row 8 q + 4 h + i of a tile stands for column
+// 16 h + 4 q + i, so that the lane's 16 results are 16 consecutive columns of its token.  k step i of a group takes experts 8 g + i and 8 g + 4 + i.
+constexpr int WX_COLS = 128;
+template <bool BF16, int KG>
 __global__ __launch_bounds__(256) void gate_dx_wide(const float* __restrict__ dl, const float* __restrict__ Wg,
                                                     void* __restrict__ dx, int64_t S, int M, int E, int accumulate) {
-  __shared__ __attribute__((aligned(16))) float wgs[WX_EB * WX_PITCH];
-  __shared__ __attribute__((aligned(16))) float dls[WX_TOK * WX_EB];
-  const int tid = threadIdx.x, cg = tid & 63, tg = tid >> 6;
-  const int cb = blockIdx.x * WX_COLS, c0 = cb + cg * 4;
-  const int64_t tb = (int64_t)blockIdx.y * WX_TOK, t0 = tb + tg * 16;
-  const bool cok = c0 < M;     // M is a multiple of 8, so 4 columns are in or out together
-  float acc[16][4];
+  const int lane = threadIdx.x & 63, row = lane & 31, half = lane >> 5;
+  const int64_t t = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 32 + row;
+  if (t - row >= S) return;
+  const bool tok = t < S;
+  const bool vec = (E & 3) == 0;      // 16-byte loads of four consecutive experts
+  auto load4 = [&](const float* base, int e) -> float4 {   // experts e .. e + 3, zeros behind the last one
+    if (vec) return e < E ? *reinterpret_cast<const float4*>(base + e) : make_float4(0.f, 0.f, 0.f, 0.f);
+    float v[4];
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    if (accumulate && cok && t0 + t < S) {
-      ldn<BF16, 4>(dx, (t0 + t) * (int64_t)M + c0, acc[t]);
-    } else {
+    for (int i = 0; i < 4; ++i) v[i] = e + i < E ? base[e + i] : 0.f;
+    return make_float4(v[0], v[1], v[2], v[3]);
+  };
+  float4 d[KG];
+  const float* drow = dl + (tok ? t : S - 1) * E;   // a token past the end: any row, not stored
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[t][q] = 0.f;
+  for (int g = 0; g < KG; ++g) d[g] = load4(drow, 8 * g + 4 * half);
+  const int cb = blockIdx.y * WX_COLS, ce = min(M, cb + WX_COLS);
+  const int wcol = 16 * ((row >> 2) & 1) + 4 * (row >> 3) + (row & 3);   // the column that this lane's row stands for
+  for (int c0 = cb; c0 < ce; c0 += 32) {
+    const float* wrow = Wg + (int64_t)min(c0 + wcol, M - 1) * E;
+    const int c = c0 + 16 * half;    // M is a multiple of 8: runs of 8 columns are in or out together
+    RawRow<BF16, 8> old[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (accumulate && tok && c + 8 * q < M) old[q].load(dx, t * (int64_t)M + c + 8 * q); else old[q].zero();
     }
-  }
-  for (int ec = 0; ec < E; ec += WX_EB) {
-    __syncthreads();
-    for (int i = tid; i < WX_COLS * WX_EB; i += 256) {      // Wg[cb + c][ec + e], read along e
-      const int c = i / WX_EB, e = i - c * WX_EB;
-      wgs[e * WX_PITCH + c] = (cb + c < M && ec + e < E) ? Wg[(int64_t)(cb + c) * E + ec + e] : 0.f;
+    f32x16_t acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+    for (int g = 0; g < KG; ++g) {
+      const float4 wv = load4(wrow, 8 * g + 4 * half);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv.x, d[g].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv.y, d[g].y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv.z, d[g].z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv.w, d[g].w, acc, 0, 0, 0);
     }
-    for (int i = tid; i < WX_TOK * WX_EB; i += 256) {
-      const int t = i / WX_EB, e = i - t * WX_EB;
-      dls[i] = (tb + t < S && ec + e < E) ? dl[(tb + t) * E + ec + e] : 0.f;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      float o[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[i] = old[q].get(i) + acc[8 * q + i];
+      if (tok && c + 8 * q < M) st8g<BF16>(dx, t * (int64_t)M + c + 8 * q, o);
     }
-    __syncthreads();
-#pragma unroll 2
-    for (int e4 = 0; e4 < WX_EB; e4 += 4) {
-      float4 wv[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wv[j] = *reinterpret_cast<const float4*>(&wgs[(e4 + j) * WX_PITCH + cg * 4]);
-#pragma unroll
-      for (int t = 0; t < 16; ++t) {
-        const float4 d = *reinterpret_cast<const float4*>(&dls[(tg * 16 + t) * WX_EB + e4]);
-        const float dv[4] = {d.x, d.y, d.z, d.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[t][0] = fmaf(dv[j], wv[j].x, acc[t][0]);
-          acc[t][1] = fmaf(dv[j], wv[j].y, acc[t][1]);
-          acc[t][2] = fmaf(dv[j], wv[j].z, acc[t][2]);
-          acc[t][3] = fmaf(dv[j], wv[j].w, acc[t][3]);
-        }
-      }
-    }
-  }
-  if (cok) {
-#pragma unroll
-    for (int t = 0; t < 16; ++t)
-      if (t0 + t < S) stn<BF16, 4>(dx, (t0 + t) * (int64_t)M + c0, acc[t]);
   }
 }
 
-// gate_dwg_wide: a block owns one token chunk x 256 columns x 64 experts (grid.z walks the expert
-// blocks); thread = 4 columns x 16 experts (64 accumulators).  16 tokens at a time: their x pieces
-// are requested first, the dl rows staged in LDS and read as broadcasts (a wave shares its 16 experts).
+// gate_dwg_wide: a wave owns one token chunk, 128 columns of M and 64 experts: 4 x 2 tiles, in which lane l % 32 stands
+// for columns 4 (l % 32) + {0..3} and experts 2 (l % 32) + {0, 1}, so that a token's pieces of x and dl are whole lines; k step:
+// two tokens, one per half of the wave.  Four steps are requested while the four before are multiplied, and two waves share a SIMD.
 // partial[chunk][m][e] for m < M, plus row m = M (column sums of dl) for the bias gradient.
+constexpr int WW_COLS = 128;
 template <bool BF16>
-__global__ __launch_bounds__(256) void gate_dwg_wide(const void* __restrict__ x, const float* __restrict__ dl,
+__global__ __launch_bounds__(256, 2) void gate_dwg_wide(const void* __restrict__ x, const float* __restrict__ dl,
                                                      float* __restrict__ partial, int64_t S, int M, int E, int chunk) {
-  __shared__ __attribute__((aligned(16))) float dls[16 * 64];
-  const int tid = threadIdx.x, cg = tid & 63, eg = tid >> 6;
-  const int c0 = blockIdx.x * 256 + cg * 4;
-  const int eb = blockIdx.z * 64;
-  const bool cok = c0 < M;
+  constexpr int U = 4;
+  const int lane = threadIdx.x & 63, li = lane & 31, half = lane >> 5;
+  const int mb = (blockIdx.x * 4 + (threadIdx.x >> 6)) * WW_COLS;
+  if (mb >= M) return;
+  const int e0 = blockIdx.z * 64 + 2 * li;
   const int64_t tb = (int64_t)blockIdx.y * chunk;
   const int64_t te = (tb + chunk < S) ? tb + chunk : S;
+  const int c0 = min(mb + 4 * li, M - 4);           // a lane behind the last column: any columns, not stored
+  const int ea = min(e0, E - 1), eb = min(e0 + 1, E - 1);
+  f32x16_t acc[4][2];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[b][f][i] = 0.f;
+  float sum[2] = {0.f, 0.f};
+  RawRow<BF16, 4> xr[2][U];
+  float dr[2][U][2];
+  auto fetch = [&](int set, int64_t t0) {   // tokens behind the end: the last one, masked when multiplied
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t t = min(t0 + 2 * u + half, te - 1);
+      xr[set][u].load(x, t * (int64_t)M + c0);
+      dr[set][u][0] = dl[t * E + ea];
+      dr[set][u][1] = dl[t * E + eb];
+    }
+  };
+  auto multiply = [&](int set, int64_t t0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = t0 + 2 * u + half < te;
+      const float d0 = in ? dr[set][u][0] : 0.f, d1 = in ? dr[set][u][1] : 0.f;
+      sum[0] += d0; sum[1] += d1;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const float a = in ? xr[set][u].get(b) : 0.f;
+        acc[b][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, d0, acc[b][0], 0, 0, 0);
+        acc[b][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, d1, acc[b][1], 0, 0, 0);
+      }
+    }
+  };
+  fetch(0, tb);
+  for (int64_t t0 = tb; t0 < te; t0 += 4 * U) {   // two sets of 2 U tokens
+    if (t0 + 2 * U < te) fetch(1, t0 + 2 * U);
+    multiply(0, t0);
+    if (t0 + 2 * U < te) {
+      if (t0 + 4 * U < te) fetch(0, t0 + 4 * U);
+      multiply(1, t0 + 2 * U);
+    }
+  }
   float* out = partial + (int64_t)blockIdx.y * (M + 1) * E;
-  float acc[16][4];
 #pragma unroll
-  for (int j = 0; j < 16; ++j)
+  for (int i = 0; i < 16; ++i)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[j][q] = 0.f;
-  float colsum = 0.f;
-  for (int64_t t0 = tb; t0 < te; t0 += 16) {
-    RawRow<BF16, 4> xr[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      if (cok && t0 + u < te) xr[u].load(x, (t0 + u) * (int64_t)M + c0); else xr[u].zero();
-    }
-    __syncthreads();
-    for (int i = tid; i < 16 * 64; i += 256) {
-      const int t = i >> 6, e = i & 63;
-      dls[i] = (t0 + t < te && eb + e < E) ? dl[(t0 + t) * E + eb + e] : 0.f;
-    }
-    __syncthreads();
-    if (blockIdx.x == 0 && tid < 64)
-      for (int t = 0; t < 16; ++t) colsum += dls[t * 64 + tid];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const float xv[4] = {xr[u].get(0), xr[u].get(1), xr[u].get(2), xr[u].get(3)};
-#pragma unroll
-      for (int j4 = 0; j4 < 16; j4 += 4) {
-        const float4 d = *reinterpret_cast<const float4*>(&dls[u * 64 + eg * 16 + j4]);
-        const float dv[4] = {d.x, d.y, d.z, d.w};
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[j4 + jj][q] = fmaf(xv[q], dv[jj], acc[j4 + jj][q]);
+    for (int b = 0; b < 4; ++b) {
+      const int m = mb + 4 * (8 * (i >> 2) + 4 * half + (i & 3)) + b;
+      if (m < M) {
+        if (e0 < E) out[(int64_t)m * E + e0] = acc[b][0][i];
+        if (e0 + 1 < E) out[(int64_t)m * E + e0 + 1] = acc[b][1][i];
       }
     }
-  }
-  if (cok) {
+  if (mb == 0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int e = eb + eg * 16 + j;
-        if (e < E) out[(int64_t)(c0 + q) * E + e] = acc[j][q];
-      }
+    for (int f = 0; f < 2; ++f) {
+      const float s = sum[f] + __shfl_xor(sum[f], 32, 64);
+      if (half == 0 && e0 + f < E) out[(int64_t)M * E + e0 + f] = s;
+    }
   }
-  if (blockIdx.x == 0 && tid < 64 && eb + tid < E) out[(int64_t)M * E + eb + tid] = colsum;
 }
 
 }  // namespace
@@ -443,29 +503,32 @@ extern "C" int moe_gate_bwd(const float* dw, const float* w, const int32_t* idx,
   const bool bf = x_dtype == MOE_BF16;
   const int64_t n = (int64_t)(M + 1) * E;
   if (E <= 16) {   // one fused kernel, then the reduction of the partial sums
-    const int chunk = dwg_chunk(S, E);
+    const int EC = E <= 8 ? 8 : 16;
+    const int64_t chunk = fused_chunk(S);
     const int nchunk = (int)((S + chunk - 1) / chunk);
     float* partial = (float*)ws;
-    const int cols = E <= 8 ? 64 * 4 : 128 * 4;   // columns per block
-    const dim3 grid((unsigned)((M + cols - 1) / cols), (unsigned)nchunk);
-#define MOE_FUSED(BF, EC, CPT, NT) hipLaunchKernelGGL((gate_bwd_fused<BF, EC, CPT, NT>), grid, dim3(NT), 0, st, dw, w, idx, logits, x, \
-                                                       Wg, S, M, E, k, norm, chunk, dlogits, dx, dx_accumulate, partial)
-    if (bf) { if (E <= 8) MOE_FUSED(true, 8, 4, 64); else MOE_FUSED(true, 16, 4, 128); }
-    else { if (E <= 8) MOE_FUSED(false, 8, 4, 64); else MOE_FUSED(false, 16, 4, 128); }
+    const dim3 grid((unsigned)((M + 255) / 256), (unsigned)nchunk);
+#define MOE_FUSED(BF, EC_) hipLaunchKernelGGL((gate_bwd_fused<BF, EC_>), grid, dim3(64 * FW), 0, st, dw, w, idx, logits, x, \
+                                              Wg, S, M, E, k, norm, chunk, dlogits, dx, dx_accumulate, partial)
+    if (bf) { if (EC == 8) MOE_FUSED(true, 8); else MOE_FUSED(true, 16); }
+    else { if (EC == 8) MOE_FUSED(false, 8); else MOE_FUSED(false, 16); }
 #undef MOE_FUSED
     hipLaunchKernelGGL(gate_dwg_reduce, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial, nchunk, M, E, dWg,
                        dgate_bias);
     return moe::check_launch();
   }
-  hipLaunchKernelGGL(gate_dlogits, dim3((unsigned)((S + 255) / 256)), dim3(256), 0, st, dw, w, idx, logits, S, E, k,
+  hipLaunchKernelGGL(gate_dlogits, dim3((unsigned)((S + 3) / 4)), dim3(256), 0, st, dw, w, idx, logits, S, E, k,
                      norm, dlogits);
-  const dim3 grid_dx((unsigned)((M + WX_COLS - 1) / WX_COLS), (unsigned)((S + WX_TOK - 1) / WX_TOK));
-  if (bf) hipLaunchKernelGGL(gate_dx_wide<true>, grid_dx, dim3(256), 0, st, dlogits, Wg, dx, S, M, E, dx_accumulate);
-  else hipLaunchKernelGGL(gate_dx_wide<false>, grid_dx, dim3(256), 0, st, dlogits, Wg, dx, S, M, E, dx_accumulate);
+  const dim3 grid_dx((unsigned)((S + 127) / 128), (unsigned)((M + WX_COLS - 1) / WX_COLS));
+#define MOE_DX(kg) do { \
+    if (bf) hipLaunchKernelGGL((gate_dx_wide<true, kg>), grid_dx, dim3(256), 0, st, dlogits, Wg, dx, S, M, E, dx_accumulate); \
+    else hipLaunchKernelGGL((gate_dx_wide<false, kg>), grid_dx, dim3(256), 0, st, dlogits, Wg, dx, S, M, E, dx_accumulate); } while (0)
+  if (E <= 32) MOE_DX(4); else if (E <= 64) MOE_DX(8); else if (E <= 128) MOE_DX(16); else MOE_DX(32);
+#undef MOE_DX
   const int chunk = dwg_chunk(S, E);
   const int nchunk = (int)((S + chunk - 1) / chunk);
   float* partial = (float*)ws;
-  const dim3 grid_w((unsigned)((M + 255) / 256), (unsigned)nchunk, (unsigned)((E + 63) / 64));
+  const dim3 grid_w((unsigned)((M + 4 * WW_COLS - 1) / (4 * WW_COLS)), (unsigned)nchunk, (unsigned)((E + 63) / 64));
   if (bf) hipLaunchKernelGGL(gate_dwg_wide<true>, grid_w, dim3(256), 0, st, x, dlogits, partial, S, M, E, chunk);
   else hipLaunchKernelGGL(gate_dwg_wide<false>, grid_w, dim3(256), 0, st, x, dlogits, partial, S, M, E, chunk);
   hipLaunchKernelGGL(gate_dwg_reduce, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial, nchunk, M, E, dWg,

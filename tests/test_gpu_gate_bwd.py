@@ -18,6 +18,11 @@ pytestmark = pytest.mark.gpu
     # token and column tails, fewer than 8 experts, both weight normalisations, more than 65536 tokens
     (2048, 256, 8, 1, 0, "bf16", 1), (2049, 264, 8, 2, 1, "bf16", 1), (4099, 1032, 5, 2, 0, "bf16", 0),
     (3000, 520, 1, 1, 0, "bf16", 1), (70001, 72, 8, 2, 1, "bf16", 1),
+    # edges of the fused kernel's waves and chunks (4 tokens a stage, 16 a block, 256 dlogits rows at a time), of its 256
+    # columns, and of the matrix-core kernels' 32 tokens, 128 columns and 8, 32, 64, 128 experts
+    (15, 256, 16, 2, 1, "bf16", 1), (17, 264, 13, 3, 0, "f32", 1), (4097, 248, 8, 1, 0, "f32", 0), (70001, 8, 16, 2, 1, "f32", 1),
+    (31, 136, 24, 2, 0, "bf16", 1), (33, 120, 32, 4, 1, "f32", 0), (65, 128, 33, 1, 0, "bf16", 1), (127, 8, 64, 6, 1, "bf16", 1),
+    (4097, 520, 65, 2, 0, "f32", 1), (129, 264, 128, 8, 1, "bf16", 0), (300, 24, 129, 3, 0, "bf16", 1),
 ])
 def test_gate_bwd(S, M, E, k, norm, dtype, acc):
     rng = np.random.default_rng(S + E)
