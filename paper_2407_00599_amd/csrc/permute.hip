@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256) void combine_rows(const void* __restrict__ Yre
   }
 }
 
-// The common case (k <= 2 choices per token, 1, 2 or 4 partial sums per slot) with K and P fixed at
+// The common cases (up to 4 choices per token with few partial sums per slot, and 6 or 8 with one) with K and P fixed at
 // compile time: all K * P * NCH row pieces of a step are requested before the first is used, NCH
 // 512-element chunks per step so that about eight 16-byte loads per lane are in flight.
 template <bool BF16>
@@ -384,6 +384,7 @@ extern "C" int moe_combine_fwd(const void* Yret, int dtype, int n_part, int64_t 
     return moe::check_launch();                                                                                     \
   }
   COMBINE_KP(1, 1) COMBINE_KP(1, 2) COMBINE_KP(1, 4) COMBINE_KP(2, 1) COMBINE_KP(2, 2) COMBINE_KP(2, 4)
+  COMBINE_KP(3, 1) COMBINE_KP(3, 2) COMBINE_KP(4, 1) COMBINE_KP(4, 2) COMBINE_KP(6, 1) COMBINE_KP(8, 1)
 #undef COMBINE_KP
   if (bf) hipLaunchKernelGGL(combine_rows<true>, grid, block, 0, st, Yret, idx, slot, w, y, S, M, k, C, n_part, ps);
   else hipLaunchKernelGGL(combine_rows<false>, grid, block, 0, st, Yret, idx, slot, w, y, S, M, k, C, n_part, ps);
@@ -414,6 +415,7 @@ extern "C" int moe_combine_bwd(const void* dy, const void* Yret, int dtype, int 
     return moe::check_launch();                                                                                        \
   }
   COMBINE_DW_KP(1, 1) COMBINE_DW_KP(1, 2) COMBINE_DW_KP(1, 4) COMBINE_DW_KP(2, 1) COMBINE_DW_KP(2, 2) COMBINE_DW_KP(2, 4)
+  COMBINE_DW_KP(3, 1) COMBINE_DW_KP(3, 2) COMBINE_DW_KP(4, 1) COMBINE_DW_KP(4, 2) COMBINE_DW_KP(6, 1) COMBINE_DW_KP(8, 1)
 #undef COMBINE_DW_KP
   if (dYret) {
     if (bf) hipLaunchKernelGGL(dispatch_rows<true>, grid_r, block, 0, st, dy, inv, w, dYret, rows, M, k, C, (int64_t)0, C);

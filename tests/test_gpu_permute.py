@@ -22,6 +22,9 @@ def routing(S, E, k, C, seed, skew=1.0):
 @pytest.mark.parametrize("S,M,E,k,C,dtype", [
     (1, 8, 1, 1, 1, "f32"), (100, 64, 4, 2, 30, "f32"), (300, 520, 8, 2, 60, "bf16"), (1000, 1024, 16, 3, 150, "bf16"),
     (257, 4096, 8, 2, 70, "bf16"), (513, 72, 64, 8, 50, "f32"),
+    # the other choice counts with kernels of their own; 2056 columns: past one step of 512 x 4
+    (130, 2056, 8, 3, 40, "f32"), (203, 1032, 8, 4, 90, "bf16"), (100, 2056, 16, 6, 30, "bf16"), (99, 8, 16, 8, 40, "bf16"),
+    (64, 520, 8, 5, 40, "bf16"),
 ])
 def test_dispatch_and_combine(S, M, E, k, C, dtype):
     idx, slot, inv, w = routing(S, E, k, C, seed=S + M)
