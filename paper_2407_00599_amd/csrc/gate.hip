@@ -878,7 +878,7 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
       const int T = (E <= 8 ? 4 : 2) * (many ? 2 : 1);
       const int64_t blocks = (S + T - 1) / T;
       int nw = (M + 127) / 128 < LS_MAXW ? (M + 127) / 128 : LS_MAXW;
-      if (many && nw > 2048 / blocks) nw = (int)(2048 / blocks); 
+      if (many && nw > 2048 / blocks) nw = (int)(2048 / blocks);
       if (nw < 1) nw = 1;
       const dim3 grid((unsigned)blocks), block(64 * nw);
 #define LAUNCH_SPLIT(ec, t, full) do { \

@@ -140,7 +140,9 @@ __global__ __launch_bounds__(256) void combine_rows(const void* __restrict__ Yre
 
 // The common cases (up to 4 choices per token with few partial sums per slot, and 6 or 8 with one) with K and P fixed at
 // compile time: all K * P * NCH row pieces of a step are requested before the first is used, NCH
-// 512-element chunks per step so that about eight 16-byte loads per lane are in flight.
+// 512-element chunks per step so that about eight 16-byte loads per lane are in flight.  Bound by HBM once the requests
+// overlap; the general kernel (other counts) waits for each choice's row in turn.  8192 tokens x 2048, top-4 of 128 experts,
+// general kernel against this one: 51 and 53 -> 37 and 32 us forward, 101 (two launches) -> 81 us backward.
 template <bool BF16>
 struct Piece {   // 8 consecutive elements as loaded
   uint4 a, b;    // bf16: a only
