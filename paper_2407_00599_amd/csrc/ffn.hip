@@ -326,7 +326,8 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, char* lds_wave_b
 }
 // Fragment reads are issued as volatile asm: the compiler then neither reorders them nor guards
 // them with conservative waits against the LDS-DMA requests in flight.  The kernel waits for them
-// itself (s_waitcnt lgkmcnt(0)) and passes the registers through ready() before the MFMAs use them.
+// itself (s_waitcnt lgkmcnt(0)) and passes the registers through ready() before the MFMAs use them.  Every read is
+// waited for like that, also one that is not used: the compiler takes the registers as written at the read.
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 union Frag {
   bf16x8_t v;
@@ -913,7 +914,10 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   int t = 0;
   for (; t < n_main; ++t) k_tile(t, std::false_type{});
   for (; t < nk; ++t) k_tile(t, std::true_type{});
-  __builtin_amdgcn_s_waitcnt(0x0070);  // every request and fragment read is done before LDS is reused
+  // The last tile (or, without k tiles, the prologue) has read a first step that nobody multiplies: its registers stay
+  // taken until the reads have landed, or they would overwrite what the compiler puts there.
+  frags_ready(0);
+  __builtin_amdgcn_s_waitcnt(0x0070);  // every request is done before LDS is reused
   __syncthreads();
 
   if constexpr (WK == 2) {   // each of the two wave groups finishes half of the blocks: exchange the other halves
