@@ -283,7 +283,7 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc
 // tensor: the zero fill of an out-of-range request can reach LDS after the wait for it is over, and would then
 // destroy what the slot was refilled with.  Rows and columns outside the problem and padding rows are fetched
 // from another row / column (what they yield is not stored, or stored as zeros), k indexes behind the end of a k tile
-// from its first one (the A fragments are masked).
+// from its first one (the fragments of both operands are masked).
 //   operand with k contiguous in memory : [row][64 k] (128-byte rows, 8 chunks), chunk c of row r in slot
 //       c ^ ((r >> 1) & 7); fragments are read with ds_read_b128.
 //   operand with k as the slow index    : [64 k][T cols], chunk c of k-row k in slot c ^ 4 (k & 3) (T = 64:
@@ -774,7 +774,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   KTile ka{0, 0}, kb{0, 0};
   int g_entry = 0;        // GATHER: slot-map entries of g_next, the tile after ka
   KTile g_next{0, 0};
-  uint64_t k_mask[SA];    // TN: which k-rows of tiles t .. t + SA - 1 exist
+  uint64_t k_mask[SA];    // TN: which k-rows of tiles t .. t + SA - 1 exist (GATHER: and are occupied)
+  int k_lim[SA];          // GATHER: their numbers of rows
   auto mask_of = [&](const KTile& kt, uint64_t full) -> uint64_t {
     return kt.lim >= DK ? full : kt.lim <= 0 ? 0ull : full & ((1ull << kt.lim) - 1ull);
   };
@@ -793,6 +794,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     auto pro_a = [&](int t) {
       const uint64_t full = GATHER ? gather_rows(g_pro[t]) : ~0ull;
       k_mask[t] = mask_of(pro[t], full);
+      k_lim[t] = pro[t].lim;
     };
 #pragma unroll
     for (int st = -SA; st <= -2; ++st) {
@@ -838,27 +840,35 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
       else { if (!LAST || ka.lim > 0) request_a(ka, wa, R - RB); }
     });
   };
-  // zeroes the k-rows of set `set` (step ST of a tile) that do not exist, in the A fragments
-  auto mask_frags = [&](uint64_t mask, auto st_tag, int set) {
+  // zeroes the k-rows of set `set` (step ST of a tile) that do not exist, in both operands: what was fetched in their
+  // place may be an infinity.  (GATHER: an empty slot is a row of zeros in A only, as in the dispatched buffer.)
+  auto mask_frags = [&](uint64_t mask_a, uint64_t mask_b, auto st_tag, int set) {
     constexpr int ST = decltype(st_tag)::value;
-    const uint32_t bits = (uint32_t)(mask >> (16 * (wk * SPT + ST))) >> (8 * (lane >> 5));
-    u32x4_t m;
+    auto lanes = [&](uint64_t mask) {
+      const uint32_t bits = (uint32_t)(mask >> (16 * (wk * SPT + ST))) >> (8 * (lane >> 5));
+      u32x4_t m;
 #pragma unroll
-    for (int d = 0; d < 4; ++d) m[d] = ((bits >> (2 * d)) & 1u) * 0x0000FFFFu + ((bits >> (2 * d + 1)) & 1u) * 0xFFFF0000u;
+      for (int d = 0; d < 4; ++d) m[d] = ((bits >> (2 * d)) & 1u) * 0x0000FFFFu + ((bits >> (2 * d + 1)) & 1u) * 0xFFFF0000u;
+      return m;
+    };
+    const u32x4_t ma = lanes(mask_a), mb = GATHER ? lanes(mask_b) : ma;
 #pragma unroll
-    for (int i = 0; i < MB; ++i) fa[set][i].q &= m;
+    for (int i = 0; i < MB; ++i) fa[set][i].q &= ma;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) fb[set][j].q &= mb;
   };
   // one k tile; LAST: one of the last SA tiles, whose refills may be past the end
   auto k_tile = [&](int t, auto last_tag) {
     constexpr bool LAST = decltype(last_tag)::value;
     const int na = sa + 1 == SA ? 0 : sa + 1, nb = sb + 1 == SB ? 0 : sb + 1;   // slots of tile t+1
     const uint64_t mask = KIND == KIND_TN ? k_mask[0] : LAST ? mask_of(ktile_at(t), ~0ull) : ~0ull;
+    const uint64_t mask_b = GATHER ? mask_of(KTile{0, k_lim[0]}, ~0ull) : mask;
     unrolled<0, SPT>([&](auto st) {
       constexpr int ST = decltype(st)::value, set = ST & 1;
       using NEXT = std::integral_constant<int, (ST + 1) % SPT>;
       frags_ready(set);
       if constexpr (KIND == KIND_TN || LAST) {
-        if (mask != ~0ull) mask_frags(mask, st, set);
+        if (mask != ~0ull) mask_frags(mask, mask_b, st, set);
       }
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (ST < SPT - 1) {
@@ -890,8 +900,9 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
             g_entry = gather_fetch(g_next.row0);
           }
 #pragma unroll
-          for (int u = 0; u + 1 < SA; ++u) k_mask[u] = k_mask[u + 1];
+          for (int u = 0; u + 1 < SA; ++u) { k_mask[u] = k_mask[u + 1]; k_lim[u] = k_lim[u + 1]; }
           k_mask[SA - 1] = mask_of(ka, full);
+          k_lim[SA - 1] = ka.lim;
         } else {
           ka = ktile_at(t + SA);
           kb = ktile_at(t + SB);
