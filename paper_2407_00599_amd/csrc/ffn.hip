@@ -1345,6 +1345,7 @@ void launch_gemm(GemmArgs a, int dtype, int tile, hipStream_t st) {
 }
 
 inline bool valid_tile(int tile) { return tile >= MOE_TILE_AUTO && tile <= MOE_TILE_192; }
+inline bool ignores_counts(int dtype, int tile) { return dtype == MOE_BF16 && tile == MOE_TILE_SMALL; }
 
 int check_ffn_shape(int dtype, int n_src, int G, int64_t C, int M, int H, int esp_idx, int n_esp) {
   MOE_REQUIRE(dtype == MOE_F32 || dtype == MOE_BF16, MOE_EINVAL);
@@ -1427,7 +1428,7 @@ static int ffn_fwd_impl(const void* X, const int32_t* gather, int gather_k, int6
 
   GemmArgs a{};
   a.G = G; a.n_src = n_src; a.Cc = (int)C; a.R = (int)(n_src * C);
-  a.cnt = tile == MOE_TILE_SMALL ? nullptr : row_counts;
+  a.cnt = ignores_counts(dtype, tile) ? nullptr : row_counts;
   // Z = X * W1[:, h0:h0+Hl] ; A = GeLU(Z)
   a.A = X; a.lda = M;
   a.gather = gather; a.gather_k = gather_k; a.gather_rows = gather_rows; a.gather_magic = magic_of(gather_k);
@@ -1487,7 +1488,7 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
 
   GemmArgs a{};
   a.G = G; a.n_src = n_src; a.Cc = (int)C; a.R = (int)(n_src * C);
-  a.cnt = tile == MOE_TILE_SMALL ? nullptr : row_counts;
+  a.cnt = ignores_counts(dtype, tile) ? nullptr : row_counts;
   // dA = dY * W2[h0:h0+Hl, :]^T ; dZ = dA * GeLU'(Z)
   a.A = dY; a.lda = M;
   a.B = W2; a.ldb = M; a.b_goff = (int64_t)H * M; a.b_off = h0 * M;

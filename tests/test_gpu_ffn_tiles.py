@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from oracle import moe_oracle as O
-from paper_2407_00599_amd import synth
+from paper_2407_00599_amd import api, synth
 from test_gpu_ffn import gpu_ffn
 from util import DEV, TOL, ROWS, EXPERT, to_dev, to_host, assert_close, torch_dtype
 
@@ -61,3 +61,17 @@ def test_auto_tiles_and_compacted_rows(n_src, G, C, M, H, dtype):
     for _ in range(4):         # the pipeline's requests race with nothing: every run gives the same bits
         for a, b in zip(got, gpu_ffn(*args, n_src, G, C, M, H, 0, 1, torch_dtype(dtype), cnt)):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("tile", [api.MOE_TILE_SMALL, api.MOE_TILE_256, api.MOE_TILE_192])
+def test_fp32_ignores_the_tile_hint(tile):
+    """The row counts hold whatever the hint: rows behind them, here full of values, are taken as padding."""
+    n_src, G, C, M, H = 2, 3, 45, 72, 136
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    new = lambda *s: torch.randn(*s, generator=gen, device=DEV)      # noqa: E731
+    X, dY, W1, W2 = new(n_src, G, C, M), new(n_src, G, C, M), new(G, M, H), new(G, H, M)
+    cnt = torch.tensor([[0, 45, 7], [40, 1, 33]], dtype=torch.int32, device=DEV)
+    run = lambda t: gpu_ffn(X, dY, W1, W2, n_src, G, C, M, H, 0, 1, torch.float32, cnt, t)      # noqa: E731
+    for a, b in zip(run(api.MOE_TILE_AUTO), run(tile)):
+        assert torch.equal(a, b)
