@@ -218,7 +218,7 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
   for (int e = 0; e < EC; ++e)
 #pragma unroll
     for (int q = 0; q < CPT; ++q) acc[e][q] = 0.f;
-  float colsum = 0.f;   // thread e < E of column block 0 sums dl[:, e] for the bias row
+  float colsum[4] = {0.f, 0.f, 0.f, 0.f};   // thread e < E of column block 0 sums dl[:, e] for the bias row, four sums of a quarter
 
   for (int64_t c0 = tb; c0 < te; c0 += FUSED_CHUNK) {
     const int nc = (int)(te - c0 < FUSED_CHUNK ? te - c0 : FUSED_CHUNK);
@@ -269,8 +269,10 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
         dl_out[c0 * E + i] = dls[t * EC + e];
       }
       if (tid < EC) {
-#pragma unroll 8
-        for (int t = 0; t < nc; ++t) colsum += dls[t * EC + tid];
+#pragma unroll 2
+        for (int t = 0; t < nc; t += 4)   // (rows behind the end are zeros)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) colsum[u] += dls[(t + u) * EC + tid];
       }
     }
     for (int u0 = wave * FT; u0 < nc; u0 += FW * FT) {
@@ -328,7 +330,7 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
     const int m = i / EC, e = i - m * EC;
     if (mb + m < M && e < E) out[(int64_t)(mb + m) * E + e] = outs[0][e * PITCH + m];
   }
-  if (blockIdx.x == 0 && tid < E && tid < EC) out[(int64_t)M * E + tid] = colsum;
+  if (blockIdx.x == 0 && tid < E && tid < EC) out[(int64_t)M * E + tid] = (colsum[0] + colsum[1]) + (colsum[2] + colsum[3]);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -52,3 +52,27 @@ def test_gate_bwd(S, M, E, k, norm, dtype, acc):
     assert_close(to_host(dx), ref_dx, 1e-5 if dtype == "f32" else 4e-3, "dx", ROWS)
     if k == 1 and norm:
         assert np.all(to_host(dl) == 0)
+
+
+@pytest.mark.parametrize("S", [16, 100, 4096, 5000, 70001])
+def test_bias_gradient_rounding(S):
+    """The bias gradient of up to 16 experts: fp32 sums over quarters of a token chunk, added up in fp64.  At most
+    chunk / 4 + 2 fp32 additions reach a term, each off by at most 2^-24 of a sum no larger than the chunk's sum of
+    magnitudes, and the result is rounded once: |error| <= (chunk / 4 + 3) 2^-24 sum |dlogits|.  One large term per 16
+    tokens among terms that vanish next to it, so that one long chain over 16 tokens would miss the bound."""
+    M, E, k = 8, 8, 2
+    g = np.where(np.arange(S) % 16 == 0, 4.0, 4.0 * 2.0 ** -25)
+    dw = np.stack([g, np.zeros(S)], 1).astype(np.float32)                  # dl[t, 0] = 0.25 (dw0 - dw1) = -dl[t, 1]
+    idx = np.tile(np.array([0, 1], np.int32), (S, 1))
+    w = np.full((S, k), 0.5, np.float32)
+    dl = torch.empty(S, E, device=DEV); dWg = torch.empty(M, E, device=DEV); db = torch.empty(E, device=DEV)
+    dx = torch.empty(S, M, device=DEV)
+    ws = torch.full((api.moe_gate_bwd_workspace_bytes(S, M, E),), 255, dtype=torch.uint8, device=DEV)
+    api.moe_gate_bwd(to_dev(dw), to_dev(w), to_dev(idx), torch.zeros(S, E, device=DEV), torch.zeros(S, M, device=DEV),
+                     torch.zeros(M, E, device=DEV), S, M, E, k, 1, dl, dWg, db, dx, 0, ws)
+    torch.cuda.synchronize()
+    l64 = to_host(dl)
+    assert np.array_equal(l64[:, 0], g / 4) and np.array_equal(l64[:, 1], -g / 4)
+    chunk = -(-(-(-S // 256)) // 16) * 16
+    bound = (chunk / 4 + 3) * 2.0 ** -24 * np.abs(l64).sum(axis=0)
+    assert (np.abs(to_host(db) - l64.sum(axis=0)) <= bound).all()
