@@ -111,17 +111,13 @@ def measure(name, steps, warmup, settle, fused_ok=True, extras=False, tile=0):
     ms_per_step = (t1 - t0) * 1e3 / K
     per_call = {n: sum(ev[s][i].elapsed_time(ev[s][i + 1]) for s in probed) / len(probed) for i, n in enumerate(names)}
 
-    # FLOPs = what the six launches multiply out: row tiles that are all capacity padding are skipped by the
-    # kernels and not counted (moe_ffn_executed_flops mirrors the kernels' skipping rule on a host copy of the counts)
+    # FLOPs = what the six launches multiply out: an expert's occupied rows, rounded up to whole row tiles in the row-tiled
+    # GEMMs (moe_ffn_executed_flops plans the launches as the calls do, from a host copy of the counts)
     rows = L.n_src * L.G * L.C
     cnt_host = None if L.row_counts is None else L.row_counts.cpu().numpy()
     dtc = api.MOE_BF16 if cfg.dtype == "bf16" else api.MOE_F32
     fl_fwd, fl_bwd = (api.moe_ffn_executed_flops(dtc, L.n_src, L.G, L.C, cfg.M, cfg.H, L.n_esp, cnt_host, b, tile) for b in (0, 1))
     occupied = rows if cnt_host is None else int(np.minimum(cnt_host, L.C).sum())
-    if cnt_host is not None and (L.n_src > 1 or cfg.dtype == "f32"):
-        # that arithmetic takes row tiles chunk by chunk (and f32 as if nothing were skipped); the kernels pack the occupied
-        # rows of an expert's chunks and multiply fewer: price the occupied rows alone, which they cannot do without
-        fl_fwd, fl_bwd = (n_gemm * 2.0 * occupied * cfg.M * L.Hl for n_gemm in (2, 4))
     flops_per_launch = (fl_fwd + fl_bwd) / 6.0
     fwd_name, bwd_name = ("ffn_fwd_gather", "ffn_bwd_gather") if fused_step else ("ffn_fwd", "ffn_bwd")
     gemm_ms = (per_call[fwd_name] + per_call[bwd_name]) / 6.0

@@ -184,11 +184,11 @@ enum { MOE_TILE_AUTO = 0, MOE_TILE_SMALL = 1, MOE_TILE_256 = 2, MOE_TILE_192 = 3
 
 /* Floating-point operations the forward (backward = 0: 2 GEMMs) or backward (backward = 1: 4 GEMMs)
  * call multiplies out for this shape and tile hint: 2 * M * H_l per multiplied row
- * and GEMM, where a row counts if it lies in a row tile that is not skipped (row-tiled GEMMs, tiles taken
- * chunk by chunk) or below the count (weight-gradient reductions, n_src = 1; with several chunks every
- * row counts).  With several chunks the calls multiply fewer rows than this: an upper bound there.  row_counts_host is a HOST copy of the
- * row_counts passed to the calls, or NULL (every row is multiplied).  Pure host arithmetic, used by
- * the benchmark to price the matrix pipes by executed work.  0 for invalid shapes. */
+ * and GEMM.  With row counts an expert's occupied rows are packed over its chunks; the row-tiled GEMMs
+ * multiply them rounded up to whole row tiles (at most all n_src*C rows), the weight-gradient
+ * reductions exactly them.  row_counts_host is a HOST copy of the row_counts passed to the calls, or
+ * NULL (every row is multiplied).  Pure host arithmetic, used by the benchmark to price the matrix
+ * pipes by executed work.  0 for invalid shapes. */
 double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C, int M, int H, int n_esp,
                               const int32_t* row_counts_host, int tile, int backward);
 

@@ -1288,6 +1288,12 @@ TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile, bool wide = false) {
   return t;
 }
 
+// The three backward GEMMs that only depend on dZ go out in one launch if both weight gradients take 256 x 256 tiles.
+bool merged_backward(GemmArgs& w2, GemmArgs& w1, int tile) {   // prepares the two
+  const TilePlan t2 = prepare_bf16(w2, true, tile), t1 = prepare_bf16(w1, true, tile);
+  return t2.tile_m == 256 && t1.tile_m == 256;
+}
+
 // Workgroups of a problem, a multiple of 8: every XCD takes an equal share of the tiles to multiply and, with row
 // counts, an equal share of the tiles of zeros, each share rounded up.
 int grid_of(const GemmArgs& a) { return (a.total_tiles + (a.cnt ? 14 : 7)) / 8 * 8; }
@@ -1303,6 +1309,12 @@ int plan_f32(int64_t tiles_64x64, int64_t tiles_32x64) {   // 2: 64 x 64, 1: 32 
   const int64_t enough = 4 * (int64_t)num_cus();
   return tiles_64x64 >= enough ? 2 : tiles_32x64 >= enough ? 1 : 0;
 }
+int f32_tile_m(int size) { return size == 2 ? 64 : 32; }
+int plan_f32(const GemmArgs& a, bool tn) { return plan_f32(tiles_f32(a, tn, 64, 64), tiles_f32(a, tn, 32, 64)); }
+int plan_f32_trio(const GemmArgs& dx, const GemmArgs& w2, const GemmArgs& w1) {   // of the merged backward launch
+  return plan_f32(tiles_f32(dx, false, 64, 64) + tiles_f32(w2, true, 64, 64) + tiles_f32(w1, true, 64, 64),
+                  tiles_f32(dx, false, 32, 64) + tiles_f32(w2, true, 32, 64) + tiles_f32(w1, true, 32, 64));
+}
 void prepare_f32(GemmArgs& a, int tile_m, int tile_n) {
   a.tiles_m = (a.Mdim + tile_m - 1) / tile_m;
   a.tiles_n = (a.Ndim + tile_n - 1) / tile_n;
@@ -1312,7 +1324,7 @@ void prepare_f32(GemmArgs& a, int tile_m, int tile_n) {
 template <int KIND, int EPI>
 void launch_gemm(GemmArgs a, int dtype, int tile, hipStream_t st) {
   if (dtype == MOE_F32) {
-    const int size = plan_f32(tiles_f32(a, KIND == KIND_TN, 64, 64), tiles_f32(a, KIND == KIND_TN, 32, 64));
+    const int size = plan_f32(a, KIND == KIND_TN);
     auto launch = [&](auto tm_tag, auto tn_tag) {
       constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
       prepare_f32(a, TM, TN);
@@ -1364,30 +1376,21 @@ int check_ffn_shape(int dtype, int n_src, int G, int64_t C, int M, int H, int es
 
 }  // namespace
 
-// multiplied rows of a row-tiled GEMM (outputs [R rows per expert] x N), or of the reduction of a
-// weight-gradient GEMM, given host-side row counts
-static double rows_multiplied(int tile, bool tn, int dtype, int n_src, int G, int64_t C, int Mdim, int Ndim, int Kdim,
-                              const int32_t* cnt) {
-  const int64_t R = (int64_t)n_src * C;
-  const TilePlan t = plan_tiles(tile, tn, G, !tn && cnt ? (int)(((int64_t)Mdim * 9 + 9) / 10) : Mdim, Ndim, Kdim);
-  if (cnt == nullptr || dtype != MOE_BF16 || tile == MOE_TILE_SMALL) return (double)G * (double)R;
+// Rows of all experts that a GEMM multiplies: the occupied ones, in the row-tiled GEMMs (tile_m > 0) rounded up to whole
+// row tiles of each expert's compacted rows.
+static double rows_multiplied(const GemmArgs& a, int tile_m) {
   double rows = 0;
-  for (int g = 0; g < G; ++g) {
-    if (tn) {
-      if (n_src != 1) { rows += (double)R; continue; }
-      const int64_t c = cnt[g] < 0 ? 0 : cnt[g];
-      rows += (double)(c < C ? c : C);
-    } else {
-      for (int64_t m0 = 0; m0 < R; m0 += t.tile_m) {
-        const int64_t r_end = m0 + t.tile_m < R ? m0 + t.tile_m : R;
-        bool pad = true;
-        for (int64_t sc = m0 / C; sc * C < r_end; ++sc) {
-          const int64_t c_lo = m0 - sc * C > 0 ? m0 - sc * C : 0;
-          if (c_lo < cnt[sc * G + g]) { pad = false; break; }
-        }
-        if (!pad) rows += (double)(r_end - m0);
+  for (int g = 0; g < a.G; ++g) {
+    int64_t n = a.R;
+    if (a.cnt != nullptr) {
+      n = 0;
+      for (int s = 0; s < a.n_src; ++s) {
+        const int32_t c = a.cnt[(int64_t)s * a.G + g];
+        n += c < 0 ? 0 : c < a.Cc ? c : a.Cc;
       }
     }
+    if (tile_m > 0) n = (n + tile_m - 1) / tile_m * tile_m;
+    rows += (double)(n < a.R ? n : a.R);
   }
   return rows;
 }
@@ -1396,14 +1399,26 @@ extern "C" double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C,
                                          const int32_t* row_counts_host, int tile, int backward) {
   if (check_ffn_shape(dtype, n_src, G, C, M, H, 0, n_esp) != MOE_OK || !valid_tile(tile)) return 0.0;
   const int Hl = H / n_esp;
-  const int R = (int)(n_src * C);
-  const int32_t* c = row_counts_host;
-  const double mh = 2.0 * (double)M * (double)Hl;
-  auto rows = [&](bool tn, int Mdim, int Ndim, int Kdim) { return rows_multiplied(tile, tn, dtype, n_src, G, C, Mdim, Ndim, Kdim, c); };
-  if (!backward)   // Z = X W1 (rows x Hl), Y = A W2 (rows x M)
-    return mh * (rows(false, R, Hl, M) + rows(false, R, M, Hl));
-  // dA = dY W2^T (rows x Hl), dW2 (Hl x M over the rows), dW1 (M x Hl over the rows), dX = dZ W1^T (rows x M)
-  return mh * (rows(false, R, Hl, M) + rows(true, Hl, M, R) + rows(true, M, Hl, R) + rows(false, R, M, Hl));
+  GemmArgs a{};   // the problems as the calls below plan them
+  a.G = G; a.n_src = n_src; a.Cc = (int)C; a.R = (int)(n_src * C);
+  a.cnt = ignores_counts(dtype, tile) ? nullptr : row_counts_host;
+  auto gemm = [&](int Mdim, int Ndim, int Kdim) {
+    GemmArgs p = a;
+    p.Mdim = Mdim; p.Ndim = Ndim; p.Kdim = Kdim;
+    return p;
+  };
+  auto alone = [&](GemmArgs p) { return dtype == MOE_F32 ? f32_tile_m(plan_f32(p, false)) : prepare_bf16(p, false, tile).tile_m; };
+  const GemmArgs to_h = gemm(a.R, Hl, M), to_m = gemm(a.R, M, Hl);
+  double rows;
+  if (!backward) {   // Z = X W1 (rows x Hl), Y = A W2 (rows x M)
+    rows = rows_multiplied(a, alone(to_h)) + rows_multiplied(a, alone(to_m));
+  } else {           // dA = dY W2^T (rows x Hl), dX = dZ W1^T (rows x M), dW2 (Hl x M) and dW1 (M x Hl) over the rows
+    GemmArgs w2 = gemm(Hl, M, a.R), w1 = gemm(M, Hl, a.R), dx = to_m;
+    const int dx_m = dtype == MOE_F32 ? f32_tile_m(plan_f32_trio(dx, w2, w1))
+                                      : prepare_bf16(dx, false, tile, merged_backward(w2, w1, tile)).tile_m;
+    rows = rows_multiplied(a, alone(to_h)) + rows_multiplied(a, dx_m) + 2.0 * rows_multiplied(a, 0);
+  }
+  return 2.0 * (double)M * (double)Hl * rows;
 }
 
 extern "C" size_t moe_ffn_workspace_bytes(int dtype, int n_src, int G, int64_t C, int M, int H, int n_esp) {
@@ -1517,10 +1532,10 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
   dx.C = dX; dx.ldc = M; dx.c_goff = 0; dx.c_off = 0;
   dx.Mdim = a.R; dx.Ndim = M; dx.Kdim = Hl;
   if (dtype == MOE_BF16) {
-    // the three are independent: one launch, long row tiles first, if all of them take the LDS-DMA kernel
+    // the three are independent: one launch, long row tiles first
     GemmArgs px = dx, p2 = w2, p1 = w1;
-    const TilePlan tx = prepare_bf16(px, false, tile, true), t2 = prepare_bf16(p2, true, tile), t1 = prepare_bf16(p1, true, tile);
-    if (t2.tile_m == 256 && t1.tile_m == 256) {
+    if (merged_backward(p2, p1, tile)) {
+      const TilePlan tx = prepare_bf16(px, false, tile, true);
       const int nbx = grid_of(px), nb2 = grid_of(p2), nb1 = grid_of(p1);
       const dim3 grid((unsigned)(nbx + nb2 + nb1));
       auto launch = [&](auto cfg) {
@@ -1536,8 +1551,7 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
     }
   }
   if (dtype == MOE_F32) {   // one launch here too
-    const int size = plan_f32(tiles_f32(dx, false, 64, 64) + tiles_f32(w2, true, 64, 64) + tiles_f32(w1, true, 64, 64),
-                              tiles_f32(dx, false, 32, 64) + tiles_f32(w2, true, 32, 64) + tiles_f32(w1, true, 32, 64));
+    const int size = plan_f32_trio(dx, w2, w1);
     auto launch = [&](auto tm_tag, auto tn_tag) {
       constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
       prepare_f32(dx, TM, TN); prepare_f32(w2, TM, TN); prepare_f32(w1, TM, TN);

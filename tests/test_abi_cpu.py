@@ -157,7 +157,7 @@ def test_executed_flops_accounting(L):
     full = 2.0 * G * C * M * H
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1) == 2 * full                 # two GEMMs over every row
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, None, True) == 4 * full
-    assert f(api.MOE_F32, n_src, G, C, M, H, 1, np.zeros((1, G), np.int32)) == 2 * full   # fp32 kernels never skip
+    assert f(api.MOE_F32, n_src, G, C, M, H, 1, np.zeros((1, G), np.int32)) == 0.0
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, np.full((1, G), C, np.int32)) == 2 * full
     assert f(api.MOE_BF16, n_src, G, C, M, 4100, 3) == 0.0                 # invalid shape
     # empty experts: nothing is multiplied, forward or backward
@@ -172,9 +172,18 @@ def test_executed_flops_accounting(L):
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, np.full((1, G), C + 7, np.int32), True, tile=t256) == 4 * full
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, np.full((1, G), 512, np.int32), tile=t256) == 2 * (2.0 * G * 512 * M * H)
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, np.full((1, G), 513, np.int32), tile=t256) == 2 * (2.0 * G * 768 * M * H)
-    # several source chunks: the reductions run over all rows, the row tiles follow each chunk's count
+    # several source chunks: the occupied rows of an expert are packed
     got = f(api.MOE_BF16, 2, G, 1024, M, H, 1, np.array([[0] * G, [1] * G], np.int32), True, tile=t256)
-    assert got == 2 * (2.0 * G * 256 * M * H) + 2 * (2.0 * G * 2048 * M * H)
+    assert got == 2 * (2.0 * G * 256 * M * H) + 2 * (2.0 * G * 1 * M * H)
+    got = f(api.MOE_BF16, 3, G, 1024, M, H, 1, np.array([[100] * G, [2000] * G, [-5] * G], np.int32), True, tile=t256)
+    assert got == 2 * (2.0 * G * 1280 * M * H) + 2 * (2.0 * G * 1124 * M * H)
+    # fp32: 64-row tiles where there are enough of them, else 32-row tiles; the hint changes nothing
+    for t in range(4):
+        assert f(api.MOE_F32, n_src, G, C, M, H, 1, one, True, tile=t) == 2 * (2.0 * G * 64 * M * H) + 2 * (2.0 * G * 1 * M * H)
+        assert f(api.MOE_F32, n_src, G, C, 64, 64, 1, one, tile=t) == 2 * (2.0 * G * 32 * 64 * 64)
+    # dX in the merged backward launch, which has no tiles of 64 columns, takes 64 rows; alone, as A W2 does, it would take 32
+    assert f(api.MOE_BF16, n_src, G, 64, M, H, 1, one) == 2.0 * G * (64 + 32) * M * H
+    assert f(api.MOE_BF16, n_src, G, 64, M, H, 1, one, True) == 2.0 * G * (64 + 64 + 2) * M * H
     # 192-row tiles in the row-tiled GEMMs only; the small kernel never skips; an unknown hint is an invalid call
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, one, tile=api.MOE_TILE_192) == 2 * (2.0 * G * 192 * M * H)
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, one, tile=api.MOE_TILE_SMALL) == 2 * full
