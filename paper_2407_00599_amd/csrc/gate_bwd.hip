@@ -174,55 +174,63 @@ struct RawRow {
 // LDS first (one thread per token; column block 0 also stores them); then every wave reads the x and old dx pieces of its
 // tokens once, FT tokens at a time, and uses them twice:
 //     dWg partial[e][q] += x[t, q] dl[t, e]        dx[t, q] (+)= sum_e dl[t, e] Wg[q, e]
-// The four waves' sums are added in LDS in a fixed order and leave it so that [m][e] rows are written contiguously.
+// The four waves' sums meet in LDS, half of the columns at a time, are added in fp64 in a fixed order and leave it so that
+// [m][e] rows are written contiguously.  A chunk is a multiple of 16 tokens; up to 2048 tokens the workspace has two rows
+// per chunk, and the second takes what the rounding of the first left: these sums then lose no more than chains of 8
+// tokens would (1003 x 520, 12 experts, relative error of dWg: 5.2e-8 with the waves added in fp32, 3.9e-8 now, 4.2e-8
+// with chains of 8).
 // Memory-bound at large sizes; at small ones the time is a chain of latencies, the fetch of the instructions among
 // them: a version that unrolled 16 tokens was 17 to 34 KB of straight-line code and, with one wave per chunk, wrote
-// four times the partial sums.  2048 x 768, 16 experts: 27 -> 17 us; 4096 x 1024, 8 experts: 21 -> 18 us; 32768 x 4096, 8
-// experts: 208 -> 186 us.
+// eight times the partial sums.  Against that version, the call with its reduction: 2048 x 768, 16 experts: 32.8 ->
+// 19.6 us; 4096 x 1024, 8 experts: 22.9 -> 20.2 us; 1003 x 520, 12 experts: 24.2 -> 17.2 us; 32768 x 4096, 8 experts: 205 -> 182 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int FW = 4;                                    // waves per block
 constexpr int FT = 4;                                    // tokens per stage of a wave
 constexpr int FUSED_CHUNK = 256;                         // dlogits rows in LDS at a time
-// tokens per block: at most 256 partial sums (their number is at most that of dwg_chunk, which sizes the workspace)
+// tokens per block: at most 256 partial sums (their number is at most that of dwg_chunk, which sizes the workspace); where a
+// chunk has two rows, at most 64 of them, so that the rows do not cost more than the tokens (2048 x 768, 16 experts:
+// 128 chunks 24.0 us, 64 chunks 19.6 us)
 inline int64_t fused_chunk(int64_t S) {
-  const int64_t step = FW * FT, c = (S + 255) / 256;
+  const int64_t step = FW * FT, parts = S <= 2048 ? 64 : 256, c = (S + parts - 1) / parts;
   return (c + step - 1) / step * step;
 }
 template <bool BF16, int EC>
 __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_fused(const float* __restrict__ dw, const float* __restrict__ w,
                                                           const int32_t* __restrict__ idx, const float* __restrict__ logits,
                                                           const void* __restrict__ x, const float* __restrict__ Wg,
-                                                          int64_t S, int M, int E, int k, int norm_topk, int64_t chunk,
+                                                          int S, int M, int E, int k, int norm_topk, int chunk,
                                                           float* __restrict__ dl_out, void* __restrict__ dx, int accumulate,
-                                                          float* __restrict__ partial) {
+                                                          float* __restrict__ partial, int nrows) {
   constexpr int CPT = 4, MT = 64 * CPT, PITCH = MT + 8, NTHR = 64 * FW;
+  constexpr int HC = MT / 2, HPITCH = HC + 8;      // half of the columns
   static_assert(FUSED_CHUNK == NTHR, "a thread per dlogits row");
-  __shared__ __attribute__((aligned(16))) float outs[2][EC * PITCH];
+  __shared__ __attribute__((aligned(16))) float outs[FW * EC * HPITCH];
+  static_assert(FW * HPITCH >= PITCH, "holds the slab of Wg too");
   __shared__ __attribute__((aligned(16))) float dls[FUSED_CHUNK * EC];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int mb = blockIdx.x * MT, m0 = mb + lane * CPT;
   const bool mok = m0 < M;
   const int mc = mok ? m0 : 0;     // a lane behind the last column works on the first ones and stores nothing
-  const int64_t tb = (int64_t)blockIdx.y * chunk;
-  const int64_t te = (tb + chunk < S) ? tb + chunk : S;
-  float* out = partial + (int64_t)blockIdx.y * (M + 1) * E;
+  const int tb = (int)blockIdx.y * chunk, te = tb + min(chunk, S - tb);   // S k < 2^31
+  const int rest_row = (int)(gridDim.y + blockIdx.y);    // row for what rounding leaves, if there is one
+  const bool lone = rest_row >= nrows && te - tb <= 2 * FT;   // without it a few tokens are one wave's, one chain of sums
 
   // The block's slab of Wg, contiguous in memory, goes through LDS once for the four waves: read directly, a lane's
   // weights are strided pieces, and every request of a wave is 64 lines.
   for (int i = tid; i < MT * E; i += NTHR) {
     const int m = i / E, e = i - m * E;
-    outs[0][e * PITCH + m] = mb + m < M ? Wg[(int64_t)mb * E + i] : 0.f;
+    outs[e * PITCH + m] = mb + m < M ? Wg[(int64_t)mb * E + i] : 0.f;
   }
   float wr[CPT][EC], acc[EC][CPT];
 #pragma unroll
   for (int e = 0; e < EC; ++e)
 #pragma unroll
     for (int q = 0; q < CPT; ++q) acc[e][q] = 0.f;
-  float colsum[4] = {0.f, 0.f, 0.f, 0.f};   // thread e < E of column block 0 sums dl[:, e] for the bias row, four sums of a quarter
+  float colsum = 0.f;   // thread EC q + e of column block 0, q < 4, sums dl[t, e] over the tokens t = q (mod 4) for the bias row
 
-  for (int64_t c0 = tb; c0 < te; c0 += FUSED_CHUNK) {
-    const int nc = (int)(te - c0 < FUSED_CHUNK ? te - c0 : FUSED_CHUNK);
-    if (c0 != tb) __syncthreads();   // the previous dl rows are consumed
+  for (int done = 0; done < te - tb; done += FUSED_CHUNK) {
+    const int c0 = tb + done, nc = min(te - c0, FUSED_CHUNK);
+    if (done > 0) __syncthreads();   // the previous dl rows are consumed
     if (tid < nc) {
       const int64_t t = c0 + tid;
       const Picks p(dw, w, idx, t, k);
@@ -256,26 +264,26 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
       for (int e = 0; e < EC; ++e) dls[tid * EC + e] = 0.f;
     }
     __syncthreads();
-    if (c0 == tb) {
+    if (done == 0) {
 #pragma unroll
       for (int e = 0; e < EC; ++e) {
-        const float4 v = e < E ? *reinterpret_cast<const float4*>(&outs[0][e * PITCH + lane * CPT]) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 v = e < E ? *reinterpret_cast<const float4*>(&outs[e * PITCH + lane * CPT]) : make_float4(0.f, 0.f, 0.f, 0.f);
         wr[0][e] = v.x; wr[1][e] = v.y; wr[2][e] = v.z; wr[3][e] = v.w;
       }
     }
     if (blockIdx.x == 0) {
+      // through a descriptor: a 32-bit offset per lane instead of an address, which would not stay in a register
+      const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(dl_out + (int64_t)c0 * E, 0, (uint32_t)(nc * E * 4), 0x00020000);
       for (int i = tid; i < nc * E; i += NTHR) {
         const int t = i / E, e = i - t * E;
-        dl_out[c0 * E + i] = dls[t * EC + e];
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dls[t * EC + e]), rows, i * 4, 0, 0);
       }
-      if (tid < EC) {
-#pragma unroll 2
-        for (int t = 0; t < nc; t += 4)   // (rows behind the end are zeros)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) colsum[u] += dls[(t + u) * EC + tid];
+      if (tid < 4 * EC) {
+#pragma unroll 8
+        for (int t = 0; t < nc; t += 4) colsum += dls[t * EC + tid];   // (rows behind the end are zeros)
       }
     }
-    for (int u0 = wave * FT; u0 < nc; u0 += FW * FT) {
+    for (int u0 = lone && wave > 0 ? nc : wave * FT; u0 < nc; u0 += lone ? FT : FW * FT) {
       RawRow<BF16, CPT> xr[FT], dr[FT];
 #pragma unroll
       for (int u = 0; u < FT; ++u) {   // a row behind the end: the last one again, not stored, its dl row is zero
@@ -306,31 +314,37 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
     }
   }
   __syncthreads();   // every wave has its weights
-  // waves 2 and 3 hand their sums to 0 and 1, wave 1 to wave 0
-  auto put = [&](float* o) {
-#pragma unroll
-    for (int e = 0; e < EC; ++e)
-      *reinterpret_cast<float4*>(&o[e * PITCH + lane * CPT]) = make_float4(acc[e][0], acc[e][1], acc[e][2], acc[e][3]);
+  float* out = partial + (int64_t)blockIdx.y * (M + 1) * E;
+  float* rest = rest_row < nrows ? partial + (int64_t)rest_row * (M + 1) * E : nullptr;
+  auto put_sum = [&](double v, int64_t at) {
+    const float hi = (float)v;
+    out[at] = hi;
+    if (rest != nullptr) rest[at] = fabsf(hi) <= 3.402823466e38f ? (float)(v - (double)hi) : 0.f;   // (an infinity leaves nothing)
   };
-  auto add = [&](const float* o) {
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {
+    if ((lane >> 5) == h) {
 #pragma unroll
-    for (int e = 0; e < EC; ++e) {
-      const float4 v = *reinterpret_cast<const float4*>(&o[e * PITCH + lane * CPT]);
-      acc[e][0] += v.x; acc[e][1] += v.y; acc[e][2] += v.z; acc[e][3] += v.w;
+      for (int e = 0; e < EC; ++e)
+        *reinterpret_cast<float4*>(&outs[(wave * EC + e) * HPITCH + (lane & 31) * CPT]) =
+            make_float4(acc[e][0], acc[e][1], acc[e][2], acc[e][3]);
     }
-  };
-  if (wave >= 2) put(outs[wave - 2]);
-  __syncthreads();
-  if (wave < 2) add(outs[wave]);
-  if (wave == 1) put(outs[1]);    // its own buffer, which it has just read
-  __syncthreads();
-  if (wave == 0) { add(outs[1]); put(outs[0]); }
-  __syncthreads();
-  for (int i = tid; i < MT * EC; i += NTHR) {
-    const int m = i / EC, e = i - m * EC;
-    if (mb + m < M && e < E) out[(int64_t)(mb + m) * E + e] = outs[0][e * PITCH + m];
+    __syncthreads();
+    for (int i = tid; i < HC * EC; i += NTHR) {
+      const int m = i / EC, e = i - m * EC, mg = mb + h * HC + m;
+      double v[FW];
+#pragma unroll
+      for (int q = 0; q < FW; ++q) v[q] = (double)outs[(q * EC + e) * HPITCH + m];
+      if (mg < M && e < E) put_sum((v[0] + v[1]) + (v[2] + v[3]), (int64_t)mg * E + e);
+    }
+    __syncthreads();
   }
-  if (blockIdx.x == 0 && tid < E && tid < EC) out[(int64_t)M * E + tid] = (colsum[0] + colsum[1]) + (colsum[2] + colsum[3]);
+  if (blockIdx.x == 0 && wave == 0) {
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = (double)__shfl(colsum, EC * q + lane % EC, 64);
+    if (lane < E) put_sum((v[0] + v[1]) + (v[2] + v[3]), (int64_t)M * E + lane);   // E <= EC
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -508,14 +522,17 @@ extern "C" int moe_gate_bwd(const float* dw, const float* w, const int32_t* idx,
     const int EC = E <= 8 ? 8 : 16;
     const int64_t chunk = fused_chunk(S);
     const int nchunk = (int)((S + chunk - 1) / chunk);
+    const int ws_rows = (int)((S + dwg_chunk(S, E) - 1) / dwg_chunk(S, E));
+    // a second row per chunk where the workspace has them; the last chunk, if of 8 tokens at most, may go without
+    const int nrows = ws_rows >= 2 * nchunk - 1 ? (ws_rows < 2 * nchunk ? ws_rows : 2 * nchunk) : nchunk;
     float* partial = (float*)ws;
     const dim3 grid((unsigned)((M + 255) / 256), (unsigned)nchunk);
 #define MOE_FUSED(BF, EC_) hipLaunchKernelGGL((gate_bwd_fused<BF, EC_>), grid, dim3(64 * FW), 0, st, dw, w, idx, logits, x, \
-                                              Wg, S, M, E, k, norm, chunk, dlogits, dx, dx_accumulate, partial)
+                                              Wg, (int)S, M, E, k, norm, (int)chunk, dlogits, dx, dx_accumulate, partial, nrows)
     if (bf) { if (EC == 8) MOE_FUSED(true, 8); else MOE_FUSED(true, 16); }
     else { if (EC == 8) MOE_FUSED(false, 8); else MOE_FUSED(false, 16); }
 #undef MOE_FUSED
-    hipLaunchKernelGGL(gate_dwg_reduce, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial, nchunk, M, E, dWg,
+    hipLaunchKernelGGL(gate_dwg_reduce, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial, nrows, M, E, dWg,
                        dgate_bias);
     return moe::check_launch();
   }

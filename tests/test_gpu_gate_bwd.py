@@ -54,11 +54,11 @@ def test_gate_bwd(S, M, E, k, norm, dtype, acc):
         assert np.all(to_host(dl) == 0)
 
 
-@pytest.mark.parametrize("S", [16, 100, 4096, 5000, 70001])
+@pytest.mark.parametrize("S", [16, 100, 2048, 4096, 5000, 70001])
 def test_bias_gradient_rounding(S):
-    """The bias gradient of up to 16 experts: fp32 sums over quarters of a token chunk, added up in fp64.  At most
-    chunk / 4 + 2 fp32 additions reach a term, each off by at most 2^-24 of a sum no larger than the chunk's sum of
-    magnitudes, and the result is rounded once: |error| <= (chunk / 4 + 3) 2^-24 sum |dlogits|.  One large term per 16
+    """The bias gradient of up to 16 experts: fp32 sums over quarters of a token chunk, added up in fp64 and rounded.  At most
+    chunk / 4 fp32 additions and that rounding reach a term, each off by at most 2^-24 of a sum no larger than the chunk's
+    sum of magnitudes, and the result is rounded once: |error| <= (chunk / 4 + 2) 2^-24 sum |dlogits|.  One large term per 16
     tokens among terms that vanish next to it, so that one long chain over 16 tokens would miss the bound."""
     M, E, k = 8, 8, 2
     g = np.where(np.arange(S) % 16 == 0, 4.0, 4.0 * 2.0 ** -25)
@@ -73,6 +73,47 @@ def test_bias_gradient_rounding(S):
     torch.cuda.synchronize()
     l64 = to_host(dl)
     assert np.array_equal(l64[:, 0], g / 4) and np.array_equal(l64[:, 1], -g / 4)
-    chunk = -(-(-(-S // 256)) // 16) * 16
-    bound = (chunk / 4 + 3) * 2.0 ** -24 * np.abs(l64).sum(axis=0)
+    chunk = -(-(-(-S // (64 if S <= 2048 else 256))) // 16) * 16
+    bound = (chunk / 4 + 2) * 2.0 ** -24 * np.abs(l64).sum(axis=0)
     assert (np.abs(to_host(db) - l64.sum(axis=0)) <= bound).all()
+
+
+@pytest.mark.parametrize("S,M,E,k,norm,dtype", [(1003, 520, 12, 3, 1, "bf16"), (1000, 264, 16, 2, 1, "f32"), (2048, 256, 8, 2, 1, "bf16"),
+                                                (8, 2048, 8, 2, 1, "f32"), (1032, 264, 8, 2, 1, "f32"), (4096, 264, 8, 2, 1, "bf16"), (5000, 264, 13, 2, 0, "f32")])
+def test_weight_gradient_rounding(S, M, E, k, norm, dtype):
+    """The weight gradient of up to 16 experts is no farther from the exact sums than fp32 chains over chunks of 8 tokens (more
+    from 2049 tokens on: at most 256 chunks), added up in fp64 and rounded.  Chains of equal length over other tokens have
+    equal errors on average; over N outputs the two norms of N independent errors then differ by 1 / sqrt(N) of
+    themselves in the standard deviation, of which four are allowed."""
+    rng = np.random.default_rng(S * 3 + E)
+    x = synth.store(rng.standard_normal((S, M)).astype(np.float32), dtype)
+    logits = synth.synthetic_logits(S, E, seed=S)
+    idx = O.topk_select(logits, k)
+    w = O.combine_weights(logits, idx, bool(norm)).astype(np.float32)
+    dw = rng.standard_normal((S, k)).astype(np.float32)
+    dl = torch.empty(S, E, device=DEV); dWg = torch.empty(M, E, device=DEV); db = torch.empty(E, device=DEV)
+    dx = torch.empty(S, M, dtype=torch_dtype(dtype), device=DEV)
+    ws = torch.full((api.moe_gate_bwd_workspace_bytes(S, M, E),), 255, dtype=torch.uint8, device=DEV)
+    api.moe_gate_bwd(to_dev(dw), to_dev(w), to_dev(idx), to_dev(logits), to_dev(x), torch.zeros(M, E, device=DEV), S, M, E, k, norm,
+                     dl, dWg, db, dx, 0, ws)
+    torch.cuda.synchronize()
+    x64, l64 = x.val.astype(np.float64), to_host(dl)
+    exact = x64.T @ l64
+    chunk = max(8, -(-(-(-S // 256)) // 8) * 8)
+    chained = np.zeros((M, E))
+    for t0 in range(0, S, chunk):
+        acc = np.zeros((M, E), np.float32)
+        for t in range(t0, min(S, t0 + chunk)):
+            acc = (acc + x64[t][:, None] * l64[t][None, :]).astype(np.float32)      # fused multiply-add: one rounding
+        chained += acc
+    err = lambda a: np.linalg.norm(a - exact)      # noqa: E731
+    assert err(to_host(dWg)) <= (1 + 4 / np.sqrt(M * E)) * err(chained.astype(np.float32).astype(np.float64))
+
+    # infinities stay infinities
+    t, e = S // 2, int(idx[S // 2, 0])
+    xi = to_dev(x).clone()
+    xi[t, 3] = float("inf")
+    api.moe_gate_bwd(to_dev(dw), to_dev(w), to_dev(idx), to_dev(logits), xi, torch.zeros(M, E, device=DEV), S, M, E, k, norm,
+                     dl, dWg, db, dx, 0, ws)
+    torch.cuda.synchronize()
+    assert to_host(dWg)[3, e] == np.inf * np.sign(l64[t, e]) and np.isfinite(np.delete(to_host(dWg), 3, axis=0)).all()
