@@ -847,6 +847,11 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     auto lanes = [&](uint64_t mask) {
       const uint32_t bits = (uint32_t)(mask >> (16 * (wk * SPT + ST))) >> (8 * (lane >> 5));
       u32x4_t m;
+      if (KIND != KIND_TN) {   // K % 8 == 0: a lane's 8 values exist together
+        const uint32_t all = (bits & 1u) ? ~0u : 0u;
+        m = u32x4_t{all, all, all, all};
+        return m;
+      }
 #pragma unroll
       for (int d = 0; d < 4; ++d) m[d] = ((bits >> (2 * d)) & 1u) * 0x0000FFFFu + ((bits >> (2 * d + 1)) & 1u) * 0xFFFF0000u;
       return m;
@@ -868,7 +873,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
       using NEXT = std::integral_constant<int, (ST + 1) % SPT>;
       frags_ready(set);
       if constexpr (KIND == KIND_TN || LAST) {
-        if (mask != ~0ull) mask_frags(mask, mask_b, st, set);
+        if (__builtin_expect(mask != ~0ull, 0)) mask_frags(mask, mask_b, st, set);   // (its code stays out of the k loop's way)
       }
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (ST < SPT - 1) {
