@@ -31,11 +31,18 @@ CASES = [
     # S, k, E, C, M, H, n_esp, esp_idx, dtype, tile, fill
     (64, 2, 4, 40, 64, 128, 1, 0, "f32", 0, 1.0),
     (100, 1, 3, 50, 72, 256, 2, 1, "f32", 0, 0.5),
-    (256, 2, 2, 130, 128, 256, 1, 0, "bf16", api.MOE_TILE_SMALL, 1.0),   # 128x128 register-staged kernel
-    (700, 2, 2, 300, 512, 768, 1, 0, "bf16", api.MOE_TILE_256, 1.0),     # 256-row LDS-DMA tiles
+    (256, 2, 2, 130, 128, 256, 1, 0, "bf16", api.MOE_TILE_SMALL, 1.0),   # 128x128 tiles
+    (700, 2, 2, 300, 512, 768, 1, 0, "bf16", api.MOE_TILE_256, 1.0),     # 256-row tiles
     (700, 2, 3, 230, 264, 1040, 2, 0, "bf16", api.MOE_TILE_192, 0.7),    # 192-row tiles, ESP slice, ragged everything
     (512, 4, 4, 600, 256, 512, 1, 0, "bf16", 0, 0.4),                    # mostly empty slots
     (9, 8, 8, 20, 136, 520, 1, 0, "bf16", api.MOE_TILE_256, 1.0),        # k = E = 8, few tokens
+    # the tiles that the plan picks by itself for few rows per expert
+    (64, 2, 8, 20, 264, 520, 1, 0, "bf16", 0, 0.8),                      # 32x64 in the first GEMM, 128x128 weight gradients
+    (300, 2, 4, 100, 520, 2056, 1, 0, "bf16", 0, 1.0),                   # 64x64 (with counts 32x64), merged backward launch
+    (500, 3, 20, 40, 512, 2048, 1, 0, "bf16", 0, 1.0),                   # 64x128, more than 16 experts
+    (900, 2, 24, 70, 520, 1032, 1, 0, "bf16", 0, 0.6),
+    (200, 2, 80, 6, 64, 64, 1, 0, "bf16", 0, 1.0),                       # more than 64 experts
+    (300, 3, 20, 40, 72, 136, 1, 0, "f32", 0, 0.7),
 ]
 
 
