@@ -23,7 +23,7 @@
  *     *_workspace_bytes() helper returns (ws may be NULL when that size is 0).
  *   - `dtype` is MOE_F32 or MOE_BF16 and names the storage type of activations and expert
  *     weights.  Gate weights, logits, combine weights and their gradients are always fp32,
- *     index tensors int32.  Accumulation is fp32 (fp64 for the gate logits).
+ *     index tensors int32.  Accumulation is fp32 (fp64 for the gate logits and the fp32 expert FFN).
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*, NULL = default stream);
  *     no call synchronises with the host.  Outputs are fully overwritten, never accumulated,
  *     unless stated.

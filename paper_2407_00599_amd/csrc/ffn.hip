@@ -84,9 +84,9 @@ __device__ __forceinline__ int64_t a_src_row(const GemmArgs& p, int r, int g) {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-// Guarded 16-byte loads go through buffer descriptors: a lane that must not load passes an
-// offset beyond num_records and receives zeros, without a branch, so the whole k loop body is
-// one basic block whose loads, LDS traffic and MFMAs can be interleaved.
+// The epilogue's 16-byte accesses go through buffer descriptors: a lane that must not load or store passes an offset
+// beyond num_records, which reads as zeros and stores nothing, without a branch.  (The requests of the k loop go through
+// descriptors too, but always lie inside their tensor: see gemm_dma_tile.)
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 constexpr uint32_t OOB = 0xFFFFFFF0u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
@@ -1245,9 +1245,11 @@ struct TilePlan {
   int tile_m, tile_n;
 };
 // The tiles a row-tiled GEMM may take, and what one costs (microseconds, measured): a k tile of 64 with few and with all
-// compute units busy (a compute unit holds one workgroup of the first two, two of the others), and everything
-// outside the k loop.  Large tiles move the fewest bytes per flop; small ones fill the chip when there are few
-// rows, and their k tile is short when a long reduction is what a launch waits for.
+// compute units busy (in a launch of its own; a compute unit then holds one workgroup of the first two, two of the
+// others), and everything outside the k loop.  Large tiles move the fewest bytes per flop; small ones fill the chip when
+// there are few rows, and their k tile is short when a long reduction is what a launch waits for.
+// For dX in the merged backward launch the same prices are an approximation: there a compute unit holds one workgroup
+// whatever its tile (the launch reserves the LDS of a 256 x 256 tile), and the weight gradients queue behind dX.
 struct TileCost {
   TilePlan tile;
   int per_cu;

@@ -894,7 +894,7 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
       // fp32 activations (or token rows past 32-bit offsets)
       const int EC = E <= 8 ? 8 : 16;
       const int T = E <= 8 ? 4 : 2;
-      // many tokens: 8-wave blocks halve the Wg staging work per token; few tokens: 4-wave blocks fill the chip
+      // 8-wave blocks halve the Wg staging work per token (bf16: rows past 4 GiB are many tokens); fp32 keeps blocks of 4
       const int nw = (S >= 16384 && bf) ? 8 : 4;
       const dim3 grid((unsigned)((S + nw * T - 1) / (nw * T))), block(64 * nw);
 #define LAUNCH_SMALL(ec, t) do { \

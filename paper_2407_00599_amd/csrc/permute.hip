@@ -143,6 +143,8 @@ __global__ __launch_bounds__(256) void combine_rows(const void* __restrict__ Yre
 // 512-element chunks per step so that about eight 16-byte loads per lane are in flight.  Bound by HBM once the requests
 // overlap; the general kernel (other counts) waits for each choice's row in turn.  8192 tokens x 2048, top-4 of 128 experts,
 // general kernel against this one: 51 and 53 -> 37 and 32 us forward, 101 (two launches) -> 81 us backward.
+// Where the counts end is not a measured line: 5 and 7 choices, 3 and 4 with more than two partial sums, 6 and 8 with
+// more than one have stayed with the general kernel; fixed counts were not tried there.
 template <bool BF16>
 struct Piece {   // 8 consecutive elements as loaded
   uint4 a, b;    // bf16: a only
