@@ -15,8 +15,8 @@
 // g at physical row ((r / C) * G + g) * C + r % C, so no permutation pass is needed and only
 // the last row tile of an expert is ragged.
 //
-// bf16 path: one kernel, MFMA v_mfma_f32_32x32x16_bf16 with fp32 accumulation, over a family of tiles from 256 x 256
-// down to 32 x 64 (described in front of gemm_dma_tile; plan_tiles chooses).  Global memory goes straight to LDS
+// bf16 path: one kernel, MFMA (v_mfma_f32_16x16x32_bf16 in the two largest tiles, v_mfma_f32_32x32x16_bf16 in the
+// others) with fp32 accumulation, over a family of tiles from 256 x 256 down to 32 x 64 (described in front of gemm_dma_tile; plan_tiles chooses).  Global memory goes straight to LDS
 // (buffer_load ... lds) in k tiles of 64; operands whose memory layout has k as the slow index stay in that layout in
 // LDS and are read with the transposing LDS load, so no transpose pass exists.  The MFMA is issued with the operands
 // swapped (D^T = B^T A^T) so that a lane ends up with 4 consecutive output columns.
@@ -83,6 +83,7 @@ __device__ __forceinline__ int64_t a_src_row(const GemmArgs& p, int r, int g) {
 // ------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // The epilogue's 16-byte accesses go through buffer descriptors: a lane that must not load or store passes an offset
 // beyond num_records, which reads as zeros and stores nothing, without a branch.  (The requests of the k loop go through
@@ -147,9 +148,14 @@ __device__ __forceinline__ void stb16(__amdgpu_buffer_rsrc_t r, uint32_t byte_of
   const u32x4_t q = {v.x, v.y, v.z, v.w};
   __builtin_amdgcn_raw_buffer_store_b128(q, r, (int)byte_off, 0, STREAM ? 2 : 0);
 }
-template <int KIND, int EPI, int MB, int NBK>
-__device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc)[MB][NBK], char* wave_lds, int g,
-                                               int mwave, int mshift, int nbase, const uint32_t (&out_off)[2],
+// The accumulators come in MFMA blocks of MR x MR; a 32 x 32 piece of the wave tile is four groups of 4 consecutive
+// columns per lane either way (quad()).
+template <int MR> struct AccBlock;
+template <> struct AccBlock<32> { typedef f32x16_t type; };
+template <> struct AccBlock<16> { typedef f32x4_t type; };
+template <int KIND, int EPI, int MR, int MB, int NBK, int AM, int AN>
+__device__ __forceinline__ void store_tile_lds(const GemmArgs& p, typename AccBlock<MR>::type (&acc)[AM][AN],
+                                               char* wave_lds, int g, int mwave, int mshift, int nbase, const uint32_t (&out_off)[2],
                                                int lane, bool zero_fill = false) {
   constexpr int CW = 32 * NBK;            // columns of the wave tile
   constexpr int PITCH_B = 2 * CW + 16;    // staged row pitch, bytes
@@ -217,8 +223,14 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc
 #pragma unroll
     for (int t = 0; t < NT_; ++t) zq_next[t] = ldb16<true>(rZ, off[0][t] & ~1u);
   }
-  // accumulator phase: row lane % 32, for block j and q4: 4 columns at 32 j + 8 q4 + 4 (lane / 32)
-  const int acc_off = (lane & 31) * PITCH_B + (lane >> 5) * 8;
+  // accumulator phase, group q4 of block j: MR = 32: row lane % 32, 4 columns at 32 j + 8 q4 + 4 (lane / 32);
+  // MR = 16: row 16 (q4 / 2) + lane % 16, 4 columns at 32 j + 16 (q4 % 2) + 4 (lane / 16)
+  static_assert(AM == MB * 32 / MR && AN == NBK * 32 / MR, "accumulator blocks of the wave tile");
+  const int acc_off = (lane & (MR - 1)) * PITCH_B + (lane / MR) * 8;
+  auto quad = [&](int i, int j, int q4, int e) -> float {
+    if constexpr (MR == 32) return acc[i][j][q4 * 4 + e];
+    else return acc[2 * i + (q4 >> 1)][2 * j + (q4 & 1)][e];
+  };
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
     if (EPI == EPI_DGELU) {  // bring in the saved pre-activation, row-wise; the next block's is requested first
@@ -233,9 +245,10 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc
     for (int j = 0; j < NBK; ++j) {
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        const float v[4] = {acc[i][j][q4 * 4 + 0], acc[i][j][q4 * 4 + 1], acc[i][j][q4 * 4 + 2], acc[i][j][q4 * 4 + 3]};
-        char* a0 = buf0 + acc_off + j * 64 + q4 * 16;
-        char* a1 = buf1 + acc_off + j * 64 + q4 * 16;
+        const float v[4] = {quad(i, j, q4, 0), quad(i, j, q4, 1), quad(i, j, q4, 2), quad(i, j, q4, 3)};
+        const int at = acc_off + j * 64 + (MR == 32 ? q4 * 16 : (q4 >> 1) * 16 * PITCH_B + (q4 & 1) * 32);
+        char* a0 = buf0 + at;
+        char* a1 = buf1 + at;
         if (EPI == EPI_STORE) {
           *reinterpret_cast<uint2*>(a0) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
         } else if (EPI == EPI_GELU) {
@@ -273,8 +286,8 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA tile with an LDS-DMA pipeline.
 //
-// TM x TN output tile, k tile 64, WM x WN waves over the tile times WK waves over the four 16-wide MFMA
-// steps of a k tile (their sums are added through LDS at the end).  Global memory goes straight to LDS
+// TM x TN output tile, k tile 64, WM x WN waves over the tile times WK waves over the MFMA steps of a k tile (two
+// of 32 k; WK = 2: four of 16 k, two per group, whose sums are added through LDS at the end).  Global memory goes straight to LDS
 // (buffer_load ... lds, 16 bytes per lane, no VGPR staging, no ds_write) into two rings of whole k tiles, SA
 // tiles of the A operand and SB of the B operand.  A k tile is 64 wide so that every request of a k-contiguous
 // operand covers whole 128-byte lines.  A wave instruction fills 1 KiB of consecutive 16-byte slots in lane
@@ -287,11 +300,12 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc
 //   operand with k contiguous in memory : [row][64 k] (128-byte rows, 8 chunks), chunk c of row r in slot
 //       c ^ ((r >> 1) & 7); fragments are read with ds_read_b128.
 //   operand with k as the slow index    : [64 k][T cols], chunk c of k-row k in slot c ^ 4 (k & 3) (T = 64:
-//       c ^ 4 ((k >> 1) & 1)); fragments are read with the transposing LDS load ds_read_b64_tr_b16: a
+//       c ^ 4 ((k >> 1) & 1); 16 x 16 MFMAs: also ^ 2 ((k >> 3) & 1), because the 16-lane groups then differ in k);
+//       fragments are read with the transposing LDS load ds_read_b64_tr_b16: a
 //       16-lane group reads a 4(k) x 16(col) patch (lane s: k-row s/4, 8-byte piece s%4) and lane i receives
 //       the 4 k-values of column i.
-// Pipeline: the fragments of MFMA step s+1 are read under step s.  Once per k tile, inside its last step (when
-// the fragments of that step are in registers, so nobody needs the tile's LDS any more), each wave waits until
+// Pipeline: the fragments of MFMA step s+1 are read under step s, each between two MFMAs (Reads).  Once per k tile, inside its
+// last step (when the fragments of that step are in registers, so nobody needs the tile's LDS any more), each wave waits until
 // its own requests for the next tile have landed, all waves meet at a barrier, the fragments of the next tile's
 // first step are read, and the freed slots are refilled: tile t+SB of B, then tile t+SA of A, one request
 // between MFMA rows.  The last SA tiles have nothing to request behind them; they are a loop of their own, in which a
@@ -300,23 +314,33 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, f32x16_t (&acc
 // of tiles from L2; with few tiles, the latency of a k tile.  k tiles of 64 instead of 32 (64-byte pieces of
 // k-contiguous rows fetch half a cache line and look every line up twice): 8 experts of 16384 x 4096 x 7168, per
 // GEMM, 6.83 / 6.44 (forward) and 6.90 / 7.59 (backward) -> 6.3 / 5.9 and 6.1 / 6.1 ms, 1.1 - 1.2 -> 1.2 - 1.35
-// PFLOP/s.  A finer wait per MFMA row, four waves of 128 x 128 and rows padded off a power of two measured no better.
+// PFLOP/s.  Four waves of 128 x 128 and rows padded off a power of two measured no better.
+// Which MFMA: under the power limit 16x16x32 costs less energy per flop than 32x32x16 (on random operands in registers 2.05
+// against 1.81 PFLOP/s, operands from LDS 1.80 against 1.55).  In this kernel it buys clock, 1.74 against 1.51 GHz, and
+// pays only with the reads spread between the MFMAs: reads behind every fourth MFMA, 65 % of the cycles busy and no
+// gain; spread, 69 %: the three launches of the GEMMs above and the merged backward launch 6.74 / 6.27 / 6.45 / 18.99 ->
+// 6.57 / 6.11 / 6.25 / 18.39 ms.  The tiles with two wave groups over k keep 32x32x16, which gives each group two steps
+// per k tile.  Tried without gain: rows of the last step in front of the barrier 2 -> 3 or 4 (to 4 % slower at 12 k tiles),
+// s_setprio for half of the waves, a second barrier that frees B's slot in the first step (-1 to +3 % in single launches).
 // ------------------------------------------------------------------------------------------
 #define LDS_AS __attribute__((address_space(3)))
 constexpr int DK = 64;   // k tile
 // s_waitcnt immediate that waits until at most n vector-memory operations are outstanding (gfx9 encoding)
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
+constexpr int lgkmcnt_imm(int n) { return 0xC07F | (n << 8); }   // LDS operations of a wave end in order
 
 template <int TM_, int TN_, int WM_, int WN_, int WK_, int SA_, int SB_>
 struct TileCfg {
   static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, WK = WK_, SA = SA_, SB = SB_;
   static constexpr int NW = WM * WN * WK;             // waves
-  static constexpr int MB = TM / WM / 32, NB = TN / WN / 32;   // 32 x 32 blocks per wave
+  static constexpr int MR = WK == 1 ? 16 : 32;        // MFMA: MR x MR x KS
+  static constexpr int KS = 512 / MR;
+  static constexpr int MB = TM / WM / MR, NB = TN / WN / MR;   // MFMA blocks per wave
   static constexpr int RA = TM / 8 / NW, RB = TN / 8 / NW;     // requests (1 KiB) per wave and k tile
-  static constexpr int SPT = 4 / WK;                  // MFMA steps per wave and k tile
+  static constexpr int SPT = DK / KS / WK;            // MFMA steps per wave and k tile
   static constexpr int A_UNIT = TM * DK * 2, B_UNIT = TN * DK * 2;
   static constexpr int LDS = SA * A_UNIT + SB * B_UNIT;
-  static_assert(SPT == 2 || SPT == 4, "one or two wave groups over k");
+  static_assert(SPT == 2, "two steps: one register set of B fragments each");
   static_assert(TM / 8 % NW == 0 && TN / 8 % NW == 0, "requests are dealt evenly");
   static_assert(SA == SB || SA == SB + 1, "ring depths");
 };
@@ -540,6 +564,39 @@ struct ChunkWalk {
   }
 };
 
+// The fragment reads of a tile's k loop.  A row's A fragment is replaced by the next step's once the row has been
+// multiplied, the B fragments, which every row uses, have a register set per step.  The next step's reads are taken in
+// the order B0 A0 B1 A1 ... and spread between the MFMAs (place: behind which MFMA of the step), so that
+// they do not queue up in front of the multiplications.  A row waits for its own fragments by count: the LDS reads of a
+// wave return in order.
+template <int KIND, typename CF>
+struct Reads {
+  static constexpr int MB = CF::MB, NB = CF::NB, N = MB + NB;
+  static constexpr int BR = MB > 4 ? 2 : 1;          // rows of a k tile's last step in front of the barrier
+  static_assert(MB >= NB, "the order of the reads");
+  static constexpr bool is_b(int op) { return op < 2 * NB && op % 2 == 0; }
+  static constexpr int of(int op) { return op < 2 * NB ? op / 2 : op - NB; }     // which fragment
+  static constexpr int ins(int op) { return (is_b(op) ? KIND != KIND_NT : KIND == KIND_TN) ? 2 : 1; }   // LDS instructions
+  static constexpr int place(int st, int op) {
+    if (st == CF::SPT - 1) return BR * NB - 1 + op * (MB * NB - BR * NB) / (N - 1);   // behind the barrier
+    return is_b(op) ? of(op) * NB + NB / 2 : of(op) + 1 < MB ? (of(op) + 1) * NB : MB * NB - 1;
+  }
+  static constexpr bool in_place() {                 // no A fragment is replaced before its row has been multiplied
+    for (int op = 0; op < N; ++op)
+      if (!is_b(op) && (place(0, op) < of(op) * NB + NB - 1 || place(1, op) < of(op) * NB + NB - 1)) return false;
+    return true;
+  }
+  static_assert(in_place(), "the order of the reads");
+  // LDS instructions that may still be in flight when row `row` of step st is about to be multiplied
+  static constexpr int newer(int st, int row) {
+    int n = 0;
+    const int need = row == 0 ? (NB > 1 ? 2 * NB - 2 : 1) : row < NB ? 2 * row + 1 : row + NB;   // row 0: every B fragment
+    for (int op = need + 1; op < N; ++op) n += ins(op);
+    for (int op = 0; op < N; ++op) n += place(st, op) < row * NB ? ins(op) : 0;
+    return n < 15 ? n : 15;
+  }
+};
+
 // GATHER: the k-slow A operand of a weight-gradient GEMM (X^T dZ) is the token matrix read through the
 // inverse slot map (row r of the chunk is token gather[g C + r] / gather_k); n_src = 1.
 template <int KIND, int EPI, typename CF, bool GATHER = false>
@@ -547,7 +604,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   constexpr bool A_NC = (KIND == KIND_TN);                     // A has k as the slow index
   constexpr bool B_NC = (KIND == KIND_NN || KIND == KIND_TN);  // B has k as the slow index
   constexpr int TM = CF::TM, TN = CF::TN, WM = CF::WM, WN = CF::WN, WK = CF::WK, SA = CF::SA, SB = CF::SB;
-  constexpr int MB = CF::MB, NB = CF::NB, RA = CF::RA, RB = CF::RB, SPT = CF::SPT;
+  constexpr int MB = CF::MB, NB = CF::NB, RA = CF::RA, RB = CF::RB, SPT = CF::SPT, MR = CF::MR, KS = CF::KS;
+  constexpr int WTM = TM / WM, WTN = TN / WN;   // wave tile
   static_assert(!A_NC || TM == 64 || TM == 128 || TM == 256, "k-slow tiles are a power of two wide");
   static_assert(!GATHER || (KIND == KIND_TN && CF::NW == 8), "row gather in the reduction: eight k-rows per wave");
 
@@ -579,7 +637,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
 #pragma unroll
     for (int j = 0; j < RA; ++j) r[j] = m0 + (wave * RA + j) * 8 + (lane >> 3);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) r[RA + j] = m0 + wm * (32 * MB) + 64 * j + lane;
+    for (int j = 0; j < 2; ++j) r[RA + j] = m0 + wm * WTM + 64 * j + lane;
     if (compact) {
       compact_rows<RA + 2>(p, g, r, row, occ);
     } else {
@@ -607,16 +665,17 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     for (int j = 0; j < 2; ++j)
       if (r[RA + j] < p.Mdim) out_off[j] = (uint32_t)row[RA + j] * (uint32_t)p.ldc * 2u + (occ[RA + j] ? 0u : 1u);
   }
-  constexpr int EMB = (WK == 2 && MB >= 2) ? MB / 2 : MB;      // row and column blocks a wave finishes
-  constexpr int ENB = (WK == 2 && MB < 2 && NB >= 2) ? NB / 2 : NB;
+  // 32 x 32 pieces a wave finishes (WK = 2: MR = 32, a piece is an MFMA block)
+  constexpr int EMB = (WK == 2 && MB >= 2) ? MB / 2 : WTM / 32;
+  constexpr int ENB = (WK == 2 && MB < 2 && NB >= 2) ? NB / 2 : WTN / 32;
   constexpr bool ONE = WK == 2 && MB < 2 && NB < 2;            // a single block: the second group's waves finish nothing
   const int e_i = (WK == 2 && MB >= 2) ? wk * EMB : 0, e_j = (WK == 2 && MB < 2 && NB >= 2) ? wk * ENB : 0;
-  const int e_n = n0 + wn * (32 * NB) + 32 * e_j;
+  const int e_n = n0 + wn * WTN + 32 * e_j;
   char* e_lds = smem + wave * (CF::LDS / CF::NW / 64 * 64);
   if (KIND != KIND_TN && what == 2) {   // padding rows only: every result is zero (dZ of a padding row is never read)
     if (EPI != EPI_DGELU) {
       f32x16_t none[EMB][ENB] = {};
-      store_tile_lds<KIND, EPI, EMB, ENB>(p, none, e_lds, g, m0 + wm * (32 * MB), 32 * e_i, e_n, out_off, lane, true);
+      store_tile_lds<KIND, EPI, 32, EMB, ENB>(p, none, e_lds, g, m0 + wm * WTM, 32 * e_i, e_n, out_off, lane, true);
     }
     return;
   }
@@ -632,7 +691,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   int a_k[RA], b_k[RB];
   constexpr int ACPR = TM / 8, BCPR = TN / 8;   // k-slow: 16-byte chunks per k-row
   const uint32_t lda2 = (uint32_t)p.lda * 2u, ldb2 = (uint32_t)p.ldb * 2u;
-  auto swz_nc = [](int k, int cpr) { return cpr >= 16 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); };
+  auto swz_nc = [](int k, int cpr) { return cpr >= 16 ? 4 * (k & 3) + (MR == 16 ? 2 * ((k >> 3) & 1) : 0) : 4 * ((k >> 1) & 1); };
 #pragma unroll
   for (int j = 0; j < RA; ++j) {
     const int q = wave * RA + j;
@@ -705,68 +764,63 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   uint32_t a_fr[A_NC ? MB : 1], b_fr[B_NC ? NB : 1];
   {
     const int b = lane >> 4, s = lane & 15;
-    const int chunk = ((2 * wk * SPT + (lane >> 5)) ^ ((lane >> 1) & 7)) * 16;
-    const int knc = 16 * wk * SPT + 8 * (b >> 1) + (s >> 2);
+    const int chunk = ((wk * SPT * (KS / 8) + lane / MR) ^ ((lane >> 1) & 7)) * 16;
+    const int oct = MR == 32 ? b >> 1 : b, half = MR == 32 ? 16 * (b & 1) : 0;   // k-slow: the 16-lane group's patch
+    const int knc = KS * wk * SPT + 8 * oct + (s >> 2);
     if (!A_NC) {
-      a_fr[0] = lds0 + (wm * (32 * MB) + (lane & 31)) * 128 + chunk;
+      a_fr[0] = lds0 + (wm * WTM + (lane & (MR - 1))) * 128 + chunk;
     } else {
 #pragma unroll
       for (int i = 0; i < (A_NC ? MB : 1); ++i) {
-        const int col = wm * (32 * MB) + 32 * i + 16 * (b & 1) + 4 * (s & 3);
-        a_fr[i] = lds0 + knc * (2 * TM) + (((col >> 3) ^ swz_nc(s >> 2, ACPR)) * 16) + ((s & 1) * 8);
+        const int col = wm * WTM + MR * i + half + 4 * (s & 3);
+        a_fr[i] = lds0 + knc * (2 * TM) + (((col >> 3) ^ swz_nc(knc, ACPR)) * 16) + ((s & 1) * 8);
       }
     }
     if (!B_NC) {
-      b_fr[0] = lds0 + SA * CF::A_UNIT + (wn * (32 * NB) + (lane & 31)) * 128 + chunk;
+      b_fr[0] = lds0 + SA * CF::A_UNIT + (wn * WTN + (lane & (MR - 1))) * 128 + chunk;
     } else {
 #pragma unroll
       for (int j = 0; j < (B_NC ? NB : 1); ++j) {
-        const int col = wn * (32 * NB) + 32 * j + 16 * (b & 1) + 4 * (s & 3);
-        b_fr[j] = lds0 + SA * CF::A_UNIT + knc * (2 * TN) + (((col >> 3) ^ swz_nc(s >> 2, BCPR)) * 16) + ((s & 1) * 8);
+        const int col = wn * WTN + MR * j + half + 4 * (s & 3);
+        b_fr[j] = lds0 + SA * CF::A_UNIT + knc * (2 * TN) + (((col >> 3) ^ swz_nc(knc, BCPR)) * 16) + ((s & 1) * 8);
       }
     }
   }
-  Frag fa[2][MB], fb[2][NB];
-  // fragments of this wave's step ST in the ring slots go to register set ST & 1; piece 0 = B, piece 1 + n = A blocks
-  // 2 n, 2 n + 1 (so the reads can be spread between MFMAs)
-  constexpr int NPIECE = 1 + (MB + 1) / 2;
-  auto read_piece = [&](int slot_a, int slot_b, auto st_tag, auto piece_tag) {
-    constexpr int ST = decltype(st_tag)::value, P = decltype(piece_tag)::value, set = ST & 1;
-    if constexpr (P == 0) {
+  // a row's A fragment is replaced by the next step's once the row has been multiplied; B has a register set per step
+  Frag fa[MB], fb[2][NB];
+  using RD = Reads<KIND, CF>;
+  constexpr int BR = RD::BR;
+  auto read_op = [&](int slot_a, int slot_b, auto st_tag, auto op_tag) {   // read `op` of step ST
+    constexpr int ST = decltype(st_tag)::value, OP = decltype(op_tag)::value, I = RD::of(OP);
+    if constexpr (RD::is_b(OP)) {
       const uint32_t so = (uint32_t)slot_b * CF::B_UNIT;
-      unrolled<0, NB>([&](auto j) {
-        constexpr int J = decltype(j)::value;
-        if constexpr (!B_NC) lds_read_kc<J * 4096>(fb[set][J], (b_fr[0] + so) ^ (32u * ST));
-        else lds_read_nc<ST * 32 * TN, 8 * TN>(fb[set][J], b_fr[B_NC ? J : 0] + so);
-      });
+      if constexpr (!B_NC) lds_read_kc<I * MR * 128>(fb[ST][I], (b_fr[0] + so) ^ (2u * KS * ST));
+      else lds_read_nc<ST * KS * 2 * TN, 8 * TN>(fb[ST][I], b_fr[B_NC ? I : 0] + so);
     } else {
       const uint32_t so = (uint32_t)slot_a * CF::A_UNIT;
-      unrolled<2 * (P - 1), (2 * P < MB ? 2 * P : MB)>([&](auto i) {
-        constexpr int I = decltype(i)::value;
-        if constexpr (!A_NC) lds_read_kc<I * 4096>(fa[set][I], (a_fr[0] + so) ^ (32u * ST));
-        else lds_read_nc<ST * 32 * TM, 8 * TM>(fa[set][I], a_fr[A_NC ? I : 0] + so);
-      });
+      if constexpr (!A_NC) lds_read_kc<I * MR * 128>(fa[I], (a_fr[0] + so) ^ (2u * KS * ST));
+      else lds_read_nc<ST * KS * 2 * TM, 8 * TM>(fa[I], a_fr[A_NC ? I : 0] + so);
     }
   };
   auto frags_ready = [&](int set) {
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
 #pragma unroll
-    for (int i = 0; i < MB; ++i) ready(fa[set][i]);
+    for (int i = 0; i < MB; ++i) ready(fa[i]);
 #pragma unroll
     for (int j = 0; j < NB; ++j) ready(fb[set][j]);
   };
 
-  f32x16_t acc[MB][NB];
+  typename AccBlock<MR>::type acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+      for (int q = 0; q < MR * MR / 64; ++q) acc[i][j][q] = 0.f;
 
   // Refill set t (issued after the barrier of tile t): tile t+SB of B, then tile t+SA of A.  kb, ka: its tiles.
   constexpr int NREQ = RA + RB;
-  constexpr int PT_LAST = MB > 1 ? MB - 1 : 1;                       // issue points behind the barrier, in the last step
+  constexpr int PT_LAST = MB - BR + 1;                               // issue points behind the barrier, in the last step
   constexpr int PTS = PT_LAST + (SPT - 1) * MB;                      // ... and in the steps before the next barrier
   constexpr int PER = (NREQ + PTS - 1) / PTS;
   constexpr int N_LAST = PT_LAST * PER < NREQ ? PT_LAST * PER : NREQ;   // requests issued in the last step
@@ -822,12 +876,11 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     __builtin_amdgcn_s_barrier();
   }
   using K0 = std::integral_constant<int, 0>;
-  unrolled<0, NPIECE>([&](auto pc) { read_piece(0, 0, K0{}, pc); });
+  unrolled<0, RD::N>([&](auto op) { read_op(0, 0, K0{}, op); });
 
-  auto mfma_row = [&](int set, int i) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j].v, fa[set][i].v, acc[i][j], 0, 0, 0);
+  auto mfma = [&](int set, int i, int j) {
+    if constexpr (MR == 32) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j].v, fa[i].v, acc[i][j], 0, 0, 0);
+    else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][j].v, fa[i].v, acc[i][j], 0, 0, 0);
   };
   int sa = 0, sb = 0;                 // ring slots of the current tile
   int wa = SA - 1, wb = SB - 1;       // ring slots that the refill set in progress goes to
@@ -842,10 +895,10 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   };
   // zeroes the k-rows of set `set` (step ST of a tile) that do not exist, in both operands: what was fetched in their
   // place may be an infinity.  (GATHER: an empty slot is a row of zeros in A only, as in the dispatched buffer.)
-  auto mask_frags = [&](uint64_t mask_a, uint64_t mask_b, auto st_tag, int set) {
+  auto mask_frags = [&](uint64_t mask_a, uint64_t mask_b, auto st_tag) {
     constexpr int ST = decltype(st_tag)::value;
     auto lanes = [&](uint64_t mask) {
-      const uint32_t bits = (uint32_t)(mask >> (16 * (wk * SPT + ST))) >> (8 * (lane >> 5));
+      const uint32_t bits = (uint32_t)(mask >> (KS * (wk * SPT + ST))) >> (8 * (lane / MR));
       u32x4_t m;
       if (KIND != KIND_TN) {   // K % 8 == 0: a lane's 8 values exist together
         const uint32_t all = (bits & 1u) ? ~0u : 0u;
@@ -858,9 +911,9 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     };
     const u32x4_t ma = lanes(mask_a), mb = GATHER ? lanes(mask_b) : ma;
 #pragma unroll
-    for (int i = 0; i < MB; ++i) fa[set][i].q &= ma;
+    for (int i = 0; i < MB; ++i) fa[i].q &= ma;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) fb[set][j].q &= mb;
+    for (int j = 0; j < NB; ++j) fb[ST][j].q &= mb;
   };
   // one k tile; LAST: one of the last SA tiles, whose refills may be past the end
   auto k_tile = [&](int t, auto last_tag) {
@@ -869,60 +922,68 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     const uint64_t mask = KIND == KIND_TN ? k_mask[0] : LAST ? mask_of(ktile_at(t), ~0ull) : ~0ull;
     const uint64_t mask_b = GATHER ? mask_of(KTile{0, k_lim[0]}, ~0ull) : mask;
     unrolled<0, SPT>([&](auto st) {
-      constexpr int ST = decltype(st)::value, set = ST & 1;
-      using NEXT = std::integral_constant<int, (ST + 1) % SPT>;
-      frags_ready(set);
+      constexpr int ST = decltype(st)::value;
+      using NEXT = std::integral_constant<int, 1 - ST>;
+      // row 0 needs its own A fragment and all B fragments; a step with missing k rows waits for everything and masks it
+      __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(RD::newer(ST, 0)));
+#pragma unroll
+      for (int j = 0; j < NB; ++j) ready(fb[ST][j]);
+      ready(fa[0]);
       if constexpr (KIND == KIND_TN || LAST) {
-        if (__builtin_expect(mask != ~0ull, 0)) mask_frags(mask, mask_b, st, set);   // (its code stays out of the k loop's way)
+        if (__builtin_expect(mask != ~0ull, 0)) {   // (its code stays out of the k loop's way)
+          frags_ready(ST);
+          mask_frags(mask, mask_b, st);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (ST < SPT - 1) {
-        unrolled<0, MB>([&](auto i) {
-          constexpr int I = decltype(i)::value;
-          mfma_row(set, I);
-          __builtin_amdgcn_sched_barrier(0);
-          unrolled<0, NPIECE>([&](auto pc) {
-            if constexpr (decltype(pc)::value * MB / NPIECE == I) read_piece(sa, sb, NEXT{}, pc);
-          });
-          issue(std::integral_constant<int, (PT_LAST + ST * MB + I) * PER>{}, last_tag);
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      } else {
-        mfma_row(set, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(LAST ? 0 : IN_FLIGHT));   // this wave's requests for tile t+1 have landed
-        __builtin_amdgcn_s_barrier();                        // everyone is done with tile t, and tile t+1 is complete
-        __builtin_amdgcn_sched_barrier(0);
-        wa = sa; wb = sb;
-        if (KIND == KIND_TN) {
-          const KTile nx = GATHER ? g_next : next_ktile();
-          if constexpr (SA > SB) kb = ka; else kb = nx;
-          ka = nx;
-          uint64_t full = ~0ull;
-          if (GATHER) {
-            full = gather_rows(g_entry);
-            g_next = next_ktile();
-            g_entry = gather_fetch(g_next.row0);
-          }
-#pragma unroll
-          for (int u = 0; u + 1 < SA; ++u) { k_mask[u] = k_mask[u + 1]; k_lim[u] = k_lim[u + 1]; }
-          k_mask[SA - 1] = mask_of(ka, full);
-          k_lim[SA - 1] = ka.lim;
-        } else {
-          ka = ktile_at(t + SA);
-          kb = ktile_at(t + SB);
+      unrolled<0, MB>([&](auto i) {
+        constexpr int I = decltype(i)::value;
+        if constexpr (I > 0) {
+          if constexpr (ST < SPT - 1 || I < BR) __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(RD::newer(ST, I)));
+          ready(fa[I]);
         }
-        unrolled<0, PT_LAST>([&](auto i1) {
-          constexpr int I1 = decltype(i1)::value;
-          unrolled<0, NPIECE>([&](auto pc) {
-            if constexpr (decltype(pc)::value * PT_LAST / NPIECE == I1) read_piece(na, nb, NEXT{}, pc);
-          });
-          issue(std::integral_constant<int, I1 * PER>{}, last_tag);
+        unrolled<0, NB>([&](auto j) {
+          constexpr int J = decltype(j)::value, AT = I * NB + J;
           __builtin_amdgcn_sched_barrier(0);
-          if constexpr (I1 + 1 < MB) mfma_row(set, I1 + 1);
+          mfma(ST, I, J);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (ST == SPT - 1 && AT == BR * NB - 1) {
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(LAST ? 0 : IN_FLIGHT) & 0xF0FF);   // this wave's requests for tile t+1 have landed; so have its reads of tile t
+            __builtin_amdgcn_s_barrier();                        // everyone is done with tile t, and tile t+1 is complete
+            __builtin_amdgcn_sched_barrier(0);
+            wa = sa; wb = sb;
+            if (KIND == KIND_TN) {
+              const KTile nx = GATHER ? g_next : next_ktile();
+              if constexpr (SA > SB) kb = ka; else kb = nx;
+              ka = nx;
+              uint64_t full = ~0ull;
+              if (GATHER) {
+                full = gather_rows(g_entry);
+                g_next = next_ktile();
+                g_entry = gather_fetch(g_next.row0);
+              }
+#pragma unroll
+              for (int u = 0; u + 1 < SA; ++u) { k_mask[u] = k_mask[u + 1]; k_lim[u] = k_lim[u + 1]; }
+              k_mask[SA - 1] = mask_of(ka, full);
+              k_lim[SA - 1] = ka.lim;
+            } else {
+              ka = ktile_at(t + SA);
+              kb = ktile_at(t + SB);
+            }
+          }
+          unrolled<0, RD::N>([&](auto op) {
+            if constexpr (RD::place(ST, decltype(op)::value) == AT) {
+              if constexpr (ST < SPT - 1) read_op(sa, sb, NEXT{}, op);
+              else read_op(na, nb, NEXT{}, op);
+            }
+          });
+          if constexpr (J == NB - 1) {
+            if constexpr (ST < SPT - 1) issue(std::integral_constant<int, (PT_LAST + ST * MB + I) * PER>{}, last_tag);
+            else if constexpr (I >= BR - 1) issue(std::integral_constant<int, (I - BR + 1) * PER>{}, last_tag);
+          }
           __builtin_amdgcn_sched_barrier(0);
         });
-      }
+      });
     });
     sa = na; sb = nb;
   };
@@ -971,9 +1032,9 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
         }
     __syncthreads();
     if (ONE && wk != 0) return;
-    store_tile_lds<KIND, EPI, EMB, ENB>(p, mine, e_lds, g, m0 + wm * (32 * MB), 32 * e_i, e_n, out_off, lane);
+    store_tile_lds<KIND, EPI, 32, EMB, ENB>(p, mine, e_lds, g, m0 + wm * WTM, 32 * e_i, e_n, out_off, lane);
   } else {
-    store_tile_lds<KIND, EPI, MB, NB>(p, acc, e_lds, g, m0 + wm * (32 * MB), 0, e_n, out_off, lane);
+    store_tile_lds<KIND, EPI, MR, EMB, ENB>(p, acc, e_lds, g, m0 + wm * WTM, 0, e_n, out_off, lane);
   }
 }
 
