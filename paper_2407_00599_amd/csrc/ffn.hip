@@ -156,7 +156,7 @@ template <> struct AccBlock<16> { typedef f32x4_t type; };
 template <int KIND, int EPI, int MR, int MB, int NBK, int AM, int AN>
 __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, typename AccBlock<MR>::type (&acc)[AM][AN],
                                                char* wave_lds, int g, int mwave, int mshift, int nbase, const uint32_t (&out_off)[2],
-                                               int lane, bool zero_fill = false) {
+                                               int lane) {
   constexpr int CW = 32 * NBK;            // columns of the wave tile
   constexpr int PITCH_B = 2 * CW + 16;    // staged row pitch, bytes
   constexpr int BUF = 32 * PITCH_B;
@@ -206,17 +206,6 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, typename AccBl
         const uint32_t o = (uint32_t)__shfl((int)(d < 64 ? out_off[0] : out_off[1]), (d & 63) + rl, 64);
         off[i][t] = (o != OOB && col_ok) ? o + (uint32_t)ncol * 2u : OOB;   // even: bit 0 marks a row of zeros
       }
-  }
-  if (zero_fill) {   // a tile of padding rows: every result is zero
-    const uint4 z = make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int t = 0; t < NT_; ++t) {
-        stb16(rC, off[i][t] & ~1u, z);
-        if (EPI == EPI_GELU) stb16(rC2, off[i][t] & ~1u, z);
-      }
-    return;
   }
   uint4 zq_next[EPI == EPI_DGELU ? NT_ : 1];
   if (EPI == EPI_DGELU) {
@@ -404,10 +393,19 @@ __device__ __forceinline__ int xcd_tile(int x, int i, int per_xcd) {
   const int full = per_xcd & ~31;
   return i < full ? ((i & ~31) * 8 + x * 32) + (i & 31) : full * 8 + x * (per_xcd - full) + (i - full);
 }
-// With row counts the order holds the row tiles that have occupied rows first (compacted: an expert with n
-// occupied rows has ceil(n / TM) of them) and then the tiles that only have to be filled with zeros; each XCD gets an
-// equal share of both, whatever the routing.  Returns 0: no tile, 1: a tile to multiply, 2: a tile of zeros.
-template <int TM>
+// With row counts the order holds the row tiles that have occupied rows only (compacted: an expert with n occupied rows
+// has ceil(n / TM) of them).  Where padding has to be stored as zeros the workgroups behind them do that: with one chunk
+// per expert a workgroup for every tile of padding (fill_tile; padding rows inside a multiplied tile are stored by that
+// tile); with several, whose padding is spread over the buffer, a workgroup for an equal share of all padding rows
+// (fill_shares), about one for a tile's worth, or for four with very many.  The grid has a workgroup for every tile of the
+// capacity, and MORE_SHARES (grid_of); the rest leave at once.
+// Fewer and larger shares between the tiles, to store beside the matrix work, measured slower: a compute unit stores no more
+// than some 20 GB/s while the others load the memory system, and the whole chip 4.5 to 5 TB/s.
+// 8 experts of 3500 occupied in 20480 rows x 2048 x 2048, 32 chunks: with a workgroup that walked the rows of every tile of
+// zeros 474 / 392 / 378 us (the forward GEMMs and dZ, which stores no zeros), now 484 / 306 / 236.
+// Returns 0: nothing to do, 1: a tile to multiply, 2: padding to fill (one chunk: tile g, tm, tn; several: share g of tm).
+constexpr int MORE_SHARES = 64;
+template <int TM, bool ZEROS>
 __device__ __forceinline__ int map_tile(const GemmArgs& p, int vb, bool counted, int& g, int& tm, int& tn) {
   const int x = vb & 7, i = vb >> 3;
   if (!counted) {
@@ -419,6 +417,27 @@ __device__ __forceinline__ int map_tile(const GemmArgs& p, int vb, bool counted,
     patch_order(tile - g * tiles_per_g, p.tiles_m, p.tiles_n, tm, tn);
     return 1;
   }
+  // tile: index among the T tiles to multiply, or -1 (g and tm are set if a share of the padding is to be filled)
+  auto place = [&](int T, int& what) {
+    const int Z = p.total_tiles - T;      // tiles' worth of padding behind the multiplied tiles
+    const int idle = -T & 255;            // compute units without a tile in the last round
+    const int nz = !ZEROS ? 0 : p.n_src == 1 ? Z : idle > 0 && Z <= 2 * idle ? min(2 * idle, Z + MORE_SHARES)
+                              : Z <= 1024 ? Z + MORE_SHARES : max(1024, Z / 4);
+    const int per_t = (T + 7) / 8, per_z = (nz + 7) / 8, n = per_t + per_z;
+    what = 0;
+    if (i >= n) return -1;
+    if (i >= per_t) {
+      g = (i - per_t) * 8 + x;
+      tm = nz;
+      what = g < nz ? 2 : 0;
+      return -1;
+    }
+    const int tile = xcd_tile(x, i, per_t);
+    if (tile >= T) return -1;
+    what = 1;
+    return tile;
+  };
+  int what;
   if (p.n_src == 1 && p.G <= 16) {   // few counts: scalar loads, which hit the scalar cache from a compute unit's second tile on
     int o[16], occ_all = 0;
 #pragma unroll
@@ -428,11 +447,10 @@ __device__ __forceinline__ int map_tile(const GemmArgs& p, int vb, bool counted,
       o[e] = e < p.G ? (clamp_count(o[e], p.Cc) + TM - 1) / TM : 0;
       occ_all += o[e];
     }
-    const int T = occ_all * p.tiles_n, Z = p.total_tiles - T;
-    const int per_t = (T + 7) / 8, per_z = (Z + 7) / 8;
-    const bool zero = i >= per_t;
-    const int tile = zero ? x * per_z + (i - per_t) : xcd_tile(x, i, per_t);
-    if (zero ? (i - per_t >= per_z || tile >= Z) : tile >= T) return 0;
+    int tile = place(occ_all * p.tiles_n, what);
+    if (what == 0) return what;
+    const bool zero = what == 2;
+    if (zero) tile = g;
     int first = 0, mine = 0, og = 0, run = 0;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -442,36 +460,38 @@ __device__ __forceinline__ int map_tile(const GemmArgs& p, int vb, bool counted,
     }
     patch_order(tile - first * p.tiles_n, mine, p.tiles_n, tm, tn);
     if (zero) tm += og;
-    return zero ? 2 : 1;
+    return what;
   }
+  // 64 experts at a time, a lane each; with fewer the lanes share the chunks of an expert
   const int lane = threadIdx.x & 63;
-  auto occupied = [&](int e) {   // row tiles of expert e that hold occupied rows
+  const int width = p.G >= 64 ? 64 : p.G <= 1 ? 1 : 1 << (32 - __builtin_clz(p.G - 1));   // a power of two
+  auto occupied = [&](int e0) {      // row tiles of expert e0 + lane % width that hold occupied rows
+    const int e = e0 + (lane & (width - 1)), step = 64 / width;
     int n = 0;
     if (e < p.G) {
-#pragma unroll 8
-      for (int s = 0; s < p.n_src; ++s) n += clamp_count(p.cnt[s * p.G + e], p.Cc);
+#pragma unroll 4
+      for (int s = lane / width; s < p.n_src; s += step) n += clamp_count(p.cnt[s * p.G + e], p.Cc);
     }
-    return (n + TM - 1) / TM;
+    for (int d = width; d < 64; d <<= 1) n += __shfl_xor(n, d, 64);
+    return lane < width ? (n + TM - 1) / TM : 0;
   };
-  const int o0 = occupied(lane);
+  const int o0 = occupied(0);
   int occ_all = 0;
   for (int e0 = 0; e0 < p.G; e0 += 64) {
-    int o = e0 == 0 ? o0 : occupied(e0 + lane);
+    int o = e0 == 0 ? o0 : occupied(e0);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) o += __shfl_xor(o, d, 64);
     occ_all += o;
   }
-  occ_all = __builtin_amdgcn_readfirstlane(occ_all);
-  const int T = occ_all * p.tiles_n, Z = p.total_tiles - T;
-  const int per_t = (T + 7) / 8, per_z = (Z + 7) / 8;
-  const bool zero = i >= per_t;
-  const int tile = zero ? x * per_z + (i - per_t) : xcd_tile(x, i, per_t);
-  if (zero ? (i - per_t >= per_z || tile >= Z) : tile >= T) return 0;
-  int run = 0;   // tiles of the experts before e0
+  int tile = place(__builtin_amdgcn_readfirstlane(occ_all) * p.tiles_n, what);
+  if (what == 0 || (what == 2 && p.n_src > 1)) return what;
+  const bool zero = what == 2;
+  if (zero) tile = g;
+  int run = 0;   // row tiles of the experts before e0
   for (int e0 = 0; e0 < p.G; e0 += 64) {
-    const int o = e0 == 0 ? o0 : occupied(e0 + lane);
-    const int mine = e0 + lane < p.G ? (zero ? p.tiles_m - o : o) : 0;
-    int incl = mine;
+    const int o = e0 == 0 ? o0 : occupied(e0);
+    const int m = zero ? (lane < width && e0 + lane < p.G ? p.tiles_m - o : 0) : o;
+    int incl = m;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
       const int v = __shfl_up(incl, d, 64);
@@ -480,56 +500,117 @@ __device__ __forceinline__ int map_tile(const GemmArgs& p, int vb, bool counted,
     const unsigned long long hit = __ballot((run + incl) * p.tiles_n > tile);
     if (hit) {
       const int l = __ffsll((long long)hit) - 1;
-      const int before = __shfl(incl - mine, l, 64), og = __shfl(o, l, 64), mg = __shfl(mine, l, 64);
-      g = __builtin_amdgcn_readfirstlane(e0 + l);
-      patch_order(tile - (run + before) * p.tiles_n, mg, p.tiles_n, tm, tn);
-      tm = __builtin_amdgcn_readfirstlane(tm + (zero ? og : 0));
-      tn = __builtin_amdgcn_readfirstlane(tn);
-      return zero ? 2 : 1;
+      const int before = __builtin_amdgcn_readlane(incl - m, l), mine = __builtin_amdgcn_readlane(m, l);
+      g = e0 + l;
+      patch_order(tile - (run + before) * p.tiles_n, mine, p.tiles_n, tm, tn);
+      if (zero) tm += __builtin_amdgcn_readlane(o, l);
+      return what;
     }
-    run += __shfl(incl, 63, 64);
+    run += __builtin_amdgcn_readlane(incl, 63);
   }
   return 0;
 }
 
-// Compacted row order of an expert that receives several chunks with row counts: its occupied rows first, chunk by
-// chunk, then the padding rows, chunk by chunk.  Finds the physical rows of N positions; occ = an occupied row.
-template <int N>
-__device__ __forceinline__ void compact_rows(const GemmArgs& p, int g, const int (&r)[N], int (&row)[N], bool (&occ)[N]) {
-  const int lane = threadIdx.x & 63;
-  int total = 0;
-  for (int s0 = 0; s0 < p.n_src; s0 += 64) {
-    int c = s0 + lane < p.n_src ? clamp_count(p.cnt[(s0 + lane) * p.G + g], p.Cc) : 0;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
-    total += c;
+// Stores the rows of row tile tm of expert g in n0 .. n0 + TN - 1 as zeros (one chunk per expert).  ESZ = bytes per element;
+// TWO = the second output as well.
+template <int ESZ, int TM, int TN, bool TWO>
+__device__ __forceinline__ void fill_tile(const GemmArgs& p, int g, int tm, int tn) {
+  constexpr int CPR = TN * ESZ / 16;       // 16-byte pieces per row
+  const int col = tn * TN + (threadIdx.x % CPR) * (16 / ESZ);
+  if (col >= p.Ndim) return;
+  const u32x4_t z = {0u, 0u, 0u, 0u};
+  const int step = blockDim.x / CPR, end = min((tm + 1) * TM, p.Cc);
+  for (int r = tm * TM + threadIdx.x / CPR; r < end; r += step) {
+    const int64_t at = ((int64_t)g * p.Cc + r) * p.ldc + col;
+    *reinterpret_cast<u32x4_t*>(reinterpret_cast<char*>(p.C) + at * ESZ) = z;
+    if (TWO) *reinterpret_cast<u32x4_t*>(reinterpret_cast<char*>(p.C2) + at * ESZ) = z;
   }
-  total = __builtin_amdgcn_readfirstlane(total);
+}
+
+// Stores share `at` of `shares` of the padding rows of all chunks as zeros: a chunk's padding is one run of memory up to its
+// end.
+template <int ESZ, bool TWO>
+__device__ __forceinline__ void fill_shares(const GemmArgs& p, int at, int shares) {
+  const int lane = threadIdx.x & 63, chunks = p.n_src * p.G;     // n_src G Cc < 2^31 (checked on the host)
+  const int row_units = (int)(p.ldc * ESZ / 16);                 // 16-byte pieces per row
+  auto padding = [&](int c) { return c < chunks ? p.Cc - clamp_count(p.cnt[c], p.Cc) : 0; };
+  int rows = 0;
+  for (int c0 = 0; c0 < chunks; c0 += 64) rows += padding(c0 + lane);
 #pragma unroll
-  for (int n = 0; n < N; ++n) { row[n] = 0; occ[n] = r[n] < total; }
-  int pre = 0, pad = total;   // positions of this chunk's first occupied / padding row
-  for (int s0 = 0; s0 < p.n_src; s0 += 64) {
-    const int cl = s0 + lane < p.n_src ? clamp_count(p.cnt[(s0 + lane) * p.G + g], p.Cc) : 0;
-    const int ns = min(64, p.n_src - s0);
-    for (int s = 0; s < ns; ++s) {
-      const int c = __builtin_amdgcn_readlane(cl, s);
-      const int base = ((s0 + s) * p.G + g) * p.Cc;
+  for (int d = 32; d >= 1; d >>= 1) rows += __shfl_xor(rows, d, 64);
+  rows = __builtin_amdgcn_readfirstlane(rows);
+  const int per = (int)(((unsigned)rows + shares - 1) / (unsigned)shares), r0 = min((int64_t)per * at, (int64_t)rows), r1 = min(r0 + (int64_t)per, (int64_t)rows);
+  int run = 0;                                                   // padding rows in front of c0
+  for (int c0 = 0; c0 < chunks && run < r1; c0 += 64) {
+    const int n = padding(c0 + lane);
+    int incl = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int v = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += v;
+    }
+    const int first = run + incl - n;
+    unsigned long long hit = __ballot(n > 0 && first < r1 && first + n > r0);
+    while (hit) {
+      const int l = __ffsll((long long)hit) - 1;
+      hit &= hit - 1;
+      const int nl = __builtin_amdgcn_readlane(n, l), f = __builtin_amdgcn_readlane(first, l);
+      const int lo = max(r0 - f, 0), hi = min(r1 - f, nl);
+      const int64_t base = ((int64_t)(c0 + l + 1) * p.Cc - nl + lo) * row_units, units = (int64_t)(hi - lo) * row_units;
+      const u32x4_t z = {0u, 0u, 0u, 0u};
+      u32x4_t* c = reinterpret_cast<u32x4_t*>(p.C) + base;
+      u32x4_t* c2 = reinterpret_cast<u32x4_t*>(TWO ? p.C2 : p.C) + base;
+#pragma unroll 4
+      for (int64_t u = threadIdx.x; u < units; u += blockDim.x) {
+        __builtin_nontemporal_store(z, c + u);
+        if (TWO) __builtin_nontemporal_store(z, c2 + u);
+      }
+    }
+    run += __builtin_amdgcn_readlane(incl, 63);
+  }
+}
+
+// Compacted row order of an expert that receives several chunks with row counts: its occupied rows, chunk by chunk.  Finds
+// the physical rows of N positions in [m0, m0 + span); occ = there is one.  A span touches few of the chunks.
+template <int N>
+__device__ __forceinline__ void compact_rows(const GemmArgs& p, int g, int m0, int span, const int (&r)[N], int (&row)[N],
+                                             bool (&occ)[N]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int n = 0; n < N; ++n) { row[n] = 0; occ[n] = false; }
+  int run = 0;   // positions of the chunks before s0
+  for (int s0 = 0; s0 < p.n_src && run < m0 + span; s0 += 64) {
+    const int c = s0 + lane < p.n_src ? clamp_count(p.cnt[(s0 + lane) * p.G + g], p.Cc) : 0;
+    int incl = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int v = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += v;
+    }
+    unsigned long long hit = __ballot(c > 0 && run + incl > m0 && run + incl - c < m0 + span);
+    while (hit) {
+      const int l = __ffsll((long long)hit) - 1;
+      hit &= hit - 1;
+      const int cl = __builtin_amdgcn_readlane(c, l), first = run + __builtin_amdgcn_readlane(incl, l) - cl;
+      const int base = ((s0 + l) * p.G + g) * p.Cc;
 #pragma unroll
       for (int n = 0; n < N; ++n) {
-        const int at = occ[n] ? pre : pad;
-        if (r[n] >= at) row[n] = base + (occ[n] ? 0 : c) + (r[n] - at);
+        const int d = r[n] - first;
+        if ((uint32_t)d < (uint32_t)cl) { row[n] = base + d; occ[n] = true; }
       }
-      pre += c;
-      pad += p.Cc - c;
     }
+    run += __builtin_amdgcn_readlane(incl, 63);
   }
 }
 
 struct KTile {
   int row0, lim;   // first row of the k tile in the operand (row-tiled GEMMs: first k), rows (k values) that exist
 };
-// The reduction of a weight gradient runs over the expert's rows chunk by chunk (a k tile never crosses a chunk), and a
-// chunk's k tiles end at its row count; empty chunks are passed over.
+// The reduction of a weight gradient runs over the expert's rows chunk by chunk, up to each chunk's row count; empty
+// chunks are passed over.  With few chunks a k tile never crosses a chunk, so that its grouping is the same with and without row
+// counts; with PACK_CHUNKS of them or more (half a k tile lost in each) the rows are packed: a k tile is made of
+// pieces of several chunks.
+constexpr int PACK_CHUNKS = 4;
 struct ChunkWalk {
   const GemmArgs& p;
   int g, cnt = 0, s0 = 0, row = 0, left = 0;   // cnt: rows of chunk s0 + lane
@@ -540,20 +621,20 @@ struct ChunkWalk {
     cnt = s < p.n_src ? (p.cnt != nullptr ? clamp_count(p.cnt[s * p.G + g], p.Cc) : p.Cc) : 0;
     mask = __ballot(cnt > 0);
   }
-  __device__ __forceinline__ int start(int step) {   // returns the number of k tiles
+  __device__ __forceinline__ int start(int step, bool packed) {   // returns the number of k tiles
     int nk = 0;
     for (s0 = 0; s0 < p.n_src; s0 += 64) {
       load();
-      int n = (cnt + step - 1) / step;
+      int n = packed ? cnt : (cnt + step - 1) / step;
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
       nk += __builtin_amdgcn_readfirstlane(n);
     }
     s0 = 0;
     if (p.n_src > 64) load();
-    return nk;
+    return packed ? (nk + step - 1) / step : nk;
   }
-  __device__ __forceinline__ KTile next(int step) {   // past the end: no rows
+  __device__ __forceinline__ KTile next(int step) {   // the next rows of one chunk, at most `step`; past the end: no rows
     if (left <= 0) {
       while (mask == 0 && s0 + 64 < p.n_src) { s0 += 64; load(); }
       if (mask == 0) return KTile{0, 0};
@@ -602,16 +683,20 @@ struct Reads {
   }
 };
 
-// GATHER: the k-slow A operand of a weight-gradient GEMM (X^T dZ) is the token matrix read through the
-// inverse slot map (row r of the chunk is token gather[g C + r] / gather_k); n_src = 1.
-template <int KIND, int EPI, typename CF, bool GATHER = false>
+// How a weight-gradient GEMM finds its k-rows.  GATHER: the k-slow A operand (X^T dZ) is the token matrix read through the
+// inverse slot map (row r of the chunk is token gather[g C + r] / gather_k); n_src = 1.  PACKED: k tiles of pieces of
+// several chunks (ChunkWalk).
+enum { ROWS_PLAIN = 0, ROWS_GATHER = 1, ROWS_PACKED = 2 };
+template <int KIND, int EPI, typename CF, int ROWS = ROWS_PLAIN>
 __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int vb) {
+  constexpr bool GATHER = ROWS == ROWS_GATHER, PIECES = ROWS == ROWS_PACKED;
   constexpr bool A_NC = (KIND == KIND_TN);                     // A has k as the slow index
   constexpr bool B_NC = (KIND == KIND_NN || KIND == KIND_TN);  // B has k as the slow index
   constexpr int TM = CF::TM, TN = CF::TN, WM = CF::WM, WN = CF::WN, WK = CF::WK, SA = CF::SA, SB = CF::SB;
   constexpr int MB = CF::MB, NB = CF::NB, RA = CF::RA, RB = CF::RB, SPT = CF::SPT, MR = CF::MR, KS = CF::KS;
   constexpr int WTM = TM / WM, WTN = TN / WN;   // wave tile
   static_assert(!A_NC || TM == 64 || TM == 128 || TM == 256, "k-slow tiles are a power of two wide");
+  static_assert(ROWS == ROWS_PLAIN || KIND == KIND_TN, "rows of a reduction");
   static_assert(!GATHER || (KIND == KIND_TN && CF::NW == 8), "row gather in the reduction: eight k-rows per wave");
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -621,8 +706,9 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
 
   int g, tm, tn;
   const bool counted = KIND != KIND_TN && p.cnt != nullptr;
-  const int what = map_tile<TM>(p, vb, counted, g, tm, tn);
+  const int what = map_tile<TM, EPI != EPI_DGELU>(p, vb, counted, g, tm, tn);   // (dZ of a padding row is never read)
   if (what == 0) return;
+  if (KIND != KIND_TN && __builtin_expect(what == 2, 0)) return p.n_src == 1 ? fill_tile<2, TM, TN, EPI == EPI_GELU>(p, g, tm, tn) : fill_shares<2, EPI == EPI_GELU>(p, g, tm);
   const int m0 = tm * TM, n0 = tn * TN;
   const bool compact = counted && p.n_src > 1;
 
@@ -638,18 +724,21 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   uint32_t out_off[2] = {OOB, OOB};   // byte offset of the row in the output (+ 1: a row of zeros), or OOB
   if (KIND != KIND_TN) {
     int r[RA + 2], row[RA + 2];
-    bool occ[RA + 2];
+    bool occ[RA + 2], here[2];   // there is a row to multiply; there is a row to store (zeros if not occ)
 #pragma unroll
     for (int j = 0; j < RA; ++j) r[j] = m0 + (wave * RA + j) * 8 + (lane >> 3);
 #pragma unroll
     for (int j = 0; j < 2; ++j) r[RA + j] = m0 + wm * WTM + 64 * j + lane;
     if (compact) {
-      compact_rows<RA + 2>(p, g, r, row, occ);
+      compact_rows<RA + 2>(p, g, m0, TM, r, row, occ);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) here[j] = occ[RA + j];
     } else {
       const int cnt_g = counted ? clamp_count(p.cnt[g], p.Cc) : p.Mdim;
 #pragma unroll
       for (int j = 0; j < RA + 2; ++j) {
         occ[j] = r[j] < cnt_g;
+        if (j >= RA) here[j - RA] = r[j] < p.Mdim;
         row[j] = p.n_src == 1 ? g * p.Cc + r[j] : (int)phys_row(min(r[j], p.Mdim - 1), g, p.G, p.Cc);
       }
       if (p.gather != nullptr) {   // rows are the tokens that the slots hold; an empty slot is a row of zeros
@@ -665,10 +754,10 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
       }
     }
 #pragma unroll
-    for (int j = 0; j < RA; ++j) q_row[j] = (r[j] < p.Mdim && occ[j]) ? row[j] : 0;   // no row: any row of the tensor
+    for (int j = 0; j < RA; ++j) q_row[j] = occ[j] ? row[j] : 0;   // no row: any row of the tensor
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      if (r[RA + j] < p.Mdim) out_off[j] = (uint32_t)row[RA + j] * (uint32_t)p.ldc * 2u + (occ[RA + j] ? 0u : 1u);
+      if (here[j]) out_off[j] = (uint32_t)row[RA + j] * (uint32_t)p.ldc * 2u + (occ[RA + j] ? 0u : 1u);
   }
   // 32 x 32 pieces a wave finishes (WK = 2: MR = 32, a piece is an MFMA block)
   constexpr int EMB = (WK == 2 && MB >= 2) ? MB / 2 : WTM / 32;
@@ -677,18 +766,10 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   const int e_i = (WK == 2 && MB >= 2) ? wk * EMB : 0, e_j = (WK == 2 && MB < 2 && NB >= 2) ? wk * ENB : 0;
   const int e_n = n0 + wn * WTN + 32 * e_j;
   char* e_lds = smem + wave * (CF::LDS / CF::NW / 64 * 64);
-  if (KIND != KIND_TN && what == 2) {   // padding rows only: every result is zero (dZ of a padding row is never read)
-    if (EPI != EPI_DGELU) {
-      f32x16_t none[EMB][ENB] = {};
-      store_tile_lds<KIND, EPI, 32, EMB, ENB>(p, none, e_lds, g, m0 + wm * WTM, 32 * e_i, e_n, out_off, lane, true);
-    }
-    return;
-  }
 
   // ---- k tiles: Kdim / 64 of a row-tiled GEMM, the walk over the expert's chunks for a weight gradient ----
   ChunkWalk walk(p, g);
-  const int nk = KIND == KIND_TN ? walk.start(DK) : (p.Kdim + DK - 1) / DK;
-  auto next_ktile = [&]() { return walk.next(DK); };
+  const int nk = KIND == KIND_TN ? walk.start(DK, PIECES) : (p.Kdim + DK - 1) / DK;
 
   // ---- per-lane request coordinates: byte offset of the lane's row / column, the k index within the tile that the
   // request covers (k-slow) or starts at (k-contiguous), and the byte offset of that k index ----
@@ -752,15 +833,47 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     }
     return __ballot(full);
   };
+  // PIECES: byte offsets of this lane's k-rows in the newest k tile (A's next requests) and the one before it (B's)
+  uint32_t ka_off[PIECES ? RA : 1], kb_off[PIECES ? RB : 1], kb_new[PIECES ? RB : 1];
+  static_assert(!PIECES || SA == SB + 1, "B's requests are a k tile behind A's");
+  auto next_ktile = [&]() -> KTile {
+    KTile t = walk.next(DK);
+    if constexpr (PIECES) {
+#pragma unroll
+      for (int j = 0; j < RB; ++j) { kb_off[j] = kb_new[j]; kb_new[j] = (uint32_t)t.row0 * ldb2 + b_ko[j]; }
+#pragma unroll
+      for (int j = 0; j < RA; ++j) ka_off[j] = (uint32_t)t.row0 * lda2 + a_ko[j];
+      {
+        while (t.lim < DK) {
+          const KTile piece = walk.next(DK - t.lim);
+          if (piece.lim == 0) break;
+          const uint32_t d = (uint32_t)(piece.row0 - t.lim);
+#pragma unroll
+          for (int j = 0; j < RA; ++j) ka_off[j] = a_k[j] >= t.lim ? d * lda2 + a_ko[j] : ka_off[j];
+#pragma unroll
+          for (int j = 0; j < RB; ++j) kb_new[j] = b_k[j] >= t.lim ? d * ldb2 + b_ko[j] : kb_new[j];
+          t.lim += piece.lim;
+        }
+      }
+      if (t.lim < DK) {   // missing k rows are fetched from the tile's first one
+#pragma unroll
+        for (int j = 0; j < RA; ++j) ka_off[j] = a_k[j] < t.lim ? ka_off[j] : (uint32_t)t.row0 * lda2;
+#pragma unroll
+        for (int j = 0; j < RB; ++j) kb_new[j] = b_k[j] < t.lim ? kb_new[j] : (uint32_t)t.row0 * ldb2;
+      }
+    }
+    return t;
+  };
   // One request (1 KiB) of k tile kt into ring slot `slot`.
   auto request_a = [&](const KTile& kt, int slot, int j) {
-    const uint32_t add = GATHER ? g_now[j] : A_NC ? (uint32_t)kt.row0 * lda2 : (uint32_t)kt.row0 * 2u;
-    dma16(rA, smem + slot * CF::A_UNIT + (wave * RA + j) * 1024, a_req[j] + add + (a_k[j] < kt.lim ? a_ko[j] : 0u));
+    const uint32_t in = a_k[j] < kt.lim ? a_ko[j] : 0u;   // missing k rows are fetched from the tile's first one
+    const uint32_t add = GATHER ? g_now[j] : PIECES ? ka_off[PIECES ? j : 0] : (A_NC ? (uint32_t)kt.row0 * lda2 : (uint32_t)kt.row0 * 2u) + in;
+    dma16(rA, smem + slot * CF::A_UNIT + (wave * RA + j) * 1024, a_req[j] + add);
   };
   auto request_b = [&](const KTile& kt, int slot, int j) {
-    const uint32_t add = B_NC ? (uint32_t)kt.row0 * ldb2 : (uint32_t)kt.row0 * 2u;
-    dma16(rB, smem + SA * CF::A_UNIT + slot * CF::B_UNIT + (wave * RB + j) * 1024,
-          b_req[j] + add + (b_k[j] < kt.lim ? b_ko[j] : 0u));
+    const uint32_t in = b_k[j] < kt.lim ? b_ko[j] : 0u;
+    const uint32_t add = PIECES ? kb_off[PIECES ? j : 0] : (B_NC ? (uint32_t)kt.row0 * ldb2 : (uint32_t)kt.row0 * 2u) + in;
+    dma16(rB, smem + SA * CF::A_UNIT + slot * CF::B_UNIT + (wave * RB + j) * 1024, b_req[j] + add);
   };
   auto ktile_at = [&](int t) -> KTile { return KTile{t * DK, p.Kdim - t * DK}; };   // row-tiled GEMMs
 
@@ -825,10 +938,11 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
 
   // Refill set t (issued after the barrier of tile t): tile t+SB of B, then tile t+SA of A.  kb, ka: its tiles.
   constexpr int NREQ = RA + RB;
-  constexpr int PT_LAST = MB - BR + 1;                               // issue points behind the barrier, in the last step
-  constexpr int PTS = PT_LAST + (SPT - 1) * MB;                      // ... and in the steps before the next barrier
-  constexpr int PER = (NREQ + PTS - 1) / PTS;
-  constexpr int N_LAST = PT_LAST * PER < NREQ ? PT_LAST * PER : NREQ;   // requests issued in the last step
+  // The requests of a set are spread evenly over the MFMAs up to the next barrier: issued together they stall the waves.
+  constexpr int SL_LAST = (MB - BR) * NB + 1, SL = SL_LAST + (SPT - 1) * MB * NB;   // slots: in the last step, in all
+  constexpr auto slot_of = [](int r) constexpr { return r * SL / NREQ; };
+  constexpr auto before = [](int slot) constexpr { int n = 0; for (int r = 0; r < NREQ; ++r) n += r * SL / NREQ < slot; return n; };
+  constexpr int N_LAST = before(SL_LAST);                            // requests issued in the last step
   constexpr int IN_FLIGHT = (SA > SB ? RA : 0) + (SB - 2) * (NREQ + (GATHER ? 1 : 0));    // newer requests than those of tile t+1, at barrier t
   KTile ka{0, 0}, kb{0, 0};
   int g_entry = 0;        // GATHER: slot-map entries of g_next, the tile after ka
@@ -842,7 +956,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   {
     KTile pro[SA];
 #pragma unroll
-    for (int t = 0; t < SA; ++t) pro[t] = KIND == KIND_TN ? next_ktile() : ktile_at(t);
+    for (int t = 0; t < SA; ++t)
+      if (!PIECES) pro[t] = KIND == KIND_TN ? next_ktile() : ktile_at(t);
     int g_pro[SA];
     if (GATHER) {
 #pragma unroll
@@ -857,6 +972,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     };
 #pragma unroll
     for (int st = -SA; st <= -2; ++st) {
+      if (PIECES) pro[st + SA] = next_ktile();
       if (st + SB >= 0) {
 #pragma unroll
         for (int j = 0; j < RB; ++j)
@@ -867,6 +983,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
       for (int j = 0; j < RA; ++j)
         if (pro[st + SA].lim > 0) request_a(pro[st + SA], st + SA, j);
     }
+    if (PIECES) pro[SA - 1] = next_ktile();
     ka = pro[SA - 1];
     kb = pro[SB - 1];
     pro_a(SA - 1);
@@ -889,13 +1006,14 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   };
   int sa = 0, sb = 0;                 // ring slots of the current tile
   int wa = SA - 1, wb = SB - 1;       // ring slots that the refill set in progress goes to
-  auto issue = [&](auto from_tag, auto last_tag) {    // the next PER requests; LAST: the tile may be past the end
-    constexpr int F = decltype(from_tag)::value, N = PER;
+  auto issue = [&](auto slot_tag, auto last_tag) {    // the requests of a slot; LAST: the tile may be past the end
     constexpr bool LAST = decltype(last_tag)::value;
-    unrolled<F, (F + N < NREQ ? F + N : NREQ)>([&](auto r) {
+    unrolled<0, NREQ>([&](auto r) {
       constexpr int R = decltype(r)::value;
-      if constexpr (R < RB) { if (!LAST || kb.lim > 0) request_b(kb, wb, R); }
-      else { if (!LAST || ka.lim > 0) request_a(ka, wa, R - RB); }
+      if constexpr (slot_of(R) == decltype(slot_tag)::value) {
+        if constexpr (R < RB) { if (!LAST || kb.lim > 0) request_b(kb, wb, R); }
+        else { if (!LAST || ka.lim > 0) request_a(ka, wa, R - RB); }
+      }
     });
   };
   // zeroes the k-rows of set `set` (step ST of a tile) that do not exist, in both operands: what was fetched in their
@@ -982,10 +1100,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
               else read_op(na, nb, NEXT{}, op);
             }
           });
-          if constexpr (J == NB - 1) {
-            if constexpr (ST < SPT - 1) issue(std::integral_constant<int, (PT_LAST + ST * MB + I) * PER>{}, last_tag);
-            else if constexpr (I >= BR - 1) issue(std::integral_constant<int, (I - BR + 1) * PER>{}, last_tag);
-          }
+          if constexpr (ST < SPT - 1) issue(std::integral_constant<int, SL_LAST + ST * MB * NB + AT>{}, last_tag);
+          else if constexpr (AT >= BR * NB - 1) issue(std::integral_constant<int, AT - BR * NB + 1>{}, last_tag);
           __builtin_amdgcn_sched_barrier(0);
         });
       });
@@ -1043,10 +1159,10 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   }
 }
 
-template <int KIND, int EPI, typename CF, bool GATHER = false>
+template <int KIND, int EPI, typename CF, int ROWS = ROWS_PLAIN>
 __global__ __launch_bounds__(64 * CF::NW) void ffn_gemm_dma(const GemmArgs p) {
   __shared__ __attribute__((aligned(1024))) char smem[CF::LDS];
-  gemm_dma_tile<KIND, EPI, CF, GATHER>(p, smem, (int)blockIdx.x);
+  gemm_dma_tile<KIND, EPI, CF, ROWS>(p, smem, (int)blockIdx.x);
 }
 
 using Tile256 = TileCfg<256, 256, 2, 4, 1, 3, 2>;
@@ -1059,14 +1175,14 @@ using Tile32x64 = TileCfg<32, 64, 1, 2, 2, 6, 6>;
 // The three GEMMs of the backward pass that only depend on dZ, in one launch: dX = dZ W1^T (row-tiled,
 // the long tiles, first in the grid) and the two weight gradients.  nbx and nbw are the (multiple-of-8)
 // workgroup counts of the first two problems.
-template <typename CFX, bool GATHER_W1 = false>   // GATHER_W1: the third problem reads its A operand through a slot map
+template <typename CFX, int ROWS>   // ROWS_GATHER: the third problem only
 __global__ __launch_bounds__(512) void ffn_bwd_trio(const GemmArgs px, const GemmArgs pw2, const GemmArgs pw1, int nbx,
                                                     int nbw) {
   __shared__ __attribute__((aligned(1024))) char smem[Tile256::LDS];
   const int b = (int)blockIdx.x;
   if (b < nbx) gemm_dma_tile<KIND_NT, EPI_STORE, CFX>(px, smem, b);
-  else if (b < nbx + nbw) gemm_dma_tile<KIND_TN, EPI_STORE, Tile256>(pw2, smem, b - nbx);
-  else gemm_dma_tile<KIND_TN, EPI_STORE, Tile256, GATHER_W1>(pw1, smem, b - nbx - nbw);
+  else if (b < nbx + nbw) gemm_dma_tile<KIND_TN, EPI_STORE, Tile256, ROWS == ROWS_GATHER ? ROWS_PLAIN : ROWS>(pw2, smem, b - nbx);
+  else gemm_dma_tile<KIND_TN, EPI_STORE, Tile256, ROWS>(pw1, smem, b - nbx - nbw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1097,8 +1213,9 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
   int g, tm, tn;
   const bool counted = KIND != KIND_TN && p.cnt != nullptr;
-  const int what = map_tile<TM>(p, vb, counted, g, tm, tn);
+  const int what = map_tile<TM, EPI != EPI_DGELU>(p, vb, counted, g, tm, tn);   // (dZ of a padding row is never read)
   if (what == 0) return;
+  if (KIND != KIND_TN && __builtin_expect(what == 2, 0)) return p.n_src == 1 ? fill_tile<4, TM, TN, EPI == EPI_GELU>(p, g, tm, tn) : fill_shares<4, EPI == EPI_GELU>(p, g, tm);
   const int m0 = tm * TM, n0 = tn * TN;
   const float* __restrict__ A = reinterpret_cast<const float*>(p.A);
   const float* __restrict__ B = reinterpret_cast<const float*>(p.B) + (KIND == KIND_TN ? 0 : (int64_t)g * p.b_goff + p.b_off);
@@ -1108,17 +1225,19 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int
   bool o_zero = false;
   if (KIND != KIND_TN) {
     int r[UA + 1], row[UA + 1];
-    bool occ[UA + 1];
+    bool occ[UA + 1], here = false;   // there is a row to multiply; there is a row to store (zeros if not occ)
 #pragma unroll
     for (int u = 0; u < UA; ++u) r[u] = m0 + (tid + 256 * u) / (FK / 4);
     r[UA] = m0 + lane;
     if (counted && p.n_src > 1) {
-      compact_rows<UA + 1>(p, g, r, row, occ);
+      compact_rows<UA + 1>(p, g, m0, TM, r, row, occ);
+      here = occ[UA];
     } else {
       const int cnt_g = counted ? clamp_count(p.cnt[g], p.Cc) : p.Mdim;
 #pragma unroll
       for (int u = 0; u <= UA; ++u) {
         occ[u] = r[u] < cnt_g;
+        if (u == UA) here = r[u] < p.Mdim;
         row[u] = (int)phys_row(min(r[u], p.Mdim - 1), g, p.G, p.Cc);
         if (p.gather != nullptr) {
           const int64_t tok = a_src_row(p, min(r[u], p.Mdim - 1), g);
@@ -1128,12 +1247,12 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int
       }
     }
 #pragma unroll
-    for (int u = 0; u < UA; ++u) a_row[u] = (r[u] < p.Mdim && occ[u]) ? row[u] : 0;   // no row: any row, its results are not stored
-    o_row = r[UA] < p.Mdim ? row[UA] : -1;
+    for (int u = 0; u < UA; ++u) a_row[u] = occ[u] ? row[u] : 0;   // no row: any row, its results are not stored
+    o_row = here ? row[UA] : -1;
     o_zero = !occ[UA];
   }
   ChunkWalk walk(p, g);
-  const int nk = what == 2 ? 0 : KIND == KIND_TN ? walk.start(FK) : (p.Kdim + FK - 1) / FK;
+  const int nk = KIND == KIND_TN ? walk.start(FK, false) : (p.Kdim + FK - 1) / FK;
 
   auto swz = [](int k, int T) constexpr { return ((k >> 2) & (T / 8 - 1)) * 8; };   // see the layout above
   // This thread's pieces: where they start at k = 0 (k-contiguous: row and k offset; k-slow: column), and their k.  A
@@ -1367,9 +1486,13 @@ bool merged_backward(GemmArgs& w2, GemmArgs& w1, int tile) {   // prepares the t
   return t2.tile_m == 256 && t1.tile_m == 256;
 }
 
+bool packs_chunks(const GemmArgs& a) { return a.n_src >= PACK_CHUNKS && a.cnt != nullptr; }
+
 // Workgroups of a problem, a multiple of 8: every XCD takes an equal share of the tiles to multiply and, with row
-// counts, an equal share of the tiles of zeros, each share rounded up.
-int grid_of(const GemmArgs& a) { return (a.total_tiles + (a.cnt ? 14 : 7)) / 8 * 8; }
+// counts, of the shares of the padding (map_tile), each rounded up.
+int grid_of(const GemmArgs& a) {
+  return (a.total_tiles + (a.cnt ? 14 : 7)) / 8 * 8 + (a.cnt && a.n_src > 1 ? MORE_SHARES : 0);
+}
 
 // fp32 tiles: the largest (fewest conversions per product) that gives every compute unit enough workgroups to even out
 using I32 = std::integral_constant<int, 32>;
@@ -1413,7 +1536,8 @@ void launch_gemm(GemmArgs a, int dtype, int tile, hipStream_t st) {
   auto launch = [&](auto cfg) {
     using CF = decltype(cfg);
     if constexpr (KIND == KIND_TN) {
-      if (a.gather != nullptr) hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF, true>), grid, dim3(64 * CF::NW), 0, st, a);
+      if (a.gather != nullptr) hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF, ROWS_GATHER>), grid, dim3(64 * CF::NW), 0, st, a);
+      else if (packs_chunks(a)) hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF, ROWS_PACKED>), grid, dim3(64 * CF::NW), 0, st, a);
       else hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF>), grid, dim3(64 * CF::NW), 0, st, a);
     } else {
       hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF>), grid, dim3(64 * CF::NW), 0, st, a);
@@ -1613,8 +1737,9 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
       const dim3 grid((unsigned)(nbx + nb2 + nb1));
       auto launch = [&](auto cfg) {
         using CF = decltype(cfg);
-        if (gather) hipLaunchKernelGGL((ffn_bwd_trio<CF, true>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-        else hipLaunchKernelGGL((ffn_bwd_trio<CF>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
+        if (gather) hipLaunchKernelGGL((ffn_bwd_trio<CF, ROWS_GATHER>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
+        else if (packs_chunks(p2)) hipLaunchKernelGGL((ffn_bwd_trio<CF, ROWS_PACKED>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
+        else hipLaunchKernelGGL((ffn_bwd_trio<CF, ROWS_PLAIN>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
       };
       if (tx.tile_m == 256) launch(Tile256{});
       else if (tx.tile_m == 192) launch(Tile192{});

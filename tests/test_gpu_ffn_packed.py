@@ -1,0 +1,42 @@
+"""Expert FFN with row counts over many source chunks: k tiles of the weight gradients that are made of pieces of several
+chunks, and padding rows stored apart from the tiles (none, a few rows, most of the buffer)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_oracle as O
+from paper_2407_00599_amd import synth
+from test_gpu_ffn import gpu_ffn
+from util import DEV, TOL, ROWS, EXPERT, to_dev, to_host, assert_close, torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_src,G,C,M,H,lo,hi,dtype", [
+    (4, 2, 129, 264, 520, 0, 129, "bf16"),        # as few chunks as are packed
+    (40, 1, 12, 136, 264, 0, 3, "bf16"),          # a k tile of twenty pieces and more, one tile in all
+    (90, 2, 7, 72, 136, 0, 8, "bf16"),            # more than 64 chunks, a k tile across the sixty-fourth
+    (5, 3, 64, 72, 136, 64, 65, "bf16"),          # no padding at all
+    (6, 2, 700, 264, 520, 0, 2, "bf16"),          # almost nothing but padding
+    (6, 20, 100, 64, 64, 0, 40, "bf16"),          # more than 16 experts
+    (6, 2, 700, 72, 136, 0, 40, "f32"),
+])
+def test_packed_chunks(n_src, G, C, M, H, lo, hi, dtype):
+    rng = np.random.default_rng(n_src * 1009 + C)
+    occ = rng.integers(lo, hi, size=(n_src, G)).clip(0, C)
+    Xn = rng.standard_normal((n_src, G, C, M)).astype(np.float32)
+    dYn = rng.standard_normal((n_src, G, C, M)).astype(np.float32)
+    pad = np.arange(C)[None, None, :] >= occ[:, :, None]
+    Xn[pad] = 0; dYn[pad] = 0
+    X, dY = synth.store(Xn, dtype), synth.store(dYn, dtype)
+    W1 = synth.store((rng.standard_normal((G, M, H)) / np.sqrt(M)).astype(np.float32), dtype)
+    W2 = synth.store((rng.standard_normal((G, H, M)) / np.sqrt(H)).astype(np.float32), dtype)
+    cnt = torch.tensor(occ.astype(np.int32), device=DEV)
+    got = gpu_ffn(*(to_dev(t) for t in (X, dY, W1, W2)), n_src, G, C, M, H, 0, 1, torch_dtype(dtype), cnt)
+    rZ, rY = O.expert_ffn_fwd(X.val, W1.val, W2.val, 0, 1)
+    rdX, rdW1, rdW2 = O.expert_ffn_bwd(dY.val, X.val, W1.val, W2.val, 0, 1)
+    for name, t, ref, group in (("Z", got[0], rZ, ROWS), ("A", got[1], O.gelu(rZ), ROWS), ("Y", got[2], rY, ROWS),
+                                ("dX", got[3], rdX, ROWS), ("dW1", got[4], rdW1, EXPERT), ("dW2", got[5], rdW2, EXPERT)):
+        assert_close(to_host(t), ref, TOL[dtype], name, group)
+    for t in got[:4]:
+        assert np.all(to_host(t)[pad] == 0.0)
