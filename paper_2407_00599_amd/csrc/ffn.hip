@@ -28,6 +28,8 @@
 // fp32 path: a kernel on the fp64 matrix cores (fp64 accumulation), row counts used the same way.
 #include <math.h>
 
+#include <algorithm>
+
 #include <type_traits>
 
 #include "common.h"
@@ -37,7 +39,7 @@ namespace {
 using namespace moe;
 
 enum { KIND_NN = 1, KIND_NT = 2, KIND_TN = 3 };
-enum { EPI_STORE = 0, EPI_GELU = 1, EPI_DGELU = 2 };
+enum { EPI_STORE = 0, EPI_GELU = 1, EPI_DGELU = 2, EPI_PART = 3 };   // EPI_PART: fp32 partial sums of a split reduction
 
 struct GemmArgs {
   const void* A;
@@ -61,6 +63,8 @@ struct GemmArgs {
   int64_t b_off, c_off;              // constant offset of the ESP slice, elements
   int tiles_m, tiles_n, total_tiles;
   uint64_t a_bytes, b_bytes;         // bf16 path: byte sizes of the A and B tensors (buffer descriptors)
+  int splits;                        // EPI_PART: parts of the reduction; part q of every expert's matrix in
+  float* part;                       // [splits, G, Mdim, Ndim]
 };
 
 __device__ __forceinline__ int64_t phys_row(int r, int g, int G, int Cc) {
@@ -634,6 +638,21 @@ struct ChunkWalk {
     if (p.n_src > 64) load();
     return packed ? (nk + step - 1) / step : nk;
   }
+  __device__ __forceinline__ void skip(int tiles, int step, bool packed) {   // passes over the first k tiles
+    int n = packed ? tiles * step : tiles;   // rows, or k tiles
+    while (n > 0) {
+      if (mask == 0) { if (s0 + 64 >= p.n_src) return; s0 += 64; load(); continue; }
+      const int l = __ffsll((long long)mask) - 1, c = __builtin_amdgcn_readlane(cnt, l);
+      const int has = packed ? c : (c + step - 1) / step;
+      mask &= mask - 1;
+      if (has > n) {
+        const int rows = packed ? n : n * step;
+        left = c - rows;
+        row = ((s0 + l) * p.G + g) * p.Cc + rows;
+      }
+      n -= has;
+    }
+  }
   __device__ __forceinline__ KTile next(int step) {   // the next rows of one chunk, at most `step`; past the end: no rows
     if (left <= 0) {
       while (mask == 0 && s0 + 64 < p.n_src) { s0 += 64; load(); }
@@ -706,6 +725,12 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
 
   int g, tm, tn;
   const bool counted = KIND != KIND_TN && p.cnt != nullptr;
+  int part = 0;   // EPI_PART: which part of the reduction; the parts of a tile are total_tiles apart
+  if (EPI == EPI_PART) {
+    const int per = (p.total_tiles + 7) / 8 * 8;
+    part = vb / per;
+    vb -= part * per;
+  }
   const int what = map_tile<TM, EPI != EPI_DGELU>(p, vb, counted, g, tm, tn);   // (dZ of a padding row is never read)
   if (what == 0) return;
   if (KIND != KIND_TN && __builtin_expect(what == 2, 0)) return p.n_src == 1 ? fill_tile<2, TM, TN, EPI == EPI_GELU>(p, g, tm, tn) : fill_shares<2, EPI == EPI_GELU>(p, g, tm);
@@ -769,7 +794,13 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
 
   // ---- k tiles: Kdim / 64 of a row-tiled GEMM, the walk over the expert's chunks for a weight gradient ----
   ChunkWalk walk(p, g);
-  const int nk = KIND == KIND_TN ? walk.start(DK, PIECES) : (p.Kdim + DK - 1) / DK;
+  int nk = KIND == KIND_TN ? walk.start(DK, PIECES) : (p.Kdim + DK - 1) / DK;
+  int k_left = nk;               // k tiles that the walk has not been asked for
+  if (EPI == EPI_PART) {         // this part's
+    const int t0 = (int)((int64_t)nk * part / p.splits), t1 = (int)((int64_t)nk * (part + 1) / p.splits);
+    walk.skip(t0, DK, PIECES);
+    k_left = nk = t1 - t0;
+  }
 
   // ---- per-lane request coordinates: byte offset of the lane's row / column, the k index within the tile that the
   // request covers (k-slow) or starts at (k-contiguous), and the byte offset of that k index ----
@@ -837,14 +868,15 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   uint32_t ka_off[PIECES ? RA : 1], kb_off[PIECES ? RB : 1], kb_new[PIECES ? RB : 1];
   static_assert(!PIECES || SA == SB + 1, "B's requests are a k tile behind A's");
   auto next_ktile = [&]() -> KTile {
-    KTile t = walk.next(DK);
+    KTile t{0, 0};                                   // past the end: no rows
+    if (EPI != EPI_PART || k_left-- > 0) t = walk.next(DK);
     if constexpr (PIECES) {
 #pragma unroll
       for (int j = 0; j < RB; ++j) { kb_off[j] = kb_new[j]; kb_new[j] = (uint32_t)t.row0 * ldb2 + b_ko[j]; }
 #pragma unroll
       for (int j = 0; j < RA; ++j) ka_off[j] = (uint32_t)t.row0 * lda2 + a_ko[j];
       {
-        while (t.lim < DK) {
+        while (t.lim > 0 && t.lim < DK) {
           const KTile piece = walk.next(DK - t.lim);
           if (piece.lim == 0) break;
           const uint32_t d = (uint32_t)(piece.row0 - t.lim);
@@ -1153,6 +1185,21 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
         }
     __syncthreads();
     if (ONE && wk != 0) return;
+    if constexpr (EPI == EPI_PART) {   // straight from the registers: 4 columns of a row per lane and group
+      float* dst = p.part + ((int64_t)part * p.G + g) * p.Mdim * p.Ndim;
+#pragma unroll
+      for (int i = 0; i < EMB; ++i)
+#pragma unroll
+        for (int j = 0; j < ENB; ++j)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const int m = m0 + wm * WTM + 32 * (e_i + i) + (lane & 31), n = e_n + 32 * j + 8 * q4 + 4 * (lane >> 5);
+            if (m < p.Mdim && n < p.Ndim)
+              *reinterpret_cast<float4*>(dst + (int64_t)m * p.Ndim + n) =
+                  make_float4(mine[i][j][q4 * 4], mine[i][j][q4 * 4 + 1], mine[i][j][q4 * 4 + 2], mine[i][j][q4 * 4 + 3]);
+          }
+      return;
+    }
     store_tile_lds<KIND, EPI, 32, EMB, ENB>(p, mine, e_lds, g, m0 + wm * WTM, 32 * e_i, e_n, out_off, lane);
   } else {
     store_tile_lds<KIND, EPI, MR, EMB, ENB>(p, acc, e_lds, g, m0 + wm * WTM, 0, e_n, out_off, lane);
@@ -1174,15 +1221,35 @@ using Tile32x64 = TileCfg<32, 64, 1, 2, 2, 6, 6>;
 
 // The three GEMMs of the backward pass that only depend on dZ, in one launch: dX = dZ W1^T (row-tiled,
 // the long tiles, first in the grid) and the two weight gradients.  nbx and nbw are the (multiple-of-8)
-// workgroup counts of the first two problems.
-template <typename CFX, int ROWS>   // ROWS_GATHER: the third problem only
+// workgroup counts of the first two problems.  EPI: of the weight gradients.
+template <typename CFX, typename CFW, int EPI, int ROWS>   // ROWS_GATHER: the third problem only
 __global__ __launch_bounds__(512) void ffn_bwd_trio(const GemmArgs px, const GemmArgs pw2, const GemmArgs pw1, int nbx,
                                                     int nbw) {
-  __shared__ __attribute__((aligned(1024))) char smem[Tile256::LDS];
+  static_assert(CFX::NW == 8 && CFW::NW == 8, "one block size");
+  __shared__ __attribute__((aligned(1024))) char smem[CFX::LDS > CFW::LDS ? CFX::LDS : CFW::LDS];
   const int b = (int)blockIdx.x;
   if (b < nbx) gemm_dma_tile<KIND_NT, EPI_STORE, CFX>(px, smem, b);
-  else if (b < nbx + nbw) gemm_dma_tile<KIND_TN, EPI_STORE, Tile256, ROWS == ROWS_GATHER ? ROWS_PLAIN : ROWS>(pw2, smem, b - nbx);
-  else gemm_dma_tile<KIND_TN, EPI_STORE, Tile256, ROWS>(pw1, smem, b - nbx - nbw);
+  else if (b < nbx + nbw) gemm_dma_tile<KIND_TN, EPI, CFW, ROWS == ROWS_GATHER ? ROWS_PLAIN : ROWS>(pw2, smem, b - nbx);
+  else gemm_dma_tile<KIND_TN, EPI, CFW, ROWS>(pw1, smem, b - nbx - nbw);
+}
+
+// Adds the parts of the two split weight gradients in order and stores them in bf16: a thread owns 4 columns of a row.
+__global__ __launch_bounds__(256) void ffn_add_parts(const GemmArgs pw2, const GemmArgs pw1, int64_t n2, int64_t n) {
+  int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (u >= n) return;
+  const GemmArgs& p = u < n2 ? pw2 : pw1;
+  if (u >= n2) u -= n2;
+  const int64_t size = (int64_t)p.G * p.Mdim * p.Ndim, at = u * 4;
+  const float* src = p.part + at;
+  float4 v = *reinterpret_cast<const float4*>(src);
+#pragma unroll 8
+  for (int q = 1; q < p.splits; ++q) {
+    const float4 w = *reinterpret_cast<const float4*>(src + q * size);
+    v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+  }
+  const int64_t row = at / p.Ndim, g = row / p.Mdim;
+  bf16_t* dst = reinterpret_cast<bf16_t*>(p.C) + g * p.c_goff + p.c_off + (row - g * p.Mdim) * p.ldc + (at - row * p.Ndim);
+  *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1480,10 +1547,22 @@ TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile, bool wide = false) {
   return t;
 }
 
-// The three backward GEMMs that only depend on dZ go out in one launch if both weight gradients take 256 x 256 tiles.
-bool merged_backward(GemmArgs& w2, GemmArgs& w1, int tile) {   // prepares the two
+// The three backward GEMMs that only depend on dZ go out in one launch if both weight gradients take 256 x 256 tiles,
+// or both 128 x 128 tiles without the caller asking for them; returns which (0: launches of their own).
+int merged_backward(GemmArgs& w2, GemmArgs& w1, int tile) {   // prepares the two
   const TilePlan t2 = prepare_bf16(w2, true, tile), t1 = prepare_bf16(w1, true, tile);
-  return t2.tile_m == 256 && t1.tile_m == 256;
+  return t2.tile_m != t1.tile_m || (t2.tile_m != 256 && tile != MOE_TILE_AUTO) ? 0 : t2.tile_m;
+}
+// Parts of the reductions of the two weight gradients where both take 128 x 128 tiles: few tiles leave compute units idle, and
+// a reduction over thousands of rows is then what the launch waits for.  Parts of at least 12 k tiles, so that the
+// partial sums (written, read and added in a launch of their own) cost less than the k tiles they save, and no more workgroups
+// than the chip holds.  Depends on the shape only.
+int weight_parts(int n_src, int G, int64_t C, int M, int Hl) {
+  const int64_t tiles256 = (int64_t)G * ((M + 255) / 256) * ((Hl + 255) / 256);
+  if (tiles256 >= 64) return 1;
+  const int64_t tiles = 2 * (int64_t)G * ((M + 127) / 128) * ((Hl + 127) / 128), nk = ((int64_t)n_src * C + 63) / 64;
+  const int64_t parts = std::min<int64_t>({2 * (int64_t)num_cus() / tiles, nk / 12, 64});
+  return parts < 2 ? 1 : (int)parts;
 }
 
 bool packs_chunks(const GemmArgs& a) { return a.n_src >= PACK_CHUNKS && a.cnt != nullptr; }
@@ -1611,17 +1690,27 @@ extern "C" double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C,
     rows = rows_multiplied(a, alone(to_h)) + rows_multiplied(a, alone(to_m));
   } else {           // dA = dY W2^T (rows x Hl), dX = dZ W1^T (rows x M), dW2 (Hl x M) and dW1 (M x Hl) over the rows
     GemmArgs w2 = gemm(Hl, M, a.R), w1 = gemm(M, Hl, a.R), dx = to_m;
-    const int dx_m = dtype == MOE_F32 ? f32_tile_m(plan_f32_trio(dx, w2, w1))
-                                      : prepare_bf16(dx, false, tile, merged_backward(w2, w1, tile)).tile_m;
+    auto dx_tile = [&]() {
+      const int merged = merged_backward(w2, w1, tile);
+      return merged == 128 ? Tile64x128::TM : prepare_bf16(dx, false, tile, merged == 256).tile_m;
+    };
+    const int dx_m = dtype == MOE_F32 ? f32_tile_m(plan_f32_trio(dx, w2, w1)) : dx_tile();
     rows = rows_multiplied(a, alone(to_h)) + rows_multiplied(a, dx_m) + 2.0 * rows_multiplied(a, 0);
   }
   return 2.0 * (double)M * (double)Hl * rows;
 }
 
+static size_t dz_bytes(int n_src, int G, int64_t C, int Hl, size_t esz) {
+  return moe::align_up((size_t)n_src * G * C * (size_t)Hl * esz, 256);
+}
+static size_t part_bytes(int parts, int G, int M, int Hl) { return moe::align_up((size_t)parts * G * M * Hl * 4, 256); }
+
 extern "C" size_t moe_ffn_workspace_bytes(int dtype, int n_src, int G, int64_t C, int M, int H, int n_esp) {
   if (check_ffn_shape(dtype, n_src, G, C, M, H, 0, n_esp) != MOE_OK) return 0;
   const size_t esz = dtype == MOE_BF16 ? 2 : 4;
-  return moe::align_up((size_t)n_src * G * C * (size_t)(H / n_esp) * esz, 256);   // dZ
+  const int Hl = H / n_esp;
+  const int parts = dtype == MOE_BF16 ? weight_parts(n_src, G, C, M, Hl) : 1;
+  return dz_bytes(n_src, G, C, Hl, esz) + (parts > 1 ? 2 * part_bytes(parts, G, M, Hl) : 0);
 }
 
 static uint32_t magic_of(int k) { return k > 1 ? (uint32_t)((0x100000000ull + (uint64_t)k - 1) / (uint64_t)k) : 0u; }
@@ -1688,8 +1777,8 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
   MOE_REQUIRE(valid_tile(tile), MOE_EINVAL);
   MOE_REQUIRE_PTR(dY); MOE_REQUIRE_PTR(X); MOE_REQUIRE_PTR(Z); MOE_REQUIRE_PTR(A); MOE_REQUIRE_PTR(W1);
   MOE_REQUIRE_PTR(W2); MOE_REQUIRE_PTR(dX); MOE_REQUIRE_PTR(dW1); MOE_REQUIRE_PTR(dW2);
-  const size_t need = moe_ffn_workspace_bytes(dtype, n_src, G, C, M, H, n_esp);
-  MOE_REQUIRE(ws != nullptr && ws_bytes >= need, MOE_EWORKSPACE);
+  const size_t dz = dz_bytes(n_src, G, C, H / n_esp, dtype == MOE_BF16 ? 2 : 4);
+  MOE_REQUIRE(ws != nullptr && ws_bytes >= dz, MOE_EWORKSPACE);   // with less than the full size the reductions are not split
   MOE_REQUIRE(moe::aligned16(ws), MOE_EALIGN);
   MOE_REQUIRE((((uintptr_t)row_counts) & 3u) == 0, MOE_EALIGN);
   hipStream_t st = (hipStream_t)stream;
@@ -1731,20 +1820,44 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
   if (dtype == MOE_BF16) {
     // the three are independent: one launch, long row tiles first
     GemmArgs px = dx, p2 = w2, p1 = w1;
-    if (merged_backward(p2, p1, tile)) {
-      const TilePlan tx = prepare_bf16(px, false, tile, true);
-      const int nbx = grid_of(px), nb2 = grid_of(p2), nb1 = grid_of(p1);
+    const int merged = merged_backward(p2, p1, tile);
+    auto launch = [&](auto cfx, auto cfw, auto epi) {
+      using CFX = decltype(cfx);
+      using CFW = decltype(cfw);
+      constexpr int EPI = decltype(epi)::value;
+      px.tiles_m = (px.Mdim + CFX::TM - 1) / CFX::TM;
+      px.tiles_n = (px.Ndim + CFX::TN - 1) / CFX::TN;
+      px.total_tiles = px.G * px.tiles_m * px.tiles_n;
+      const int parts = EPI == EPI_PART ? p2.splits : 1;
+      const int nbx = grid_of(px), nb2 = (p2.total_tiles + 7) / 8 * 8 * parts, nb1 = (p1.total_tiles + 7) / 8 * 8 * parts;
       const dim3 grid((unsigned)(nbx + nb2 + nb1));
-      auto launch = [&](auto cfg) {
-        using CF = decltype(cfg);
-        if (gather) hipLaunchKernelGGL((ffn_bwd_trio<CF, ROWS_GATHER>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-        else if (packs_chunks(p2)) hipLaunchKernelGGL((ffn_bwd_trio<CF, ROWS_PACKED>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-        else hipLaunchKernelGGL((ffn_bwd_trio<CF, ROWS_PLAIN>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-      };
-      if (tx.tile_m == 256) launch(Tile256{});
-      else if (tx.tile_m == 192) launch(Tile192{});
-      else if (tx.tile_m == 128) launch(Tile128{});
-      else launch(Tile64x128{});
+      if (gather) hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, ROWS_GATHER>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
+      else if (packs_chunks(p2)) hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, ROWS_PACKED>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
+      else hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, ROWS_PLAIN>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
+    };
+    using Store = std::integral_constant<int, EPI_STORE>;
+    using Part = std::integral_constant<int, EPI_PART>;
+    if (merged == 256) {
+      const TilePlan tx = prepare_bf16(px, false, tile, true);
+      if (tx.tile_m == 256) launch(Tile256{}, Tile256{}, Store{});
+      else if (tx.tile_m == 192) launch(Tile192{}, Tile256{}, Store{});
+      else if (tx.tile_m == 128) launch(Tile128{}, Tile256{}, Store{});
+      else launch(Tile64x128{}, Tile256{}, Store{});
+      return moe::check_launch();
+    }
+    if (merged == 128) {
+      prepare_bf16(px, false, tile, true);   // buffer sizes
+      const int parts = weight_parts(n_src, G, C, M, Hl);
+      if (parts > 1 && ws_bytes >= moe_ffn_workspace_bytes(dtype, n_src, G, C, M, H, n_esp)) {
+        p2.splits = p1.splits = parts;
+        p2.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + dz);
+        p1.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + dz + part_bytes(parts, G, M, Hl));
+        launch(Tile64x128{}, Tile128{}, Part{});
+        const int64_t n = (int64_t)G * M * Hl / 4;   // H_l is a multiple of 8
+        hipLaunchKernelGGL(ffn_add_parts, dim3((unsigned)((2 * n + 255) / 256)), dim3(256), 0, st, p2, p1, n, 2 * n);
+      } else {
+        launch(Tile64x128{}, Tile128{}, Store{});
+      }
       return moe::check_launch();
     }
   }

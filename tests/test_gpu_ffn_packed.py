@@ -1,5 +1,5 @@
 """Expert FFN with row counts over many source chunks: k tiles of the weight gradients that are made of pieces of several
-chunks, and padding rows stored apart from the tiles (none, a few rows, most of the buffer)."""
+chunks, padding rows stored apart from the tiles (none, a few rows, most of the buffer), and reductions in parts."""
 import numpy as np
 import pytest
 import torch
@@ -7,6 +7,7 @@ import torch
 from oracle import moe_oracle as O
 from paper_2407_00599_amd import synth
 from test_gpu_ffn import gpu_ffn
+from test_gpu_ffn_gather import test_fused_dispatch_forward as fused_dispatch
 from util import DEV, TOL, ROWS, EXPERT, to_dev, to_host, assert_close, torch_dtype
 
 pytestmark = pytest.mark.gpu
@@ -20,6 +21,10 @@ pytestmark = pytest.mark.gpu
     (6, 2, 700, 264, 520, 0, 2, "bf16"),          # almost nothing but padding
     (6, 20, 100, 64, 64, 0, 40, "bf16"),          # more than 16 experts
     (6, 2, 700, 72, 136, 0, 40, "f32"),
+    (1, 2, 1700, 136, 264, 0, 1701, "bf16"),      # weight gradients in parts: a single chunk,
+    (3, 1, 2100, 264, 520, 0, 2101, "bf16"),      # whole chunks,
+    (30, 2, 300, 136, 264, 0, 301, "bf16"),       # packed chunks,
+    (30, 2, 300, 72, 136, 0, 4, "bf16"),          # and more parts than k tiles
 ])
 def test_packed_chunks(n_src, G, C, M, H, lo, hi, dtype):
     rng = np.random.default_rng(n_src * 1009 + C)
@@ -40,3 +45,9 @@ def test_packed_chunks(n_src, G, C, M, H, lo, hi, dtype):
         assert_close(to_host(t), ref, TOL[dtype], name, group)
     for t in got[:4]:
         assert np.all(to_host(t)[pad] == 0.0)
+
+
+@pytest.mark.parametrize("fill", [0.05, 0.9])
+def test_parts_through_a_slot_map(fill):
+    """Weight gradients in parts whose rows come through a slot map: the bits of dispatch + FFN."""
+    fused_dispatch(1800, 2, 2, 1700, 136, 264, 1, 0, "bf16", 0, fill, True)
