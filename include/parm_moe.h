@@ -168,8 +168,10 @@ int moe_dispatch_slots(const void* x, int dtype, int64_t S, int M, int E, int k,
  *   dW1 [G, M, H], dW2 [G, H, M]  FULL tensors; only the shard's columns / rows are written
  *                        (overwritten, dtype, fp32 accumulation over all n_src*C rows)
  * --------------------------------------------------------------------------------------- */
-/* Scratch the backward call needs (the gradient of the pre-activation, [n_src,G,C,H_l]); the
- * forward call needs none.  0 for invalid shapes. */
+/* Scratch the backward call uses: the gradient of the pre-activation, [n_src,G,C,H_l], which it needs,
+ * and behind it, in bf16 with few weight-gradient tiles over many rows, fp32 partial sums of the two weight
+ * gradients; with less than the full size these reductions are not cut into parts.  The forward call needs
+ * none.  0 for invalid shapes. */
 size_t moe_ffn_workspace_bytes(int dtype, int n_src, int G, int64_t C, int M, int H, int n_esp);
 
 /* Tile hint of the bf16 grouped GEMMs, an argument of every expert-FFN call.  It selects among

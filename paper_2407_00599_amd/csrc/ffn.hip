@@ -29,7 +29,6 @@
 #include <math.h>
 
 #include <algorithm>
-
 #include <type_traits>
 
 #include "common.h"
@@ -406,7 +405,7 @@ __device__ __forceinline__ int xcd_tile(int x, int i, int per_xcd) {
 // Fewer and larger shares between the tiles, to store beside the matrix work, measured slower: a compute unit stores no more
 // than some 20 GB/s while the others load the memory system, and the whole chip 4.5 to 5 TB/s.
 // 8 experts of 3500 occupied in 20480 rows x 2048 x 2048, 32 chunks: with a workgroup that walked the rows of every tile of
-// zeros 474 / 392 / 378 us (the forward GEMMs and dZ, which stores no zeros), now 484 / 306 / 236.
+// zeros 471 / 391 / 380 us (the forward GEMMs and dZ, which stores no zeros), now 427 / 296 / 238.
 // Returns 0: nothing to do, 1: a tile to multiply, 2: padding to fill (one chunk: tile g, tm, tn; several: share g of tm).
 constexpr int MORE_SHARES = 64;
 template <int TM, bool ZEROS>
@@ -613,7 +612,8 @@ struct KTile {
 // The reduction of a weight gradient runs over the expert's rows chunk by chunk, up to each chunk's row count; empty
 // chunks are passed over.  With few chunks a k tile never crosses a chunk, so that its grouping is the same with and without row
 // counts; with PACK_CHUNKS of them or more (half a k tile lost in each) the rows are packed: a k tile is made of
-// pieces of several chunks.
+// pieces of several chunks.  32 chunks of 110 rows on average, 8 experts x 2048 x 2048, merged backward launch: 991 -> 851 us,
+// a part of it from the padding; 4 chunks of 180 rows: 41.9 -> 39.1 us.
 constexpr int PACK_CHUNKS = 4;
 struct ChunkWalk {
   const GemmArgs& p;
@@ -970,7 +970,9 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
 
   // Refill set t (issued after the barrier of tile t): tile t+SB of B, then tile t+SA of A.  kb, ka: its tiles.
   constexpr int NREQ = RA + RB;
-  // The requests of a set are spread evenly over the MFMAs up to the next barrier: issued together they stall the waves.
+  // The requests of a set are spread evenly over the MFMAs up to the next barrier: issued together they stall the waves (all
+  // behind the barrier, 128 x 128 tiles over 860 k tiles: 604 -> 724 us; two at a time, the merged launch of 256 x 256
+  // tiles: 17.1 -> 18.1 ms).
   constexpr int SL_LAST = (MB - BR) * NB + 1, SL = SL_LAST + (SPT - 1) * MB * NB;   // slots: in the last step, in all
   constexpr auto slot_of = [](int r) constexpr { return r * SL / NREQ; };
   constexpr auto before = [](int slot) constexpr { int n = 0; for (int r = 0; r < NREQ; ++r) n += r * SL / NREQ < slot; return n; };
@@ -1554,9 +1556,12 @@ int merged_backward(GemmArgs& w2, GemmArgs& w1, int tile) {   // prepares the tw
   return t2.tile_m != t1.tile_m || (t2.tile_m != 256 && tile != MOE_TILE_AUTO) ? 0 : t2.tile_m;
 }
 // Parts of the reductions of the two weight gradients where both take 128 x 128 tiles: few tiles leave compute units idle, and
-// a reduction over thousands of rows is then what the launch waits for.  Parts of at least 12 k tiles, so that the
-// partial sums (written, read and added in a launch of their own) cost less than the k tiles they save, and no more workgroups
-// than the chip holds.  Depends on the shape only.
+// a reduction over thousands of rows is then what the launch waits for.  Parts of at least 12 k tiles (a k tile takes 0.6 us
+// there, writing, reading and adding the partial sums in a launch of their own 4 to 9 us), and no more workgroups than the
+// chip holds.  Depends on the shape only.  2 experts of 55 000 rows x 512 x 128, 16 tiles: 503 + 552 us in two launches, 66 for
+// dX -> 203 us for all three, 8.5 to add.  Few rows gain by the one launch: 8 experts of 274 rows x 128 x 1216, 88 tiles:
+// 8.0 + 10.2 + 8.1 -> 12.4 us.  One launch of 128 x 128 tiles measured no better from 64 tiles of 256 x 256 on
+// (72 to 256 of them: 0.93 to 1.33 times the time).
 int weight_parts(int n_src, int G, int64_t C, int M, int Hl) {
   const int64_t tiles256 = (int64_t)G * ((M + 255) / 256) * ((Hl + 255) / 256);
   if (tiles256 >= 64) return 1;
