@@ -375,9 +375,9 @@ __device__ __forceinline__ void unrolled(F&& f) {
 // of a merged launch start at multiples of 8).  Linear tile order: expert by expert, blocks of 16 row tiles, in a block
 // strips of 4 tile columns, in a strip row by row.  32 consecutive tiles (what an XCD's 32 CUs run at the same time) then
 // form an 8 x 4 patch, which shares 8 + 4 operand slices per k step in that XCD's L2 instead of 1 + 32, and the XCDs take
-// consecutive patches: the whole chip is in one 16 x 16 block, whose operands the last-level cache holds until the
-// block is done, so that memory delivers them about once.  (With a contiguous range of the order per XCD the eight XCDs were in
-// eight experts, and every strip fetched its rows from memory again: 8 experts of 16384 x 4096 x 7168, two forward GEMMs,
+// consecutive patches: the whole chip is in one 16 x 16 block, whose operands the last-level cache can hold until the
+// block is done (what misses L2 stays the same).  (With a contiguous range of the order per XCD the eight XCDs were in
+// eight experts, whose strips together do not fit that cache: 8 experts of 16384 x 4096 x 7168, two forward GEMMs,
 // dZ, merged backward: 6.57 / 6.11 / 6.25 / 18.39 -> 6.12 / 5.50 / 5.91 / 17.11 ms on one card.)
 // t = index within an expert of tm_n row tiles.
 __device__ __forceinline__ void patch_order(int t, int tm_n, int tiles_n, int& tm, int& tn) {
