@@ -61,6 +61,7 @@ struct GemmArgs {
   int64_t b_goff, c_goff;            // per-expert stride of weight-type operands, elements
   int64_t b_off, c_off;              // constant offset of the ESP slice, elements
   int tiles_m, tiles_n, total_tiles;
+  int run_mask;                      // tile order (xcd_tile): ~31, the XCDs take runs of 32 tiles in turn; 0, a contiguous range each
   uint64_t a_bytes, b_bytes;         // bf16 path: byte sizes of the A and B tensors (buffer descriptors)
   int splits;                        // EPI_PART: parts of the reduction; part q of every expert's matrix in
   float* part;                       // [splits, G, Mdim, Ndim]
@@ -379,21 +380,32 @@ __device__ __forceinline__ void unrolled(F&& f) {
 // block is done (what misses L2 stays the same).  (With a contiguous range of the order per XCD the eight XCDs were in
 // eight experts, whose strips together do not fit that cache: 8 experts of 16384 x 4096 x 7168, two forward GEMMs,
 // dZ, merged backward: 6.57 / 6.11 / 6.25 / 18.39 -> 6.12 / 5.50 / 5.91 / 17.11 ms on one card.)
+// Where an expert's rows fit in an XCD's L2 (tile_runs) a row-tiled GEMM keeps the contiguous ranges: an XCD then reads the
+// rows of few experts, and every strip but the first finds them in its L2.
 // t = index within an expert of tm_n row tiles.
 __device__ __forceinline__ void patch_order(int t, int tm_n, int tiles_n, int& tm, int& tn) {
   constexpr int SW = 4, RB = 16;
-  const int b = t / (RB * tiles_n), h = min(RB, tm_n - b * RB);   // row tiles of the block
-  t -= b * RB * tiles_n;
-  const int full = tiles_n / SW, strip = h * SW;
-  const int sn = min(t / strip, full), w = sn < full ? SW : tiles_n - full * SW;
-  const int r = t - sn * strip;
-  tm = r / w;
-  tn = sn * SW + (r - tm * w);
-  tm += b * RB;
+  int m0 = 0;                           // first row tile of the block
+  if (tm_n > RB) {                      // (a division that few rows do without)
+    m0 = t / (RB * tiles_n) * RB;
+    t -= m0 * tiles_n;
+    tm_n = min(RB, tm_n - m0);
+  }
+  const int full = tiles_n / SW, strip = tm_n * SW;
+  if (t < full * strip) {
+    const int sn = t / strip, r = t - sn * strip;
+    tm = r / SW;
+    tn = sn * SW + (r - tm * SW);
+  } else {
+    const int w = tiles_n - full * SW, r = t - full * strip;
+    tm = r / w;
+    tn = full * SW + (r - tm * w);
+  }
+  tm += m0;
 }
-// the i-th of n tiles (n = 8 per_xcd, rounded up) that XCD x takes: runs of 32 in turn
-__device__ __forceinline__ int xcd_tile(int x, int i, int per_xcd) {
-  const int full = per_xcd & ~31;
+// the i-th of n tiles (n = 8 per_xcd, rounded up) that XCD x takes: runs of 32 in turn, or one range
+__device__ __forceinline__ int xcd_tile(const GemmArgs& p, int x, int i, int per_xcd) {
+  const int full = per_xcd & p.run_mask;
   return i < full ? ((i & ~31) * 8 + x * 32) + (i & 31) : full * 8 + x * (per_xcd - full) + (i - full);
 }
 // With row counts the order holds the row tiles that have occupied rows only (compacted: an expert with n occupied rows
@@ -413,7 +425,7 @@ __device__ __forceinline__ int map_tile(const GemmArgs& p, int vb, bool counted,
   const int x = vb & 7, i = vb >> 3;
   if (!counted) {
     const int per_xcd = (p.total_tiles + 7) / 8;
-    const int tile = xcd_tile(x, i, per_xcd);
+    const int tile = xcd_tile(p, x, i, per_xcd);
     if (i >= per_xcd || tile >= p.total_tiles) return 0;
     const int tiles_per_g = p.tiles_m * p.tiles_n;
     g = tile / tiles_per_g;
@@ -435,7 +447,7 @@ __device__ __forceinline__ int map_tile(const GemmArgs& p, int vb, bool counted,
       what = g < nz ? 2 : 0;
       return -1;
     }
-    const int tile = xcd_tile(x, i, per_t);
+    const int tile = xcd_tile(p, x, i, per_t);
     if (tile >= T) return -1;
     what = 1;
     return tile;
@@ -1533,6 +1545,16 @@ TilePlan plan_tiles(int tile, bool tn, int G, int Mdim, int Ndim, int Kdim, bool
   return best;
 }
 
+// Tile order (GemmArgs::run_mask).  Row-tiled GEMMs: contiguous ranges while an expert's rows take no more than an XCD's 4 MB
+// of L2, runs in turn beyond it.  Forward, runs and ranges on one card: 8 experts, 1024 x 512 x 768 (1 and 1.5 MB) 28.7 and
+// 26.7 us; 16 experts, 64 x 2048 x 4096, 112 and 109; 1229 x 1024 x 4096 (2.5 and 10 MB, the first GEMM) 185 and 181; beyond
+// the line, 8 experts, 2048 x 4096 x 4096 (16 MB) 833 and 869, 8192 x 2048 x 2048 (32 MB) 921 and 944.
+// Weight gradients: runs, no clear winner otherwise (backward, few rows: 8 x 100 x 1024 x 4096 71.5 and 73.2,
+// 32 x 100 x 1024 x 1024 72.1 and 73.4, 16 x 64 x 2048 x 4096 272.8 and 267.2).
+int tile_runs(const GemmArgs& a, bool tn, int esz) {
+  return !tn && (int64_t)a.Mdim * a.Kdim * esz <= 4 << 20 ? 0 : ~31;
+}
+
 // fills the tile counts and buffer sizes of a bf16 problem
 TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile, bool wide = false) {
   const uint64_t act_rows = (uint64_t)a.n_src * a.G * a.Cc;
@@ -1546,6 +1568,7 @@ TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile, bool wide = false) {
   a.tiles_n = (a.Ndim + t.tile_n - 1) / t.tile_n;
   a.tiles_m = (a.Mdim + t.tile_m - 1) / t.tile_m;
   a.total_tiles = a.G * a.tiles_m * a.tiles_n;
+  a.run_mask = tile_runs(a, tn, 2);
   return t;
 }
 
@@ -1595,10 +1618,11 @@ int plan_f32_trio(const GemmArgs& dx, const GemmArgs& w2, const GemmArgs& w1) { 
   return plan_f32(tiles_f32(dx, false, 64, 64) + tiles_f32(w2, true, 64, 64) + tiles_f32(w1, true, 64, 64),
                   tiles_f32(dx, false, 32, 64) + tiles_f32(w2, true, 32, 64) + tiles_f32(w1, true, 32, 64));
 }
-void prepare_f32(GemmArgs& a, int tile_m, int tile_n) {
+void prepare_f32(GemmArgs& a, bool tn, int tile_m, int tile_n) {
   a.tiles_m = (a.Mdim + tile_m - 1) / tile_m;
   a.tiles_n = (a.Ndim + tile_n - 1) / tile_n;
   a.total_tiles = a.G * a.tiles_m * a.tiles_n;
+  a.run_mask = tile_runs(a, tn, 4);
 }
 
 template <int KIND, int EPI>
@@ -1607,7 +1631,7 @@ void launch_gemm(GemmArgs a, int dtype, int tile, hipStream_t st) {
     const int size = plan_f32(a, KIND == KIND_TN);
     auto launch = [&](auto tm_tag, auto tn_tag) {
       constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
-      prepare_f32(a, TM, TN);
+      prepare_f32(a, KIND == KIND_TN, TM, TN);
       hipLaunchKernelGGL((ffn_gemm_f32<KIND, EPI, TM, TN>), dim3((unsigned)grid_of(a)), dim3(256), 0, st, a);
     };
     if (size == 2) launch(I64{}, I64{});
@@ -1870,7 +1894,7 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
     const int size = plan_f32_trio(dx, w2, w1);
     auto launch = [&](auto tm_tag, auto tn_tag) {
       constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
-      prepare_f32(dx, TM, TN); prepare_f32(w2, TM, TN); prepare_f32(w1, TM, TN);
+      prepare_f32(dx, false, TM, TN); prepare_f32(w2, true, TM, TN); prepare_f32(w1, true, TM, TN);
       const int nbx = grid_of(dx), nb2 = grid_of(w2), nb1 = grid_of(w1);
       hipLaunchKernelGGL((ffn_bwd_trio_f32<TM, TN>), dim3((unsigned)(nbx + nb2 + nb1)), dim3(256), 0, st, dx, w2, w1, nbx, nb2);
     };

@@ -75,3 +75,32 @@ def test_fp32_ignores_the_tile_hint(tile):
     run = lambda t: gpu_ffn(X, dY, W1, W2, n_src, G, C, M, H, 0, 1, torch.float32, cnt, t)      # noqa: E731
     for a, b in zip(run(api.MOE_TILE_AUTO), run(tile)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n_src,G,C,M,H,dtype,tile,counted", [
+    (1, 2, 2200, 64, 2056, "bf16", api.MOE_TILE_SMALL, False),     # contiguous ranges: over 32 tiles per XCD, over 16 row tiles
+    (1, 2, 2200, 64, 2056, "bf16", api.MOE_TILE_AUTO, True),
+    (1, 2, 2200, 1032, 1032, "bf16", api.MOE_TILE_SMALL, False),   # rows beyond an XCD's L2: runs in turn, a rest behind them
+    (1, 2, 2200, 1032, 1032, "bf16", api.MOE_TILE_AUTO, True),
+    (3, 2, 730, 1032, 1032, "bf16", api.MOE_TILE_AUTO, True),
+    (1, 2, 700, 72, 520, "f32", api.MOE_TILE_AUTO, True),
+    (1, 2, 1500, 712, 264, "f32", api.MOE_TILE_AUTO, False),       # 4.3 MB of rows in fp32
+])
+def test_tile_orders(n_src, G, C, M, H, dtype, tile, counted):
+    """Every tile of a launch is computed once, in both orders in which the XCDs take them."""
+    rng = np.random.default_rng(C + M)
+    occ = rng.integers(C // 2, C + 1, size=(n_src, G)) if counted else np.full((n_src, G), C)
+    pad = np.arange(C)[None, None, :] >= occ[:, :, None]
+    Xn = rng.standard_normal((n_src, G, C, M)).astype(np.float32)
+    dYn = rng.standard_normal((n_src, G, C, M)).astype(np.float32)
+    Xn[pad] = 0; dYn[pad] = 0
+    X, dY = synth.store(Xn, dtype), synth.store(dYn, dtype)
+    W1 = synth.store((rng.standard_normal((G, M, H)) / np.sqrt(M)).astype(np.float32), dtype)
+    W2 = synth.store((rng.standard_normal((G, H, M)) / np.sqrt(H)).astype(np.float32), dtype)
+    cnt = torch.tensor(occ.astype(np.int32), device=DEV) if counted else None
+    got = gpu_ffn(*(to_dev(t) for t in (X, dY, W1, W2)), n_src, G, C, M, H, 0, 1, torch_dtype(dtype), cnt, tile)
+    rZ, rY = O.expert_ffn_fwd(X.val, W1.val, W2.val, 0, 1)
+    rdX, rdW1, rdW2 = O.expert_ffn_bwd(dY.val, X.val, W1.val, W2.val, 0, 1)
+    for name, t, ref, group in (("Z", got[0], rZ, ROWS), ("A", got[1], O.gelu(rZ), ROWS), ("Y", got[2], rY, ROWS),
+                                ("dX", got[3], rdX, ROWS), ("dW1", got[4], rdW1, EXPERT), ("dW2", got[5], rdW2, EXPERT)):
+        assert_close(to_host(t), ref, TOL[dtype], name, group)
