@@ -280,7 +280,7 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, typename AccBl
 // bf16 MFMA tile with an LDS-DMA pipeline.
 //
 // TM x TN output tile, k tile 64, WM x WN waves over the tile times WK waves over the MFMA steps of a k tile (two
-// of 32 k; WK = 2: four of 16 k, two per group, whose sums are added through LDS at the end).  Global memory goes straight to LDS
+// of 32 k or four of 16 k; WK = 2: two of the four per group, whose sums are added through LDS at the end).  Global memory goes straight to LDS
 // (buffer_load ... lds, 16 bytes per lane, no VGPR staging, no ds_write) into two rings of whole k tiles, SA
 // tiles of the A operand and SB of the B operand.  A k tile is 64 wide so that every request of a k-contiguous
 // operand covers whole 128-byte lines.  A wave instruction fills 1 KiB of consecutive 16-byte slots in lane
@@ -313,7 +313,7 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, typename AccBl
 // pays only with the reads spread between the MFMAs: reads behind every fourth MFMA, 65 % of the cycles busy and no
 // gain; spread, 69 %: the three launches of the GEMMs above and the merged backward launch 6.74 / 6.27 / 6.45 / 18.99 ->
 // 6.57 / 6.11 / 6.25 / 18.39 ms.  The tiles with two wave groups over k keep 32x32x16, which gives each group two steps
-// per k tile.  Tried without gain: rows of the last step in front of the barrier 2 -> 3 or 4 (to 4 % slower at 12 k tiles),
+// per k tile, and so do weight gradients with few k tiles (Tile256Brief), which are not under the power limit.  Tried without gain: rows of the last step in front of the barrier 2 -> 3 or 4 (to 4 % slower at 12 k tiles),
 // s_setprio for half of the waves, a second barrier that frees B's slot in the first step (-1 to +3 % in single launches).
 // ------------------------------------------------------------------------------------------
 #define LDS_AS __attribute__((address_space(3)))
@@ -322,18 +322,18 @@ constexpr int DK = 64;   // k tile
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 constexpr int lgkmcnt_imm(int n) { return 0xC07F | (n << 8); }   // LDS operations of a wave end in order
 
-template <int TM_, int TN_, int WM_, int WN_, int WK_, int SA_, int SB_>
+template <int TM_, int TN_, int WM_, int WN_, int WK_, int SA_, int SB_, int MR_ = WK_ == 1 ? 16 : 32>
 struct TileCfg {
   static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, WK = WK_, SA = SA_, SB = SB_;
   static constexpr int NW = WM * WN * WK;             // waves
-  static constexpr int MR = WK == 1 ? 16 : 32;        // MFMA: MR x MR x KS
+  static constexpr int MR = MR_;                      // MFMA: MR x MR x KS
   static constexpr int KS = 512 / MR;
   static constexpr int MB = TM / WM / MR, NB = TN / WN / MR;   // MFMA blocks per wave
   static constexpr int RA = TM / 8 / NW, RB = TN / 8 / NW;     // requests (1 KiB) per wave and k tile
   static constexpr int SPT = DK / KS / WK;            // MFMA steps per wave and k tile
   static constexpr int A_UNIT = TM * DK * 2, B_UNIT = TN * DK * 2;
   static constexpr int LDS = SA * A_UNIT + SB * B_UNIT;
-  static_assert(SPT == 2, "two steps: one register set of B fragments each");
+  static_assert(SPT % 2 == 0, "the steps take turns with the two register sets of B fragments");
   static_assert(TM / 8 % NW == 0 && TN / 8 % NW == 0, "requests are dealt evenly");
   static_assert(SA == SB || SA == SB + 1, "ring depths");
 };
@@ -682,7 +682,7 @@ struct ChunkWalk {
 };
 
 // The fragment reads of a tile's k loop.  A row's A fragment is replaced by the next step's once the row has been
-// multiplied, the B fragments, which every row uses, have a register set per step.  The next step's reads are taken in
+// multiplied, the B fragments, which every row uses, have two register sets.  The next step's reads are taken in
 // the order B0 A0 B1 A1 ... and spread between the MFMAs (place: behind which MFMA of the step), so that
 // they do not queue up in front of the multiplications.  A row waits for its own fragments by count: the LDS reads of a
 // wave return in order.
@@ -700,7 +700,7 @@ struct Reads {
   }
   static constexpr bool in_place() {                 // no A fragment is replaced before its row has been multiplied
     for (int op = 0; op < N; ++op)
-      if (!is_b(op) && (place(0, op) < of(op) * NB + NB - 1 || place(1, op) < of(op) * NB + NB - 1)) return false;
+      if (!is_b(op) && (place(0, op) < of(op) * NB + NB - 1 || place(CF::SPT - 1, op) < of(op) * NB + NB - 1)) return false;
     return true;
   }
   static_assert(in_place(), "the order of the reads");
@@ -948,7 +948,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
       }
     }
   }
-  // a row's A fragment is replaced by the next step's once the row has been multiplied; B has a register set per step
+  // a row's A fragment is replaced by the next step's once the row has been multiplied; B has two register sets
   Frag fa[MB], fb[2][NB];
   using RD = Reads<KIND, CF>;
   constexpr int BR = RD::BR;
@@ -956,8 +956,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     constexpr int ST = decltype(st_tag)::value, OP = decltype(op_tag)::value, I = RD::of(OP);
     if constexpr (RD::is_b(OP)) {
       const uint32_t so = (uint32_t)slot_b * CF::B_UNIT;
-      if constexpr (!B_NC) lds_read_kc<I * MR * 128>(fb[ST][I], (b_fr[0] + so) ^ (2u * KS * ST));
-      else lds_read_nc<ST * KS * 2 * TN, 8 * TN>(fb[ST][I], b_fr[B_NC ? I : 0] + so);
+      if constexpr (!B_NC) lds_read_kc<I * MR * 128>(fb[ST & 1][I], (b_fr[0] + so) ^ (2u * KS * ST));
+      else lds_read_nc<ST * KS * 2 * TN, 8 * TN>(fb[ST & 1][I], b_fr[B_NC ? I : 0] + so);
     } else {
       const uint32_t so = (uint32_t)slot_a * CF::A_UNIT;
       if constexpr (!A_NC) lds_read_kc<I * MR * 128>(fa[I], (a_fr[0] + so) ^ (2u * KS * ST));
@@ -1082,7 +1082,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
 #pragma unroll
     for (int i = 0; i < MB; ++i) fa[i].q &= ma;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) fb[ST][j].q &= mb;
+    for (int j = 0; j < NB; ++j) fb[ST & 1][j].q &= mb;
   };
   // one k tile; LAST: one of the last SA tiles, whose refills may be past the end
   auto k_tile = [&](int t, auto last_tag) {
@@ -1092,15 +1092,15 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
     const uint64_t mask_b = GATHER ? mask_of(KTile{0, k_lim[0]}, ~0ull) : mask;
     unrolled<0, SPT>([&](auto st) {
       constexpr int ST = decltype(st)::value;
-      using NEXT = std::integral_constant<int, 1 - ST>;
+      using NEXT = std::integral_constant<int, (ST + 1) % SPT>;
       // row 0 needs its own A fragment and all B fragments; a step with missing k rows waits for everything and masks it
       __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(RD::newer(ST, 0)));
 #pragma unroll
-      for (int j = 0; j < NB; ++j) ready(fb[ST][j]);
+      for (int j = 0; j < NB; ++j) ready(fb[ST & 1][j]);
       ready(fa[0]);
       if constexpr (KIND == KIND_TN || LAST) {
         if (__builtin_expect(mask != ~0ull, 0)) {   // (its code stays out of the k loop's way)
-          frags_ready(ST);
+          frags_ready(ST & 1);
           mask_frags(mask, mask_b, st);
         }
       }
@@ -1114,7 +1114,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
         unrolled<0, NB>([&](auto j) {
           constexpr int J = decltype(j)::value, AT = I * NB + J;
           __builtin_amdgcn_sched_barrier(0);
-          mfma(ST, I, J);
+          mfma(ST & 1, I, J);
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (ST == SPT - 1 && AT == BR * NB - 1) {
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(LAST ? 0 : IN_FLIGHT) & 0xF0FF);   // this wave's requests for tile t+1 have landed; so have its reads of tile t
@@ -1227,6 +1227,12 @@ __global__ __launch_bounds__(64 * CF::NW) void ffn_gemm_dma(const GemmArgs p) {
 }
 
 using Tile256 = TileCfg<256, 256, 2, 4, 1, 3, 2>;
+// Weight gradients over at most 16 k tiles of rows.  There the launch is bound by what a tile does outside its k loop and by the
+// writes, and the shorter steps of 32x32x16 start and drain faster.  Backward call, 16x16x32 and this, in turn: 16 experts
+// of 64 / 256 / 512 x 2048 x 4096 267 / 430 / 582 and 264 / 421 / 578 us; 4 of 4 x 256 x 768 x 3072 93.6 and 91.6; 2 of
+// 512 x 1024 x 3584 49.5 and 48.7; beyond, 25 k tiles, 8 of 1600 x 1024 x 4096 414 and 418.
+constexpr int BRIEF_ROWS = 16 * DK;
+using Tile256Brief = TileCfg<256, 256, 2, 4, 1, 3, 2, 32>;
 using Tile192 = TileCfg<192, 256, 2, 4, 1, 3, 2>;
 using Tile128 = TileCfg<128, 128, 2, 2, 2, 3, 2>;
 using Tile64x128 = TileCfg<64, 128, 1, 4, 2, 3, 3>;
@@ -1868,10 +1874,14 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
     using Part = std::integral_constant<int, EPI_PART>;
     if (merged == 256) {
       const TilePlan tx = prepare_bf16(px, false, tile, true);
-      if (tx.tile_m == 256) launch(Tile256{}, Tile256{}, Store{});
-      else if (tx.tile_m == 192) launch(Tile192{}, Tile256{}, Store{});
-      else if (tx.tile_m == 128) launch(Tile128{}, Tile256{}, Store{});
-      else launch(Tile64x128{}, Tile256{}, Store{});
+      auto with_dx = [&](auto cfw) {
+        if (tx.tile_m == 256) launch(Tile256{}, cfw, Store{});
+        else if (tx.tile_m == 192) launch(Tile192{}, cfw, Store{});
+        else if (tx.tile_m == 128) launch(Tile128{}, cfw, Store{});
+        else launch(Tile64x128{}, cfw, Store{});
+      };
+      if (a.R <= BRIEF_ROWS) with_dx(Tile256Brief{});
+      else with_dx(Tile256{});
       return moe::check_launch();
     }
     if (merged == 128) {

@@ -77,6 +77,25 @@ def test_fp32_ignores_the_tile_hint(tile):
         assert torch.equal(a, b)
 
 
+def check_ffn(rng, n_src, G, C, M, H, dtype, tile, occ):
+    """Forward and backward against the CPU checker; occ [n_src, G] = row counts that are passed, None = none are."""
+    Xn = rng.standard_normal((n_src, G, C, M)).astype(np.float32)
+    dYn = rng.standard_normal((n_src, G, C, M)).astype(np.float32)
+    if occ is not None:
+        pad = np.arange(C)[None, None, :] >= occ[:, :, None]
+        Xn[pad] = 0; dYn[pad] = 0
+    X, dY = synth.store(Xn, dtype), synth.store(dYn, dtype)
+    W1 = synth.store((rng.standard_normal((G, M, H)) / np.sqrt(M)).astype(np.float32), dtype)
+    W2 = synth.store((rng.standard_normal((G, H, M)) / np.sqrt(H)).astype(np.float32), dtype)
+    cnt = None if occ is None else torch.tensor(occ.astype(np.int32), device=DEV)
+    got = gpu_ffn(*(to_dev(t) for t in (X, dY, W1, W2)), n_src, G, C, M, H, 0, 1, torch_dtype(dtype), cnt, tile)
+    rZ, rY = O.expert_ffn_fwd(X.val, W1.val, W2.val, 0, 1)
+    rdX, rdW1, rdW2 = O.expert_ffn_bwd(dY.val, X.val, W1.val, W2.val, 0, 1)
+    for name, t, ref, group in (("Z", got[0], rZ, ROWS), ("A", got[1], O.gelu(rZ), ROWS), ("Y", got[2], rY, ROWS),
+                                ("dX", got[3], rdX, ROWS), ("dW1", got[4], rdW1, EXPERT), ("dW2", got[5], rdW2, EXPERT)):
+        assert_close(to_host(t), ref, TOL[dtype], name, group)
+
+
 @pytest.mark.parametrize("n_src,G,C,M,H,dtype,tile,counted", [
     (1, 2, 2200, 64, 2056, "bf16", api.MOE_TILE_SMALL, False),     # contiguous ranges: over 32 tiles per XCD, over 16 row tiles
     (1, 2, 2200, 64, 2056, "bf16", api.MOE_TILE_AUTO, True),
@@ -89,18 +108,18 @@ def test_fp32_ignores_the_tile_hint(tile):
 def test_tile_orders(n_src, G, C, M, H, dtype, tile, counted):
     """Every tile of a launch is computed once, in both orders in which the XCDs take them."""
     rng = np.random.default_rng(C + M)
-    occ = rng.integers(C // 2, C + 1, size=(n_src, G)) if counted else np.full((n_src, G), C)
-    pad = np.arange(C)[None, None, :] >= occ[:, :, None]
-    Xn = rng.standard_normal((n_src, G, C, M)).astype(np.float32)
-    dYn = rng.standard_normal((n_src, G, C, M)).astype(np.float32)
-    Xn[pad] = 0; dYn[pad] = 0
-    X, dY = synth.store(Xn, dtype), synth.store(dYn, dtype)
-    W1 = synth.store((rng.standard_normal((G, M, H)) / np.sqrt(M)).astype(np.float32), dtype)
-    W2 = synth.store((rng.standard_normal((G, H, M)) / np.sqrt(H)).astype(np.float32), dtype)
-    cnt = torch.tensor(occ.astype(np.int32), device=DEV) if counted else None
-    got = gpu_ffn(*(to_dev(t) for t in (X, dY, W1, W2)), n_src, G, C, M, H, 0, 1, torch_dtype(dtype), cnt, tile)
-    rZ, rY = O.expert_ffn_fwd(X.val, W1.val, W2.val, 0, 1)
-    rdX, rdW1, rdW2 = O.expert_ffn_bwd(dY.val, X.val, W1.val, W2.val, 0, 1)
-    for name, t, ref, group in (("Z", got[0], rZ, ROWS), ("A", got[1], O.gelu(rZ), ROWS), ("Y", got[2], rY, ROWS),
-                                ("dX", got[3], rdX, ROWS), ("dW1", got[4], rdW1, EXPERT), ("dW2", got[5], rdW2, EXPERT)):
-        assert_close(to_host(t), ref, TOL[dtype], name, group)
+    occ = rng.integers(C // 2, C + 1, size=(n_src, G)) if counted else None
+    check_ffn(rng, n_src, G, C, M, H, dtype, tile, occ)
+
+
+@pytest.mark.parametrize("n_src,C,rows", [
+    (1, 1024, None), (1, 1025, None), (1, 1024, (700, 1026)), (1, 1025, (700, 1026)),     # one chunk
+    (2, 512, (0, 513)), (2, 513, (0, 513)), (8, 128, None), (5, 205, None),               # a k tile of one chunk each
+    (8, 128, (0, 129)), (5, 206, (0, 206)), (32, 32, (0, 33)), (41, 26, (0, 26)),         # of pieces of several chunks
+])
+@pytest.mark.parametrize("tile", [api.MOE_TILE_256, api.MOE_TILE_192])
+def test_weight_gradients_of_few_k_tiles(n_src, C, rows, tile):
+    """256 x 256 weight-gradient tiles on both sides of the row count that decides their MFMA."""
+    rng = np.random.default_rng(C + n_src)
+    occ = rng.integers(rows[0], rows[1], size=(n_src, 2)) if rows else None
+    check_ffn(rng, n_src, 2, C, 264, 520, "bf16", tile, occ)
