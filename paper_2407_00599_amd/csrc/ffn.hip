@@ -1371,7 +1371,19 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int
     }
   }
   float4 ra[UA], rb[UB];
+  // A full chunk has a path of its own: what a partial one looks at otherwise stands in front of every load, and how the compiler
+  // forms those addresses decided the length of a chunk (one expert, 224 x 192 x 10984, backward: 645 us, and 662 after a
+  // change elsewhere in the kernel; with this path 644, forward 249 -> 227; 8 experts of 256 x 512 x 2048 175 -> 162, 293 -> 286).
   auto fetch = [&](const KTile& kt) {
+    if (kt.lim >= FK && (KIND != KIND_TN || p.gather == nullptr)) {
+#pragma unroll
+      for (int u = 0; u < UA; ++u)
+        ra[u] = *reinterpret_cast<const float4*>(A_NC ? pa[u] + (int64_t)(kt.row0 + a_k[u]) * p.lda : pa[u] + kt.row0);
+#pragma unroll
+      for (int u = 0; u < UB; ++u)
+        rb[u] = *reinterpret_cast<const float4*>(B_NC ? pb[u] + (int64_t)(kt.row0 + b_k[u]) * p.ldb : pb[u] + kt.row0);
+      return;
+    }
     const bool part = kt.lim < FK;
 #pragma unroll
     for (int u = 0; u < UA; ++u) {
