@@ -1573,16 +1573,17 @@ int tile_runs(const GemmArgs& a, bool tn, int esz) {
   return !tn && (int64_t)a.Mdim * a.Kdim * esz <= 4 << 20 ? 0 : ~31;
 }
 
+// Rows that a problem is priced for.  Rows of capacity padding are not multiplied; how many there are is not known here.  Where
+// counts are passed it is nine rows in ten (capacity factors are 1 to 1.25), so that a last row tile that will mostly be
+// padding does not decide the height.
+int priced_rows(const GemmArgs& a, bool tn) { return !tn && a.cnt ? (int)(((int64_t)a.Mdim * 9 + 9) / 10) : a.Mdim; }
+
 // fills the tile counts and buffer sizes of a bf16 problem
 TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile, bool wide = false) {
   const uint64_t act_rows = (uint64_t)a.n_src * a.G * a.Cc;
   a.a_bytes = (a.gather ? (uint64_t)a.gather_rows : act_rows) * (uint64_t)a.lda * 2;
   a.b_bytes = tn ? act_rows * (uint64_t)a.ldb * 2 : (uint64_t)a.G * (uint64_t)a.b_goff * 2;
-  // Rows of capacity padding are not multiplied; how many there are is not known here.  Where counts are passed the
-  // plan is priced for nine rows in ten (capacity factors are 1 to 1.25), so that a last row tile that will mostly be
-  // padding does not decide the height.
-  const int rows = !tn && a.cnt ? (int)(((int64_t)a.Mdim * 9 + 9) / 10) : a.Mdim;
-  const TilePlan t = plan_tiles(tile, tn, a.G, rows, a.Ndim, a.Kdim, wide);
+  const TilePlan t = plan_tiles(tile, tn, a.G, priced_rows(a, tn), a.Ndim, a.Kdim, wide);
   a.tiles_n = (a.Ndim + t.tile_n - 1) / t.tile_n;
   a.tiles_m = (a.Mdim + t.tile_m - 1) / t.tile_m;
   a.total_tiles = a.G * a.tiles_m * a.tiles_n;
@@ -1595,6 +1596,15 @@ TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile, bool wide = false) {
 int merged_backward(GemmArgs& w2, GemmArgs& w1, int tile) {   // prepares the two
   const TilePlan t2 = prepare_bf16(w2, true, tile), t1 = prepare_bf16(w1, true, tile);
   return t2.tile_m != t1.tile_m || (t2.tile_m != 256 && tile != MOE_TILE_AUTO) ? 0 : t2.tile_m;
+}
+// dX beside weight gradients of 128 x 128 tiles takes 64 x 128 ones, two workgroups to a compute unit as theirs.  That pays while
+// they are one round of the chip; beyond it dX goes out alone, in the tiles of its own plan.  Backward call, merged and alone:
+// 8 experts of 274 x 128 x 1216 (40 tiles) 22.0 and 26.0 us, 1 of 512 x 2048 x 1792 (128) 35.2 and 40.1, 8 of 1024 x 512 x 768
+// (480) 51.0 and 52.3; 7 of 1024 x 768 x 768 (630) 63.7 and 61.0, 30 of 1000 x 512 x 256 (1800) 71.2 and 58.9, 7 of
+// 4096 x 768 x 768 (2436) 176.7 and 147.2, 1 of 32768 x 2048 x 1792 (8192) 1093 and 945.
+bool dx_alone(const GemmArgs& dx) {
+  const int64_t tiles = (int64_t)dx.G * ((priced_rows(dx, false) + 63) / 64) * ((dx.Ndim + 127) / 128);
+  return tiles > 2 * (int64_t)num_cus();
 }
 // Parts of the reductions of the two weight gradients where both take 128 x 128 tiles: few tiles leave compute units idle, and
 // a reduction over thousands of rows is then what the launch waits for.  Parts of at least 12 k tiles (a k tile takes 0.6 us
@@ -1623,7 +1633,7 @@ int grid_of(const GemmArgs& a) {
 using I32 = std::integral_constant<int, 32>;
 using I64 = std::integral_constant<int, 64>;
 int64_t tiles_f32(const GemmArgs& a, bool tn, int tile_m, int tile_n) {
-  const int64_t rows = tn || a.cnt == nullptr ? a.Mdim : ((int64_t)a.Mdim * 9 + 9) / 10;   // as in prepare_bf16
+  const int64_t rows = priced_rows(a, tn);
   return (int64_t)a.G * ((rows + tile_m - 1) / tile_m) * ((a.Ndim + tile_n - 1) / tile_n);
 }
 int plan_f32(int64_t tiles_64x64, int64_t tiles_32x64) {   // 2: 64 x 64, 1: 32 x 64, 0: 32 x 32
@@ -1739,7 +1749,7 @@ extern "C" double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C,
     GemmArgs w2 = gemm(Hl, M, a.R), w1 = gemm(M, Hl, a.R), dx = to_m;
     auto dx_tile = [&]() {
       const int merged = merged_backward(w2, w1, tile);
-      return merged == 128 ? Tile64x128::TM : prepare_bf16(dx, false, tile, merged == 256).tile_m;
+      return merged == 128 && !dx_alone(dx) ? Tile64x128::TM : prepare_bf16(dx, false, tile, merged == 256).tile_m;
     };
     const int dx_m = dtype == MOE_F32 ? f32_tile_m(plan_f32_trio(dx, w2, w1)) : dx_tile();
     rows = rows_multiplied(a, alone(to_h)) + rows_multiplied(a, dx_m) + 2.0 * rows_multiplied(a, 0);
@@ -1868,6 +1878,7 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
     // the three are independent: one launch, long row tiles first
     GemmArgs px = dx, p2 = w2, p1 = w1;
     const int merged = merged_backward(p2, p1, tile);
+    const bool alone = merged == 128 && dx_alone(px);
     auto launch = [&](auto cfx, auto cfw, auto epi) {
       using CFX = decltype(cfx);
       using CFW = decltype(cfw);
@@ -1876,7 +1887,7 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
       px.tiles_n = (px.Ndim + CFX::TN - 1) / CFX::TN;
       px.total_tiles = px.G * px.tiles_m * px.tiles_n;
       const int parts = EPI == EPI_PART ? p2.splits : 1;
-      const int nbx = grid_of(px), nb2 = (p2.total_tiles + 7) / 8 * 8 * parts, nb1 = (p1.total_tiles + 7) / 8 * 8 * parts;
+      const int nbx = alone ? 0 : grid_of(px), nb2 = (p2.total_tiles + 7) / 8 * 8 * parts, nb1 = (p1.total_tiles + 7) / 8 * 8 * parts;
       const dim3 grid((unsigned)(nbx + nb2 + nb1));
       if (gather) hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, ROWS_GATHER>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
       else if (packs_chunks(p2)) hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, ROWS_PACKED>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
@@ -1909,6 +1920,7 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
       } else {
         launch(Tile64x128{}, Tile128{}, Store{});
       }
+      if (alone) launch_gemm<KIND_NT, EPI_STORE>(dx, dtype, tile, st);
       return moe::check_launch();
     }
   }

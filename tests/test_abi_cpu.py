@@ -184,6 +184,18 @@ def test_executed_flops_accounting(L):
     # dX in the merged backward launch, which has no tiles of 64 columns, takes 64 rows; alone, as A W2 does, it would take 32
     assert f(api.MOE_BF16, n_src, G, 64, M, H, 1, one) == 2.0 * G * (64 + 32) * M * H
     assert f(api.MOE_BF16, n_src, G, 64, M, H, 1, one, True) == 2.0 * G * (64 + 64 + 2) * M * H
+    # beside weight gradients of 128 x 128 tiles dX takes 64-row tiles up to one round of the chip, and beyond it those of its
+    # own plan: the ones of A W2, a GEMM of the same sizes
+    for G_, C_, M_, H_, alone in ((7, 4096, 768, 768, True), (63, 2048, 256, 256, True), (1, 8192, 2048, 1792, True),
+                                  (8, 274, 128, 1216, False), (1, 512, 2048, 1792, False)):
+        for n_src_ in (1, 2):
+            cnt = np.ones((n_src_, G_), np.int32)
+            fwd, bwd = (f(api.MOE_BF16, n_src_, G_, C_ // n_src_, M_, H_, 1, cnt, b) for b in (False, True))
+            to_h, weights = 2.0 * G_ * M_ * H_, 2 * (2.0 * G_ * n_src_ * M_ * H_)      # per row; dW1 and dW2
+            rows_h = bwd / to_h - weights / to_h                                       # rows of dA's tiles and of dX's
+            assert (rows_h == fwd / to_h) if alone else rows_h - 64 in (32, 64, 128, 192, 256), (G_, C_, M_, H_)
+            if alone:
+                assert fwd / to_h != 2 * 64       # (a shape that tells the two apart)
     # 192-row tiles in the row-tiled GEMMs only; the small kernel never skips; an unknown hint is an invalid call
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, one, tile=api.MOE_TILE_192) == 2 * (2.0 * G * 192 * M * H)
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, one, tile=api.MOE_TILE_SMALL) == 2 * full

@@ -123,3 +123,16 @@ def test_weight_gradients_of_few_k_tiles(n_src, C, rows, tile):
     rng = np.random.default_rng(C + n_src)
     occ = rng.integers(rows[0], rows[1], size=(n_src, 2)) if rows else None
     check_ffn(rng, n_src, 2, C, 264, 520, "bf16", tile, occ)
+
+
+@pytest.mark.parametrize("n_src,G,C,M,H,counted", [
+    (1, 20, 1700, 72, 72, False),      # reductions in parts
+    (1, 20, 1700, 72, 72, True),
+    (6, 20, 300, 72, 136, True),       # packed chunks
+    (1, 63, 600, 136, 72, True),       # whole reductions
+])
+def test_dx_beside_small_weight_gradients_and_alone(n_src, G, C, M, H, counted):
+    """Weight gradients of 128 x 128 tiles whose dX has more than one round of tiles: a launch of its own."""
+    rng = np.random.default_rng(C + G)
+    occ = rng.integers(C // 2, C + 1, size=(n_src, G)) if counted else None
+    check_ffn(rng, n_src, G, C, M, H, "bf16", api.MOE_TILE_AUTO, occ)
