@@ -380,8 +380,8 @@ __device__ __forceinline__ void unrolled(F&& f) {
 // block is done (what misses L2 stays the same).  (With a contiguous range of the order per XCD the eight XCDs were in
 // eight experts, whose strips together do not fit that cache: 8 experts of 16384 x 4096 x 7168, two forward GEMMs,
 // dZ, merged backward: 6.57 / 6.11 / 6.25 / 18.39 -> 6.12 / 5.50 / 5.91 / 17.11 ms on one card.)
-// Where an expert's rows fit in an XCD's L2 (tile_runs) a row-tiled GEMM keeps the contiguous ranges: an XCD then reads the
-// rows of few experts, and every strip but the first finds them in its L2.
+// Where an expert's operands fit in an XCD's L2 (tile_runs) a row-tiled GEMM keeps the contiguous ranges: an XCD then reads
+// those of few experts, and every strip but the first finds them in its L2.
 // t = index within an expert of tm_n row tiles.
 __device__ __forceinline__ void patch_order(int t, int tm_n, int tiles_n, int& tm, int& tn) {
   constexpr int SW = 4, RB = 16;
@@ -1563,14 +1563,15 @@ TilePlan plan_tiles(int tile, bool tn, int G, int Mdim, int Ndim, int Kdim, bool
   return best;
 }
 
-// Tile order (GemmArgs::run_mask).  Row-tiled GEMMs: contiguous ranges while an expert's rows take no more than an XCD's 4 MB
-// of L2, runs in turn beyond it.  Forward, runs and ranges on one card: 8 experts, 1024 x 512 x 768 (1 and 1.5 MB) 28.7 and
-// 26.7 us; 16 experts, 64 x 2048 x 4096, 112 and 109; 1229 x 1024 x 4096 (2.5 and 10 MB, the first GEMM) 185 and 181; beyond
-// the line, 8 experts, 2048 x 4096 x 4096 (16 MB) 833 and 869, 8192 x 2048 x 2048 (32 MB) 921 and 944.
+// Tile order (GemmArgs::run_mask).  Row-tiled GEMMs: contiguous ranges while both operands of an expert fit in an XCD's 4 MB of
+// L2, which then fetches them once; runs in turn beyond it.  Forward pair, runs and ranges on one card: 8 experts of
+// 1024 x 512 x 768 (2 MB) 32.7 and 32.2 us, without counts 28.7 and 26.7; 8 of 1500 x 256 x 1024 35.2 and 33.5; 12 of
+// 276 x 520 x 1544, without counts, 40.9 and 39.2; beyond the line 12 of 618 x 256 x 13656 (7 MB) 285 and 289, 8 of
+// 96 x 4096 x 14336 (113 MB) 394 and 403, 8 of 2048 x 4096 x 4096 833 and 869 (but 16 of 64 x 2048 x 4096 113 and 111).
 // Weight gradients: runs, no clear winner otherwise (backward, few rows: 8 x 100 x 1024 x 4096 71.5 and 73.2,
 // 32 x 100 x 1024 x 1024 72.1 and 73.4, 16 x 64 x 2048 x 4096 272.8 and 267.2).
 int tile_runs(const GemmArgs& a, bool tn, int esz) {
-  return !tn && (int64_t)a.Mdim * a.Kdim * esz <= 4 << 20 ? 0 : ~31;
+  return !tn && ((int64_t)a.Mdim + a.Ndim) * a.Kdim * esz <= 4 << 20 ? 0 : ~31;
 }
 
 // Rows that a problem is priced for.  Rows of capacity padding are not multiplied; how many there are is not known here.  Where

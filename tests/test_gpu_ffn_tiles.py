@@ -99,11 +99,11 @@ def check_ffn(rng, n_src, G, C, M, H, dtype, tile, occ):
 @pytest.mark.parametrize("n_src,G,C,M,H,dtype,tile,counted", [
     (1, 2, 2200, 64, 2056, "bf16", api.MOE_TILE_SMALL, False),     # contiguous ranges: over 32 tiles per XCD, over 16 row tiles
     (1, 2, 2200, 64, 2056, "bf16", api.MOE_TILE_AUTO, True),
-    (1, 2, 2200, 1032, 1032, "bf16", api.MOE_TILE_SMALL, False),   # rows beyond an XCD's L2: runs in turn, a rest behind them
+    (1, 2, 2200, 1032, 1032, "bf16", api.MOE_TILE_SMALL, False),   # operands beyond an XCD's L2: runs in turn, a rest behind them
     (1, 2, 2200, 1032, 1032, "bf16", api.MOE_TILE_AUTO, True),
     (3, 2, 730, 1032, 1032, "bf16", api.MOE_TILE_AUTO, True),
     (1, 2, 700, 72, 520, "f32", api.MOE_TILE_AUTO, True),
-    (1, 2, 1500, 712, 264, "f32", api.MOE_TILE_AUTO, False),       # 4.3 MB of rows in fp32
+    (1, 2, 1500, 712, 264, "f32", api.MOE_TILE_AUTO, False),       # 5 MB of operands in fp32
 ])
 def test_tile_orders(n_src, G, C, M, H, dtype, tile, counted):
     """Every tile of a launch is computed once, in both orders in which the XCDs take them."""
