@@ -1227,11 +1227,11 @@ __global__ __launch_bounds__(64 * CF::NW) void ffn_gemm_dma(const GemmArgs p) {
 }
 
 using Tile256 = TileCfg<256, 256, 2, 4, 1, 3, 2>;
-// Weight gradients over at most 16 k tiles of rows.  There the launch is bound by what a tile does outside its k loop and by the
-// writes, and the shorter steps of 32x32x16 start and drain faster.  Backward call, 16x16x32 and this, in turn: 16 experts
-// of 64 / 256 / 512 x 2048 x 4096 267 / 430 / 582 and 264 / 421 / 578 us; 4 of 4 x 256 x 768 x 3072 93.6 and 91.6; 2 of
-// 512 x 1024 x 3584 49.5 and 48.7; beyond, 25 k tiles, 8 of 1600 x 1024 x 4096 414 and 418.
-constexpr int BRIEF_ROWS = 16 * DK;
+// Weight gradients over at most 8 k tiles of rows, k tiles of one chunk.  There the launch is bound by what a tile does outside its
+// k loop and by the writes, and the shorter steps of 32x32x16 start and drain faster.  Backward call, 16x16x32 and this, in
+// turn: 16 experts of 64 / 256 / 512 x 2048 x 4096 267 / 430 / 582 and 264 / 421 / 578 us; 24 of 200 x 1024 x 2048 133.2 and 131.1;
+// 2 of 512 x 1024 x 3584 49.5 and 48.7; beyond, 16 of 900 x 1024 x 1024 130.7 and 132.4, 4 of 700 x 2048 x 4096 191.9 and 194.5.
+constexpr int BRIEF_ROWS = 8 * DK;
 using Tile256Brief = TileCfg<256, 256, 2, 4, 1, 3, 2, 32>;
 using Tile192 = TileCfg<192, 256, 2, 4, 1, 3, 2>;
 using Tile128 = TileCfg<128, 128, 2, 2, 2, 3, 2>;
@@ -1889,10 +1889,15 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
       px.total_tiles = px.G * px.tiles_m * px.tiles_n;
       const int parts = EPI == EPI_PART ? p2.splits : 1;
       const int nbx = alone ? 0 : grid_of(px), nb2 = (p2.total_tiles + 7) / 8 * 8 * parts, nb1 = (p1.total_tiles + 7) / 8 * 8 * parts;
-      const dim3 grid((unsigned)(nbx + nb2 + nb1));
-      if (gather) hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, ROWS_GATHER>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-      else if (packs_chunks(p2)) hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, ROWS_PACKED>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
-      else hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, ROWS_PLAIN>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
+      auto go = [&](auto rows) {
+        hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, decltype(rows)::value>), dim3((unsigned)(nbx + nb2 + nb1)), dim3(512), 0, st,
+                           px, p2, p1, nbx, nb2);
+      };
+      if (gather) return go(std::integral_constant<int, ROWS_GATHER>{});
+      if constexpr (!std::is_same<CFW, Tile256Brief>::value) {
+        if (packs_chunks(p2)) return go(std::integral_constant<int, ROWS_PACKED>{});
+      }
+      go(std::integral_constant<int, ROWS_PLAIN>{});
     };
     using Store = std::integral_constant<int, EPI_STORE>;
     using Part = std::integral_constant<int, EPI_PART>;
@@ -1904,7 +1909,7 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
         else if (tx.tile_m == 128) launch(Tile128{}, cfw, Store{});
         else launch(Tile64x128{}, cfw, Store{});
       };
-      if (a.R <= BRIEF_ROWS) with_dx(Tile256Brief{});
+      if (a.R <= BRIEF_ROWS && !packs_chunks(p2)) with_dx(Tile256Brief{});
       else with_dx(Tile256{});
       return moe::check_launch();
     }

@@ -42,9 +42,9 @@ CASES = [
     (500, 3, 20, 40, 512, 2048, 1, 0, "bf16", 0, 1.0),                   # 64x128, more than 16 experts
     (900, 2, 24, 70, 520, 1032, 1, 0, "bf16", 0, 0.6),
     (200, 2, 80, 6, 64, 64, 1, 0, "bf16", 0, 1.0),                       # more than 64 experts
-    # 256 x 256 weight gradients of at most 1024 rows, and of more
-    (1100, 2, 2, 1024, 264, 520, 1, 0, "bf16", api.MOE_TILE_256, 0.9),
-    (1100, 2, 2, 1025, 264, 520, 1, 0, "bf16", api.MOE_TILE_256, 0.9),
+    # 256 x 256 weight gradients of at most 512 rows, and of more
+    (600, 2, 2, 512, 264, 520, 1, 0, "bf16", api.MOE_TILE_256, 0.9),
+    (600, 2, 2, 513, 264, 520, 1, 0, "bf16", api.MOE_TILE_256, 0.9),
     (300, 3, 20, 40, 72, 136, 1, 0, "f32", 0, 0.7),
 ]
 

@@ -113,9 +113,9 @@ def test_tile_orders(n_src, G, C, M, H, dtype, tile, counted):
 
 
 @pytest.mark.parametrize("n_src,C,rows", [
-    (1, 1024, None), (1, 1025, None), (1, 1024, (700, 1026)), (1, 1025, (700, 1026)),     # one chunk
-    (2, 512, (0, 513)), (2, 513, (0, 513)), (8, 128, None), (5, 205, None),               # a k tile of one chunk each
-    (8, 128, (0, 129)), (5, 206, (0, 206)), (32, 32, (0, 33)), (41, 26, (0, 26)),         # of pieces of several chunks
+    (1, 512, None), (1, 513, None), (1, 512, (300, 514)), (1, 513, (300, 514)),           # one chunk
+    (2, 256, (0, 257)), (2, 257, (0, 257)), (8, 64, None), (5, 103, None),                # a k tile of one chunk each
+    (8, 64, (0, 65)), (5, 103, (0, 103)), (16, 32, (0, 33)), (41, 13, (0, 13)), (90, 21, (0, 22)),   # of pieces of several chunks
 ])
 @pytest.mark.parametrize("tile", [api.MOE_TILE_256, api.MOE_TILE_192])
 def test_weight_gradients_of_few_k_tiles(n_src, C, rows, tile):
