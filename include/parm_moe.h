@@ -161,7 +161,10 @@ int moe_dispatch_slots(const void* x, int dtype, int64_t S, int M, int E, int k,
  *                        are local).  Results are the same as without it -- FFN(0) = 0 and zero rows
  *                        add nothing to the weight gradients -- but padding rows are not multiplied
  *                        beyond the last row tile of an expert (their outputs are stored as zeros),
- *                        and the weight-gradient reductions stop at each chunk's count.
+ *                        and the weight-gradient reductions stop at each chunk's count.  From four
+ *                        chunks on (n_src >= 4) the bf16 weight gradients take the occupied rows of
+ *                        all chunks together: their fp32 sums are then grouped differently than
+ *                        without counts, and an element can be rounded to a neighbouring value.
  *
  * Backward (chain rule of the above), given dY [n_src,G,C,M] and the saved Z and A:
  *   dX  [n_src, G, C, M]  out
@@ -170,7 +173,8 @@ int moe_dispatch_slots(const void* x, int dtype, int64_t S, int M, int E, int k,
  * --------------------------------------------------------------------------------------- */
 /* Scratch the backward call uses: the gradient of the pre-activation, [n_src,G,C,H_l], which it needs,
  * and behind it, in bf16 with few weight-gradient tiles over many rows, fp32 partial sums of the two weight
- * gradients; with less than the full size these reductions are not cut into parts.  The forward call needs
+ * gradients; with less than the full size these reductions are not cut into parts, so that their fp32 sums are
+ * grouped differently and an element can be rounded to a neighbouring value.  The forward call needs
  * none.  0 for invalid shapes. */
 size_t moe_ffn_workspace_bytes(int dtype, int n_src, int G, int64_t C, int M, int H, int n_esp);
 

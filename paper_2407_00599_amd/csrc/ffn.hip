@@ -627,21 +627,33 @@ struct KTile {
 // pieces of several chunks.  32 chunks of 110 rows on average, 8 experts x 2048 x 2048, merged backward launch: 991 -> 851 us,
 // a part of it from the padding; 4 chunks of 180 rows: 41.9 -> 39.1 us.
 constexpr int PACK_CHUNKS = 4;
+// Of a reduction cut into parts, whole k tiles of one chunk are dealt to the parts in turn, by their index in the capacity: the
+// parts are equally long whatever the counts, and the sums are grouped the same with and without them (PARTS).  Packed k
+// tiles, which only exist with counts, are cut into consecutive runs (skip).
+template <bool PARTS = false>
 struct ChunkWalk {
   const GemmArgs& p;
-  int g, cnt = 0, s0 = 0, row = 0, left = 0;   // cnt: rows of chunk s0 + lane
+  int g, part, cnt = 0, s0 = 0, row = 0, left = 0;   // cnt: rows of chunk s0 + lane
   unsigned long long mask = 0;
-  __device__ __forceinline__ ChunkWalk(const GemmArgs& p_, int g_) : p(p_), g(g_) {}
+  __device__ __forceinline__ ChunkWalk(const GemmArgs& p_, int g_, int part_ = 0) : p(p_), g(g_), part(part_) {}
   __device__ __forceinline__ void load() {     // counts of chunks s0 .. s0 + 63, one per lane
     const int s = s0 + (threadIdx.x & 63);
     cnt = s < p.n_src ? (p.cnt != nullptr ? clamp_count(p.cnt[s * p.G + g], p.Cc) : p.Cc) : 0;
     mask = __ballot(cnt > 0);
+  }
+  __device__ __forceinline__ int first_tile(int s, int step) const {   // of this part in chunk s
+    const int at = (part - s * ((p.Cc + step - 1) / step)) % p.splits;
+    return at < 0 ? at + p.splits : at;
   }
   __device__ __forceinline__ int start(int step, bool packed) {   // returns the number of k tiles
     int nk = 0;
     for (s0 = 0; s0 < p.n_src; s0 += 64) {
       load();
       int n = packed ? cnt : (cnt + step - 1) / step;
+      if (PARTS) {
+        const int at = first_tile(s0 + (threadIdx.x & 63), step);
+        n = n > at ? (n - at - 1) / p.splits + 1 : 0;
+      }
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
       nk += __builtin_amdgcn_readfirstlane(n);
@@ -650,33 +662,31 @@ struct ChunkWalk {
     if (p.n_src > 64) load();
     return packed ? (nk + step - 1) / step : nk;
   }
-  __device__ __forceinline__ void skip(int tiles, int step, bool packed) {   // passes over the first k tiles
-    int n = packed ? tiles * step : tiles;   // rows, or k tiles
+  __device__ __forceinline__ void skip(int n) {   // passes over the first n rows
     while (n > 0) {
       if (mask == 0) { if (s0 + 64 >= p.n_src) return; s0 += 64; load(); continue; }
       const int l = __ffsll((long long)mask) - 1, c = __builtin_amdgcn_readlane(cnt, l);
-      const int has = packed ? c : (c + step - 1) / step;
       mask &= mask - 1;
-      if (has > n) {
-        const int rows = packed ? n : n * step;
-        left = c - rows;
-        row = ((s0 + l) * p.G + g) * p.Cc + rows;
+      if (c > n) {
+        left = c - n;
+        row = ((s0 + l) * p.G + g) * p.Cc + n;
       }
-      n -= has;
+      n -= c;
     }
   }
   __device__ __forceinline__ KTile next(int step) {   // the next rows of one chunk, at most `step`; past the end: no rows
-    if (left <= 0) {
+    while (left <= 0) {
       while (mask == 0 && s0 + 64 < p.n_src) { s0 += 64; load(); }
       if (mask == 0) return KTile{0, 0};
-      const int l = __ffsll((long long)mask) - 1;
+      const int l = __ffsll((long long)mask) - 1, at = PARTS ? first_tile(s0 + l, step) * step : 0;
       mask &= mask - 1;
-      left = __builtin_amdgcn_readlane(cnt, l);
-      row = ((s0 + l) * p.G + g) * p.Cc;
+      left = __builtin_amdgcn_readlane(cnt, l) - at;
+      row = ((s0 + l) * p.G + g) * p.Cc + at;
     }
     const KTile t{row, min(left, step)};
-    row += step;
-    left -= step;
+    const int on = PARTS ? step * p.splits : step;
+    row += on;
+    left -= on;
     return t;
   }
 };
@@ -805,12 +815,12 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   char* e_lds = smem + wave * (CF::LDS / CF::NW / 64 * 64);
 
   // ---- k tiles: Kdim / 64 of a row-tiled GEMM, the walk over the expert's chunks for a weight gradient ----
-  ChunkWalk walk(p, g);
+  ChunkWalk<EPI == EPI_PART && !PIECES> walk(p, g, part);
   int nk = KIND == KIND_TN ? walk.start(DK, PIECES) : (p.Kdim + DK - 1) / DK;
-  int k_left = nk;               // k tiles that the walk has not been asked for
-  if (EPI == EPI_PART) {         // this part's
+  int k_left = nk;               // packed parts: k tiles that the walk has not been asked for
+  if (EPI == EPI_PART && PIECES) {
     const int t0 = (int)((int64_t)nk * part / p.splits), t1 = (int)((int64_t)nk * (part + 1) / p.splits);
-    walk.skip(t0, DK, PIECES);
+    walk.skip(t0 * DK);
     k_left = nk = t1 - t0;
   }
 
@@ -881,7 +891,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   static_assert(!PIECES || SA == SB + 1, "B's requests are a k tile behind A's");
   auto next_ktile = [&]() -> KTile {
     KTile t{0, 0};                                   // past the end: no rows
-    if (EPI != EPI_PART || k_left-- > 0) t = walk.next(DK);
+    if (EPI != EPI_PART || !PIECES || k_left-- > 0) t = walk.next(DK);
     if constexpr (PIECES) {
 #pragma unroll
       for (int j = 0; j < RB; ++j) { kb_off[j] = kb_new[j]; kb_new[j] = (uint32_t)t.row0 * ldb2 + b_ko[j]; }
@@ -1338,7 +1348,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int
     o_row = here ? row[UA] : -1;
     o_zero = !occ[UA];
   }
-  ChunkWalk walk(p, g);
+  ChunkWalk<> walk(p, g);
   const int nk = KIND == KIND_TN ? walk.start(FK, false) : (p.Kdim + FK - 1) / FK;
 
   auto swz = [](int k, int T) constexpr { return ((k >> 2) & (T / 8 - 1)) * 8; };   // see the layout above
@@ -1608,9 +1618,9 @@ bool dx_alone(const GemmArgs& dx) {
   return tiles > 2 * (int64_t)num_cus();
 }
 // Parts of the reductions of the two weight gradients where both take 128 x 128 tiles: few tiles leave compute units idle, and
-// a reduction over thousands of rows is then what the launch waits for.  Parts of at least 12 k tiles (a k tile takes 0.6 us
-// there, writing, reading and adding the partial sums in a launch of their own 4 to 9 us), and no more workgroups than the
-// chip holds.  Depends on the shape only.  2 experts of 55 000 rows x 512 x 128, 16 tiles: 503 + 552 us in two launches, 66 for
+// a reduction over thousands of rows is then what the launch waits for.  Parts of at least 12 k tiles of the capacity (a k tile
+// takes 0.6 us there, writing, reading and adding the partial sums in a launch of their own 4 to 9 us), and no more workgroups
+// than the chip holds.  2 experts of 55 000 rows x 512 x 128, 16 tiles: 503 + 552 us in two launches, 66 for
 // dX -> 203 us for all three, 8.5 to add.  Few rows gain by the one launch: 8 experts of 274 rows x 128 x 1216, 88 tiles:
 // 8.0 + 10.2 + 8.1 -> 12.4 us.  One launch of 128 x 128 tiles measured no better from 64 tiles of 256 x 256 on
 // (72 to 256 of them: 0.93 to 1.33 times the time).

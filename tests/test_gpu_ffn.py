@@ -90,6 +90,11 @@ def test_ffn_fwd_bwd_elementwise(n_src, G, C, M, H, n_esp, esp_idx, dtype, tile)
     (1, 2, 600, 264, 520, [[193, 384]], T192),          # 192-row tiles, counts at tile edges
     (3, 2, 300, 256, 512, [[0, 300], [40, 0], [299, 1]], 0),   # several source chunks
     (2, 1, 150, 128, 256, [[10, ], [149, ]], SMALL),    # small problem: the register-staged kernel ignores the counts
+    # weight gradients whose reductions are cut into parts: one chunk, half and all of it occupied; a chunk almost empty; several
+    (1, 2, 1700, 136, 264, [[850, 1700]], 0),
+    (1, 1, 3300, 72, 136, [[1001]], 0),
+    (2, 2, 1100, 136, 264, [[1100, 3], [65, 0]], 0),
+    (3, 1, 1100, 264, 520, [[0], [1100], [300]], 0),
 ])
 def test_row_counts_change_nothing(n_src, G, C, M, H, occ, tile):
     """Telling the FFN which rows are capacity padding must not change any result (only the time)."""
