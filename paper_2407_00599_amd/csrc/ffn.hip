@@ -1620,15 +1620,16 @@ bool dx_alone(const GemmArgs& dx) {
 // Parts of the reductions of the two weight gradients where both take 128 x 128 tiles: few tiles leave compute units idle, and
 // a reduction over thousands of rows is then what the launch waits for.  Parts of at least 12 k tiles of the capacity (a k tile
 // takes 0.6 us there, writing, reading and adding the partial sums in a launch of their own 4 to 9 us), and no more workgroups
-// than the chip holds.  2 experts of 55 000 rows x 512 x 128, 16 tiles: 503 + 552 us in two launches, 66 for
+// than the chip holds.  A part of the workspace's size, so it is arithmetic on the shape and asks no device.  2 experts of 55 000 rows x 512 x 128, 16 tiles: 503 + 552 us in two launches, 66 for
 // dX -> 203 us for all three, 8.5 to add.  Few rows gain by the one launch: 8 experts of 274 rows x 128 x 1216, 88 tiles:
 // 8.0 + 10.2 + 8.1 -> 12.4 us.  One launch of 128 x 128 tiles measured no better from 64 tiles of 256 x 256 on
 // (72 to 256 of them: 0.93 to 1.33 times the time).
+constexpr int CHIP_CUS = 256;   // compute units of an MI355X
 int weight_parts(int n_src, int G, int64_t C, int M, int Hl) {
   const int64_t tiles256 = (int64_t)G * ((M + 255) / 256) * ((Hl + 255) / 256);
   if (tiles256 >= 64) return 1;
   const int64_t tiles = 2 * (int64_t)G * ((M + 127) / 128) * ((Hl + 127) / 128), nk = ((int64_t)n_src * C + 63) / 64;
-  const int64_t parts = std::min<int64_t>({2 * (int64_t)num_cus() / tiles, nk / 12, 64});
+  const int64_t parts = std::min<int64_t>({2 * CHIP_CUS / tiles, nk / 12, 64});
   return parts < 2 ? 1 : (int)parts;
 }
 

@@ -3,6 +3,8 @@ header declares, and rejects bad arguments on the host before anything is launch
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -200,6 +202,36 @@ def test_executed_flops_accounting(L):
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, one, tile=api.MOE_TILE_192) == 2 * (2.0 * G * 192 * M * H)
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, one, tile=api.MOE_TILE_SMALL) == 2 * full
     assert f(api.MOE_BF16, n_src, G, C, M, H, 1, one, tile=7) == 0.0
+
+
+def test_size_queries_ask_no_device(L, tmp_path):
+    """A program may ask for sizes before it forks or picks a device: the queries are arithmetic.  Stand-ins for the runtime's
+    queries, loaded in front of it by a process of its own, count what they are asked."""
+    src, so = tmp_path / "count.c", tmp_path / "count.so"
+    src.write_text("int calls; int hipGetDevice(int* d) { ++calls; *d = 0; return 0; }\n"
+                   "int hipDeviceGetAttribute(int* v, int a, int d) { ++calls; *v = 256; return 0; }\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(so), str(src)], check=True)
+    prog = """
+import ctypes, sys
+count = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+L = ctypes.CDLL(sys.argv[2])
+i, q, f = ctypes.c_int, ctypes.c_int64, ctypes.c_double
+for name in ("moe_ffn_workspace_bytes", "moe_gate_workspace_bytes", "moe_gate_bwd_workspace_bytes"):
+    getattr(L, name).restype = ctypes.c_size_t
+sizes = [L.moe_ffn_workspace_bytes(i(dt), i(n), i(2), q(2100), i(256), i(512), i(1)) for dt in (0, 1) for n in (1, 5)]
+sizes += [L.moe_gate_workspace_bytes(q(4096), i(8), i(2)), L.moe_gate_bwd_workspace_bytes(q(4096), i(256), i(8))]
+assert all(sizes), sizes
+asked = ctypes.c_int.in_dll(count, "calls").value
+L.moe_ffn_executed_flops.restype = f
+L.moe_ffn_executed_flops(i(1), i(1), i(2), q(2100), i(256), i(512), i(1), None, i(0), i(0))
+print(asked, ctypes.c_int.in_dll(count, "calls").value)
+"""
+    from paper_2407_00599_amd import build
+    r = subprocess.run([sys.executable, "-c", prog, str(so), build.LIB], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    asked, after = map(int, r.stdout.split())
+    assert after > 0          # the stand-ins are in front: planning a launch does ask
+    assert asked == 0
 
 
 def test_gate_bwd_argument_checks(L):
