@@ -1602,11 +1602,12 @@ TilePlan prepare_bf16(GemmArgs& a, bool tn, int tile, bool wide = false) {
   return t;
 }
 
-// The three backward GEMMs that only depend on dZ go out in one launch if both weight gradients take 256 x 256 tiles,
-// or both 128 x 128 tiles without the caller asking for them; returns which (0: launches of their own).
+// The three backward GEMMs that only depend on dZ go out in one launch unless the caller asks for MOE_TILE_SMALL; returns the
+// tile of the two weight gradients (H_l x M and M x H_l: as many tiles each), or 0: launches of their own.
 int merged_backward(GemmArgs& w2, GemmArgs& w1, int tile) {   // prepares the two
-  const TilePlan t2 = prepare_bf16(w2, true, tile), t1 = prepare_bf16(w1, true, tile);
-  return t2.tile_m != t1.tile_m || (t2.tile_m != 256 && tile != MOE_TILE_AUTO) ? 0 : t2.tile_m;
+  prepare_bf16(w1, true, tile);
+  const TilePlan t = prepare_bf16(w2, true, tile);
+  return tile == MOE_TILE_SMALL ? 0 : t.tile_m;
 }
 // dX beside weight gradients of 128 x 128 tiles takes 64 x 128 ones, two workgroups to a compute unit as theirs.  That pays while
 // they are one round of the chip; beyond it dX goes out alone, in the tiles of its own plan.  Backward call, merged and alone:
@@ -1653,7 +1654,7 @@ int plan_f32(int64_t tiles_64x64, int64_t tiles_32x64) {   // 2: 64 x 64, 1: 32 
   return tiles_64x64 >= enough ? 2 : tiles_32x64 >= enough ? 1 : 0;
 }
 int f32_tile_m(int size) { return size == 2 ? 64 : 32; }
-int plan_f32(const GemmArgs& a, bool tn) { return plan_f32(tiles_f32(a, tn, 64, 64), tiles_f32(a, tn, 32, 64)); }
+int plan_f32(const GemmArgs& a) { return plan_f32(tiles_f32(a, false, 64, 64), tiles_f32(a, false, 32, 64)); }   // of a row-tiled GEMM
 int plan_f32_trio(const GemmArgs& dx, const GemmArgs& w2, const GemmArgs& w1) {   // of the merged backward launch
   return plan_f32(tiles_f32(dx, false, 64, 64) + tiles_f32(w2, true, 64, 64) + tiles_f32(w1, true, 64, 64),
                   tiles_f32(dx, false, 32, 64) + tiles_f32(w2, true, 32, 64) + tiles_f32(w1, true, 32, 64));
@@ -1665,40 +1666,41 @@ void prepare_f32(GemmArgs& a, bool tn, int tile_m, int tile_n) {
   a.run_mask = tile_runs(a, tn, 4);
 }
 
-template <int KIND, int EPI>
+template <int KIND, int EPI>   // row-tiled GEMMs
 void launch_gemm(GemmArgs a, int dtype, int tile, hipStream_t st) {
-  if (dtype == MOE_F32) {
-    const int size = plan_f32(a, KIND == KIND_TN);
-    auto launch = [&](auto tm_tag, auto tn_tag) {
-      constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
-      prepare_f32(a, KIND == KIND_TN, TM, TN);
-      hipLaunchKernelGGL((ffn_gemm_f32<KIND, EPI, TM, TN>), dim3((unsigned)grid_of(a)), dim3(256), 0, st, a);
-    };
-    if (size == 2) launch(I64{}, I64{});
-    else if (size == 1) launch(I32{}, I64{});
-    else launch(I32{}, I32{});
-    return;
+  static_assert(KIND != KIND_TN, "weight gradients go out in the merged launches, or through launch_weight_small");
+  if constexpr (KIND == KIND_NN || EPI == EPI_DGELU) {   // (the fp32 dX is always in the merged launch)
+    if (dtype == MOE_F32) {
+      const int size = plan_f32(a);
+      auto launch = [&](auto tm_tag, auto tn_tag) {
+        constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
+        prepare_f32(a, false, TM, TN);
+        hipLaunchKernelGGL((ffn_gemm_f32<KIND, EPI, TM, TN>), dim3((unsigned)grid_of(a)), dim3(256), 0, st, a);
+      };
+      if (size == 2) launch(I64{}, I64{});
+      else if (size == 1) launch(I32{}, I64{});
+      else launch(I32{}, I32{});
+      return;
+    }
   }
-  const TilePlan t = prepare_bf16(a, KIND == KIND_TN, tile);
-  const dim3 grid((unsigned)grid_of(a));
+  const TilePlan t = prepare_bf16(a, false, tile);
   auto launch = [&](auto cfg) {
     using CF = decltype(cfg);
-    if constexpr (KIND == KIND_TN) {
-      if (a.gather != nullptr) hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF, ROWS_GATHER>), grid, dim3(64 * CF::NW), 0, st, a);
-      else if (packs_chunks(a)) hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF, ROWS_PACKED>), grid, dim3(64 * CF::NW), 0, st, a);
-      else hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF>), grid, dim3(64 * CF::NW), 0, st, a);
-    } else {
-      hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF>), grid, dim3(64 * CF::NW), 0, st, a);
-    }
+    hipLaunchKernelGGL((ffn_gemm_dma<KIND, EPI, CF>), dim3((unsigned)grid_of(a)), dim3(64 * CF::NW), 0, st, a);
   };
-  if (t.tile_m == 128) return launch(Tile128{});
-  if (t.tile_m == 256) return launch(Tile256{});
-  if constexpr (KIND != KIND_TN) {
-    if (t.tile_m == 192) launch(Tile192{});
-    else if (t.tile_m == 64 && t.tile_n == 128) launch(Tile64x128{});
-    else if (t.tile_m == 64) launch(Tile64{});
-    else launch(Tile32x64{});
-  }
+  if (t.tile_m == 256) launch(Tile256{});
+  else if (t.tile_m == 192) launch(Tile192{});
+  else if (t.tile_m == 128) launch(Tile128{});
+  else if (t.tile_m == 64 && t.tile_n == 128) launch(Tile64x128{});
+  else if (t.tile_m == 64) launch(Tile64{});
+  else launch(Tile32x64{});
+}
+// a bf16 weight gradient by the hint MOE_TILE_SMALL, which ignores row counts
+void launch_weight_small(GemmArgs a, hipStream_t st) {
+  prepare_bf16(a, true, MOE_TILE_SMALL);
+  const dim3 grid((unsigned)grid_of(a)), block(64 * Tile128::NW);
+  if (a.gather != nullptr) hipLaunchKernelGGL((ffn_gemm_dma<KIND_TN, EPI_STORE, Tile128, ROWS_GATHER>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((ffn_gemm_dma<KIND_TN, EPI_STORE, Tile128>), grid, block, 0, st, a);
 }
 
 inline bool valid_tile(int tile) { return tile >= MOE_TILE_AUTO && tile <= MOE_TILE_192; }
@@ -1752,7 +1754,7 @@ extern "C" double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C,
     p.Mdim = Mdim; p.Ndim = Ndim; p.Kdim = Kdim;
     return p;
   };
-  auto alone = [&](GemmArgs p) { return dtype == MOE_F32 ? f32_tile_m(plan_f32(p, false)) : prepare_bf16(p, false, tile).tile_m; };
+  auto alone = [&](GemmArgs p) { return dtype == MOE_F32 ? f32_tile_m(plan_f32(p)) : prepare_bf16(p, false, tile).tile_m; };
   const GemmArgs to_h = gemm(a.R, Hl, M), to_m = gemm(a.R, M, Hl);
   double rows;
   if (!backward) {   // Z = X W1 (rows x Hl), Y = A W2 (rows x M)
@@ -1954,8 +1956,8 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
     else launch(I32{}, I32{});
     return moe::check_launch();
   }
-  launch_gemm<KIND_TN, EPI_STORE>(w2, dtype, tile, st);
-  launch_gemm<KIND_TN, EPI_STORE>(w1, dtype, tile, st);
+  launch_weight_small(w2, st);
+  launch_weight_small(w1, st);
   launch_gemm<KIND_NT, EPI_STORE>(dx, dtype, tile, st);
   return moe::check_launch();
 }
