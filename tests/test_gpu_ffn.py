@@ -14,14 +14,18 @@ from util import DEV, TOL, ROWS, EXPERT, to_dev, to_host, rel_err, assert_close,
 pytestmark = pytest.mark.gpu
 
 
-def gpu_ffn(X, dY, W1, W2, n_src, G, C, M, H, esp_idx, n_esp, tdt, row_counts=None, tile=0):
+def gpu_ffn(X, dY, W1, W2, n_src, G, C, M, H, esp_idx, n_esp, tdt, row_counts=None, tile=0, ws_bytes=None):
+    """Every output but the full-size weight gradients (3.0) starts as NaN, and so does the scratch memory: a row that no
+    workgroup stores, or a read of one that nobody writes, shows."""
     Hl = H // n_esp
     dt = api.MOE_BF16 if tdt == torch.bfloat16 else api.MOE_F32
-    Z = torch.empty(n_src, G, C, Hl, dtype=tdt, device=DEV); Y = torch.empty(n_src, G, C, M, dtype=tdt, device=DEV)
-    dX = torch.empty_like(Y)
-    dW1 = torch.full((G, M, H), 3.0, dtype=tdt, device=DEV); dW2 = torch.full((G, H, M), 3.0, dtype=tdt, device=DEV)
-    A = torch.empty_like(Z)
-    ws = torch.empty(api.moe_ffn_workspace_bytes(dt, n_src, G, C, M, H, n_esp), dtype=torch.uint8, device=DEV)
+    new = lambda *s, v=float("nan"): torch.full(s, v, dtype=tdt, device=DEV)      # noqa: E731
+    Z, A = new(n_src, G, C, Hl), new(n_src, G, C, Hl)
+    Y, dX = new(n_src, G, C, M), new(n_src, G, C, M)
+    dW1, dW2 = new(G, M, H, v=3.0), new(G, H, M, v=3.0)
+    if ws_bytes is None:
+        ws_bytes = api.moe_ffn_workspace_bytes(dt, n_src, G, C, M, H, n_esp)
+    ws = torch.full((ws_bytes,), 0xFF, dtype=torch.uint8, device=DEV)
     api.moe_expert_ffn_fwd(X, W1, W2, n_src, G, C, M, H, esp_idx, n_esp, Z, A, Y, row_counts, tile)
     api.moe_expert_ffn_bwd(dY, X, Z, A, W1, W2, n_src, G, C, M, H, esp_idx, n_esp, dX, dW1, dW2, ws, row_counts, tile)
     torch.cuda.synchronize()

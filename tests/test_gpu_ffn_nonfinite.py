@@ -78,3 +78,50 @@ def test_infinity_in_the_first_row_of_a_partial_k_tile(n_src, gather, dtype, til
     expect(dx, dX, (a, 1), "dX"), expect(dw1, dW1, (1, a, 5), "dW1"), expect(dw2, dW2, NOTHING, "dW2")
     dx, dw1, dw2 = bwd(Z, A, dY, with_inf(W1, 1, 9, HCOL), W2)    # dX = dZ W1^T
     expect(dx, dX, (a, 1, a, 9), "dX"), expect(dw1, dW1, NOTHING, "dW1"), expect(dw2, dW2, NOTHING, "dW2")
+
+
+@pytest.mark.parametrize("n_src,C,occ,tile", [
+    (5, 40, [[40, 7], [0, 40], [33, 40], [40, 3], [20, 38]], api.MOE_TILE_AUTO),      # pieces of several chunks: 133 and 128 rows
+    (5, 40, [[40, 7], [0, 40], [33, 40], [40, 3], [20, 38]], api.MOE_TILE_256),
+    (2, 600, [[500, 600], [599, 3]], api.MOE_TILE_256),                               # a k tile of one chunk
+    (30, 120, [[(7 * s) % 121, 120 - 3 * s] for s in range(30)], api.MOE_TILE_AUTO),  # packed, in parts
+    (1, 1700, [[1601, 1700]], api.MOE_TILE_AUTO),                                     # one chunk, in parts
+    (2, 1000, [[1000, 999], [70, 0]], api.MOE_TILE_AUTO),
+])
+def test_infinity_in_the_first_row_of_a_partial_k_tile_with_row_counts(n_src, C, occ, tile):
+    """As above for the weight gradients with row counts: the rows that the last k tile of an expert (packed) or of a chunk lacks
+    are fetched from its first row, where dY is infinite."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(11)
+    counts = torch.tensor(occ, dtype=torch.int32, device=DEV)
+    pad = torch.arange(C, device=DEV)[None, None, :] >= counts[:, :, None]
+    positive = lambda *s: (torch.rand(*s, generator=gen, device=DEV) + 0.1).to(torch.bfloat16)      # noqa: E731
+    X, dY = positive(n_src, G, C, M), positive(n_src, G, C, M)
+    X[pad] = 0
+    dY[pad] = 0
+    W1, W2 = positive(G, M, H) / M, positive(G, H, M) / H
+    ws = torch.empty(api.moe_ffn_workspace_bytes(api.MOE_BF16, n_src, G, C, M, H, 1), dtype=torch.uint8, device=DEV)
+    Z, A, Y = (torch.empty(n_src, G, C, n, dtype=torch.bfloat16, device=DEV) for n in (H, H, M))
+    api.moe_expert_ffn_fwd(X, W1, W2, n_src, G, C, M, H, 0, 1, Z, A, Y, counts, tile)
+
+    def bwd(dy):
+        dX, dW1, dW2 = torch.empty_like(X), torch.empty_like(W1), torch.empty_like(W2)
+        api.moe_expert_ffn_bwd(dy, X, Z, A, W1, W2, n_src, G, C, M, H, 0, 1, dX, dW1, dW2, ws, counts, tile)
+        return dX, dW1, dW2
+
+    dX, dW1, dW2 = bwd(dY)
+    assert dX.isfinite().all() and (dW1 > 0).all() and (dW2 > 0).all()
+    for g in range(G):
+        rows = [min(o[g], C) for o in occ]
+        if n_src >= 4:                       # packed: the position of the last k tile's first row among the expert's rows
+            at = (sum(rows) - 1) // 64 * 64
+            s = next(i for i in range(n_src) if at < sum(rows[:i + 1]))
+            row = at - sum(rows[:s])
+        else:
+            s = max(range(n_src), key=lambda i: rows[i])
+            row = (rows[s] - 1) // 64 * 64
+        dy = dY.clone()
+        dy[s, g, row, 3] = INF
+        dx, dw1, dw2 = bwd(dy)
+        a = slice(None)
+        expect(dx, dX, (s, g, row), "dX"), expect(dw1, dW1, (g,), "dW1"), expect(dw2, dW2, (g, a, 3), "dW2")
