@@ -674,14 +674,22 @@ struct ChunkWalk {
       n -= c;
     }
   }
-  __device__ __forceinline__ KTile next(int step) {   // the next rows of one chunk, at most `step`; past the end: no rows
-    while (left <= 0) {
+  __device__ __forceinline__ bool enter(int step) {   // the next chunk that has rows; false: past the end
+    if (__builtin_expect(mask == 0, 0)) {              // (out of the k loop's way)
       while (mask == 0 && s0 + 64 < p.n_src) { s0 += 64; load(); }
-      if (mask == 0) return KTile{0, 0};
-      const int l = __ffsll((long long)mask) - 1, at = PARTS ? first_tile(s0 + l, step) * step : 0;
-      mask &= mask - 1;
-      left = __builtin_amdgcn_readlane(cnt, l) - at;
-      row = ((s0 + l) * p.G + g) * p.Cc + at;
+      if (mask == 0) return false;
+    }
+    const int l = __ffsll((long long)mask) - 1, at = PARTS ? first_tile(s0 + l, step) * step : 0;
+    mask &= mask - 1;
+    left = __builtin_amdgcn_readlane(cnt, l) - at;
+    row = ((s0 + l) * p.G + g) * p.Cc + at;
+    return true;
+  }
+  __device__ __forceinline__ KTile next(int step) {   // the next rows of one chunk, at most `step`; past the end: no rows
+    if constexpr (PARTS) {                             // (a chunk may have no k tile of this part)
+      while (left <= 0) { if (!enter(step)) return KTile{0, 0}; }
+    } else {
+      if (left <= 0 && !enter(step)) return KTile{0, 0};
     }
     const KTile t{row, min(left, step)};
     const int on = PARTS ? step * p.splits : step;
