@@ -158,23 +158,23 @@ def moe_gate_bwd_workspace_bytes(S, M, E) -> int:
 def moe_gate_topk(x, Wg, gate_bias, S_total, M, E, k, C, mp_idx, n_mp, norm_topk,
                   logits, idx, slot, w, inv, counts, ws):
     wp, wb = _ws_args(ws)
-    _check((_lib or lib()).moe_gate_topk(_ptr(x), dtype_code(x) if x is not None else MOE_F32, _ptr(Wg), _ptr(gate_bias),
-                               S_total, M, E, k, C, mp_idx, n_mp, norm_topk,
-                               _ptr(logits), _ptr(idx), _ptr(slot), _ptr(w), _ptr(inv), _ptr(counts),
-                               wp, wb, _stream()), "moe_gate_topk")
+    _check((_lib or lib()).moe_gate_topk(_ptr(x), dtype_code(x) if x is not None else MOE_F32, _ptr(Wg),
+                                         _ptr(gate_bias), S_total, M, E, k, C, mp_idx, n_mp, norm_topk, _ptr(logits),
+                                         _ptr(idx), _ptr(slot), _ptr(w), _ptr(inv), _ptr(counts), wp, wb, _stream()),
+           "moe_gate_topk")
 
 
 def moe_gate_topk_static(x, Wg, gate_bias, S_total, M, E, k, C, mp_idx, n_mp, norm_topk,
                          logits, idx, slot, w, inv, counts):
-    _check((_lib or lib()).moe_gate_topk_static(_ptr(x), dtype_code(x) if x is not None else MOE_F32, _ptr(Wg), _ptr(gate_bias),
-                                      S_total, M, E, k, C, mp_idx, n_mp, norm_topk,
-                                      _ptr(logits), _ptr(idx), _ptr(slot), _ptr(w), _ptr(inv), _ptr(counts),
-                                      _stream()), "moe_gate_topk_static")
+    _check((_lib or lib()).moe_gate_topk_static(_ptr(x), dtype_code(x) if x is not None else MOE_F32, _ptr(Wg),
+                                                _ptr(gate_bias), S_total, M, E, k, C, mp_idx, n_mp, norm_topk,
+                                                _ptr(logits), _ptr(idx), _ptr(slot), _ptr(w), _ptr(inv), _ptr(counts),
+                                                _stream()), "moe_gate_topk_static")
 
 
 def moe_dispatch(x, S, M, E, k, C, inv, w, buf):
-    _check((_lib or lib()).moe_dispatch(_ptr(x), dtype_code(x), S, M, E, k, C, _ptr(inv), _ptr(w), _ptr(buf), _stream()),
-           "moe_dispatch")
+    _check((_lib or lib()).moe_dispatch(_ptr(x), dtype_code(x), S, M, E, k, C, _ptr(inv), _ptr(w), _ptr(buf),
+                                        _stream()), "moe_dispatch")
 
 
 def moe_alpha_beta_fit(xs, ts):
@@ -183,8 +183,8 @@ def moe_alpha_beta_fit(xs, ts):
     ax = (ctypes.c_double * n)(*[float(v) for v in xs])
     at = (ctypes.c_double * len(ts))(*[float(v) for v in ts])
     a, b = ctypes.c_double(), ctypes.c_double()
-    _check((_lib or lib()).moe_alpha_beta_fit(ax, at, min(n, len(ts)) if n == len(ts) else 0, ctypes.byref(a), ctypes.byref(b)),
-           "moe_alpha_beta_fit")
+    _check((_lib or lib()).moe_alpha_beta_fit(ax, at, min(n, len(ts)) if n == len(ts) else 0, ctypes.byref(a),
+                                              ctypes.byref(b)), "moe_alpha_beta_fit")
     return a.value, b.value
 
 
@@ -199,8 +199,8 @@ def moe_choose_schedule(a_ag, b_ag, a_a2a, b_a2a, a_o, b_o, B, L, E, M, k, f, n_
 
 
 def moe_dispatch_slots(x, S, M, E, k, C, c0, c1, inv, w, buf):
-    _check((_lib or lib()).moe_dispatch_slots(_ptr(x), dtype_code(x), S, M, E, k, C, c0, c1, _ptr(inv), _ptr(w), _ptr(buf),
-                                    _stream()), "moe_dispatch_slots")
+    _check((_lib or lib()).moe_dispatch_slots(_ptr(x), dtype_code(x), S, M, E, k, C, c0, c1, _ptr(inv), _ptr(w),
+                                              _ptr(buf), _stream()), "moe_dispatch_slots")
 
 
 def moe_ffn_executed_flops(dtype, n_src, G, C, M, H, n_esp, row_counts_host=None, backward=False, tile=0) -> float:
@@ -215,46 +215,48 @@ def moe_ffn_executed_flops(dtype, n_src, G, C, M, H, n_esp, row_counts_host=None
 
 
 def moe_expert_ffn_fwd(X, W1, W2, n_src, G, C, M, H, esp_idx, n_esp, Z, A, Y, row_counts=None, tile=0):
-    _check((_lib or lib()).moe_expert_ffn_fwd(_ptr(X), dtype_code(X), _ptr(W1), _ptr(W2), n_src, G, C, M, H, esp_idx, n_esp,
-                                    _ptr(row_counts), tile, _ptr(Z), _ptr(A), _ptr(Y), _stream()), "moe_expert_ffn_fwd")
+    _check((_lib or lib()).moe_expert_ffn_fwd(_ptr(X), dtype_code(X), _ptr(W1), _ptr(W2), n_src, G, C, M, H, esp_idx,
+                                              n_esp, _ptr(row_counts), tile, _ptr(Z), _ptr(A), _ptr(Y), _stream()),
+           "moe_expert_ffn_fwd")
 
 
 def moe_expert_ffn_fwd_gather(x, inv, S, k, W1, W2, E, C, M, H, esp_idx, n_esp, Z, A, Y, row_counts=None, tile=0):
-    _check((_lib or lib()).moe_expert_ffn_fwd_gather(_ptr(x), dtype_code(x), S, _ptr(inv), k, _ptr(W1), _ptr(W2), E, C, M, H,
-                                           esp_idx, n_esp, _ptr(row_counts), tile, _ptr(Z), _ptr(A), _ptr(Y), _stream()),
-           "moe_expert_ffn_fwd_gather")
+    _check((_lib or lib()).moe_expert_ffn_fwd_gather(_ptr(x), dtype_code(x), S, _ptr(inv), k, _ptr(W1), _ptr(W2), E, C,
+                                                     M, H, esp_idx, n_esp, _ptr(row_counts), tile, _ptr(Z), _ptr(A),
+                                                     _ptr(Y), _stream()), "moe_expert_ffn_fwd_gather")
 
 
 def moe_expert_ffn_bwd(dY, X, Z, A, W1, W2, n_src, G, C, M, H, esp_idx, n_esp, dX, dW1, dW2, ws, row_counts=None,
                        tile=0):
     wp, wb = _ws_args(ws)
     _check((_lib or lib()).moe_expert_ffn_bwd(_ptr(dY), _ptr(X), _ptr(Z), _ptr(A), _ptr(W1), _ptr(W2), dtype_code(X),
-                                    n_src, G, C, M, H, esp_idx, n_esp, _ptr(row_counts), tile, _ptr(dX), _ptr(dW1),
-                                    _ptr(dW2), wp, wb, _stream()), "moe_expert_ffn_bwd")
+                                              n_src, G, C, M, H, esp_idx, n_esp, _ptr(row_counts), tile, _ptr(dX),
+                                              _ptr(dW1), _ptr(dW2), wp, wb, _stream()), "moe_expert_ffn_bwd")
 
 
 def moe_expert_ffn_bwd_gather(dY, x, inv, S, k, Z, A, W1, W2, E, C, M, H, esp_idx, n_esp, dX, dW1, dW2, ws,
                               row_counts=None, tile=0):
     wp, wb = _ws_args(ws)
-    _check((_lib or lib()).moe_expert_ffn_bwd_gather(_ptr(dY), _ptr(x), S, _ptr(inv), k, _ptr(Z), _ptr(A), _ptr(W1), _ptr(W2),
-                                           dtype_code(x), E, C, M, H, esp_idx, n_esp, _ptr(row_counts), tile, _ptr(dX),
-                                           _ptr(dW1), _ptr(dW2), wp, wb, _stream()), "moe_expert_ffn_bwd_gather")
+    _check((_lib or lib()).moe_expert_ffn_bwd_gather(_ptr(dY), _ptr(x), S, _ptr(inv), k, _ptr(Z), _ptr(A), _ptr(W1),
+                                                     _ptr(W2), dtype_code(x), E, C, M, H, esp_idx, n_esp,
+                                                     _ptr(row_counts), tile, _ptr(dX), _ptr(dW1), _ptr(dW2), wp, wb,
+                                                     _stream()), "moe_expert_ffn_bwd_gather")
 
 
 def moe_combine_fwd(Yret, n_part, S, M, E, k, C, idx, slot, w, y):
     _check((_lib or lib()).moe_combine_fwd(_ptr(Yret), dtype_code(Yret), n_part, S, M, E, k, C, _ptr(idx), _ptr(slot),
-                                 _ptr(w), _ptr(y), _stream()), "moe_combine_fwd")
+                                           _ptr(w), _ptr(y), _stream()), "moe_combine_fwd")
 
 
 def moe_combine_bwd(dy, Yret, n_part, S, M, E, k, C, idx, slot, inv, w, dYret, dw):
     _check((_lib or lib()).moe_combine_bwd(_ptr(dy), _ptr(Yret), dtype_code(dy), n_part, S, M, E, k, C, _ptr(idx),
-                                 _ptr(slot), _ptr(inv), _ptr(w), _ptr(dYret), _ptr(dw), _stream()),
+                                           _ptr(slot), _ptr(inv), _ptr(w), _ptr(dYret), _ptr(dw), _stream()),
            "moe_combine_bwd")
 
 
 def moe_gate_bwd(dw, w, idx, logits, x, Wg, S, M, E, k, norm_topk, dlogits, dWg, dgate_bias, dx,
                  dx_accumulate, ws):
     wp, wb = _ws_args(ws)
-    _check((_lib or lib()).moe_gate_bwd(_ptr(dw), _ptr(w), _ptr(idx), _ptr(logits), _ptr(x), dtype_code(x), _ptr(Wg),
-                              S, M, E, k, norm_topk, _ptr(dlogits), _ptr(dWg), _ptr(dgate_bias), _ptr(dx),
-                              int(dx_accumulate), wp, wb, _stream()), "moe_gate_bwd")
+    _check((_lib or lib()).moe_gate_bwd(_ptr(dw), _ptr(w), _ptr(idx), _ptr(logits), _ptr(x), dtype_code(x), _ptr(Wg), S,
+                                        M, E, k, norm_topk, _ptr(dlogits), _ptr(dWg), _ptr(dgate_bias), _ptr(dx),
+                                        int(dx_accumulate), wp, wb, _stream()), "moe_gate_bwd")

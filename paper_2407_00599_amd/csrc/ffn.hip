@@ -15,15 +15,17 @@
 // g at physical row ((r / C) * G + g) * C + r % C, so no permutation pass is needed and only
 // the last row tile of an expert is ragged.
 //
-// bf16 path: one kernel, MFMA (v_mfma_f32_16x16x32_bf16 in the two largest tiles, v_mfma_f32_32x32x16_bf16 in the
-// others) with fp32 accumulation, over a family of tiles from 256 x 256 down to 32 x 64 (described in front of gemm_dma_tile; plan_tiles chooses).  Global memory goes straight to LDS
-// (buffer_load ... lds) in k tiles of 64; operands whose memory layout has k as the slow index stay in that layout in
-// LDS and are read with the transposing LDS load, so no transpose pass exists.  The MFMA is issued with the operands
-// swapped (D^T = B^T A^T) so that a lane ends up with 4 consecutive output columns.
+// bf16 path: one kernel, MFMA (v_mfma_f32_16x16x32_bf16 in the two largest tiles but for weight gradients of few k tiles,
+// v_mfma_f32_32x32x16_bf16 in the others) with fp32 accumulation, over a family of tiles from 256 x 256 down to 32 x 64
+// (described in front of gemm_dma_tile; plan_tiles chooses).  Global memory goes straight to LDS (buffer_load ... lds) in
+// k tiles of 64; operands whose memory layout has k as the slow index stay in that layout in LDS and are read with the
+// transposing LDS load, so no transpose pass exists.  The MFMA is issued with the operands swapped (D^T = B^T A^T) so that a
+// lane ends up with 4 consecutive output columns.
 //
 // Row counts (capacity padding): the row-tiled GEMMs take an expert's rows in compacted order, the occupied rows of
 // all its chunks first, so that only ceil(occupied / tile) row tiles are multiplied however the occupancy is spread
-// over the chunks; the weight gradients skip the k tiles of a chunk that lie behind its count.
+// over the chunks; the weight gradients skip the k tiles of a chunk that lie behind its count, and from four chunks on pack the
+// occupied rows.
 //
 // fp32 path: a kernel on the fp64 matrix cores (fp64 accumulation), row counts used the same way.
 #include <math.h>
@@ -61,7 +63,7 @@ struct GemmArgs {
   int64_t b_goff, c_goff;            // per-expert stride of weight-type operands, elements
   int64_t b_off, c_off;              // constant offset of the ESP slice, elements
   int tiles_m, tiles_n, total_tiles;
-  int run_mask;                      // tile order (xcd_tile): ~31, the XCDs take runs of 32 tiles in turn; 0, a contiguous range each
+  int run_mask;                      // tile order (xcd_tile): ~31: the XCDs take runs of 32 tiles in turn; 0: a range each
   uint64_t a_bytes, b_bytes;         // bf16 path: byte sizes of the A and B tensors (buffer descriptors)
   int splits;                        // EPI_PART: parts of the reduction; part q of every expert's matrix in
   float* part;                       // [splits, G, Mdim, Ndim]
@@ -159,8 +161,8 @@ template <> struct AccBlock<32> { typedef f32x16_t type; };
 template <> struct AccBlock<16> { typedef f32x4_t type; };
 template <int KIND, int EPI, int MR, int MB, int NBK, int AM, int AN>
 __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, typename AccBlock<MR>::type (&acc)[AM][AN],
-                                               char* wave_lds, int g, int mwave, int mshift, int nbase, const uint32_t (&out_off)[2],
-                                               int lane) {
+                                               char* wave_lds, int g, int mwave, int mshift, int nbase,
+                                               const uint32_t (&out_off)[2], int lane) {
   constexpr int CW = 32 * NBK;            // columns of the wave tile
   constexpr int PITCH_B = 2 * CW + 16;    // staged row pitch, bytes
   constexpr int BUF = 32 * PITCH_B;
@@ -280,9 +282,9 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, typename AccBl
 // bf16 MFMA tile with an LDS-DMA pipeline.
 //
 // TM x TN output tile, k tile 64, WM x WN waves over the tile times WK waves over the MFMA steps of a k tile (two
-// of 32 k or four of 16 k; WK = 2: two of the four per group, whose sums are added through LDS at the end).  Global memory goes straight to LDS
-// (buffer_load ... lds, 16 bytes per lane, no VGPR staging, no ds_write) into two rings of whole k tiles, SA
-// tiles of the A operand and SB of the B operand.  A k tile is 64 wide so that every request of a k-contiguous
+// of 32 k or four of 16 k; WK = 2: two of the four per group, whose sums are added through LDS at the end).  Global memory
+// goes straight to LDS (buffer_load ... lds, 16 bytes per lane, no VGPR staging, no ds_write) into two rings of whole k
+// tiles, SA tiles of the A operand and SB of the B operand.  A k tile is 64 wide so that every request of a k-contiguous
 // operand covers whole 128-byte lines.  A wave instruction fills 1 KiB of consecutive 16-byte slots in lane
 // order, so a tile is stored unpadded and bank conflicts are avoided by permuting WHICH 16-byte chunk of a row
 // each lane fetches (an XOR swizzle that the fragment reads undo).  Every lane of a request fetches from inside the
@@ -313,8 +315,9 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs& p, typename AccBl
 // pays only with the reads spread between the MFMAs: reads behind every fourth MFMA, 65 % of the cycles busy and no
 // gain; spread, 69 %: the three launches of the GEMMs above and the merged backward launch 6.74 / 6.27 / 6.45 / 18.99 ->
 // 6.57 / 6.11 / 6.25 / 18.39 ms.  The tiles with two wave groups over k keep 32x32x16, which gives each group two steps
-// per k tile, and so do weight gradients with few k tiles (Tile256Brief), which are not under the power limit.  Tried without gain: rows of the last step in front of the barrier 2 -> 3 or 4 (to 4 % slower at 12 k tiles),
-// s_setprio for half of the waves, a second barrier that frees B's slot in the first step (-1 to +3 % in single launches).
+// per k tile, and so do weight gradients with few k tiles (Tile256Brief), which are not under the power limit.  Tried
+// without gain: rows of the last step in front of the barrier 2 -> 3 or 4 (to 4 % slower at 12 k tiles), s_setprio for half
+// of the waves, a second barrier that frees B's slot in the first step (-1 to +3 % in single launches).
 // ------------------------------------------------------------------------------------------
 #define LDS_AS __attribute__((address_space(3)))
 constexpr int DK = 64;   // k tile
@@ -414,10 +417,14 @@ __device__ __forceinline__ int xcd_tile(const GemmArgs& p, int x, int i, int per
 // tile); with several, whose padding is spread over the buffer, a workgroup for an equal share of all padding rows
 // (fill_shares), about one for a tile's worth, or for four with very many.  The grid has a workgroup for every tile of the
 // capacity, and MORE_SHARES (grid_of); the rest leave at once.
+// How many shares there are matters little.  One for each tile's worth of padding, and one for four, forward and backward call:
+// 8 experts of 3500 occupied in 20480 rows x 2048 x 2048, 32 chunks, 713 / 961 and 700 / 942 us; 4 of 8 chunks of
+// 512 x 1024 x 2048, half full, 114.1 / 171.4 and 110.7 / 171.6; 16 chunks of 300 x 1024 x 1024, a third full, 50.2 / 78.5 and
+// 51.7 / 75.6.  (place() counts 256 compute units with one workgroup each; with small tiles there is room for more.)
 // Fewer and larger shares between the tiles, to store beside the matrix work, measured slower: a compute unit stores no more
 // than some 20 GB/s while the others load the memory system, and the whole chip 4.5 to 5 TB/s.
-// 8 experts of 3500 occupied in 20480 rows x 2048 x 2048, 32 chunks: with a workgroup that walked the rows of every tile of
-// zeros 471 / 391 / 380 us (the forward GEMMs and dZ, which stores no zeros), now 427 / 296 / 238.
+// With a workgroup that walked the rows of every tile of zeros the first of these shapes took 471 / 391 / 380 us (the forward
+// GEMMs and dZ, which stores no zeros), with shares 427 / 296 / 238.
 // Returns 0: nothing to do, 1: a tile to multiply, 2: padding to fill (one chunk: tile g, tm, tn; several: share g of tm).
 constexpr int MORE_SHARES = 64;
 template <int TM, bool ZEROS>
@@ -453,7 +460,7 @@ __device__ __forceinline__ int map_tile(const GemmArgs& p, int vb, bool counted,
     return tile;
   };
   int what;
-  if (p.n_src == 1 && p.G <= 16) {   // few counts: scalar loads, which hit the scalar cache from a compute unit's second tile on
+  if (p.n_src == 1 && p.G <= 16) {   // few counts: scalar loads, in the scalar cache from a compute unit's second tile on
     int o[16], occ_all = 0;
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[e] = p.cnt[min(e, p.G - 1)];
@@ -554,7 +561,8 @@ __device__ __forceinline__ void fill_shares(const GemmArgs& p, int at, int share
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) rows += __shfl_xor(rows, d, 64);
   rows = __builtin_amdgcn_readfirstlane(rows);
-  const int per = (int)(((unsigned)rows + shares - 1) / (unsigned)shares), r0 = min((int64_t)per * at, (int64_t)rows), r1 = min(r0 + (int64_t)per, (int64_t)rows);
+  const int per = (int)(((unsigned)rows + shares - 1) / (unsigned)shares);
+  const int r0 = min((int64_t)per * at, (int64_t)rows), r1 = min(r0 + (int64_t)per, (int64_t)rows);
   int run = 0;                                                   // padding rows in front of c0
   for (int c0 = 0; c0 < chunks && run < r1; c0 += 64) {
     const int n = padding(c0 + lane);
@@ -622,10 +630,12 @@ struct KTile {
   int row0, lim;   // first row of the k tile in the operand (row-tiled GEMMs: first k), rows (k values) that exist
 };
 // The reduction of a weight gradient runs over the expert's rows chunk by chunk, up to each chunk's row count; empty
-// chunks are passed over.  With few chunks a k tile never crosses a chunk, so that its grouping is the same with and without row
-// counts; with PACK_CHUNKS of them or more (half a k tile lost in each) the rows are packed: a k tile is made of
+// chunks are passed over.  With few chunks a k tile never crosses a chunk, so that its grouping is the same with and without
+// row counts; with PACK_CHUNKS of them or more (half a k tile lost in each) the rows are packed: a k tile is made of
 // pieces of several chunks.  32 chunks of 110 rows on average, 8 experts x 2048 x 2048, merged backward launch: 991 -> 851 us,
-// a part of it from the padding; 4 chunks of 180 rows: 41.9 -> 39.1 us.
+// a part of it from the padding; 4 chunks of 180 rows: 41.9 -> 39.1 us.  Two or three chunks would gain 0 to 5 % (backward
+// call, 8 experts x 1024 x 2048, 60 % full: 3 chunks of 100 rows 63.1 -> 60.1 us, 3 of 200 83.8 -> 81.1, 2 of 700 151.5 ->
+// 150.9); they stay whole for the same bits with and without counts.
 constexpr int PACK_CHUNKS = 4;
 // Of a reduction cut into parts, whole k tiles of one chunk are dealt to the parts in turn, by their index in the capacity: the
 // parts are equally long whatever the counts, and the sums are grouped the same with and without them (PARTS).  Packed k
@@ -763,7 +773,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   }
   const int what = map_tile<TM, EPI != EPI_DGELU>(p, vb, counted, g, tm, tn);   // (dZ of a padding row is never read)
   if (what == 0) return;
-  if (KIND != KIND_TN && __builtin_expect(what == 2, 0)) return p.n_src == 1 ? fill_tile<2, TM, TN, EPI == EPI_GELU>(p, g, tm, tn) : fill_shares<2, EPI == EPI_GELU>(p, g, tm);
+  if (KIND != KIND_TN && __builtin_expect(what == 2, 0))
+    return p.n_src == 1 ? fill_tile<2, TM, TN, EPI == EPI_GELU>(p, g, tm, tn) : fill_shares<2, EPI == EPI_GELU>(p, g, tm);
   const int m0 = tm * TM, n0 = tn * TN;
   const bool compact = counted && p.n_src > 1;
 
@@ -838,7 +849,9 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   int a_k[RA], b_k[RB];
   constexpr int ACPR = TM / 8, BCPR = TN / 8;   // k-slow: 16-byte chunks per k-row
   const uint32_t lda2 = (uint32_t)p.lda * 2u, ldb2 = (uint32_t)p.ldb * 2u;
-  auto swz_nc = [](int k, int cpr) { return cpr >= 16 ? 4 * (k & 3) + (MR == 16 ? 2 * ((k >> 3) & 1) : 0) : 4 * ((k >> 1) & 1); };
+  auto swz_nc = [](int k, int cpr) {
+    return cpr >= 16 ? 4 * (k & 3) + (MR == 16 ? 2 * ((k >> 3) & 1) : 0) : 4 * ((k >> 1) & 1);
+  };
 #pragma unroll
   for (int j = 0; j < RA; ++j) {
     const int q = wave * RA + j;
@@ -929,7 +942,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   // One request (1 KiB) of k tile kt into ring slot `slot`.
   auto request_a = [&](const KTile& kt, int slot, int j) {
     const uint32_t in = a_k[j] < kt.lim ? a_ko[j] : 0u;   // missing k rows are fetched from the tile's first one
-    const uint32_t add = GATHER ? g_now[j] : PIECES ? ka_off[PIECES ? j : 0] : (A_NC ? (uint32_t)kt.row0 * lda2 : (uint32_t)kt.row0 * 2u) + in;
+    const uint32_t add = GATHER ? g_now[j] : PIECES ? ka_off[PIECES ? j : 0] : (uint32_t)kt.row0 * (A_NC ? lda2 : 2u) + in;
     dma16(rA, smem + slot * CF::A_UNIT + (wave * RA + j) * 1024, a_req[j] + add);
   };
   auto request_b = [&](const KTile& kt, int slot, int j) {
@@ -1005,9 +1018,14 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
   // tiles: 17.1 -> 18.1 ms).
   constexpr int SL_LAST = (MB - BR) * NB + 1, SL = SL_LAST + (SPT - 1) * MB * NB;   // slots: in the last step, in all
   constexpr auto slot_of = [](int r) constexpr { return r * SL / NREQ; };
-  constexpr auto before = [](int slot) constexpr { int n = 0; for (int r = 0; r < NREQ; ++r) n += r * SL / NREQ < slot; return n; };
+  constexpr auto before = [](int slot) constexpr {
+    int n = 0;
+    for (int r = 0; r < NREQ; ++r) n += r * SL / NREQ < slot;
+    return n;
+  };
   constexpr int N_LAST = before(SL_LAST);                            // requests issued in the last step
-  constexpr int IN_FLIGHT = (SA > SB ? RA : 0) + (SB - 2) * (NREQ + (GATHER ? 1 : 0));    // newer requests than those of tile t+1, at barrier t
+  // newer requests than those of tile t+1, at barrier t
+  constexpr int IN_FLIGHT = (SA > SB ? RA : 0) + (SB - 2) * (NREQ + (GATHER ? 1 : 0));
   KTile ka{0, 0}, kb{0, 0};
   int g_entry = 0;        // GATHER: slot-map entries of g_next, the tile after ka
   KTile g_next{0, 0};
@@ -1135,7 +1153,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& p, char* smem, int
           mfma(ST & 1, I, J);
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (ST == SPT - 1 && AT == BR * NB - 1) {
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(LAST ? 0 : IN_FLIGHT) & 0xF0FF);   // this wave's requests for tile t+1 have landed; so have its reads of tile t
+            // this wave's requests for tile t+1 have landed; so have its reads of tile t
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(LAST ? 0 : IN_FLIGHT) & 0xF0FF);
             __builtin_amdgcn_s_barrier();                        // everyone is done with tile t, and tile t+1 is complete
             __builtin_amdgcn_sched_barrier(0);
             wa = sa; wb = sb;
@@ -1245,10 +1264,11 @@ __global__ __launch_bounds__(64 * CF::NW) void ffn_gemm_dma(const GemmArgs p) {
 }
 
 using Tile256 = TileCfg<256, 256, 2, 4, 1, 3, 2>;
-// Weight gradients over at most 8 k tiles of rows, k tiles of one chunk.  There the launch is bound by what a tile does outside its
-// k loop and by the writes, and the shorter steps of 32x32x16 start and drain faster.  Backward call, 16x16x32 and this, in
-// turn: 16 experts of 64 / 256 / 512 x 2048 x 4096 267 / 430 / 582 and 264 / 421 / 578 us; 24 of 200 x 1024 x 2048 133.2 and 131.1;
-// 2 of 512 x 1024 x 3584 49.5 and 48.7; beyond, 16 of 900 x 1024 x 1024 130.7 and 132.4, 4 of 700 x 2048 x 4096 191.9 and 194.5.
+// Weight gradients over at most 8 k tiles of rows, k tiles of one chunk.  There the launch is bound by what a tile does
+// outside its k loop and by the writes, and the shorter steps of 32x32x16 start and drain faster.  Backward call, 16x16x32 and
+// this, in turn: 16 experts of 64 / 256 / 512 x 2048 x 4096 267 / 430 / 582 and 264 / 421 / 578 us; 24 of 200 x 1024 x 2048 133.2
+// and 131.1; 2 of 512 x 1024 x 3584 49.5 and 48.7; beyond, 16 of 900 x 1024 x 1024 130.7 and 132.4, 4 of 700 x 2048 x 4096 191.9
+// and 194.5.
 constexpr int BRIEF_ROWS = 8 * DK;
 using Tile256Brief = TileCfg<256, 256, 2, 4, 1, 3, 2, 32>;
 using Tile192 = TileCfg<192, 256, 2, 4, 1, 3, 2>;
@@ -1320,7 +1340,8 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int
   const bool counted = KIND != KIND_TN && p.cnt != nullptr;
   const int what = map_tile<TM, EPI != EPI_DGELU>(p, vb, counted, g, tm, tn);   // (dZ of a padding row is never read)
   if (what == 0) return;
-  if (KIND != KIND_TN && __builtin_expect(what == 2, 0)) return p.n_src == 1 ? fill_tile<4, TM, TN, EPI == EPI_GELU>(p, g, tm, tn) : fill_shares<4, EPI == EPI_GELU>(p, g, tm);
+  if (KIND != KIND_TN && __builtin_expect(what == 2, 0))
+    return p.n_src == 1 ? fill_tile<4, TM, TN, EPI == EPI_GELU>(p, g, tm, tn) : fill_shares<4, EPI == EPI_GELU>(p, g, tm);
   const int m0 = tm * TM, n0 = tn * TN;
   const float* __restrict__ A = reinterpret_cast<const float*>(p.A);
   const float* __restrict__ B = reinterpret_cast<const float*>(p.B) + (KIND == KIND_TN ? 0 : (int64_t)g * p.b_goff + p.b_off);
@@ -1389,9 +1410,10 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int
     }
   }
   float4 ra[UA], rb[UB];
-  // A full chunk has a path of its own: what a partial one looks at otherwise stands in front of every load, and how the compiler
-  // forms those addresses decided the length of a chunk (one expert, 224 x 192 x 10984, backward: 645 us, and 662 after a
-  // change elsewhere in the kernel; with this path 644, forward 249 -> 227; 8 experts of 256 x 512 x 2048 175 -> 162, 293 -> 286).
+  // A full chunk has a path of its own: what a partial one looks at otherwise stands in front of every load, and how the
+  // compiler forms those addresses decided the length of a chunk (one expert, 224 x 192 x 10984, backward: 645 us, and 662 after
+  // a change elsewhere in the kernel; with this path 644, forward 249 -> 227; 8 experts of 256 x 512 x 2048 175 -> 162 and
+  // 293 -> 286).
   auto fetch = [&](const KTile& kt) {
     if (kt.lim >= FK && (KIND != KIND_TN || p.gather == nullptr)) {
 #pragma unroll
@@ -1514,7 +1536,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int
 }
 
 template <int KIND, int EPI, int TM, int TN>
-__global__ __launch_bounds__(256, 4) void ffn_gemm_f32(const GemmArgs p) {   // (the second bound keeps the accumulators out of the AGPRs)
+__global__ __launch_bounds__(256, 4) void ffn_gemm_f32(const GemmArgs p) {   // (the 4 keeps the accumulators out of the AGPRs)
   __shared__ __attribute__((aligned(16))) double smem[f32_lds<TM, TN>() / 8];
   gemm_f32_tile<KIND, EPI, TM, TN>(p, smem, (int)blockIdx.x);
 }
@@ -1550,8 +1572,10 @@ struct TilePlan {
 // compute units busy (in a launch of its own; a compute unit then holds one workgroup of the first two, two of the
 // others), and everything outside the k loop.  Large tiles move the fewest bytes per flop; small ones fill the chip when
 // there are few rows, and their k tile is short when a long reduction is what a launch waits for.
-// For dX in the merged backward launch the same prices are an approximation: there a compute unit holds one workgroup
-// whatever its tile (the launch reserves the LDS of a 256 x 256 tile), and the weight gradients queue behind dX.
+// The prices of the two largest tiles are those of a loop with 32x32x16 MFMAs and requests in bursts; the present one is
+// shorter with every compute unit busy, and they have not been measured again.  For dX in the merged backward launch with
+// 256 x 256 weight gradients they are an approximation: there a compute unit holds one workgroup whatever its tile (the
+// launch reserves the LDS of a 256 x 256 tile), and the weight gradients queue behind dX.
 struct TileCost {
   TilePlan tile;
   int per_cu;
@@ -1617,8 +1641,8 @@ int merged_backward(GemmArgs& w2, GemmArgs& w1, int tile) {   // prepares the tw
   const TilePlan t = prepare_bf16(w2, true, tile);
   return tile == MOE_TILE_SMALL ? 0 : t.tile_m;
 }
-// dX beside weight gradients of 128 x 128 tiles takes 64 x 128 ones, two workgroups to a compute unit as theirs.  That pays while
-// they are one round of the chip; beyond it dX goes out alone, in the tiles of its own plan.  Backward call, merged and alone:
+// dX beside weight gradients of 128 x 128 tiles takes 64 x 128 ones, two workgroups to a compute unit as theirs.  That pays
+// while they are one round of the chip; beyond it dX goes out alone, in the tiles of its own plan.  Backward call, merged and alone:
 // 8 experts of 274 x 128 x 1216 (40 tiles) 22.0 and 26.0 us, 1 of 512 x 2048 x 1792 (128) 35.2 and 40.1, 8 of 1024 x 512 x 768
 // (480) 51.0 and 52.3; 7 of 1024 x 768 x 768 (630) 63.7 and 61.0, 30 of 1000 x 512 x 256 (1800) 71.2 and 58.9, 7 of
 // 4096 x 768 x 768 (2436) 176.7 and 147.2, 1 of 32768 x 2048 x 1792 (8192) 1093 and 945.
@@ -1629,10 +1653,10 @@ bool dx_alone(const GemmArgs& dx) {
 // Parts of the reductions of the two weight gradients where both take 128 x 128 tiles: few tiles leave compute units idle, and
 // a reduction over thousands of rows is then what the launch waits for.  Parts of at least 12 k tiles of the capacity (a k tile
 // takes 0.6 us there, writing, reading and adding the partial sums in a launch of their own 4 to 9 us), and no more workgroups
-// than the chip holds.  A part of the workspace's size, so it is arithmetic on the shape and asks no device.  2 experts of 55 000 rows x 512 x 128, 16 tiles: 503 + 552 us in two launches, 66 for
-// dX -> 203 us for all three, 8.5 to add.  Few rows gain by the one launch: 8 experts of 274 rows x 128 x 1216, 88 tiles:
-// 8.0 + 10.2 + 8.1 -> 12.4 us.  One launch of 128 x 128 tiles measured no better from 64 tiles of 256 x 256 on
-// (72 to 256 of them: 0.93 to 1.33 times the time).
+// than the chip holds.  A part of the workspace's size, so it is arithmetic on the shape and asks no device.  2 experts of
+// 55 000 rows x 512 x 128, 16 tiles, backward call: 1028 us whole, 167 in parts.  Few rows gain by the one launch: 8 experts of
+// 274 rows x 128 x 1216, 88 tiles, 8.0 + 10.2 + 8.1 -> 12.4 us.  One launch of 128 x 128 tiles measured no better from 64
+// tiles of 256 x 256 on (72 to 256 of them: 0.93 to 1.33 times the time).
 constexpr int CHIP_CUS = 256;   // compute units of an MI355X
 int weight_parts(int n_src, int G, int64_t C, int M, int Hl) {
   const int64_t tiles256 = (int64_t)G * ((M + 255) / 256) * ((Hl + 255) / 256);
@@ -1662,7 +1686,9 @@ int plan_f32(int64_t tiles_64x64, int64_t tiles_32x64) {   // 2: 64 x 64, 1: 32 
   return tiles_64x64 >= enough ? 2 : tiles_32x64 >= enough ? 1 : 0;
 }
 int f32_tile_m(int size) { return size == 2 ? 64 : 32; }
-int plan_f32(const GemmArgs& a) { return plan_f32(tiles_f32(a, false, 64, 64), tiles_f32(a, false, 32, 64)); }   // of a row-tiled GEMM
+int plan_f32(const GemmArgs& a) {   // of a row-tiled GEMM
+  return plan_f32(tiles_f32(a, false, 64, 64), tiles_f32(a, false, 32, 64));
+}
 int plan_f32_trio(const GemmArgs& dx, const GemmArgs& w2, const GemmArgs& w1) {   // of the merged backward launch
   return plan_f32(tiles_f32(dx, false, 64, 64) + tiles_f32(w2, true, 64, 64) + tiles_f32(w1, true, 64, 64),
                   tiles_f32(dx, false, 32, 64) + tiles_f32(w2, true, 32, 64) + tiles_f32(w1, true, 32, 64));
@@ -1909,10 +1935,11 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
       px.tiles_n = (px.Ndim + CFX::TN - 1) / CFX::TN;
       px.total_tiles = px.G * px.tiles_m * px.tiles_n;
       const int parts = EPI == EPI_PART ? p2.splits : 1;
-      const int nbx = alone ? 0 : grid_of(px), nb2 = (p2.total_tiles + 7) / 8 * 8 * parts, nb1 = (p1.total_tiles + 7) / 8 * 8 * parts;
+      const int nbx = alone ? 0 : grid_of(px);
+      const int nb2 = (p2.total_tiles + 7) / 8 * 8 * parts, nb1 = (p1.total_tiles + 7) / 8 * 8 * parts;
+      const dim3 grid((unsigned)(nbx + nb2 + nb1));
       auto go = [&](auto rows) {
-        hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, decltype(rows)::value>), dim3((unsigned)(nbx + nb2 + nb1)), dim3(512), 0, st,
-                           px, p2, p1, nbx, nb2);
+        hipLaunchKernelGGL((ffn_bwd_trio<CFX, CFW, EPI, decltype(rows)::value>), grid, dim3(512), 0, st, px, p2, p1, nbx, nb2);
       };
       if (gather) return go(std::integral_constant<int, ROWS_GATHER>{});
       if constexpr (!std::is_same<CFW, Tile256Brief>::value) {
