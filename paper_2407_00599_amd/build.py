@@ -20,13 +20,14 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-fvisibility=default",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 VALU ops
-    # A hot loop's speed depends on where in a 64-byte line of the instruction cache it starts, and any edit in front of it moves
-    # it: the merged backward launch of 8 experts x 16384 x 4096 x 7168, same loops, 17.44 ms with a loop at the start of a line
-    # and 17.78 behind it; the call 21.96 / 22.19 / 21.90 ms (by chance aligned / moved / aligned by this).
-    "-Xarch_device", "-falign-loops=64",
     "-Wno-unused-command-line-argument",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
+# The speed of the expert FFN's k loops depends on where in a 64-byte line of the instruction cache they start, and any edit in
+# front of them moves them: the merged backward launch of 8 experts x 16384 x 4096 x 7168, same loops, 17.44 ms with a loop at
+# the start of a line and 17.78 behind it; the call 21.96 / 22.19 / 21.90 ms (by chance aligned / moved / aligned by this).  The
+# padding costs where short loops nest (slots of the gate 6.4 -> 6.6 us), so the other sources go without.
+FILE_FLAGS = {"ffn.hip": ["-Xarch_device", "-falign-loops=64"]}
 
 
 def _stale() -> bool:
@@ -39,7 +40,7 @@ def _stale() -> bool:
 
 def _compile(src: str) -> str:
     obj = os.path.join(OBJ, src.replace(".hip", ".o"))
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:
