@@ -2,12 +2,16 @@
 // top-k selection held fixed.
 //
 //   E <= 16 : gate_bwd_fused (dlogits, dx and the dWg partial sums in one kernel) + gate_dwg_reduce.
-//   E  > 16 : gate_dlogits (one wave per token; norm_topk: dl[e_j] = w_j (dw_j - sum_j' w_j' dw_j'),
-//             otherwise dl[e] = sum_j dw_j p[e_j] (delta(e,e_j) - p[e]) with p = softmax(l)),
-//             gate_dx_wide (dx[t,m] (+)= sum_e dl[t,e] Wg[m,e]), gate_dwg_wide + gate_dwg_reduce.
+//   E  > 16 : with norm_topk and many experts per selected one, gate_dx_sparse (dlogits and dx) and gate_dwg_sparse, which take
+//             the selected experts only, + gate_dwg_reduce; otherwise gate_dlogits (one wave per token), gate_dx_wide (dx[t,m] (+)= sum_e dl[t,e]
+//             Wg[m,e]), gate_dwg_wide + gate_dwg_reduce.
+//   dl: norm_topk: dl[e_j] = w_j (dw_j - sum_j' w_j' dw_j'), otherwise dl[e] = sum_j dw_j p[e_j] (delta(e,e_j) - p[e]) with
+//   p = softmax(l).
 //   dWg[m,e] = sum_t x[t,m] dl[t,e] is formed as per-token-chunk fp32 partial sums followed by a
 //   fixed-order fp64 reduction (no atomics, so the result is the same on every run); dbias[e] =
 //   sum_t dl[t,e] rides along as an extra row m = M of the partials.
+#include <algorithm>
+
 #include "common.h"
 
 namespace {
@@ -96,12 +100,19 @@ __device__ __forceinline__ void st8g(void* base, int64_t off, const float* f) {
 // dWg[i] = sum over the chunks of partial[chunk][i], in a fixed order: the four waves of a block take
 // every fourth group of four chunks each (four running fp64 sums apiece, so sixteen loads are in flight
 // per output), and wave 0 adds the four results.
+// BY_EXPERT: the sums lie as [chunk][E][M], the bias rows [chunk][E] behind them all.
+template <bool BY_EXPERT>
 __global__ __launch_bounds__(256) void gate_dwg_reduce(const float* __restrict__ partial, int nchunk, int M, int E,
                                                        float* __restrict__ dWg, float* __restrict__ dbias) {
   __shared__ double red[4][64];
   const int o = threadIdx.x & 63, gq = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 64 + o;
-  const int64_t n = (int64_t)(M + 1) * E;
+  int64_t i = (int64_t)blockIdx.x * 64 + o;
+  int64_t n = (int64_t)(M + 1) * E;
+  const int64_t me = (int64_t)M * E, first = i;
+  if (BY_EXPERT) {
+    if (i < me) n = me;
+    else if (i < n) { partial += me * nchunk; i -= me; n = E; }
+  }
   double s[4] = {0, 0, 0, 0};
   if (i < n) {
     int c = gq * 4;
@@ -127,8 +138,8 @@ __global__ __launch_bounds__(256) void gate_dwg_reduce(const float* __restrict__
   __syncthreads();
   if (gq == 0 && i < n) {
     const double t = (red[0][o] + red[1][o]) + (red[2][o] + red[3][o]);
-    if (i < (int64_t)M * E) dWg[i] = (float)t;
-    else if (dbias) dbias[i - (int64_t)M * E] = (float)t;
+    if (first < me) dWg[BY_EXPERT ? i % M * E + i / M : i] = (float)t;
+    else if (dbias) dbias[first - me] = (float)t;
   }
 }
 
@@ -491,6 +502,362 @@ __global__ __launch_bounds__(256, 2) void gate_dwg_wide(const void* __restrict__
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// E > 16 and norm_topk: a token's dl row has its k selected experts' entries and zeros elsewhere, so both products only take
+// those.  The dense products multiply the zeros too, so that an infinity or a NaN in x or Wg makes a NaN of them: a slab or a
+// tile that holds one is multiplied with all experts.
+// ---------------------------------------------------------------------------------------------
+constexpr int SG_NT = 512, SG_NW = SG_NT / 64;
+
+// bits of a non-finite value in a 32-bit word as loaded
+template <bool BF16>
+__device__ __forceinline__ bool not_finite(uint32_t v) {
+  if (BF16) return (v & 0x7F80u) == 0x7F80u || (v & 0x7F800000u) == 0x7F800000u;
+  return (v & 0x7F800000u) == 0x7F800000u;
+}
+
+// dx and the dl rows.  A workgroup owns 64 columns of a run of tokens.  The columns' slab of Wg goes through LDS transposed
+// ([expert][column]); 16 lanes take a token's piece, 4 columns each, and add k rows of the slab.  The dl rows are stored on the
+// way, a part of them by each column block.  Bound by memory once the slab is there: 8192 x 2048, top-4 of 128, 23 us (71 MB),
+// against 65 us with all experts on the matrix cores and 5 for the dl rows; 16384 x 2048, top-2 of 64, 31 against 85 and 8.
+constexpr int SX_C = 64, SX_PITCH = SX_C + 4, SX_TPI = SG_NT / 16;   // columns; of the slab; tokens at a time
+constexpr int SX_U = 4;                                             // tokens per thread and step
+template <int EP> constexpr int sx_tokens() { return EP > 128 ? 128 : 256; }   // most tokens of a workgroup
+template <bool BF16, int EP>   // E <= EP
+__global__ __launch_bounds__(SG_NT, 4) void gate_dx_sparse(const float* __restrict__ dw, const float* __restrict__ w,
+                                                           const int32_t* __restrict__ idx, const float* __restrict__ Wg, int S,
+                                                           int M, int E, int k, float* __restrict__ dl_out,
+                                                           void* __restrict__ dx, int accumulate, int chunk) {
+  __shared__ __attribute__((aligned(16))) float wt[EP * SX_PITCH];
+  __shared__ __attribute__((aligned(16))) uint2 ent[sx_tokens<EP>() * MOE_MAX_K];   // (expert, dl); what is missing is (0, 0)
+  __shared__ int odd_s;
+  const int tid = threadIdx.x, k2 = (k + 1) & ~1, ncb = (int)gridDim.x, cx = (int)blockIdx.x, mb = cx * SX_C;
+  const int tb = (int)blockIdx.y * chunk, nt = min(chunk, S - tb);
+  const int c0 = 4 * (tid & 15), col = mb + c0, tq = tid >> 4;
+  const bool cok = col < M;
+  RawRow<BF16, 4> old[2][SX_U];
+  auto fetch = [&](int set, int t0) {
+#pragma unroll
+    for (int u = 0; u < SX_U; ++u) {
+      const int t = t0 + tq + u * SX_TPI;
+      if (accumulate && cok && t < nt) old[set][u].load(dx, (int64_t)(tb + t) * M + col); else old[set][u].zero();
+    }
+  };
+  if (tid == 0) odd_s = 0;
+  const bool vec = (E & 3) == 0;
+  constexpr int NV = SX_C * EP / 4 / SG_NT;        // pieces of 4 experts per thread: 8 lanes take 8 of a row, 8 rows to a wave
+  float4 wv[NV];
+  if (vec) {
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+      const int i = tid + n * SG_NT, m = (i >> 3) % SX_C, c = (i >> 3) / SX_C * 8 + (i & 7);
+      wv[n] = mb + m < M && 4 * c < E ? *reinterpret_cast<const float4*>(Wg + (int64_t)(mb + m) * E + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  fetch(0, 0);
+  if (tid < nt) {
+    const Picks p(dw, w, idx, tb + tid, k);
+#pragma unroll
+    for (int j = 0; j < MOE_MAX_K; ++j)
+      if (j < k2) ent[tid * k2 + j] = (unsigned)p.e[j] < (unsigned)E ? make_uint2((uint32_t)p.e[j], __float_as_uint(p.w[j] * (p.g[j] - p.inner)))
+                                                                   : make_uint2(0u, 0u);
+  }
+  __syncthreads();
+  bool odd = false;
+  if (vec) {
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+      const int i = tid + n * SG_NT, m = (i >> 3) % SX_C, c = (i >> 3) / SX_C * 8 + (i & 7);
+      const float f[4] = {wv[n].x, wv[n].y, wv[n].z, wv[n].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        wt[(4 * c + q) * SX_PITCH + m] = f[q];
+        odd |= not_finite<false>(__float_as_uint(f[q]));
+      }
+    }
+  } else {
+    for (int i = tid; i < SX_C * E; i += SG_NT) {
+      const int m = i / E, e = i - m * E;
+      const float v = mb + m < M ? Wg[(int64_t)mb * E + i] : 0.f;
+      wt[e * SX_PITCH + m] = v;
+      odd |= not_finite<false>(__float_as_uint(v));
+    }
+  }
+  if (odd) odd_s = 1;
+  {   // this column block's share of the dl rows
+    const int r0 = (int)((int64_t)nt * cx / ncb), n = ((int)((int64_t)nt * (cx + 1) / ncb) - r0) * E;
+    for (int i = tid; i < n; i += SG_NT) {
+      const int r = r0 + i / E, e = i % E;
+      float v = 0.f;
+      for (int j = 0; j < k2; ++j) {
+        const uint2 q = ent[r * k2 + j];
+        v += (int)q.x == e ? __uint_as_float(q.y) : 0.f;
+      }
+      dl_out[(int64_t)(tb + r0) * E + i] = v;
+    }
+  }
+  __syncthreads();
+  const bool dense = odd_s != 0;
+  auto step = [&](int set, int t0) {
+    float acc[SX_U][4];
+#pragma unroll
+    for (int u = 0; u < SX_U; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[u][q] = 0.f;
+    auto add = [&](int u, int e, float d) {
+      const float4 v = *reinterpret_cast<const float4*>(wt + e * SX_PITCH + c0);
+      acc[u][0] = fmaf(d, v.x, acc[u][0]); acc[u][1] = fmaf(d, v.y, acc[u][1]);
+      acc[u][2] = fmaf(d, v.z, acc[u][2]); acc[u][3] = fmaf(d, v.w, acc[u][3]);
+    };
+    const uint2* my[SX_U];
+#pragma unroll
+    for (int u = 0; u < SX_U; ++u) my[u] = ent + min(t0 + tq + u * SX_TPI, nt - 1) * k2;
+    if (__builtin_expect(!dense, 1)) {
+      for (int j = 0; j < k2; j += 2) {
+        uint4 q[SX_U];
+#pragma unroll
+        for (int u = 0; u < SX_U; ++u) q[u] = *reinterpret_cast<const uint4*>(my[u] + j);
+#pragma unroll
+        for (int u = 0; u < SX_U; ++u) {
+          add(u, (int)q[u].x, __uint_as_float(q[u].y));
+          add(u, (int)q[u].z, __uint_as_float(q[u].w));
+        }
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < SX_U; ++u)
+        for (int e = 0; e < E; ++e) {
+          float d = 0.f;
+          for (int j = 0; j < k2; ++j) d += (int)my[u][j].x == e ? __uint_as_float(my[u][j].y) : 0.f;
+          add(u, e, d);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < SX_U; ++u) {
+      const int t = t0 + tq + u * SX_TPI;
+      float o[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = old[set][u].get(q) + acc[u][q];
+      if (cok && t < nt) st4g<BF16>(dx, (int64_t)(tb + t) * M + col, o);
+    }
+  };
+  constexpr int STEP = SX_U * SX_TPI;
+  for (int t0 = 0; t0 < nt; t0 += 2 * STEP) {
+    if (t0 + STEP < nt) fetch(1, t0 + STEP);
+    step(0, t0);
+    if (t0 + STEP < nt) {
+      if (t0 + 2 * STEP < nt) fetch(0, t0 + 2 * STEP);
+      step(1, t0 + STEP);
+    }
+  }
+}
+
+// dWg, as partial sums: [chunk][E][M], the bias rows [chunk][E] behind them all.  A workgroup owns 128 columns, 2 to a lane, of
+// a chunk of tokens.  It takes the chunk in tiles, whose rows of x go to LDS and whose entries are sorted by expert (a stable
+// counting sort: ranks by ballots, no atomics); a wave adds the rows of every eighth expert (neighbours may be popular together).
+// Rounding.  The entries of a tile are added in two fp32 chains of at most four, these in fp64, the chunk's sum is rounded.  In
+// units of the last place of one entry, the variance that an entry adds is then (n + 1) / 2 for chains of n, and 1; for the one
+// chain per expert and dwg_chunk tokens that all experts are summed in, with n entries in it, (n + 1) / 2 alone.  So these sums are
+// no farther off from n = 4 there, or from 6 where the tile is longer than that chunk.  Below that (EXACT) the products are added in
+// fp64, which costs a fifth of the kernel.  Relative error of dWg, all experts and this: 8192 x 2048, top-4 of 128 (n = 4) 5.1e-8
+// and 4.9e-8, top-4 of 24 9.1e-8 and 5.3e-8; 4096 x 512, top-2 of 160 3.9e-8 and, EXACT, 3.6e-8 (4.5e-8 in fp32 chains).
+// Bound by the chain of LDS reads (entry, row of x) per four entries and by the sort's barriers: 8192 x 2048, top-4 of 128, 31 us
+// where reading x takes 6, against 54 us on the fp32 matrix cores; 16384 x 2048, top-2 of 64, 35 against 61.
+constexpr int SW_C = 128;
+template <bool BF16> constexpr int sw_tile() { return BF16 ? 128 : 64; }   // tokens
+template <bool BF16, int EP, bool EXACT>   // E <= EP
+__global__ __launch_bounds__(SG_NT, EP > 128 ? 2 : 4) void gate_dwg_sparse(const float* __restrict__ dw, const float* __restrict__ w,
+                                                                           const int32_t* __restrict__ idx,
+                                                                           const void* __restrict__ x, int S, int M, int E, int k,
+                                                                           float* __restrict__ partial, int chunk) {
+  constexpr int ESZ = BF16 ? 2 : 4, TT = sw_tile<BF16>(), NG = TT * MOE_MAX_K / 64, EPW = EP / SG_NW;
+  __shared__ __attribute__((aligned(16))) char xs[TT * SW_C * ESZ];
+  __shared__ __attribute__((aligned(16))) uint2 list[TT * MOE_MAX_K + 3 * EP];   // (row's place, dl) by expert, in runs of whole fours
+  __shared__ float2 raw[TT * MOE_MAX_K];                                     // (w, dw) in token order
+  __shared__ int hist[NG * EP], first[EP], total[EP], odd_s;
+  constexpr int ROW = SW_C * ESZ;    // bytes
+  struct XV {                        // a lane's two columns of a row, as stored
+    uint32_t r[ESZ / 2];
+    __device__ __forceinline__ float lo() const { return __uint_as_float(BF16 ? r[0] << 16 : r[0]); }
+    __device__ __forceinline__ float hi() const { return __uint_as_float(BF16 ? r[0] & 0xFFFF0000u : r[ESZ / 2 - 1]); }
+  };
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto xval = [&](uint32_t at) -> XV {
+    XV v;
+    if (BF16) {
+      v.r[0] = *reinterpret_cast<const uint32_t*>(xs + at + lane * 4);
+    } else {
+      const uint2 q = *reinterpret_cast<const uint2*>(xs + at + lane * 8);
+      v.r[0] = q.x; v.r[ESZ / 2 - 1] = q.y;
+    }
+    return v;
+  };
+  const int cw = (int)blockIdx.x, mb = cw * SW_C, part = (int)blockIdx.y, tb = part * chunk, te = min(S, tb + chunk);
+  constexpr int PPR = SW_C * ESZ / 16, UX = TT * PPR / SG_NT;         // 16-byte pieces per row; per thread
+  constexpr int GW = NG / SG_NW;                                      // groups of 64 entries per wave
+  static_assert(NG % SG_NW == 0, "groups are dealt evenly");
+  const int xc = mb + (tid % PPR) * (16 / ESZ);                       // M is a multiple of 8: a piece is in or out
+  uint4 xr[UX];
+  float pw[GW], pg[GW];
+  int pe[GW];
+  auto fetch = [&](int t0) {
+#pragma unroll
+    for (int q = 0; q < GW; ++q) {
+      const int i = (q * SG_NW + wave) * 64 + lane;
+      const bool in = i < min(TT, te - t0) * k;
+      const int64_t at = (int64_t)t0 * k + (in ? i : 0);
+      pw[q] = w[at]; pg[q] = dw[at]; pe[q] = in ? idx[at] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < UX; ++u) {
+      const int t = t0 + tid / PPR + u * (SG_NT / PPR);
+      xr[u] = t < te && xc < M ? *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(x) + ((int64_t)t * M + xc) * ESZ)
+                               : make_uint4(0u, 0u, 0u, 0u);
+    }
+  };
+  double acc[EPW][2];
+#pragma unroll
+  for (int i = 0; i < EPW; ++i) acc[i][0] = acc[i][1] = 0.0;
+  double bias = 0.0;     // lane i: sum of dl of expert SG_NW i + wave
+  fetch(tb);
+  for (int t0 = tb; t0 < te; t0 += TT) {
+    const int nt = min(TT, te - t0);
+    __syncthreads();   // the previous tile is consumed
+    if (tid == 0) odd_s = 0;
+    for (int i = tid; i < NG * EP; i += SG_NT) hist[i] = 0;
+    int e[GW];
+    float wj[GW], gj[GW];
+#pragma unroll
+    for (int q = 0; q < GW; ++q) {
+      raw[(q * SG_NW + wave) * 64 + lane] = make_float2(pw[q], pg[q]);
+      e[q] = (unsigned)pe[q] < (unsigned)E ? pe[q] : -1;
+      wj[q] = pw[q]; gj[q] = pg[q];
+    }
+    bool odd = false;
+#pragma unroll
+    for (int u = 0; u < UX; ++u) {
+      *reinterpret_cast<uint4*>(xs + (tid + u * SG_NT) * 16) = xr[u];
+      odd |= not_finite<BF16>(xr[u].x) | not_finite<BF16>(xr[u].y) | not_finite<BF16>(xr[u].z) | not_finite<BF16>(xr[u].w);
+    }
+    __syncthreads();
+    if (odd) odd_s = 1;
+    if (t0 + TT < te) fetch(t0 + TT);
+    int rank[GW], row[GW];
+    float d[GW];
+#pragma unroll
+    for (int q = 0; q < GW; ++q) {
+      const int i = (q * SG_NW + wave) * 64 + lane;
+      unsigned long long same = __ballot(e[q] >= 0);
+      rank[q] = 0; row[q] = 0; d[q] = 0.f;
+      if (same == 0) continue;
+      for (int bit = 1; bit < E; bit <<= 1) {
+        const unsigned long long has = __ballot((e[q] & bit) != 0);
+        same &= (e[q] & bit) ? has : ~has;
+      }
+      rank[q] = __popcll(same & ((1ull << lane) - 1ull));
+      if (e[q] >= 0) {
+        if (rank[q] == 0) hist[(q * SG_NW + wave) * EP + e[q]] = __popcll(same);
+        row[q] = i / k;
+        float inner = 0.f;
+        for (int j = 0; j < k; ++j) inner = fmaf(raw[row[q] * k + j].x, raw[row[q] * k + j].y, inner);
+        d[q] = wj[q] * (gj[q] - inner);
+      }
+    }
+    __syncthreads();
+    if (tid < EP) {
+      int h[NG], run = 0;
+#pragma unroll
+      for (int q = 0; q < NG; ++q) h[q] = hist[q * EP + tid];
+#pragma unroll
+      for (int q = 0; q < NG; ++q) {
+        hist[q * EP + tid] = run;
+        run += h[q];
+      }
+      total[tid] = run;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      constexpr int PL = EP / 64;     // experts per lane
+      int v[PL], sum = 0;
+#pragma unroll
+      for (int q = 0; q < PL; ++q) { v[q] = (total[lane * PL + q] + 3) & ~3; sum += v[q]; }
+      int incl = sum;
+#pragma unroll
+      for (int s = 1; s < 64; s <<= 1) {
+        const int o = __shfl_up(incl, s, 64);
+        if (lane >= s) incl += o;
+      }
+      int run = incl - sum;
+#pragma unroll
+      for (int q = 0; q < PL; ++q) { first[lane * PL + q] = run; run += v[q]; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < GW; ++q)
+      if (e[q] >= 0) list[first[e[q]] + hist[(q * SG_NW + wave) * EP + e[q]] + rank[q]] = make_uint2((uint32_t)(row[q] * ROW), __float_as_uint(d[q]));
+    if (tid < EP)
+      for (int u = total[tid]; u & 3; ++u) list[first[tid] + u] = make_uint2(0u, 0u);
+    __syncthreads();
+    const int my_e = SG_NW * (lane < EPW ? lane : 0) + wave;
+    int my_first = first[my_e], my_total = total[my_e];
+    const bool dense = odd_s != 0;
+#pragma unroll
+    for (int i = 0; i < EPW; ++i) {
+      asm volatile("" : "+v"(my_first), "+v"(my_total));   // (the reads of the lanes stay where they are)
+      const int m = __builtin_amdgcn_readlane(my_total, i);
+      if (m == 0 && !dense) continue;
+      const uint2* run = list + __builtin_amdgcn_readlane(my_first, i);
+      if (__builtin_expect(!dense, 1)) {
+        for (int u = 0; u < m; u += 8) {
+          float s[2][2] = {{0.f, 0.f}, {0.f, 0.f}}, sb[2] = {0.f, 0.f};   // !EXACT: two chains of at most four
+          auto four = [&](int o) {
+            const uint4 q0 = *reinterpret_cast<const uint4*>(run + o), q1 = *reinterpret_cast<const uint4*>(run + o + 2);
+            const XV v[4] = {xval(q0.x), xval(q0.z), xval(q1.x), xval(q1.z)};
+            const float d[4] = {__uint_as_float(q0.y), __uint_as_float(q0.w), __uint_as_float(q1.y), __uint_as_float(q1.w)};
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+              if (EXACT) {
+                acc[i][0] = fma((double)v[n].lo(), (double)d[n], acc[i][0]);
+                acc[i][1] = fma((double)v[n].hi(), (double)d[n], acc[i][1]);
+                if (cw == 0) bias += lane == i ? (double)d[n] : 0.0;
+              } else {
+                s[n & 1][0] = fmaf(v[n].lo(), d[n], s[n & 1][0]);
+                s[n & 1][1] = fmaf(v[n].hi(), d[n], s[n & 1][1]);
+                sb[n & 1] += d[n];
+              }
+            }
+          };
+          four(u);
+          if (u + 4 < m) four(u + 4);
+          if (!EXACT) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[i][c] += (double)s[0][c] + (double)s[1][c];
+            if (cw == 0) bias += lane == i ? (double)sb[0] + (double)sb[1] : 0.0;
+          }
+        }
+      } else {
+        int u = 0;
+        for (int t = 0; t < nt; ++t) {   // the run is in token order
+          float d = 0.f;
+          for (; u < m && run[u].x == (uint32_t)(t * ROW); ++u) d += __uint_as_float(run[u].y);
+          const XV v = xval((uint32_t)(t * ROW));
+          acc[i][0] = fma((double)v.lo(), (double)d, acc[i][0]);
+          acc[i][1] = fma((double)v.hi(), (double)d, acc[i][1]);
+          bias += lane == i ? (double)d : 0.0;
+        }
+      }
+    }
+  }
+  const int m = mb + 2 * lane;
+  float* out = partial + ((int64_t)part * E + wave) * M + m;
+#pragma unroll
+  for (int i = 0; i < EPW; ++i)
+    if (SG_NW * i + wave < E && m < M)
+      *reinterpret_cast<float2*>(out + (int64_t)(SG_NW * i) * M) = make_float2((float)acc[i][0], (float)acc[i][1]);
+  if (cw == 0 && lane < EPW && SG_NW * lane + wave < E)
+    partial[(int64_t)gridDim.y * M * E + (int64_t)part * E + SG_NW * lane + wave] = (float)bias;
+}
+
 }  // namespace
 
 extern "C" size_t moe_gate_bwd_workspace_bytes(int64_t S, int M, int E) {
@@ -532,7 +899,36 @@ extern "C" int moe_gate_bwd(const float* dw, const float* w, const int32_t* idx,
     if (bf) { if (EC == 8) MOE_FUSED(true, 8); else MOE_FUSED(true, 16); }
     else { if (EC == 8) MOE_FUSED(false, 8); else MOE_FUSED(false, 16); }
 #undef MOE_FUSED
-    hipLaunchKernelGGL(gate_dwg_reduce, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial, nrows, M, E, dWg,
+    hipLaunchKernelGGL(gate_dwg_reduce<false>, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial, nrows, M, E, dWg,
+                       dgate_bias);
+    return moe::check_launch();
+  }
+  const int chunk = dwg_chunk(S, E);
+  const int nchunk = (int)((S + chunk - 1) / chunk);   // the partial sums that the workspace holds
+  float* partial = (float*)ws;
+  // Only the selected experts where they are few.  The call, all experts and this, 8192 x 2048: top-4 of 128 126 and 60 us, top-4
+  // of 17 62 and 54, top-6 of 17 62 and 63, top-8 of 24 63 and 70, top-8 of 32 64 and 65; 16384 x 2048, top-2 of 64 145 and 62;
+  // 300 x 512, top-2 of 24 29 and 16.
+  if (norm && E > 4 * k) {
+    const int64_t tile_w = bf ? sw_tile<true>() : sw_tile<false>(), ncw = (M + SW_C - 1) / SW_C, ncx = (M + SX_C - 1) / SX_C;
+    auto chunks = [&](int64_t blocks, int64_t columns, int64_t most, int64_t tile) {   // tokens of a workgroup
+      const int64_t want = std::max<int64_t>(1, std::min(most, blocks / columns)), c = (S + want - 1) / want;
+      return (c + tile - 1) / tile * tile;
+    };
+    // dWg: two workgroups to a compute unit.  8192 x 2048, top-4 of 128, kernel and reduction: 256 of them 42 + 7 us, 512 32 + 8,
+    // 1024 40 + 12.
+    const int64_t chunk_w = chunks(512, ncw, nchunk, tile_w), chunk_x = std::min<int64_t>(chunks(1024, ncx, S, SX_TPI), E > 128 ? 128 : 256);
+    const int parts = (int)((S + chunk_w - 1) / chunk_w);
+    const dim3 gx((unsigned)ncx, (unsigned)((S + chunk_x - 1) / chunk_x)), gw((unsigned)ncw, (unsigned)parts);
+    const bool exact = (int64_t)chunk * k < (tile_w > chunk ? 6 : 4) * E;   // see gate_dwg_sparse
+#define MOE_SPARSE(BF, EP) do { \
+    hipLaunchKernelGGL((gate_dx_sparse<BF, EP>), gx, dim3(SG_NT), 0, st, dw, w, idx, Wg, (int)S, M, E, k, dlogits, dx, dx_accumulate, (int)chunk_x); \
+    if (exact) hipLaunchKernelGGL((gate_dwg_sparse<BF, EP, true>), gw, dim3(SG_NT), 0, st, dw, w, idx, x, (int)S, M, E, k, partial, (int)chunk_w); \
+    else hipLaunchKernelGGL((gate_dwg_sparse<BF, EP, false>), gw, dim3(SG_NT), 0, st, dw, w, idx, x, (int)S, M, E, k, partial, (int)chunk_w); } while (0)
+    if (bf) { if (E <= 64) MOE_SPARSE(true, 64); else if (E <= 128) MOE_SPARSE(true, 128); else MOE_SPARSE(true, 256); }
+    else { if (E <= 64) MOE_SPARSE(false, 64); else if (E <= 128) MOE_SPARSE(false, 128); else MOE_SPARSE(false, 256); }
+#undef MOE_SPARSE
+    hipLaunchKernelGGL(gate_dwg_reduce<true>, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial, parts, M, E, dWg,
                        dgate_bias);
     return moe::check_launch();
   }
@@ -544,13 +940,10 @@ extern "C" int moe_gate_bwd(const float* dw, const float* w, const int32_t* idx,
     else hipLaunchKernelGGL((gate_dx_wide<false, kg>), grid_dx, dim3(256), 0, st, dlogits, Wg, dx, S, M, E, dx_accumulate); } while (0)
   if (E <= 32) MOE_DX(4); else if (E <= 64) MOE_DX(8); else if (E <= 128) MOE_DX(16); else MOE_DX(32);
 #undef MOE_DX
-  const int chunk = dwg_chunk(S, E);
-  const int nchunk = (int)((S + chunk - 1) / chunk);
-  float* partial = (float*)ws;
   const dim3 grid_w((unsigned)((M + 4 * WW_COLS - 1) / (4 * WW_COLS)), (unsigned)nchunk, (unsigned)((E + 63) / 64));
   if (bf) hipLaunchKernelGGL(gate_dwg_wide<true>, grid_w, dim3(256), 0, st, x, dlogits, partial, S, M, E, chunk);
   else hipLaunchKernelGGL(gate_dwg_wide<false>, grid_w, dim3(256), 0, st, x, dlogits, partial, S, M, E, chunk);
-  hipLaunchKernelGGL(gate_dwg_reduce, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial, nchunk, M, E, dWg,
+  hipLaunchKernelGGL(gate_dwg_reduce<false>, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, partial, nchunk, M, E, dWg,
                      dgate_bias);
   return moe::check_launch();
 }
