@@ -2,13 +2,10 @@
 // (Section III-B): logits = x Wg (+bias), top-k, combine weights, capacity slots.
 //
 // Kernels (wave64 throughout):
-//   gate_logits_small_e : E <= 16, many tokens, fp32 activations.  One wave owns 64/EC tokens; lanes split M, so x is read
-//                         once, coalesced, 16 B per lane; Wg goes through LDS as fp64, shared
-//                         by the 8 waves of a block.  fp64 accumulation, then a halving
-//                         cross-lane reduction that leaves lane i with output i.
-//   gate_logits_mfma    : E > 16.  64 tokens x 64 experts per block on the fp64 matrix cores
-//                         (v_mfma_f64_16x16x4_f64), K chunks converted to fp64 on their way into LDS.
-//   gate_logits_split   : E <= 16, few tokens.  A block owns 2 or 4 tokens, its waves split M.
+//   gate_logits_split   : E <= 16, few tokens for their M.  A block owns 2 to 8 tokens, its waves split M.
+//   gate_logits_few     : 16 tokens x 16 experts per block on the fp64 matrix cores (v_mfma_f64_16x16x4_f64), the waves split M.
+//   gate_logits_mfma4   : E <= 8, many bf16 tokens: the matrix cores' form with four 4 x 4 blocks.
+//   gate_logits_mfma    : E > 16, many tokens.  64 tokens x 64 experts per block.
 //   gate_topk           : W lanes per token, k arg-max rounds (ties -> lower expert index); softmax weights;
 //                         per-block (choice, expert) histogram for the slot scan.  With a single token block it
 //                         assigns the slots as well.
@@ -18,6 +15,7 @@
 //                         slot = base + rank if < C; inverse map; -1 tails of inv.
 // The logits are accumulated in fp64 and rounded once to fp32, so the routing decision is
 // taken on the same fp32 numbers a double-precision reference produces.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -34,134 +32,11 @@ using namespace moe;
 
 constexpr int GATE_TB = 64;   // tokens per block in gate_topk / gate_slots (one per thread)
 
-template <bool BF16>
-__device__ __forceinline__ void load8(const void* base, int64_t elem_off, bool ok, float* f) {
-  if (!ok) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) f[i] = 0.f;
-    return;
-  }
-  if (BF16) {
-    const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(base) + elem_off);
-    unpack_bf16x8(v, f);
-  } else {
-    const float4* p = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + elem_off);
-    const float4 a = p[0], b = p[1];
-    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-  }
-}
-
 __device__ __forceinline__ double shfl_xor_f64(double v, int mask) {
   int lo = __double2loint(v), hi = __double2hiint(v);
   lo = __shfl_xor(lo, mask, 64);
   hi = __shfl_xor(hi, mask, 64);
   return __hiloint2double(hi, lo);
-}
-
-// EC = experts held per lane (E <= EC), T tokens per wave, NW waves per block (T EC a power of two <= 64).
-// The block walks M in chunks of 512.  Per chunk it converts Wg[chunk, :] to fp64 once into LDS (shared by
-// the NW T tokens of the block, laid out [8][64 lanes][EC] so that a lane's EC doubles are contiguous),
-// each lane takes 8 consecutive m of every one of its wave's T tokens
-// (16-byte loads of x, the next chunk requested before this one is multiplied) and runs T*EC fp64 FMAs per
-// m.  Blocks are small (4 waves, 4 or 2 tokens per wave) and light on registers so that several are
-// resident per compute unit: one block's barriers and Wg staging hide behind another's FMAs.
-template <int EC, bool BF16, int T, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 1) void gate_logits_small_e(const void* __restrict__ x, const float* __restrict__ Wg,
-                                                               const float* __restrict__ bias, float* __restrict__ logits,
-                                                               int64_t S, int M, int E) {
-  constexpr int NOUT = T * EC;
-  static_assert(NOUT >= 2 && NOUT <= 64 && (NOUT & (NOUT - 1)) == 0, "T * EC must be a power of two <= 64");
-  __shared__ double Ws[8 * 64 * EC];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t t0 = ((int64_t)blockIdx.x * NW + wave) * T;
-  double acc[NOUT];
-#pragma unroll
-  for (int i = 0; i < NOUT; ++i) acc[i] = 0.0;
-
-  typedef uint4 XRaw[BF16 ? 1 : 2];
-  XRaw xr[T], xn[T];
-  auto load_x = [&](XRaw* dst, int m0) {
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const bool ok = (t0 + t < S) && (m0 < M);
-      const int64_t off = (t0 + t) * (int64_t)M + m0;
-      if (BF16) {
-        dst[t][0] = ok ? *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(x) + off) : make_uint4(0, 0, 0, 0);
-      } else {
-        const uint4* p = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(x) + off);
-        dst[t][0] = ok ? p[0] : make_uint4(0, 0, 0, 0);
-        dst[t][BF16 ? 0 : 1] = ok ? p[1] : make_uint4(0, 0, 0, 0);
-      }
-    }
-  };
-  load_x(xr, lane * 8);
-  for (int mb = 0; mb < M; mb += 512) {
-    __syncthreads();  // previous chunk's Ws fully consumed
-    // slot i of the chunk, laid out [mm][expert pair][lane][2]: 16-byte reads at a 16-byte lane stride
-    // slot i of the chunk holds expert i % EC of row m = 8 (i / EC % 64) + i / (64 EC): LDS writes are
-    // contiguous (the Wg reads, 32-byte pieces, come from L2)
-    for (int i = tid; i < 512 * EC; i += 64 * NW) {
-      const int e = i % EC, lp = (i / EC) & 63, mm = i / (64 * EC);
-      const int m = mb + lp * 8 + mm;
-      Ws[i] = (double)((m < M && e < E) ? Wg[(int64_t)m * E + e] : 0.f);
-    }
-    __syncthreads();
-    const bool more = mb + 512 < M;
-    if (more) load_x(xn, mb + 512 + lane * 8);
-#pragma unroll
-    for (int mm = 0; mm < 8; ++mm) {
-      double wd[EC];
-#pragma unroll
-      for (int e = 0; e < EC; ++e) wd[e] = Ws[(mm * 64 + lane) * EC + e];
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        float xf;
-        if (BF16) {
-          const uint32_t word = (&xr[t][0].x)[mm >> 1];
-          xf = __uint_as_float((mm & 1) ? (word & 0xFFFF0000u) : (word << 16));
-        } else {
-          xf = __uint_as_float((&xr[t][mm >> 2].x)[mm & 3]);
-        }
-        const double xd = (double)xf;
-#pragma unroll
-        for (int e = 0; e < EC; ++e) acc[t * EC + e] = fma(xd, wd[e], acc[t * EC + e]);
-      }
-    }
-    if (more) {
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        xr[t][0] = xn[t][0];
-        if (!BF16) xr[t][BF16 ? 0 : 1] = xn[t][BF16 ? 0 : 1];
-      }
-    }
-  }
-  // halving reduction over the lanes: after the step with lane mask lm a lane whose bit lm is set holds
-  // the upper half of its value list, summed with its partner's; once a single value is left the
-  // remaining lane bits are plain butterfly sums.  At the end lane l holds value l >> log2(64 / NOUT).
-#pragma unroll
-  for (int st = 0; st < 6; ++st) {
-    const int lm = 32 >> st;
-    if ((NOUT >> st) > 1) {
-      const int h = NOUT >> (st + 1);
-      const bool up = (lane & lm) != 0;
-#pragma unroll
-      for (int i = 0; i < h; ++i) {
-        const double keep = up ? acc[i + h] : acc[i];
-        const double send = up ? acc[i] : acc[i + h];
-        acc[i] = keep + shfl_xor_f64(send, lm);
-      }
-    } else {
-      acc[0] += shfl_xor_f64(acc[0], lm);
-    }
-  }
-  constexpr int REP = 64 / NOUT;          // lanes holding the same value
-  const int o = lane / REP;
-  const int t = o / EC, e = o % EC;
-  if (lane % REP == 0 && t0 + t < S && e < E) {
-    double v = acc[0];
-    if (bias) v += (double)bias[e];
-    logits[(t0 + t) * E + e] = (float)v;
-  }
 }
 
 // E <= 16 and few tokens, where the latency of one block's walk along M is the time of the call: a block owns T
@@ -228,7 +103,9 @@ __global__ __launch_bounds__(64 * LS_MAXW) void gate_logits_split(const void* __
       }
     }
   }
-  // halving reduction over the lanes, as in gate_logits_small_e
+  // halving reduction over the lanes: after the step with lane mask lm a lane whose bit lm is set holds
+  // the upper half of its value list, summed with its partner's; once a single value is left the
+  // remaining lane bits are plain butterfly sums.  At the end lane l holds value l >> log2(64 / NOUT).
 #pragma unroll
   for (int st = 0; st < 6; ++st) {
     const int lm = 32 >> st;
@@ -258,102 +135,148 @@ __global__ __launch_bounds__(64 * LS_MAXW) void gate_logits_split(const void* __
 }
 
 // E > 16: fp64 matrix cores.  v_mfma_f64_16x16x4_f64 multiplies a 16 x 4 by a 4 x 16 tile of doubles (lane l
-// supplies A[l % 16][l / 16] and B[l / 16][l % 16], and receives D[4 r + l / 16][l % 16], r = 0..3).  A block of
-// 4 waves owns 64 tokens x 64 experts (grid.y walks the expert blocks), a wave 16 tokens x 64 experts (four
-// accumulator tiles).  M is walked in chunks of 32: x and Wg are converted to fp64 once on their way into LDS
-// ([k][token] and [k][expert], pitch 80 doubles so that the two k planes of a 32-lane access fall into
-// different banks), in two buffers: the next chunk is converted and stored between the current one's products, and the
-// one after it requested.
+// supplies A[l % 16][l / 16] and B[l / 16][l % 16], and receives D[4 r + l / 16][l % 16], r = 0..3).  Which k a quarter of the
+// lanes feeds in which step is free as long as both operands agree: of a chunk of 32 it takes 8 consecutive ones, one a
+// step, so that a token's operand is what lies in memory and needs no LDS.
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
-constexpr int LM_KC = 32, LM_PITCH = 80;
-// KW = 2: two such groups of four waves take alternate chunks and add their sums through LDS at the end, so that a
-// compute unit that gets one block still has two waves per SIMD, one's conversions and fetches under the other's matrix
-// instructions (256 blocks: 128 -> 102 us for 16384 x 2048 x 64).
+constexpr int LM_KC = 32;
+// 8 consecutive values of a token, as stored
+template <bool BF16>
+struct TokenPiece {
+  uint4 r[BF16 ? 1 : 2];
+  __device__ __forceinline__ void load(const void* row, int k, int M) {   // zeros behind the last one
+    const uint4* p = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(row) + (int64_t)(k < M ? k : 0) * (BF16 ? 2 : 4));
+#pragma unroll
+    for (int i = 0; i < (BF16 ? 1 : 2); ++i) {
+      const uint4 v = p[i];
+      r[i] = k < M ? v : make_uint4(0u, 0u, 0u, 0u);
+    }
+  }
+  __device__ __forceinline__ double get(int i) const {
+    if (BF16) {
+      const uint32_t v = (&r[0].x)[i >> 1];
+      return (double)__uint_as_float((i & 1) ? (v & 0xFFFF0000u) : (v << 16));
+    }
+    return (double)__uint_as_float((&r[BF16 ? 0 : i >> 2].x)[i & 3]);
+  }
+};
+
+// Many tokens.  A block owns 64 tokens x 64 experts (grid.y walks the expert blocks); KW groups of four waves take alternate
+// chunks of M and add their sums through LDS at the end; a wave owns 16 tokens x 64 experts (four accumulator tiles).  The
+// weights are converted once per group on their way into LDS ([k][expert], pitch 66 doubles: the two k rows of a 32-lane read
+// fall into different halves of the banks), in two buffers: the next chunk is converted and stored between the current
+// one's products, and the one after it requested.
+// Bound by the fp64 matrix rate (77 TFLOP/s for the bare instruction) less the vector instructions between (a conversion costs
+// a tenth of a matrix instruction): one per matrix instruction here, and four waves per SIMD, so that they, the barriers and the
+// fetches hide behind other waves' products.  The fetches stand in no branch, so that the compiler can wait for them by count.
+// 16384 x 2048 x 64: 91 us with both operands staged, two waves per SIMD and guarded fetches -> 68 us (63 TFLOP/s).
+constexpr int LM_PITCH = 66;
 template <bool BF16, int KW>
-__global__ __launch_bounds__(256 * KW) void gate_logits_mfma(const void* __restrict__ x, const float* __restrict__ Wg,
-                                                        const float* __restrict__ bias, float* __restrict__ logits,
-                                                        int64_t S, int M, int E) {
-  __shared__ double stage_s[KW][2][2][LM_KC * LM_PITCH];   // two chunks of x and Wg per group
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6, kw = KW == 1 ? 0 : threadIdx.x >> 8;
+__global__ __launch_bounds__(256 * KW, 4) void gate_logits_mfma(const void* __restrict__ x, const float* __restrict__ Wg,
+                                                                const float* __restrict__ bias, float* __restrict__ logits,
+                                                                int64_t S, int M, int E) {
+  constexpr int BUF = LM_KC * LM_PITCH, RED = (KW - 1) * 256 * 17;
+  __shared__ double smem[KW * 2 * BUF > RED ? KW * 2 * BUF : RED];
+  const int tid = threadIdx.x & 255, lane = tid & 63;
+  const int kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t tb = (int64_t)blockIdx.x * 64;
-  const int e0 = blockIdx.y * 64;
-  // staging roles: x -> token tid / 4, k offset 8 (tid % 4); Wg -> expert tid % 64, k rows tid / 64 + 4 u
-  const int xt = tid >> 2, xk = (tid & 3) * 8;
-  const int wk = tid >> 6, we = tid & 63;
-  uint4 xraw[BF16 ? 1 : 2];
-  float wraw[8];
-  auto fetch = [&](int k0) {
-    const bool xok = (tb + xt < S) && (k0 + xk < M);     // M % 8 == 0: the 8 elements are in or out together
-    const int64_t xo = (tb + xt) * (int64_t)M + k0 + xk;
-    if (BF16) {
-      xraw[0] = xok ? *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(x) + xo) : make_uint4(0, 0, 0, 0);
-    } else {
-      const uint4* p = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(x) + xo);
-      xraw[0] = xok ? p[0] : make_uint4(0, 0, 0, 0);
-      xraw[BF16 ? 0 : 1] = xok ? p[1] : make_uint4(0, 0, 0, 0);
-    }
-    const float* wp = Wg + (int64_t)(k0 + wk) * E + e0 + we;
+  const int e0 = blockIdx.y * 64, kq = 8 * (lane >> 4);
+  double* ws = smem + kw * 2 * BUF;
+  constexpr uint32_t ESZ = BF16 ? 2 : 4;
+  // Fetches go through descriptors that start at the chunk: a lane's offset (bytes) stays, the rest is uniform.  What does not
+  // exist is fetched from somewhere else inside the tensor: tokens and experts past the end are not stored, values of k
+  // past the end are zeroed in both operands (only the last chunk can have some).
+  const int t = (int)min((int64_t)(wave * 16 + (lane & 15)), S - 1 - tb);
+  const uint32_t xo = (uint32_t)t * (uint32_t)M * ESZ, xk = (uint32_t)kq * ESZ;   // 64 M ESZ < 2^32 (the host's check)
+  const int k_last = (M - 1) / LM_KC * LM_KC;      // a chunk behind it is fetched from there, and counts as zeros
+  auto fetch_x = [&](TokenPiece<BF16>& d, int k0) {
+    k0 = min(k0, k_last);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(reinterpret_cast<const char*>(x)) + (tb * M + k0) * ESZ, 0, 0xFFFFFFF0u, 0x00020000);
+    const uint32_t off = xo + (k0 + LM_KC <= M ? xk : k0 + kq < M ? xk : 0u);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) wraw[u] = (k0 + wk + 4 * u < M && e0 + we < E) ? wp[(int64_t)(4 * u) * E] : 0.f;
+    for (int i = 0; i < (BF16 ? 1 : 2); ++i) {
+      typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+      const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 16 * i, 0);
+      d.r[i] = make_uint4(v.x, v.y, v.z, v.w);
+    }
   };
-  auto stage = [&](int buf) {
-    double* xs = stage_s[kw][buf][0];
-    double* ws = stage_s[kw][buf][1];
-    float xf[8];
-    if (BF16) {
-      unpack_bf16x8(xraw[0], xf);
-    } else {
-      xf[0] = __uint_as_float(xraw[0].x); xf[1] = __uint_as_float(xraw[0].y); xf[2] = __uint_as_float(xraw[0].z);
-      xf[3] = __uint_as_float(xraw[0].w); xf[4] = __uint_as_float(xraw[BF16 ? 0 : 1].x); xf[5] = __uint_as_float(xraw[BF16 ? 0 : 1].y);
-      xf[6] = __uint_as_float(xraw[BF16 ? 0 : 1].z); xf[7] = __uint_as_float(xraw[BF16 ? 0 : 1].w);
+  // staging: expert tid % 64, k rows tid / 64 + 4 u
+  const uint32_t we = (uint32_t)min(e0 + (tid & 63), E - 1) * 4u;
+  float wraw[8];
+  auto fetch_w = [&](int k0) {
+    k0 = min(k0, k_last);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wg) + (int64_t)k0 * E, 0, 0xFFFFFFF0u, 0x00020000);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      wraw[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)we, min(wave + 4 * u, M - 1 - k0) * E * 4, 0));
+  };
+  auto stage_w = [&](int buf, int k0) {
+    if (k0 + LM_KC > M) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) wraw[u] = k0 + wave + 4 * u < M ? wraw[u] : 0.f;
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) xs[(xk + u) * LM_PITCH + xt] = (double)xf[u];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) ws[(wk + 4 * u) * LM_PITCH + we] = (double)wraw[u];
+    for (int u = 0; u < 8; ++u) ws[buf * BUF + (wave + 4 * u) * LM_PITCH + (tid & 63)] = (double)wraw[u];
   };
   f64x4_t acc[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) acc[j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-
-  const int nch = (M + LM_KC * KW - 1) / (LM_KC * KW);   // chunks of this group (one past the end is zeros)
-  auto chunk = [&](int c) { return (c * KW + kw) * LM_KC; };
-  fetch(chunk(0));
-  stage(0);
-  if (nch > 1) fetch(chunk(1));
-  for (int c = 0; c < nch; ++c) {
+  const int nch = (M + LM_KC * KW - 1) / (LM_KC * KW);
+  auto chunk = [&](int c) { return (c * KW + kw) * LM_KC; };   // a group's last one may lie behind the end
+  TokenPiece<BF16> piece[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    fetch_x(piece[c], chunk(c));
+    fetch_w(chunk(c));
+    if (c == 0) stage_w(0, chunk(0));
+  }
+  auto step = [&](int c, auto set) {
+    constexpr int SET = decltype(set)::value;
     __syncthreads();   // chunk c is staged, and the other buffer is consumed
-    const double* xs = stage_s[kw][c & 1][0] + (lane >> 4) * LM_PITCH + wave * 16 + (lane & 15);
-    const double* ws = stage_s[kw][c & 1][1] + (lane >> 4) * LM_PITCH + (lane & 15);
+    const int k0 = chunk(c), k1 = chunk(c + 1), k2 = chunk(c + 2);
+    if (k0 + LM_KC > M && k0 + kq >= M) {
+#pragma unroll
+      for (int i = 0; i < (BF16 ? 1 : 2); ++i) piece[SET].r[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    const double* w = ws + SET * BUF + kq * LM_PITCH + (lane & 15);
     auto products = [&](int s0) {
 #pragma unroll
-      for (int s4 = s0; s4 < s0 + LM_KC / 8; ++s4) {
-        const double a = xs[4 * s4 * LM_PITCH];
+      for (int s = s0; s < s0 + 4; ++s) {
+        const double a = piece[SET].get(s);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, ws[4 * s4 * LM_PITCH + j * 16], acc[j], 0, 0, 0);
+        for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, w[s * LM_PITCH + j * 16], acc[j], 0, 0, 0);
       }
     };
     products(0);
-    if (c + 1 < nch) stage((c + 1) & 1);
-    if (c + 2 < nch) fetch(chunk(c + 2));
-    products(LM_KC / 8);
+    stage_w(SET ^ 1, k1);
+    fetch_w(k2);
+    products(4);
+    fetch_x(piece[SET], k2);
+  };
+  int c = 0;
+  for (; c + 1 < nch; c += 2) {
+    step(c, std::integral_constant<int, 0>{});
+    step(c + 1, std::integral_constant<int, 1>{});
   }
-  if constexpr (KW == 2) {
+  if (c < nch) step(c, std::integral_constant<int, 0>{});
+  if constexpr (KW > 1) {
     __syncthreads();
-    double* red = &stage_s[0][0][0][0] + (wave * 64 + lane) * 17;   // 17: lanes on different banks
-    static_assert(256 * 17 <= KW * 4 * LM_KC * LM_PITCH, "the sums fit in the staging buffers");
-    if (kw == 1) {
+    double* red = smem + (wave * 64 + lane) * 17;   // 17: lanes on different banks
+    if (kw > 0) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[4 * j + r] = acc[j][r];
+        for (int r = 0; r < 4; ++r) red[(kw - 1) * 256 * 17 + 4 * j + r] = acc[j][r];
     }
     __syncthreads();
-    if (kw == 1) return;
+    if (kw > 0) return;
+#pragma unroll 1
+    for (int g = 0; g < KW - 1; ++g)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[j][r] += red[4 * j + r];
+        for (int r = 0; r < 4; ++r) acc[j][r] += red[g * 256 * 17 + 4 * j + r];
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -362,13 +285,58 @@ __global__ __launch_bounds__(256 * KW) void gate_logits_mfma(const void* __restr
     const double bj = bias ? (double)bias[e] : 0.0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t t = tb + wave * 16 + 4 * r + (lane >> 4);
-      if (t < S) logits[t * E + e] = (float)(acc[j][r] + bj);
+      const int64_t to = tb + wave * 16 + 4 * r + (lane >> 4);
+      if (to < S) logits[to * E + e] = (float)(acc[j][r] + bj);
     }
   }
 }
 
-// E <= 16 and many tokens: the fp64 matrix cores in their 4-block form.  v_mfma_f64_4x4x4_4b_f64 multiplies
+// Few tokens: a block owns 16 tokens x 16 experts, and its waves split M; both operands come from memory, whose values the
+// lanes convert.  The time is the walk of one wave along M, so that the more compute units take part the better; with every one
+// busy it is the fp64 matrix rate.  The gate's call: 512 x 4096, 64 experts, 189 us with 64 x 64 tiles (8 compute units) -> 23;
+// 4096 x 2048, 64 experts, 100 -> 37; 16384 x 4096, 16 experts, 198 us with the 4-block form and 399 in fp32 with vector FMAs -> 61
+// and 70.  Requests of four chunks at a time measured no better (4096 x 2048, 128 experts, 70 -> 82 us), nor did 32 experts per wave.
+constexpr int LF_NW = 16;
+template <bool BF16>
+__global__ __launch_bounds__(64 * LF_NW, 4) void gate_logits_few(const void* __restrict__ x, const float* __restrict__ Wg,
+                                                                 const float* __restrict__ bias, float* __restrict__ logits,
+                                                                 int64_t S, int M, int E) {
+  __shared__ double red[LF_NW][4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int64_t tb = (int64_t)blockIdx.x * 16;
+  const int e0 = blockIdx.y * 16, kq = 8 * (lane >> 4);
+  const int64_t t = min(tb + (lane & 15), S - 1);     // past the end: any row and any expert, not stored
+  const void* row = reinterpret_cast<const char*>(x) + t * (int64_t)M * (BF16 ? 2 : 4);
+  const float* wcol = Wg + min(e0 + (lane & 15), E - 1);
+  f64x4_t acc[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) acc[i] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  for (int k0 = wave * LM_KC; k0 < M; k0 += nw * LM_KC) {
+    const int k = k0 + kq;      // M % 8 == 0: a lane's 8 values are in or out together
+    TokenPiece<BF16> a;
+    a.load(row, k, M);
+    float w[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const float v = wcol[(int64_t)((k < M ? k : 0) + s) * E];
+      w[s] = k < M ? v : 0.f;
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s) acc[s & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.get(s), (double)w[s], acc[s & 1], 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][r][lane] = acc[0][r] + acc[1][r];
+  __syncthreads();
+  for (int i = threadIdx.x; i < 256; i += blockDim.x) {
+    const int r = i >> 6, l = i & 63, e = e0 + (l & 15);
+    double v = 0.0;
+    for (int q = 0; q < nw; ++q) v += red[q][r][l];
+    const int64_t to = tb + 4 * r + (l >> 4);
+    if (to < S && e < E) logits[to * E + e] = (float)(bias ? v + (double)bias[e] : v);
+  }
+}
+
+// E <= 8 and many tokens: the fp64 matrix cores in their 4-block form.  v_mfma_f64_4x4x4_4b_f64 multiplies
 // four independent 4 x 4 tiles by 4 x 4 tiles (k = 4) per instruction: lane l = 16 kk + 4 blk + i supplies
 // A_blk[i][kk] and B_blk[kk][i], and receives D_blk[l / 16][l % 4] for blk = (l / 4) % 4 (layout confirmed with
 // a one-wave probe).  On this chip the instruction runs on the fp64 vector units at their FMA rate (16
@@ -377,7 +345,7 @@ __global__ __launch_bounds__(256 * KW) void gate_logits_mfma(const void* __restr
 // instruction.  The conversion bf16 -> fp64 costs 20 cycles per 64 values (v_cvt_f64_f32 is quarter rate),
 // as much as 1.25 matrix instructions, so each value is converted exactly once per wave: the four blocks are
 // four token groups (16 tokens per instruction) and the experts are taken in NP passes of 4 that share the
-// converted A operand (NP = 1, 2, 4 for E <= 4, 8, 16).
+// converted A operand (NP = 1, 2 for E <= 4, 8).
 //   x:  fetched with whole-line requests (a lane takes 16 bytes, eight consecutive lanes one 128-byte piece
 //       of a token row = 64 m, one instruction 8 rows) three steps ahead into registers, then passed through
 //       a wave-private LDS region to reach the operand layout, in which neighbouring lanes hold DIFFERENT
@@ -858,7 +826,21 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     const bool bf = x_dtype == MOE_BF16;
     const size_t esz = bf ? 2 : 4;
     const void* xs = (const char*)x + (size_t)mp_idx * S * M * esz;
-    if (E <= 16 && bf && S >= 8192 && (uint64_t)S * (uint64_t)M * 2 <= 0xFFFFFFF0ull) {
+    auto launch_few = [&]() {
+      const dim3 grid((unsigned)((S + 15) / 16), (unsigned)((E + 15) / 16)), block(64 * std::min(LF_NW, (M + LM_KC - 1) / LM_KC));
+      if (bf) hipLaunchKernelGGL(gate_logits_few<true>, grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E);
+      else hipLaunchKernelGGL(gate_logits_few<false>, grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E);
+    };
+    // Up to 16 experts.  The 16 x 16 tiles cost the same whatever S, M and E: 8192 x 1024 17 us (the call), 16384 x 4096 61, fp32 29 at
+    // 16384 x 1024.  The others are faster
+    // - with few tokens for their M, where the walk along M is the time (split): 8 experts, 512 x 1024 13.5 and 14.0, 4096 x 4096 20 and
+    //   23, but 2048 x 1024 15.7 and 14.3; 16 experts, 512 x 1024 15.5 and 13.8, 1024 x 4096 20 and 22, 4096 x 4096 41 and 23;
+    // - with many tokens in bf16, where 8 or 4 columns are not multiplied (mfma4): 8 experts, 8192 x 1024 18.3 and 17.4, 16384 x 1024
+    //   19 and 24, 32768 x 4096 69 and 114; 2 experts, 8192 x 1024 14 and 16; but 16 experts, 32768 x 4096 126 and 114.
+    const bool rows32 = (uint64_t)S * (uint64_t)M * 2 <= 0xFFFFFFF0ull;
+    const int64_t m2 = (int64_t)M * M;
+    const bool split = S < (E <= 8 ? std::max<int64_t>(1024, m2 / 2048) : std::max<int64_t>(512, m2 / 4096)) && S < 8192;
+    if (bf && E <= 8 && S >= (E <= 4 ? 8192 : 16384) && rows32) {
       // fp64 matrix cores; TW token waves (32 tokens each) per block so that the grid has about two blocks per
       // compute unit or more
       const int tw = S >= 512 * 4 * 32 ? 4 : S >= 512 * 2 * 32 ? 2 : 1;
@@ -867,11 +849,11 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
       const bf16_t* xb = (const bf16_t*)xs;
 #define LAUNCH_M4(np, tw_) hipLaunchKernelGGL((gate_logits_mfma4<np, tw_>), grid, block, 0, st, xb, Wg, gate_bias, logits, S, M, E)
 #define LAUNCH_M4_TW(np) do { if (tw == 4) LAUNCH_M4(np, 4); else if (tw == 2) LAUNCH_M4(np, 2); else LAUNCH_M4(np, 1); } while (0)
-      if (E <= 4) LAUNCH_M4_TW(1); else if (E <= 8) LAUNCH_M4_TW(2); else LAUNCH_M4_TW(4);
+      if (E <= 4) LAUNCH_M4_TW(1); else LAUNCH_M4_TW(2);
 #undef LAUNCH_M4_TW
 #undef LAUNCH_M4
-    } else if (E <= 16 && S < 8192 && (uint64_t)M * E * 4 < (1ull << 31)) {   // 32-bit offsets into Wg
-      // Few tokens: as many waves over M as it has pieces.  From a thousand tokens on, twice the tokens per block (half the
+    } else if (E <= 16 && split && (uint64_t)M * E * 4 < (1ull << 31)) {   // 32-bit offsets into Wg
+      // As many waves over M as it has pieces.  From a thousand tokens on, twice the tokens per block (half the
       // weight traffic and conversions) and waves that walk several pieces, about 2048 of them in all, so that the
       // reduction at a wave's end does not outweigh its products.
       const bool many = S >= 1024;
@@ -891,24 +873,21 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
 #undef LAUNCH_SPLIT_E
 #undef LAUNCH_SPLIT
     } else if (E <= 16) {
-      // fp32 activations (or token rows past 32-bit offsets)
-      const int EC = E <= 8 ? 8 : 16;
-      const int T = E <= 8 ? 4 : 2;
-      // 8-wave blocks halve the Wg staging work per token (bf16: rows past 4 GiB are many tokens); fp32 keeps blocks of 4
-      const int nw = (S >= 16384 && bf) ? 8 : 4;
-      const dim3 grid((unsigned)((S + nw * T - 1) / (nw * T))), block(64 * nw);
-#define LAUNCH_SMALL(ec, t) do { \
-    if (bf && nw == 8) hipLaunchKernelGGL((gate_logits_small_e<ec, true, t, 8>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E); \
-    else if (bf) hipLaunchKernelGGL((gate_logits_small_e<ec, true, t, 4>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E); \
-    else hipLaunchKernelGGL((gate_logits_small_e<ec, false, t, 4>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E); } while (0)
-      if (EC == 8) LAUNCH_SMALL(8, 4); else LAUNCH_SMALL(16, 2);
-#undef LAUNCH_SMALL
+      launch_few();
     } else {
+      // 16 x 16 tiles while 64 x 64 ones are at most 128 (half of the compute units).  The call, 64 x 64 and 16 x 16: 512 x 4096, 64
+      // experts (8) 189 and 23 us; 4096 x 2048, 64 (64) 77 and 37; 128 (128) 82 and 71; 6144 x 2048, 128 (192) 80 and 93.
+      // Four groups over M while there is one block per compute unit, 16384 x 2048, 64 experts: 81 us, two 86.
       const dim3 grid((unsigned)((S + 63) / 64), (unsigned)((E + 63) / 64));
-      const bool two = (uint64_t)grid.x * grid.y <= 256 && M > LM_KC;   // at most one block per compute unit
+      const uint64_t tiles = (uint64_t)grid.x * grid.y;
 #define LAUNCH_WIDE(bf_, kw_) hipLaunchKernelGGL((gate_logits_mfma<bf_, kw_>), grid, dim3(256 * kw_), 0, st, xs, Wg, gate_bias, logits, S, M, E)
-      if (bf) { if (two) LAUNCH_WIDE(true, 2); else LAUNCH_WIDE(true, 1); }
-      else { if (two) LAUNCH_WIDE(false, 2); else LAUNCH_WIDE(false, 1); }
+      if (tiles <= 128 || M >= 1 << 24) {   // (the other kernel has 32-bit offsets within a block's tokens)
+        launch_few();
+      } else if (tiles <= 256) {
+        if (bf) LAUNCH_WIDE(true, 4); else LAUNCH_WIDE(false, 4);
+      } else {
+        if (bf) LAUNCH_WIDE(true, 2); else LAUNCH_WIDE(false, 2);
+      }
 #undef LAUNCH_WIDE
     }
   }
