@@ -9,6 +9,7 @@
 //   gate_topk           : W lanes per token, k arg-max rounds (ties -> lower expert index); softmax weights;
 //                         per-block (choice, expert) histogram for the slot scan.  With a single token block it
 //                         assigns the slots as well.
+//                         (Up to 16 experts and three choices of few tokens the logits kernels do this.)
 //   gate_scan           : one wave per expert; exclusive scan of the histograms over token blocks and
 //                         over choices (choice-major priority), per-expert demand counts.
 //   gate_slots          : rank of each (token, choice) inside its block via wave ballots,
@@ -39,6 +40,41 @@ __device__ __forceinline__ double shfl_xor_f64(double v, int mask) {
   return __hiloint2double(hi, lo);
 }
 
+constexpr int TOPK_MAX = 3;
+struct TopK {      // what a logits kernel that also selects the experts writes (k = 0: it does not)
+  int k, norm;
+  int32_t* idx;
+  float* w;
+};
+// Top-k of one token by one thread, whose logits it holds: v[0 .. E - 1], E <= EPL.  The same steps as in gate_topk, where a lane holds
+// all of a token's experts: the k rounds are a loop, so that there is little code to fetch.  sel takes the chosen logits, `stride` apart,
+// in LDS.
+template <int EPL>
+__device__ __forceinline__ void pick_experts(const float (&v)[EPL], int E, int k, int norm_topk, float* sel, int stride,
+                                             int32_t* __restrict__ idx, float* __restrict__ w) {
+  unsigned taken = E < 32 ? ~0u << E : 0u;
+  float mx = 0.f, den = 0.f;
+  for (int j = 0; j < k; ++j) {
+    float cv = 0.f;
+    int ce = 0x7fffffff;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i)
+      if (!(taken & (1u << i)) && (ce == 0x7fffffff || v[i] > cv)) { cv = v[i]; ce = i; }
+    taken |= 1u << (ce & 31);
+    if (j == 0) mx = cv;
+    den += expf(cv - mx);
+    sel[j * stride] = cv;
+    idx[j] = min(ce, E - 1);
+  }
+  if (!norm_topk) {   // weights over all experts instead of the selected ones
+    den = 0.f;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i)
+      if (i < E) den += expf(v[i] - mx);
+  }
+  for (int j = 0; j < k; ++j) w[j] = expf(sel[j * stride] - mx) / den;
+}
+
 // E <= 16 and few tokens, where the latency of one block's walk along M is the time of the call: a block owns T
 // tokens and its waves split M (pieces of 128, 2 consecutive m per lane).  A lane's weights are 2 E consecutive floats,
 // read from L2 (with E = EC as 16-byte pieces) and converted once for the T tokens; the waves' sums are added through
@@ -50,10 +86,11 @@ constexpr int LS_MAXW = 8;
 template <int EC, bool BF16, int T, bool FULL>   // FULL: E = EC
 __global__ __launch_bounds__(64 * LS_MAXW) void gate_logits_split(const void* __restrict__ x, const float* __restrict__ Wg,
                                                                   const float* __restrict__ bias, float* __restrict__ logits,
-                                                                  int64_t S, int M, int E) {
+                                                                  int64_t S, int M, int E, const TopK tk) {
   constexpr int NOUT = T * EC;
   static_assert(NOUT == 32 || NOUT == 64, "the reduction below leaves an output in every lane or every second one");
   __shared__ double red[LS_MAXW][NOUT];
+  __shared__ float lg[T][EC + 1], sel[TOPK_MAX * T];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int64_t t0 = (int64_t)blockIdx.x * T;
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wg), 0, (uint32_t)((uint64_t)M * E * 4), 0x00020000);
@@ -130,7 +167,18 @@ __global__ __launch_bounds__(64 * LS_MAXW) void gate_logits_split(const void* __
     const int e = threadIdx.x % EC;
     double v = 0.0;
     for (int q = 0; q < nw; ++q) v += red[q][threadIdx.x];
-    if (t < S && e < E) logits[t * E + e] = (float)(bias ? v + (double)bias[e] : v);
+    const float l = (float)(bias && e < E ? v + (double)bias[e] : v);
+    if (t < S && e < E) logits[t * E + e] = l;
+    lg[threadIdx.x / EC][e] = l;
+  }
+  if (tk.k == 0) return;
+  __syncthreads();
+  if (threadIdx.x < T && t0 + threadIdx.x < S) {
+    float v[EC];
+#pragma unroll
+    for (int e = 0; e < EC; ++e) v[e] = lg[threadIdx.x][e];
+    const int64_t at = (t0 + threadIdx.x) * tk.k;
+    pick_experts<EC>(v, E, tk.k, tk.norm, sel + threadIdx.x, T, tk.idx + at, tk.w + at);
   }
 }
 
@@ -300,8 +348,9 @@ constexpr int LF_NW = 16;
 template <bool BF16>
 __global__ __launch_bounds__(64 * LF_NW, 4) void gate_logits_few(const void* __restrict__ x, const float* __restrict__ Wg,
                                                                  const float* __restrict__ bias, float* __restrict__ logits,
-                                                                 int64_t S, int M, int E) {
+                                                                 int64_t S, int M, int E, const TopK tk) {
   __shared__ double red[LF_NW][4][64];
+  __shared__ float lg[16][17], sel[TOPK_MAX * 16];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   const int64_t tb = (int64_t)blockIdx.x * 16;
   const int e0 = blockIdx.y * 16, kq = 8 * (lane >> 4);
@@ -332,7 +381,18 @@ __global__ __launch_bounds__(64 * LF_NW, 4) void gate_logits_few(const void* __r
     double v = 0.0;
     for (int q = 0; q < nw; ++q) v += red[q][r][l];
     const int64_t to = tb + 4 * r + (l >> 4);
-    if (to < S && e < E) logits[to * E + e] = (float)(bias ? v + (double)bias[e] : v);
+    const float f = (float)(bias && e < E ? v + (double)bias[e] : v);
+    if (to < S && e < E) logits[to * E + e] = f;
+    lg[4 * r + (l >> 4)][l & 15] = f;
+  }
+  if (tk.k == 0) return;      // (up to 16 experts: the block has all of a token's logits)
+  __syncthreads();
+  if (threadIdx.x < 16 && tb + threadIdx.x < S) {
+    float v[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = lg[threadIdx.x][e];
+    const int64_t at = (tb + threadIdx.x) * tk.k;
+    pick_experts<16>(v, E, tk.k, tk.norm, sel + threadIdx.x, 16, tk.idx + at, tk.w + at);
   }
 }
 
@@ -691,28 +751,57 @@ __global__ __launch_bounds__(256) void gate_scan(const int32_t* __restrict__ blo
 }
 
 // One block per GATE_TB tokens, wave j ranks choice j.
-// SELF = false: queue positions of the block's first tokens come from gate_scan (base, counts).
-// SELF = true: every block works them out itself from the histograms [block][choice][expert] -- for each
+// SLOTS_SCAN: queue positions of the block's first tokens come from gate_scan (base, counts).
+// SLOTS_HIST: every block works them out itself from the histograms [block][choice][expert] -- for each
 // (choice j, expert e) the demand of the earlier blocks, plus all demand of the earlier choices -- which saves the
 // scan launch; block 0 also writes counts.  Same integers either way.  The histogram rows are read four pairs at a time
 // by groups of threads that share the blocks between them, and the groups' sums meet in LDS.
+// SLOTS_IDX: the same from the choices themselves, which every block counts (integer sums in LDS: the order does not matter); the
+// logits kernel has then selected the experts, and there are no histograms.
 constexpr int SLOT_NT = 512;
-template <bool SELF>
+enum { SLOTS_SCAN, SLOTS_HIST, SLOTS_IDX };
+template <int FROM>
 __global__ __launch_bounds__(SLOT_NT) void gate_slots(const int32_t* __restrict__ idx, const int32_t* __restrict__ base,
                                                       int32_t* __restrict__ counts, int64_t S, int E, int k,
                                                       int64_t C, int32_t* __restrict__ slot, int32_t* __restrict__ inv) {
   static_assert(GATE_TB == 64 && SLOT_NT / 64 >= MOE_MAX_K, "a wave per choice, a lane per token");
+  constexpr bool SELF = FROM != SLOTS_SCAN;
   __shared__ __attribute__((aligned(16))) int base_s[SELF ? MOE_MAX_K * MOE_MAX_E : 1];   // queue position of this block's first (j, e) token
   __shared__ __attribute__((aligned(16))) int tot_s[SELF ? MOE_MAX_K * MOE_MAX_E : 1];    // demand of (j, e) over all blocks
   __shared__ int count_s[SELF ? MOE_MAX_E : 1];              // total demand of expert e
+  __shared__ int copies_s[FROM == SLOTS_IDX ? 2 * TOPK_MAX * 16 * 8 : 1];   // (up to 16 experts)
   const int tid = threadIdx.x, lane = tid & 63, j = tid >> 6;
   const int64_t t = (int64_t)blockIdx.x * GATE_TB + lane;
   const bool live = t < S && j < k;
   const int e = live ? idx[t * k + j] : 0;
   if (SELF) {
     const int nblk = (int)gridDim.x, me = (int)blockIdx.x, npair = k * E;
-    for (int i = tid; i < npair; i += SLOT_NT) base_s[i] = tot_s[i] = 0;
-    __syncthreads();
+    if constexpr (FROM == SLOTS_HIST) {
+      for (int i = tid; i < npair; i += SLOT_NT) base_s[i] = tot_s[i] = 0;
+      __syncthreads();
+    }
+    if constexpr (FROM == SLOTS_IDX) {
+      // [in front of this block's tokens, behind][pair][copy]: eight copies, or the lanes of a wave queue up at a few counters
+      int* cnt = copies_s;
+      for (int i = tid; i < 2 * npair * 8; i += SLOT_NT) cnt[i] = 0;
+      __syncthreads();
+      const int n = (int)(S * k), before = me * GATE_TB * k;      // S k < 2^31
+      auto count = [&](int i, int ee) { atomicAdd(&cnt[((i < before ? 0 : npair) + i % k * E + ee) * 8 + (lane & 7)], 1); };
+#pragma unroll 4
+      for (int i = tid * 4; i < (n & ~3); i += SLOT_NT * 4) {
+        const int4 v = *reinterpret_cast<const int4*>(idx + i);
+        count(i, v.x); count(i + 1, v.y); count(i + 2, v.z); count(i + 3, v.w);
+      }
+      if (tid < (n & 3)) count((n & ~3) + tid, idx[(n & ~3) + tid]);
+      __syncthreads();
+      for (int i = tid; i < npair; i += SLOT_NT) {
+        int pre = 0, post = 0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) { pre += cnt[i * 8 + c]; post += cnt[(npair + i) * 8 + c]; }
+        base_s[i] = pre;
+        tot_s[i] = pre + post;
+      }
+    }
     auto sum_rows = [&](auto vec_tag) {   // V pairs per thread and step
       constexpr int V = decltype(vec_tag)::value;
       typedef int32_t vec_t __attribute__((ext_vector_type(V)));
@@ -732,8 +821,10 @@ __global__ __launch_bounds__(SLOT_NT) void gate_slots(const int32_t* __restrict_
         for (int q = 0; q < V; ++q) { atomicAdd(&tot_s[u * V + q], tot[q]); atomicAdd(&base_s[u * V + q], pre[q]); }
       }
     };
-    if (npair % 4 == 0) sum_rows(std::integral_constant<int, 4>{});
-    else sum_rows(std::integral_constant<int, 1>{});
+    if constexpr (FROM == SLOTS_HIST) {
+      if (npair % 4 == 0) sum_rows(std::integral_constant<int, 4>{});
+      else sum_rows(std::integral_constant<int, 1>{});
+    }
     __syncthreads();
     // choice-major queues: all demand of the earlier choices at expert e comes first
     for (int ee = tid; ee < E; ee += SLOT_NT) {
@@ -822,14 +913,22 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
   int32_t* blockhist = (int32_t*)ws;
   int32_t* blockbase = (int32_t*)((char*)ws + need / 2);
 
+  bool selected = false;   // the logits kernel selects the experts too
   if (x) {
     const bool bf = x_dtype == MOE_BF16;
     const size_t esz = bf ? 2 : 4;
     const void* xs = (const char*)x + (size_t)mp_idx * S * M * esz;
+    TopK tk{0, norm, idx, w};
+    // Up to 16 experts and three choices the logits kernels select the experts as well (a thread per token, whose rounds are a chain), and
+    // gate_slots counts the choices.  The call, three launches and two: 2048 x 768, 16 experts, top-2, 12.9 and 11.3 us; 4096 x 1024,
+    // 8, top-2, 13.6 and 12.4; 6000 x 512, 16, top-2 (12000 choices) 13.0 and 13.0; 2000 x 512, 12, top-4, 12.0 and 12.6.  With at most 64 tokens gate_topk assigns the slots as well: two
+    // launches either way (32 x 1024, 8, top-2, 9.6 and 9.6; 256 x 4096 12.5 and 11.9).
+    if (E <= 16 && k <= TOPK_MAX && S > 64 && S * k <= 8192) tk.k = k;
     auto launch_few = [&]() {
+      selected = tk.k != 0;
       const dim3 grid((unsigned)((S + 15) / 16), (unsigned)((E + 15) / 16)), block(64 * std::min(LF_NW, (M + LM_KC - 1) / LM_KC));
-      if (bf) hipLaunchKernelGGL(gate_logits_few<true>, grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E);
-      else hipLaunchKernelGGL(gate_logits_few<false>, grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E);
+      if (bf) hipLaunchKernelGGL(gate_logits_few<true>, grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E, tk);
+      else hipLaunchKernelGGL(gate_logits_few<false>, grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E, tk);
     };
     // Up to 16 experts.  The 16 x 16 tiles cost the same whatever S, M and E: 8192 x 1024 17 us (the call), 16384 x 4096 61, fp32 29 at
     // 16384 x 1024.  The others are faster
@@ -864,12 +963,13 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
       if (nw < 1) nw = 1;
       const dim3 grid((unsigned)blocks), block(64 * nw);
 #define LAUNCH_SPLIT(ec, t, full) do { \
-    if (bf) hipLaunchKernelGGL((gate_logits_split<ec, true, t, full>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E); \
-    else hipLaunchKernelGGL((gate_logits_split<ec, false, t, full>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E); } while (0)
+    if (bf) hipLaunchKernelGGL((gate_logits_split<ec, true, t, full>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E, tk); \
+    else hipLaunchKernelGGL((gate_logits_split<ec, false, t, full>), grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E, tk); } while (0)
 #define LAUNCH_SPLIT_E(full8, full16) do { \
     if (E <= 8) { if (many) LAUNCH_SPLIT(8, 8, full8); else LAUNCH_SPLIT(8, 4, full8); } \
     else { if (many) LAUNCH_SPLIT(16, 4, full16); else LAUNCH_SPLIT(16, 2, full16); } } while (0)
       if (E == 8 || E == 16) LAUNCH_SPLIT_E(true, true); else LAUNCH_SPLIT_E(false, false);
+      selected = tk.k != 0;
 #undef LAUNCH_SPLIT_E
 #undef LAUNCH_SPLIT
     } else if (E <= 16) {
@@ -890,6 +990,10 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
       }
 #undef LAUNCH_WIDE
     }
+  }
+  if (selected) {
+    hipLaunchKernelGGL(gate_slots<SLOTS_IDX>, dim3(nblk), dim3(SLOT_NT), 0, st, idx, nullptr, counts, S, E, k, C, slot, inv);
+    return moe::check_launch();
   }
   // Every block reads all histograms itself up to 256 KiB of them and 64 MiB over all blocks (a few microseconds from L2,
   // what the scan launch costs).
@@ -917,10 +1021,10 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
   else done = route(integral_constant<int, 16>{}, integral_constant<int, 16>{});
   if (done) return moe::check_launch();
   if (self) {
-    hipLaunchKernelGGL(gate_slots<true>, dim3(nblk), dim3(SLOT_NT), 0, st, idx, blockhist, counts, S, E, k, C, slot, inv);
+    hipLaunchKernelGGL(gate_slots<SLOTS_HIST>, dim3(nblk), dim3(SLOT_NT), 0, st, idx, blockhist, counts, S, E, k, C, slot, inv);
   } else {
     hipLaunchKernelGGL(gate_scan, dim3((E + 3) / 4), dim3(256), 0, st, blockhist, nblk, E, k, blockbase, counts);
-    hipLaunchKernelGGL(gate_slots<false>, dim3(nblk), dim3(SLOT_NT), 0, st, idx, blockbase, counts, S, E, k, C, slot, inv);
+    hipLaunchKernelGGL(gate_slots<SLOTS_SCAN>, dim3(nblk), dim3(SLOT_NT), 0, st, idx, blockbase, counts, S, E, k, C, slot, inv);
   }
   return moe::check_launch();
 }

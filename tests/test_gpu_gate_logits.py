@@ -3,23 +3,24 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import moe_oracle as O
 from paper_2407_00599_amd import api
-from util import DEV
+from util import DEV, rel_err, to_host
 
 pytestmark = pytest.mark.gpu
 
 
-def gate(x, Wg, bias):
+def gate(x, Wg, bias, k=1, C=None, norm=0, everything=False):
     S, M = x.shape
-    E, k, C = Wg.shape[1], 1, S
+    E, C = Wg.shape[1], C or S
     i32 = torch.int32
     logits = torch.full((S, E), float("nan"), device=DEV)
     idx, slot, inv = (torch.empty(n, dtype=i32, device=DEV) for n in ((S, k), (S, k), (E, C)))
     w, counts = torch.empty(S, k, device=DEV), torch.empty(E, dtype=i32, device=DEV)
     ws = torch.empty(api.moe_gate_workspace_bytes(S, E, k), dtype=torch.uint8, device=DEV)
-    api.moe_gate_topk(x, Wg, bias, S, M, E, k, C, 0, 1, 0, logits, idx, slot, w, inv, counts, ws)
+    api.moe_gate_topk(x, Wg, bias, S, M, E, k, C, 0, 1, norm, logits, idx, slot, w, inv, counts, ws)
     torch.cuda.synchronize()
-    return logits
+    return (logits, idx, slot, inv, w, counts) if everything else logits
 
 
 # up to 16 experts: walks of a few waves (few tokens for their M), 16 x 16 tiles, the 4-block form (many bf16 tokens); beyond:
@@ -58,3 +59,27 @@ def test_non_finite_values_stay_in_their_row_and_column(S, M, E):
     rows[[S - 1, S // 2, 7]] = False
     assert torch.equal(got[rows][:, :E - 1], want[rows][:, :E - 1])
     assert not bool(torch.isfinite(got[~rows]).any()) and not bool(torch.isfinite(got[:, E - 1]).any())
+
+
+# the experts selected by the logits kernel (up to 16 experts, k <= 3, S k <= 8192), and one step beyond each line; ties by equal columns
+@pytest.mark.parametrize("S,M,E,k,C,norm", [
+    (1, 8, 1, 1, 1, 0), (63, 64, 16, 3, 5, 1), (65, 2048, 8, 2, 9, 0), (257, 40, 3, 3, 200, 1), (1023, 520, 12, 3, 250, 1),
+    (2049, 72, 16, 2, 300, 0), (2730, 64, 9, 3, 1000, 1), (2731, 64, 9, 3, 900, 0), (4096, 1024, 8, 2, 1100, 1), (4097, 64, 8, 2, 1000, 1),
+    (8191, 24, 2, 1, 4000, 0), (8192, 136, 12, 1, 600, 0), (300, 64, 16, 4, 70, 1),
+])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_routing(S, M, E, k, C, norm, dtype):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(S + E)
+    x = torch.randn(S, M, generator=g, device=DEV).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    Wg = torch.randn(M, E, generator=g, device=DEV) * 0.1
+    if E > 4:
+        Wg[:, 4] = Wg[:, 1]
+    logits, idx, slot, inv, w, counts = (to_host(t) for t in gate(x, Wg, torch.linspace(1, 0, E, device=DEV).index_fill(0, torch.tensor(
+        [min(4, E - 1)], device=DEV), 1 - 1 / max(E - 1, 1)) if E > 4 else None, k, C, norm, True))
+    logits = logits.astype(np.float32)
+    want = O.topk_select(logits, k)
+    assert np.array_equal(idx, want)
+    for got, ref in zip((slot, inv, counts), O.capacity_slots(want, E, C)):
+        assert np.array_equal(got, ref)
+    assert rel_err(w, O.combine_weights(logits, want, bool(norm))) <= 1e-5
