@@ -74,3 +74,17 @@ def test_identity_round_trip_on_device():
     surv = (slot >= 0).sum(1)
     assert (surv < k).any()
     assert np.array_equal(to_host(y), surv[:, None] * x.val.astype(np.float64))
+
+
+# the rows of empty slots: 8 or (from 32768 rows on) 64 slots to a wave, around whole waves; mostly empty, full, and no token at all for
+# some experts
+@pytest.mark.parametrize("S,M,E,k,C", [(5, 8, 3, 1, 11), (100, 264, 64, 2, 511), (100, 24, 64, 3, 512), (70, 8, 33, 2, 1001), (2000, 520, 9, 4, 800)])
+def test_combine_bwd_empty_slots(S, M, E, k, C):
+    idx, slot, inv, w = routing(S, E, k, C, seed=S + E, skew=1.0)
+    rng = np.random.default_rng(E)
+    dy, Y = (synth.store(rng.standard_normal(n).astype(np.float32), "bf16") for n in ((S, M), (1, E, C, M)))
+    dY = torch.full((E, C, M), 7.0, dtype=torch.bfloat16, device=DEV); dw = torch.full((S, k), 7.0, device=DEV)
+    api.moe_combine_bwd(to_dev(dy), to_dev(Y), 1, S, M, E, k, C, to_dev(idx), to_dev(slot), to_dev(inv), to_dev(w), dY, dw)
+    rdY, rdw = O.combine_bwd(dy.val, Y.val, idx, slot, w)
+    got = to_host(dY)
+    assert np.all(got[inv < 0] == 0.0) and rel_err(got, rdY) <= 4e-3 and rel_err(to_host(dw), rdw) <= 2e-6 * np.sqrt(M)
