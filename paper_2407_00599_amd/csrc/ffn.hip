@@ -1314,28 +1314,34 @@ __global__ __launch_bounds__(256) void ffn_add_parts(const GemmArgs pw2, const G
 // fp32 kernel: fp64 matrix cores (v_mfma_f64_16x16x4_f64: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and
 // receives D[4 r + l / 16][l % 16], r = 0..3), fp64 accumulation.
 //
-// TM x 64 tile, four waves (2 x 2), k chunks of 32: both operands are converted to fp64 once per workgroup on their way
-// into LDS ([k][row], pitch T + 16 doubles: the two k planes of a 32-lane read fall into different halves of the
-// banks; row r of k is at r ^ 8 (k / 4), so that the eight k groups that a wave writes for k-contiguous operands do too);
-// the next chunk is requested into registers before the current one is multiplied.
-// Bound by the fp64 matrix rate (70 TFLOP/s measured for the bare instruction), less the conversions (16 cycles per wave
-// and 64 values, during which the matrix unit waits: an eighth of a 64 x 64 tile) and, with few rows, the fill and
-// drain of a workgroup.  The tiles are small because the fp32 problems are.  8 experts x 4096 rows x 512 x 2048: 55 to 59
-// TFLOP/s; x 256 rows: 37 to 49, where fp64 vector FMAs on 64 x 64 tiles reached 11 to 25 and multiplied all padding.
+// TM x TN tile, four waves: TM / 16 of them own 16 rows each, with two row waves the other two take the other half of every k
+// chunk, and the halves' sums meet in LDS.  k chunks of 32.  Which k a quarter of the lanes feeds in which step is free as
+// long as both operands agree: it takes SPL consecutive ones, one a step.  So A needs no LDS: a lane's values are 16-byte pieces
+// of its row (weight gradients: single values, 16 lanes to 64 bytes).  B is converted to fp64 once per workgroup on its way into
+// LDS ([k][column], pitch TN + 2 doubles: the k rows of a 32-lane read fall into different halves of the banks), in two buffers:
+// the next chunk is converted and stored between the current one's products, and the one after it requested.  No fetch
+// stands in a branch, so that the compiler can wait for them by count: what does not exist is fetched from somewhere else in the
+// tensor and, along k, zeroed.
+// Bound by the fp64 matrix rate (77 TFLOP/s measured for the bare instruction) less the vector instructions between, of which
+// a conversion costs a tenth of a matrix instruction.  8192 rows x 2048 x 2048, forward and backward call, with both operands staged
+// and two barriers per chunk 2.31 and 4.63 ms (59 TFLOP/s) -> 2.06 and 4.07 ms (67); 8 experts of 256 x 512 x 2048 180 and
+// 324 -> 158 and 284 us; 8 of 51 x 1024 x 4096 213 and 399 -> 179 and 337; but 4 of 62 x 64 x 128, whose two chunks are latency,
+// 11.6 and 13.1 -> 12.5 and 13.9.
 // ------------------------------------------------------------------------------------------
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 constexpr int FK = 32;   // k chunk
 template <int TM, int TN>
-constexpr int f32_lds() { return FK * (TM + 16 + TN + 16) * 8; }
-template <int KIND, int EPI, int TM, int TN>
-__device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int vb) {
-  constexpr int PA = TM + 16, PB = TN + 16;
+constexpr int f32_lds() { return 2 * FK * (TN + 2) * 8; }
+template <int KIND, int EPI, int TM, int TN, bool WIDE>   // WIDE: leading dimensions that 32-bit offsets do not reach
+__device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* Bs, int vb) {
   constexpr bool A_NC = KIND == KIND_TN, B_NC = KIND != KIND_NT;   // k is the slow index in memory
-  constexpr int MB = TM / 32, NB = TN / 32;                         // 16 x 16 blocks per wave
-  constexpr int UA = TM * FK / 4 / 256, UB = TN * FK / 4 / 256;     // 16-byte pieces per thread and chunk
-  double* Bs = As + FK * PA;
+  constexpr int RW = TM / 16, KW = 4 / RW, NJ = TN / 16;            // row waves, k halves, blocks of 16 columns
+  constexpr int SPL = 8 / KW;                                       // steps of a wave per chunk
+  constexpr int PB = TN + 2, BUF = FK * PB, UB = TN * FK / 4 / 256; // 16-byte pieces of B per thread and chunk
+  static_assert(RW * KW == 4 && (KW == 1 || RW * 64 * (4 * NJ + 1) <= 2 * BUF), "the halves' sums fit in the buffers");
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rw = wave % RW, kw = wave / RW;
+  const int kb = kw * (FK / KW) + SPL * (lane >> 4);                // this lane's first k of a chunk
   int g, tm, tn;
   const bool counted = KIND != KIND_TN && p.cnt != nullptr;
   const int what = map_tile<TM, EPI != EPI_DGELU>(p, vb, counted, g, tm, tn);   // (dZ of a padding row is never read)
@@ -1346,208 +1352,257 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* As, int
   const float* __restrict__ A = reinterpret_cast<const float*>(p.A);
   const float* __restrict__ B = reinterpret_cast<const float*>(p.B) + (KIND == KIND_TN ? 0 : (int64_t)g * p.b_goff + p.b_off);
 
-  // rows: of this thread's A pieces (row-tiled GEMMs) and, lane l, of output row l of the tile
-  int a_row[UA], o_row = 0;
+  // rows (row-tiled GEMMs): of this lane's A values and, lane l, of output row l of the tile
+  int a_row = 0, o_row = 0;
   bool o_zero = false;
   if (KIND != KIND_TN) {
-    int r[UA + 1], row[UA + 1];
-    bool occ[UA + 1], here = false;   // there is a row to multiply; there is a row to store (zeros if not occ)
-#pragma unroll
-    for (int u = 0; u < UA; ++u) r[u] = m0 + (tid + 256 * u) / (FK / 4);
-    r[UA] = m0 + lane;
+    int r[2] = {m0 + rw * 16 + (lane & 15), m0 + lane}, row[2];
+    bool occ[2], here = false;   // there is a row to multiply; there is a row to store (zeros if not occ)
     if (counted && p.n_src > 1) {
-      compact_rows<UA + 1>(p, g, m0, TM, r, row, occ);
-      here = occ[UA];
+      compact_rows<2>(p, g, m0, TM, r, row, occ);
+      here = occ[1];
     } else {
       const int cnt_g = counted ? clamp_count(p.cnt[g], p.Cc) : p.Mdim;
 #pragma unroll
-      for (int u = 0; u <= UA; ++u) {
+      for (int u = 0; u < 2; ++u) {
         occ[u] = r[u] < cnt_g;
-        if (u == UA) here = r[u] < p.Mdim;
+        if (u == 1) here = r[u] < p.Mdim;
         row[u] = (int)phys_row(min(r[u], p.Mdim - 1), g, p.G, p.Cc);
         if (p.gather != nullptr) {
           const int64_t tok = a_src_row(p, min(r[u], p.Mdim - 1), g);
           occ[u] = occ[u] && tok >= 0;
-          if (u < UA) row[u] = (int)tok;
+          if (u == 0) row[u] = (int)tok;
         }
       }
     }
-#pragma unroll
-    for (int u = 0; u < UA; ++u) a_row[u] = occ[u] ? row[u] : 0;   // no row: any row, its results are not stored
-    o_row = here ? row[UA] : -1;
-    o_zero = !occ[UA];
+    a_row = occ[0] ? row[0] : 0;   // no row: any row, its results are not stored
+    o_row = here ? row[1] : -1;
+    o_zero = !occ[1];
   }
   ChunkWalk<> walk(p, g);
   const int nk = KIND == KIND_TN ? walk.start(FK, false) : (p.Kdim + FK - 1) / FK;
+  auto ktile = [&](int t) -> KTile {      // behind the last one: no k, and row 0
+    if (KIND == KIND_TN) return walk.next(FK);
+    return t < nk ? KTile{t * FK, p.Kdim - t * FK} : KTile{0, 0};
+  };
 
-  auto swz = [](int k, int T) constexpr { return ((k >> 2) & (T / 8 - 1)) * 8; };   // see the layout above
-  // This thread's pieces: where they start at k = 0 (k-contiguous: row and k offset; k-slow: column), and their k.  A
-  // column outside the problem is fetched from the tile's first one; only a partial chunk looks at k at all.
-  const float *pa[UA], *pb[UB];
-  int a_k[UA], b_k[UB];
+  // ---- A: this lane's SPL values of a chunk.  Weight gradients: column m of rows kb .. kb + SPL - 1 of the chunk.
+  const int m = min(m0 + rw * 16 + (lane & 15), p.Mdim - 1);       // (weight gradients) past the end: any column, not stored
+  const float* a_ptr = A_NC ? A + m : A + (int64_t)a_row * p.lda;
+  uint32_t a_off[A_NC ? SPL : 1];     // byte offsets from the chunk's first row
 #pragma unroll
-  for (int u = 0; u < UA; ++u) {
-    const int i = tid + 256 * u;
-    if (!A_NC) {
-      a_k[u] = (i % (FK / 4)) * 4;
-      pa[u] = A + (int64_t)a_row[u] * p.lda + a_k[u];
-    } else {
-      a_k[u] = i / (TM / 4);
-      const int m = m0 + (i % (TM / 4)) * 4;
-      pa[u] = A + (m < p.Mdim ? m : m0);
+  for (int s = 0; s < (A_NC ? SPL : 1); ++s) a_off[s] = ((uint32_t)(kb + s) * (uint32_t)p.lda + (uint32_t)m) * 4u;
+  constexpr uint32_t ALL = (1u << SPL) - 1u;
+  struct Piece {
+    float v[SPL];
+    uint32_t keep;      // which of them exist
+  };
+  const __amdgpu_buffer_rsrc_t rG = make_rsrc(p.gather, A_NC && p.gather ? (uint32_t)((int64_t)p.G * p.Cc * 4) : 0u);
+  const bool gathered = A_NC && p.gather != nullptr;
+  struct Slots {
+    int v[A_NC ? SPL : 1];
+  };
+  Slots slots;                      // gathered rows: slot-map entries of the chunk that is fetched next
+  auto fetch_map = [&](Slots& d, const KTile& kt) {     // entries behind the map read as zero; rows behind the count are masked
+#pragma unroll
+    for (int s = 0; s < (A_NC ? SPL : 1); ++s) d.v[s] = (int)__builtin_amdgcn_raw_buffer_load_b32(rG, (int)((uint32_t)(kt.row0 + kb + s) * 4u), 0, 0);
+  };
+  auto fetch_a = [&](Piece& d, const KTile& kt, const Slots& map) {
+    d.keep = (1u << min(max(kt.lim - kb, 0), SPL)) - 1u;
+    if (!A_NC) {        // K % 8 == 0: the values of a lane's quarter exist together or (SPL = 8) in halves of 4
+#pragma unroll
+      for (int q = 0; q < SPL / 4; ++q) {
+        const float4 v = *reinterpret_cast<const float4*>(a_ptr + kt.row0 + (kb + 4 * q < kt.lim ? kb + 4 * q : 0));
+        d.v[4 * q] = v.x; d.v[4 * q + 1] = v.y; d.v[4 * q + 2] = v.z; d.v[4 * q + 3] = v.w;
+      }
+    } else if (gathered) {
+#pragma unroll
+      for (int s = 0; s < SPL; ++s) {
+        const int iv = map.v[A_NC ? s : 0];
+        const uint32_t tok = p.gather_k == 1 ? (uint32_t)iv : __umulhi((uint32_t)iv, p.gather_magic);
+        const bool full = iv >= 0 && (int64_t)tok < p.gather_rows;     // an empty slot is a row of zeros
+        if (!full) d.keep &= ~(1u << s);
+        d.v[s] = a_ptr[(full && kb + s < kt.lim ? (int64_t)tok : 0) * p.lda];
+      }
+    } else if (WIDE) {
+      const float* q = a_ptr + (int64_t)kt.row0 * p.lda;
+#pragma unroll
+      for (int s = 0; s < SPL; ++s) d.v[s] = q[(kb + s < kt.lim ? (int64_t)(kb + s) : 0) * p.lda];
+    } else {            // through a descriptor that ends with the chunk's last row: rows behind it are zeros
+      const __amdgpu_buffer_rsrc_t r = make_rsrc(A + (int64_t)kt.row0 * p.lda, (uint32_t)max(min(kt.lim, FK), 0) * (uint32_t)p.lda * 4u);
+#pragma unroll
+      for (int s = 0; s < SPL; ++s) d.v[s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)a_off[A_NC ? s : 0], 0, 0));
+      d.keep = ALL;
     }
-  }
+  };
+  // ---- B: through LDS.  A column behind the last one is fetched from the tile's first one.
+  struct Rows {
+    float4 v[UB];
+  };
+  Rows rb;
+  int b_k[UB];
+  uint32_t b_at[UB], b_off[UB];      // element of the piece in its buffer; byte offset from where the chunk starts
 #pragma unroll
   for (int u = 0; u < UB; ++u) {
     const int i = tid + 256 * u;
-    if (!B_NC) {
-      b_k[u] = (i % (FK / 4)) * 4;
-      pb[u] = B + (int64_t)min(n0 + i / (FK / 4), p.Ndim - 1) * p.ldb + b_k[u];
-    } else {
+    if (B_NC) {
+      const int n = (i % (TN / 4)) * 4;
       b_k[u] = i / (TN / 4);
-      const int n = n0 + (i % (TN / 4)) * 4;
-      pb[u] = B + (n < p.Ndim ? n : n0);
+      b_at[u] = (uint32_t)(b_k[u] * PB + n);
+      b_off[u] = ((uint32_t)b_k[u] * (uint32_t)p.ldb + (uint32_t)(n0 + n < p.Ndim ? n0 + n : n0)) * 4u;
+    } else {
+      const int n = i / (FK / 4);
+      b_k[u] = (i % (FK / 4)) * 4;
+      b_at[u] = (uint32_t)(b_k[u] * PB + n);
+      b_off[u] = ((uint32_t)min(n, p.Ndim - 1 - n0) * (uint32_t)p.ldb + (uint32_t)b_k[u]) * 4u;
     }
   }
-  float4 ra[UA], rb[UB];
-  // A full chunk has a path of its own: what a partial one looks at otherwise stands in front of every load, and how the
-  // compiler forms those addresses decided the length of a chunk (one expert, 224 x 192 x 10984, backward: 645 us, and 662 after
-  // a change elsewhere in the kernel; with this path 644, forward 249 -> 227; 8 experts of 256 x 512 x 2048 175 -> 162 and
-  // 293 -> 286).
-  auto fetch = [&](const KTile& kt) {
-    if (kt.lim >= FK && (KIND != KIND_TN || p.gather == nullptr)) {
+  auto fetch_b = [&](Rows& d, const KTile& kt) {
+    if constexpr (WIDE) {
 #pragma unroll
-      for (int u = 0; u < UA; ++u)
-        ra[u] = *reinterpret_cast<const float4*>(A_NC ? pa[u] + (int64_t)(kt.row0 + a_k[u]) * p.lda : pa[u] + kt.row0);
-#pragma unroll
-      for (int u = 0; u < UB; ++u)
-        rb[u] = *reinterpret_cast<const float4*>(B_NC ? pb[u] + (int64_t)(kt.row0 + b_k[u]) * p.ldb : pb[u] + kt.row0);
+      for (int u = 0; u < UB; ++u) {
+        const int i = tid + 256 * u, k = kt.row0 + (b_k[u] < kt.lim ? b_k[u] : 0), n = n0 + (B_NC ? (i % (TN / 4)) * 4 : i / (FK / 4));
+        d.v[u] = *reinterpret_cast<const float4*>(B_NC ? B + (int64_t)k * p.ldb + (n < p.Ndim ? n : n0)
+                                                       : B + (int64_t)min(n, p.Ndim - 1) * p.ldb + k);
+      }
       return;
     }
-    const bool part = kt.lim < FK;
-#pragma unroll
-    for (int u = 0; u < UA; ++u) {
-      const int k = part && a_k[u] >= kt.lim ? 0 : a_k[u];
-      const float* src = pa[u];
-      if (!A_NC) {
-        src += kt.row0 + (k - a_k[u]);
-      } else {
-        int64_t row = kt.row0 + k;
-        if (p.gather != nullptr) row = a_src_row(p, kt.row0 + k - g * p.Cc, g);
-        src += max(row, (int64_t)0) * p.lda;
-        if (p.gather != nullptr && row < 0) { ra[u] = make_float4(0.f, 0.f, 0.f, 0.f); continue; }
-      }
-      ra[u] = *reinterpret_cast<const float4*>(src);
-      if (part && a_k[u] >= kt.lim) ra[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    const __amdgpu_buffer_rsrc_t r =     // B_NC: ends with the chunk's last row, rows behind it are zeros
+        B_NC ? make_rsrc(B + (int64_t)kt.row0 * p.ldb, (uint32_t)max(min(kt.lim, FK), 0) * (uint32_t)p.ldb * 4u)
+             : make_rsrc(B + (int64_t)n0 * p.ldb + kt.row0, OOB);
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
-      const int k = part && b_k[u] >= kt.lim ? 0 : b_k[u];
-      const float* src = B_NC ? pb[u] + (int64_t)(kt.row0 + k) * p.ldb : pb[u] + kt.row0 + (k - b_k[u]);
-      rb[u] = *reinterpret_cast<const float4*>(src);
-      if (part && b_k[u] >= kt.lim) rb[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      const uint4 v = ldb16(r, B_NC || b_k[u] < kt.lim ? b_off[u] : b_off[u] - (uint32_t)b_k[u] * 4u);
+      d.v[u] = make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
     }
   };
-  auto stage1 = [&](double* dst, int T, int pitch, bool nc, int i, const float4& v) {
-    if (nc) {     // 4 consecutive rows / columns of one k
-      const int k = i / (T / 4);
-      double* d = dst + k * pitch + (((i % (T / 4)) * 4) ^ swz(k, T));
-      d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-    } else {      // 4 consecutive k of one row
-      const int k = (i % (FK / 4)) * 4;
-      double* d = dst + k * pitch + ((i / (FK / 4)) ^ swz(k, T));
-      d[0] = v.x; d[pitch] = v.y; d[2 * pitch] = v.z; d[3 * pitch] = v.w;
+  auto stage_b = [&](Rows& src, int buf, int lim) {
+    double* d = Bs + buf * BUF;
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      if ((!B_NC || WIDE) && lim < FK) {
+        if (b_k[u] >= lim) src.v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      const double x[4] = {(double)src.v[u].x, (double)src.v[u].y, (double)src.v[u].z, (double)src.v[u].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) d[b_at[u] + (B_NC ? q : q * PB)] = x[q];
     }
   };
-  // where the lane reads its operands: the layout's XOR is a constant of a k group; its lowest bit turns over a bit of
-  // the lane's row, its highest the half of the tile the wave owns, the others an address constant
-  const double *fa[2][2], *fb[2][2];
+
+  f64x4_t acc[NJ];
 #pragma unroll
-  for (int lo = 0; lo < 2; ++lo)
+  for (int j = 0; j < NJ; ++j) acc[j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  Piece pa[2];
+  int lim_b;              // of the chunk in rb
+  KTile t2;               // chunk c + 2
+  {
+    const KTile t0 = ktile(0), t1 = ktile(1);
+    t2 = ktile(2);
+    Slots s0, s1;
+    Rows r0;
+    if (gathered) { fetch_map(s0, t0); fetch_map(s1, t1); fetch_map(slots, t2); }
+    fetch_b(r0, t0);
+    fetch_b(rb, t1);
+    fetch_a(pa[0], t0, s0);
+    fetch_a(pa[1], t1, s1);
+    stage_b(r0, 0, t0.lim);
+    lim_b = t1.lim;
+  }
+  auto step = [&](int c, auto set_tag) {
+    constexpr int SET = decltype(set_tag)::value;
+    __syncthreads();      // chunk c is staged, and the other buffer is consumed
+    if (A_NC ? gathered || WIDE : pa[SET].keep != ALL) {
 #pragma unroll
-    for (int hi = 0; hi < 2; ++hi) {
-      fa[lo][hi] = As + (lane >> 4) * PA + (wm ^ hi) * (TM / 2) + ((lane & 15) ^ (8 * lo));
-      fb[lo][hi] = Bs + (lane >> 4) * PB + (wn ^ hi) * (TN / 2) + ((lane & 15) ^ (8 * lo));
+      for (int s = 0; s < SPL; ++s) pa[SET].v[s] = (pa[SET].keep >> s) & 1u ? pa[SET].v[s] : 0.f;
     }
-  f64x4_t acc[MB][NB];
+    const double* w = Bs + SET * BUF + kb * PB + (lane & 15);
+    auto products = [&](int s0) {
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+      for (int s = s0; s < s0 + SPL / 2; ++s) {
+        const double a = (double)pa[SET].v[s];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-  auto ktile = [&](int t) { return KIND == KIND_TN ? walk.next(FK) : KTile{t * FK, p.Kdim - t * FK}; };
-  if (nk > 0) fetch(ktile(0));
-  for (int t = 0; t < nk; ++t) {
-    __syncthreads();   // the previous chunk is consumed
-#pragma unroll
-    for (int u = 0; u < UA; ++u) stage1(As, TM, PA, A_NC, tid + 256 * u, ra[u]);
-#pragma unroll
-    for (int u = 0; u < UB; ++u) stage1(Bs, TN, PB, B_NC, tid + 256 * u, rb[u]);
+        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, w[s * PB + 16 * j], acc[j], 0, 0, 0);
+      }
+    };
+    const bool live = KIND != KIND_TN || SET == 0 || c < nk;   // (the branch costs a row-tiled GEMM 1 %, more than it saves there)
+    if (live) products(0);
+    stage_b(rb, SET ^ 1, lim_b);
+    fetch_b(rb, t2);
+    lim_b = t2.lim;
+    if (live) products(SPL / 2);
+    fetch_a(pa[SET], t2, slots);
+    t2 = ktile(c + 3);
+    if (gathered) fetch_map(slots, t2);
+  };
+  for (int c = 0; c < nk; c += 2) {     // (a last step of its own would be a second copy of the code, with spills)
+    step(c, std::integral_constant<int, 0>{});
+    step(c + 1, std::integral_constant<int, 1>{});
+  }
+  if constexpr (KW == 2) {
     __syncthreads();
-    if (t + 1 < nk) fetch(ktile(t + 1));
-    unrolled<0, FK / 4>([&](auto k4_tag) {
-      constexpr int k4 = decltype(k4_tag)::value, xa = swz(4 * k4, TM), xb = swz(4 * k4, TN);
-      double a[MB], b[NB];
+    double* red = Bs + (rw * 64 + lane) * (4 * NJ + 1);   // + 1: lanes on different banks
+    if (kw == 1) {
 #pragma unroll
-      for (int i = 0; i < MB; ++i) a[i] = fa[(xa >> 3) & 1][xa / (TM / 2)][4 * k4 * PA + ((16 * i) ^ (xa & (TM / 2 - 16)))];
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) b[j] = fb[(xb >> 3) & 1][xb / (TN / 2)][4 * k4 * PB + ((16 * j) ^ (xb & (TN / 2 - 16)))];
+        for (int r = 0; r < 4; ++r) red[4 * j + r] = acc[j][r];
+    }
+    __syncthreads();
+    if (kw == 1) return;
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    });
+      for (int r = 0; r < 4; ++r) acc[j][r] += red[4 * j + r];
   }
   float* __restrict__ C = reinterpret_cast<float*>(p.C);
   float* __restrict__ C2 = reinterpret_cast<float*>(p.C2);
   const float* __restrict__ Z = reinterpret_cast<const float*>(p.Zin);
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+  for (int r = 0; r < 4; ++r) {
+    const int ml = rw * 16 + 4 * r + (lane >> 4);   // row within the tile
+    int64_t crow;
+    bool zero = false;
+    if (KIND == KIND_TN) {
+      if (m0 + ml >= p.Mdim) continue;
+      crow = (int64_t)g * p.c_goff + p.c_off + (int64_t)(m0 + ml) * p.ldc;
+    } else {
+      const int row = __shfl(o_row, ml, 64);
+      zero = __shfl((int)o_zero, ml, 64) != 0;
+      if (row < 0) continue;
+      crow = (int64_t)row * p.ldc;
+    }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int ml = wm * (TM / 2) + 16 * i + 4 * r + (lane >> 4);   // row within the tile
-      int64_t crow;
-      bool zero = false;
-      if (KIND == KIND_TN) {
-        if (m0 + ml >= p.Mdim) continue;
-        crow = (int64_t)g * p.c_goff + p.c_off + (int64_t)(m0 + ml) * p.ldc;
+    for (int j = 0; j < NJ; ++j) {
+      const int n = n0 + 16 * j + (lane & 15);
+      if (n >= p.Ndim) continue;
+      const float v = zero ? 0.f : (float)acc[j][r];
+      if (EPI == EPI_STORE) {
+        C[crow + n] = v;
+      } else if (EPI == EPI_GELU) {
+        C[crow + n] = v;
+        C2[crow + n] = gelu_f(v);
       } else {
-        const int row = __shfl(o_row, ml, 64);
-        zero = __shfl((int)o_zero, ml, 64) != 0;
-        if (row < 0) continue;
-        crow = (int64_t)row * p.ldc;
-      }
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const int n = n0 + wn * (TN / 2) + 16 * j + (lane & 15);
-        if (n >= p.Ndim) continue;
-        const float v = zero ? 0.f : (float)acc[i][j][r];
-        if (EPI == EPI_STORE) {
-          C[crow + n] = v;
-        } else if (EPI == EPI_GELU) {
-          C[crow + n] = v;
-          C2[crow + n] = gelu_f(v);
-        } else {
-          float ge, dg;
-          gelu_and_grad(Z[crow + n], ge, dg);
-          C[crow + n] = v * dg;
-        }
+        float ge, dg;
+        gelu_and_grad(Z[crow + n], ge, dg);
+        C[crow + n] = v * dg;
       }
     }
+  }
 }
 
-template <int KIND, int EPI, int TM, int TN>
+template <int KIND, int EPI, int T, bool WIDE>   // T x T tiles
 __global__ __launch_bounds__(256, 4) void ffn_gemm_f32(const GemmArgs p) {   // (the 4 keeps the accumulators out of the AGPRs)
-  __shared__ __attribute__((aligned(16))) double smem[f32_lds<TM, TN>() / 8];
-  gemm_f32_tile<KIND, EPI, TM, TN>(p, smem, (int)blockIdx.x);
+  __shared__ __attribute__((aligned(16))) double smem[f32_lds<T, T>() / 8];
+  gemm_f32_tile<KIND, EPI, T, T, WIDE>(p, smem, (int)blockIdx.x);
 }
 // the three backward GEMMs that only depend on dZ, as in ffn_bwd_trio
-template <int TM, int TN>
+template <int T, bool WIDE>
 __global__ __launch_bounds__(256, 4) void ffn_bwd_trio_f32(const GemmArgs px, const GemmArgs pw2, const GemmArgs pw1, int nbx,
                                                            int nbw) {
-  __shared__ __attribute__((aligned(16))) double smem[f32_lds<TM, TN>() / 8];
+  __shared__ __attribute__((aligned(16))) double smem[f32_lds<T, T>() / 8];
   const int b = (int)blockIdx.x;
-  if (b < nbx) gemm_f32_tile<KIND_NT, EPI_STORE, TM, TN>(px, smem, b);
-  else gemm_f32_tile<KIND_TN, EPI_STORE, TM, TN>(b < nbx + nbw ? pw2 : pw1, smem, b < nbx + nbw ? b - nbx : b - nbx - nbw);
+  if (b < nbx) gemm_f32_tile<KIND_NT, EPI_STORE, T, T, WIDE>(px, smem, b);
+  else gemm_f32_tile<KIND_TN, EPI_STORE, T, T, WIDE>(b < nbx + nbw ? pw2 : pw1, smem, b < nbx + nbw ? b - nbx : b - nbx - nbw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1674,28 +1729,31 @@ int grid_of(const GemmArgs& a) {
   return (a.total_tiles + (a.cnt ? 14 : 7)) / 8 * 8 + (a.cnt && a.n_src > 1 ? MORE_SHARES : 0);
 }
 
-// fp32 tiles: the largest (fewest conversions per product) that gives every compute unit enough workgroups to even out
+// fp32 tiles, T x T: 64 where they give every compute unit three or more and do not pad the rows by an eighth more than
+// those of 32 do.  Forward or backward call with all GEMMs but one as planned, that one in tiles of 64 and of 32: 8 experts of 256 x 512 x
+// 2048, Z (1280 tiles of 64) 159 and 168 us, Y (320) 160 and 159; 4 of 820 x 768 x 3072, Y (720) 563 and 537; 2 of 3690 x 256 x 512, Z
+// (928) 89 and 93, the merged backward launch (592) 234 and 198; 24 of 72 x 768 x 1024, Z (768, 128 rows for 96) 153 and 142;
+// 16 of 64 x 512 x 1024, merged (4224) 100 and 121.  32 x 64 was nowhere better than both.
 using I32 = std::integral_constant<int, 32>;
 using I64 = std::integral_constant<int, 64>;
-int64_t tiles_f32(const GemmArgs& a, bool tn, int tile_m, int tile_n) {
+int64_t tiles_f32(const GemmArgs& a, bool tn, int tile) {
   const int64_t rows = priced_rows(a, tn);
-  return (int64_t)a.G * ((rows + tile_m - 1) / tile_m) * ((a.Ndim + tile_n - 1) / tile_n);
+  return (int64_t)a.G * ((rows + tile - 1) / tile) * ((a.Ndim + tile - 1) / tile);
 }
-int plan_f32(int64_t tiles_64x64, int64_t tiles_32x64) {   // 2: 64 x 64, 1: 32 x 64, 0: 32 x 32
-  const int64_t enough = 4 * (int64_t)num_cus();
-  return tiles_64x64 >= enough ? 2 : tiles_32x64 >= enough ? 1 : 0;
-}
-int f32_tile_m(int size) { return size == 2 ? 64 : 32; }
+// Offsets within a tile's 64 rows of an operand are 32-bit but for leading dimensions of 16 million and more.
+bool wide_f32(const GemmArgs& a) { return std::max(a.lda, a.ldb) >= 1 << 24; }
 int plan_f32(const GemmArgs& a) {   // of a row-tiled GEMM
-  return plan_f32(tiles_f32(a, false, 64, 64), tiles_f32(a, false, 32, 64));
+  if (wide_f32(a)) return 32;
+  const int64_t rows = priced_rows(a, false), rows64 = (rows + 63) / 64 * 64, rows32 = (rows + 31) / 32 * 32;
+  return tiles_f32(a, false, 64) >= 3 * (int64_t)num_cus() && 8 * rows64 <= 9 * rows32 ? 64 : 32;
 }
 int plan_f32_trio(const GemmArgs& dx, const GemmArgs& w2, const GemmArgs& w1) {   // of the merged backward launch
-  return plan_f32(tiles_f32(dx, false, 64, 64) + tiles_f32(w2, true, 64, 64) + tiles_f32(w1, true, 64, 64),
-                  tiles_f32(dx, false, 32, 64) + tiles_f32(w2, true, 32, 64) + tiles_f32(w1, true, 32, 64));
+  if (wide_f32(dx) || wide_f32(w2) || wide_f32(w1)) return 32;
+  return tiles_f32(dx, false, 64) + tiles_f32(w2, true, 64) + tiles_f32(w1, true, 64) >= 3 * (int64_t)num_cus() ? 64 : 32;
 }
-void prepare_f32(GemmArgs& a, bool tn, int tile_m, int tile_n) {
-  a.tiles_m = (a.Mdim + tile_m - 1) / tile_m;
-  a.tiles_n = (a.Ndim + tile_n - 1) / tile_n;
+void prepare_f32(GemmArgs& a, bool tn, int tile) {
+  a.tiles_m = (a.Mdim + tile - 1) / tile;
+  a.tiles_n = (a.Ndim + tile - 1) / tile;
   a.total_tiles = a.G * a.tiles_m * a.tiles_n;
   a.run_mask = tile_runs(a, tn, 4);
 }
@@ -1705,15 +1763,15 @@ void launch_gemm(GemmArgs a, int dtype, int tile, hipStream_t st) {
   static_assert(KIND != KIND_TN, "weight gradients go out in the merged launches, or through launch_weight_small");
   if constexpr (KIND == KIND_NN || EPI == EPI_DGELU) {   // (the fp32 dX is always in the merged launch)
     if (dtype == MOE_F32) {
-      const int size = plan_f32(a);
-      auto launch = [&](auto tm_tag, auto tn_tag) {
-        constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
-        prepare_f32(a, false, TM, TN);
-        hipLaunchKernelGGL((ffn_gemm_f32<KIND, EPI, TM, TN>), dim3((unsigned)grid_of(a)), dim3(256), 0, st, a);
+      auto launch = [&](auto tile_tag, auto wide) {
+        constexpr int T = decltype(tile_tag)::value;
+        prepare_f32(a, false, T);
+        hipLaunchKernelGGL((ffn_gemm_f32<KIND, EPI, T, decltype(wide)::value>), dim3((unsigned)grid_of(a)), dim3(256), 0, st, a);
       };
-      if (size == 2) launch(I64{}, I64{});
-      else if (size == 1) launch(I32{}, I64{});
-      else launch(I32{}, I32{});
+      const int tile_f32 = plan_f32(a);
+      if (tile_f32 == 64) launch(I64{}, std::false_type{});
+      else if (!wide_f32(a)) launch(I32{}, std::false_type{});
+      else launch(I32{}, std::true_type{});
       return;
     }
   }
@@ -1788,7 +1846,7 @@ extern "C" double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C,
     p.Mdim = Mdim; p.Ndim = Ndim; p.Kdim = Kdim;
     return p;
   };
-  auto alone = [&](GemmArgs p) { return dtype == MOE_F32 ? f32_tile_m(plan_f32(p)) : prepare_bf16(p, false, tile).tile_m; };
+  auto alone = [&](GemmArgs p) { return dtype == MOE_F32 ? plan_f32(p) : prepare_bf16(p, false, tile).tile_m; };
   const GemmArgs to_h = gemm(a.R, Hl, M), to_m = gemm(a.R, M, Hl);
   double rows;
   if (!backward) {   // Z = X W1 (rows x Hl), Y = A W2 (rows x M)
@@ -1799,7 +1857,7 @@ extern "C" double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C,
       const int merged = merged_backward(w2, w1, tile);
       return merged == 128 && !dx_alone(dx) ? Tile64x128::TM : prepare_bf16(dx, false, tile, merged == 256).tile_m;
     };
-    const int dx_m = dtype == MOE_F32 ? f32_tile_m(plan_f32_trio(dx, w2, w1)) : dx_tile();
+    const int dx_m = dtype == MOE_F32 ? plan_f32_trio(dx, w2, w1) : dx_tile();
     rows = rows_multiplied(a, alone(to_h)) + rows_multiplied(a, dx_m) + 2.0 * rows_multiplied(a, 0);
   }
   return 2.0 * (double)M * (double)Hl * rows;
@@ -1979,16 +2037,15 @@ static int ffn_bwd_impl(const void* dY, const void* X, const int32_t* gather, in
     }
   }
   if (dtype == MOE_F32) {   // one launch here too
-    const int size = plan_f32_trio(dx, w2, w1);
-    auto launch = [&](auto tm_tag, auto tn_tag) {
-      constexpr int TM = decltype(tm_tag)::value, TN = decltype(tn_tag)::value;
-      prepare_f32(dx, false, TM, TN); prepare_f32(w2, true, TM, TN); prepare_f32(w1, true, TM, TN);
+    auto launch = [&](auto tile_tag, auto wide) {
+      constexpr int T = decltype(tile_tag)::value;
+      prepare_f32(dx, false, T); prepare_f32(w2, true, T); prepare_f32(w1, true, T);
       const int nbx = grid_of(dx), nb2 = grid_of(w2), nb1 = grid_of(w1);
-      hipLaunchKernelGGL((ffn_bwd_trio_f32<TM, TN>), dim3((unsigned)(nbx + nb2 + nb1)), dim3(256), 0, st, dx, w2, w1, nbx, nb2);
+      hipLaunchKernelGGL((ffn_bwd_trio_f32<T, decltype(wide)::value>), dim3((unsigned)(nbx + nb2 + nb1)), dim3(256), 0, st, dx, w2, w1, nbx, nb2);
     };
-    if (size == 2) launch(I64{}, I64{});
-    else if (size == 1) launch(I32{}, I64{});
-    else launch(I32{}, I32{});
+    if (plan_f32_trio(dx, w2, w1) == 64) launch(I64{}, std::false_type{});
+    else if (!wide_f32(dx) && !wide_f32(w2) && !wide_f32(w1)) launch(I32{}, std::false_type{});
+    else launch(I32{}, std::true_type{});
     return moe::check_launch();
   }
   launch_weight_small(w2, st);
