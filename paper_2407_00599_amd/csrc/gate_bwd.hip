@@ -31,12 +31,19 @@ struct Picks {
   float w[MOE_MAX_K], g[MOE_MAX_K];
   int e[MOE_MAX_K];
   float inner;   // sum_j w_j dw_j
+  Picks() = default;
   __device__ __forceinline__ Picks(const float* dw, const float* wt, const int32_t* idx, int64_t t, int k) {
+    fetch(dw, wt, idx, t, k);
+    add_up(k);
+  }
+  __device__ __forceinline__ void fetch(const float* dw, const float* wt, const int32_t* idx, int64_t t, int k) {
 #pragma unroll
     for (int j = 0; j < MOE_MAX_K; ++j) {
       const int64_t at = t * k + (j < k ? j : k - 1);
       w[j] = wt[at]; g[j] = dw[at]; e[j] = idx[at];
     }
+  }
+  __device__ __forceinline__ void add_up(int k) {
     inner = 0.f;
 #pragma unroll
     for (int j = 0; j < MOE_MAX_K; ++j)
@@ -151,6 +158,16 @@ __device__ __forceinline__ void st4g(void* base, int64_t off, const float* f) {
     *reinterpret_cast<float4*>(reinterpret_cast<float*>(base) + off) = make_float4(f[0], f[1], f[2], f[3]);
   }
 }
+template <bool BF16>
+__device__ __forceinline__ void st4g(__amdgpu_buffer_rsrc_t row, uint32_t at, const float (&f)[4]) {
+  if (BF16) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3])}, row, at, 0, 0);
+  } else {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])}, row, at, 0, 0);
+  }
+}
 
 // raw (unconverted) CPT elements of a row: requested for all tokens of a stage first, converted when used
 template <bool BF16, int CPT>
@@ -165,6 +182,19 @@ struct RawRow {
       for (int i = 0; i < NB / 16; ++i) {
         const uint4 v = reinterpret_cast<const uint4*>(p)[i];
         r[4 * i] = v.x; r[4 * i + 1] = v.y; r[4 * i + 2] = v.z; r[4 * i + 3] = v.w;
+      }
+    }
+  }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t row, uint32_t at) {     // at: bytes
+    constexpr int ND = BF16 ? CPT / 2 : CPT;
+    if constexpr (ND == 2) {
+      const auto v = __builtin_amdgcn_raw_buffer_load_b64(row, at, 0, 0);
+      r[0] = v[0]; r[1] = v[1];
+    } else {
+#pragma unroll
+      for (int i = 0; i < ND / 4; ++i) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(row, at + 16 * i, 0, 0);
+        r[4 * i] = v[0]; r[4 * i + 1] = v[1]; r[4 * i + 2] = v[2]; r[4 * i + 3] = v[3];
       }
     }
   }
@@ -194,6 +224,11 @@ struct RawRow {
 // them: a version that unrolled 16 tokens was 17 to 34 KB of straight-line code and, with one wave per chunk, wrote
 // eight times the partial sums.  Against that version, the call with its reduction: 2048 x 768, 16 experts: 32.8 ->
 // 19.6 us; 4096 x 1024, 8 experts: 22.9 -> 20.2 us; 1003 x 520, 12 experts: 24.2 -> 17.2 us; 32768 x 4096, 8 experts: 205 -> 182 us.
+// A wave's first stage is requested before the dlogits are formed and every later one while its predecessor is used, token by
+// token; a stage without branches keeps the compiler from moving all its sums behind them, which spilled.  The call, with requests
+// in the stage itself and with this: 2048 x 768, 16 experts: 19.4 -> 16.9 us; 4096 x 1024, 8: 19.9 -> 18.1; 8192 x 1024, top-1 of 8: 23.4 ->
+// 20.2; 32768 x 4096, 8: 182 -> 171; 16384 x 2048, top-4 of 16: 91 -> 69; fp32, 5000 x 1024, 16: 36 -> 29.  The choices' weights requested
+// earlier as well: 16.6, 19.1, 23.1, 174, 68, 28 (8 experts spill).
 // ---------------------------------------------------------------------------------------------
 constexpr int FW = 4;                                    // waves per block
 constexpr int FT = 4;                                    // tokens per stage of a wave
@@ -219,31 +254,70 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
   static_assert(FW * HPITCH >= PITCH, "holds the slab of Wg too");
   __shared__ __attribute__((aligned(16))) float dls[FUSED_CHUNK * EC];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int mb = blockIdx.x * MT, m0 = mb + lane * CPT;
-  const bool mok = m0 < M;
-  const int mc = mok ? m0 : 0;     // a lane behind the last column works on the first ones and stores nothing
+  const int mb = blockIdx.x * MT;
   const int tb = (int)blockIdx.y * chunk, te = tb + min(chunk, S - tb);   // S k < 2^31
   const int rest_row = (int)(gridDim.y + blockIdx.y);    // row for what rounding leaves, if there is one
   const bool lone = rest_row >= nrows && te - tb <= 2 * FT;   // without it a few tokens are one wave's, one chain of sums
 
-  // The block's slab of Wg, contiguous in memory, goes through LDS once for the four waves: read directly, a lane's
-  // weights are strided pieces, and every request of a wave is 64 lines.
-  for (int i = tid; i < MT * E; i += NTHR) {
-    const int m = i / E, e = i - m * E;
-    outs[e * PITCH + m] = mb + m < M ? Wg[(int64_t)mb * E + i] : 0.f;
-  }
-  float wr[CPT][EC], acc[EC][CPT];
+  float acc[EC][CPT];
 #pragma unroll
   for (int e = 0; e < EC; ++e)
 #pragma unroll
     for (int q = 0; q < CPT; ++q) acc[e][q] = 0.f;
   float colsum = 0.f;   // thread EC q + e of column block 0, q < 4, sums dl[t, e] over the tokens t = q (mod 4) for the bias row
 
-  for (int done = 0; done < te - tb; done += FUSED_CHUNK) {
+  // a wave's next stage is requested token by token as the current one is used, the first one before the dlogits are formed
+  const int n = te - tb, step = lone ? FT : FW * FT;
+  int pos = lone && wave > 0 ? n : wave * FT;
+  RawRow<BF16, CPT> xr[FT], dr[FT];
+  // Rows through descriptors: behind the chunk's end, behind the last column, and dx that is not read, zeros come without a
+  // request and stores go nowhere, so that a stage is one piece of code without branches.
+  constexpr int ESZ = BF16 ? 2 : 4;
+  const uint32_t row_bytes = (uint32_t)min(MT, M - mb) * ESZ, at = (uint32_t)lane * CPT * ESZ;
+  auto row_of = [&](const void* base, int tok, bool there) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(reinterpret_cast<const char*>(base)) + ((tb + min(tok, n - 1)) * (int64_t)M + mb) * ESZ,
+                                             0, there && tok < n ? row_bytes : 0u, 0x00020000);
+  };
+  auto fetch = [&](int u, int tok) {
+    xr[u].load(row_of(x, tok, true), at);
+    dr[u].load(row_of(dx, tok, accumulate != 0), at);
+  };
+  const uint32_t inv_e = 65536u / (uint32_t)E + 1u;   // i / E = i inv_e >> 16 for i < 4096, E <= 16
+  static_assert(MT * 16 <= 4096 && FUSED_CHUNK * 16 <= 4096, "");
+
+  for (int done = 0; done < n; done += FUSED_CHUNK) {
     const int c0 = tb + done, nc = min(te - c0, FUSED_CHUNK);
     if (done > 0) __syncthreads();   // the previous dl rows are consumed
-    if (tid < nc) {
-      const int64_t t = c0 + tid;
+    if (done == 0) {
+      // The block's slab of Wg, contiguous in memory, goes through LDS once for the four waves: read directly, a lane's
+      // weights are strided pieces, and every request of a wave is 64 lines.
+      const float* slab = Wg + (int64_t)mb * E;
+      const int ms = min(MT, M - mb);
+      if (E % 4 == 0) {
+        float4 v[EC / 4];
+#pragma unroll
+        for (int u = 0; u < EC / 4; ++u) v[u] = reinterpret_cast<const float4*>(slab)[min(tid + NTHR * u, ms * E / 4 - 1)];
+#pragma unroll
+        for (int u = 0; u < FT; ++u) fetch(u, pos + u);
+#pragma unroll
+        for (int u = 0; u < EC / 4; ++u) {
+          const int i = (tid + NTHR * u) * 4, m = (int)((uint32_t)i * inv_e >> 16), e = i - m * E;
+          if (m < MT) {
+            outs[e * PITCH + m] = v[u].x; outs[(e + 1) * PITCH + m] = v[u].y;
+            outs[(e + 2) * PITCH + m] = v[u].z; outs[(e + 3) * PITCH + m] = v[u].w;
+          }
+        }
+      } else {
+        for (int i = tid; i < ms * E; i += NTHR) {
+          const int m = (int)((uint32_t)i * inv_e >> 16);
+          outs[(i - m * E) * PITCH + m] = slab[i];
+        }
+#pragma unroll
+        for (int u = 0; u < FT; ++u) fetch(u, pos + u);
+      }
+    }
+    if (wave * 64 < nc) {
+      const int64_t t = c0 + min(tid, nc - 1);
       const Picks p(dw, w, idx, t, k);
       float row[EC];
 #pragma unroll
@@ -263,51 +337,41 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
 #pragma unroll
         for (int e = 0; e < EC; ++e) row[e] = e < E ? -(row[e] / den) * p.inner : 0.f;
       }
+      // rows behind the chunk's end: zeros, which the last stage multiplies
 #pragma unroll
-      for (int e = 0; e < EC; ++e) dls[tid * EC + e] = row[e];
-      for (int j = 0; j < k; ++j) {
-        const float wj = w[t * k + j], gj = dw[t * k + j];   // (in the cache by now; a register array would not be indexed)
-        const int ej = idx[t * k + j];
-        if ((unsigned)ej < (unsigned)E) dls[tid * EC + ej] += norm_topk ? wj * (gj - p.inner) : wj * gj;
-      }
-    } else {   // rows behind the chunk's end: zeros, which the last stage multiplies
+      for (int e = 0; e < EC; ++e) dls[tid * EC + e] = tid < nc ? row[e] : 0.f;
 #pragma unroll
-      for (int e = 0; e < EC; ++e) dls[tid * EC + e] = 0.f;
+      for (int j = 0; j < MOE_MAX_K; ++j)
+        if (tid < nc && (unsigned)p.e[j] < (unsigned)E)      // (-1 from k on)
+          dls[tid * EC + p.e[j]] += norm_topk ? p.w[j] * (p.g[j] - p.inner) : p.w[j] * p.g[j];
     }
     __syncthreads();
-    if (done == 0) {
+    float wr[CPT][EC];     // (read again for further dlogits rows: not held while these are formed)
 #pragma unroll
-      for (int e = 0; e < EC; ++e) {
-        const float4 v = e < E ? *reinterpret_cast<const float4*>(&outs[e * PITCH + lane * CPT]) : make_float4(0.f, 0.f, 0.f, 0.f);
-        wr[0][e] = v.x; wr[1][e] = v.y; wr[2][e] = v.z; wr[3][e] = v.w;
-      }
+    for (int e = 0; e < EC; ++e) {
+      const float4 v = e < E ? *reinterpret_cast<const float4*>(&outs[e * PITCH + lane * CPT]) : make_float4(0.f, 0.f, 0.f, 0.f);
+      wr[0][e] = v.x; wr[1][e] = v.y; wr[2][e] = v.z; wr[3][e] = v.w;
     }
     if (blockIdx.x == 0) {
       // through a descriptor: a 32-bit offset per lane instead of an address, which would not stay in a register
-      const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(dl_out + (int64_t)c0 * E, 0, (uint32_t)(nc * E * 4), 0x00020000);
+      const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(dl_out + (int64_t)c0 * E, 0, (uint32_t)(nc * E * 4), 0x00020000);
       for (int i = tid; i < nc * E; i += NTHR) {
-        const int t = i / E, e = i - t * E;
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dls[t * EC + e]), rows, i * 4, 0, 0);
+        const int t = (int)((uint32_t)i * inv_e >> 16), e = i - t * E;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dls[t * EC + e]), rl, i * 4, 0, 0);
       }
       if (tid < 4 * EC) {
 #pragma unroll 8
         for (int t = 0; t < nc; t += 4) colsum += dls[t * EC + tid];   // (rows behind the end are zeros)
       }
     }
-    for (int u0 = lone && wave > 0 ? nc : wave * FT; u0 < nc; u0 += lone ? FT : FW * FT) {
-      RawRow<BF16, CPT> xr[FT], dr[FT];
+    for (; pos < done + nc; pos += step) {
+      const int u0 = pos - done;
 #pragma unroll
-      for (int u = 0; u < FT; ++u) {   // a row behind the end: the last one again, not stored, its dl row is zero
-        const int64_t at = (c0 + min(u0 + u, nc - 1)) * (int64_t)M + mc;
-        xr[u].load(x, at);
-        if (accumulate) dr[u].load(dx, at); else dr[u].zero();
-      }
-#pragma unroll
-      for (int u = 0; u < FT; ++u) {
-        const bool in = u0 + u < nc;
+      for (int u = 0; u < FT; ++u) {   // a row behind the end: zeros
         float xv[CPT], dv[CPT];
 #pragma unroll
-        for (int q = 0; q < CPT; ++q) { xv[q] = in ? xr[u].get(q) : 0.f; dv[q] = dr[u].get(q); }
+        for (int q = 0; q < CPT; ++q) { xv[q] = xr[u].get(q); dv[q] = dr[u].get(q); }
+        fetch(u, pos + step + u);
 #pragma unroll
         for (int e4 = 0; e4 < EC; e4 += 4) {
           const float4 d4 = *reinterpret_cast<const float4*>(&dls[(u0 + u) * EC + e4]);
@@ -320,7 +384,7 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
               dv[q] = fmaf(d[v], wr[q][e4 + v], dv[q]);
             }
         }
-        if (in && mok) st4g<BF16>(dx, (c0 + u0 + u) * (int64_t)M + m0, dv);
+        st4g<BF16>(row_of(dx, pos + u, true), at, dv);
       }
     }
   }

@@ -54,6 +54,17 @@ def test_gate_bwd(S, M, E, k, norm, dtype, acc):
         assert np.all(to_host(dl) == 0)
 
 
+# the slab of Wg in 16-byte pieces (4 | E) that end within a block's 256 columns or behind them, and element by element; stages that are
+# requested before the dlogits rows of the next 256 tokens exist.  (norm_topk in fp32 with an old dx: dl[e_j] = w_j (dw_j - sum w dw) is
+# off by up to (k + 2) 2^-24 max|dw| times w_j where it cancels, and a row of dx consists of nothing else without one.)
+@pytest.mark.parametrize("S,M,E,k,norm,dtype,acc", [
+    (19, 40, 12, 3, 1, "bf16", 0), (300, 280, 12, 8, 1, "f32", 1), (66003, 32, 12, 2, 0, "bf16", 1), (66003, 24, 6, 2, 1, "f32", 1),
+    (2100, 264, 10, 4, 0, "bf16", 1),
+])
+def test_gate_bwd_slab_and_stages(S, M, E, k, norm, dtype, acc):
+    test_gate_bwd(S, M, E, k, norm, dtype, acc)
+
+
 @pytest.mark.parametrize("S", [16, 100, 2048, 4096, 5000, 70001])
 def test_bias_gradient_rounding(S):
     """The bias gradient of up to 16 experts: fp32 sums over quarters of a token chunk, added up in fp64 and rounded.  At most
