@@ -686,9 +686,11 @@ __global__ __launch_bounds__(topk_tokens(W, ONE) * W) void gate_topk(const float
   }
   __syncthreads();
   if constexpr (!ONE) {
-    // [choice][expert][block] for gate_scan, which reads a (choice, expert) row, or [block][choice][expert]
-    for (int i = tid; i < npair; i += NT)
-      blockhist[pair_major ? (int64_t)i * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * npair + i] = hist[i];
+    // [choice][expert][block] for gate_scan, which reads a (choice, expert) row, or bytes [block][choice][expert]
+    for (int i = tid; i < npair; i += NT) {
+      if (pair_major) blockhist[(int64_t)i * gridDim.x + blockIdx.x] = hist[i];
+      else reinterpret_cast<uint8_t*>(blockhist)[(int64_t)blockIdx.x * npair + i] = (uint8_t)hist[i];   // at most 64
+    }
   } else {
     // choice-major queues: positions of the first token of every (64 tokens, choice, expert)
     for (int e = tid; e < E; e += NT) {
@@ -754,8 +756,11 @@ __global__ __launch_bounds__(256) void gate_scan(const int32_t* __restrict__ blo
 // SLOTS_SCAN: queue positions of the block's first tokens come from gate_scan (base, counts).
 // SLOTS_HIST: every block works them out itself from the histograms [block][choice][expert] -- for each
 // (choice j, expert e) the demand of the earlier blocks, plus all demand of the earlier choices -- which saves the
-// scan launch; block 0 also writes counts.  Same integers either way.  The histogram rows are read four pairs at a time
-// by groups of threads that share the blocks between them, and the groups' sums meet in LDS.
+// scan launch; block 0 also writes counts.  Same integers either way.  A count of 64 tokens fits in a byte: rows of bytes are read
+// four pairs at a time by groups of threads that share the blocks between them, and the groups' sums meet in LDS.  The rows come from
+// the other XCDs' writes, and a thread's up to 16 requests at a time are in flight together: with a loop of strided int32 rows,
+// which the compiler left one request deep, the gate of 8192 tokens x 2048, top-4 of 128, took 87.5 us, now 81.2; 4096 x 256, top-8 of
+// 64, 21.8 and 19.1; 24000 x 64, top-3 of 32, 24.1 and 19.2.
 // SLOTS_IDX: the same from the choices themselves, which every block counts (integer sums in LDS: the order does not matter); the
 // logits kernel has then selected the experts, and there are no histograms.
 constexpr int SLOT_NT = 512;
@@ -802,28 +807,43 @@ __global__ __launch_bounds__(SLOT_NT) void gate_slots(const int32_t* __restrict_
         tot_s[i] = pre + post;
       }
     }
-    auto sum_rows = [&](auto vec_tag) {   // V pairs per thread and step
-      constexpr int V = decltype(vec_tag)::value;
-      typedef int32_t vec_t __attribute__((ext_vector_type(V)));
+    auto sum_rows = [&](auto vec_tag) {   // V pairs per thread and row
+      typedef decltype(vec_tag) vec_t;
+      constexpr int V = sizeof(vec_t);
+      const vec_t* hist = reinterpret_cast<const vec_t*>(base);
       const int nu = npair / V;
       int lanes = 1;
       while (lanes < nu && lanes < SLOT_NT) lanes <<= 1;
       const int groups = SLOT_NT / lanes, gr = tid / lanes;
-      for (int u = tid % lanes; u < nu; u += lanes) {
-        int tot[V] = {}, pre[V] = {};
-#pragma unroll 8
-        for (int b = gr; b < nblk; b += groups) {
-          const vec_t h = *reinterpret_cast<const vec_t*>(base + (int64_t)b * npair + u * V);
+      auto add_up = [&](int u, auto u_tag) {
+        constexpr int U = decltype(u_tag)::value;   // rows requested together
+        uint32_t tot[2] = {}, pre[2] = {};   // two 16-bit sums each, of up to 512 rows (see the rule) of up to 64
+        for (int b = gr; b < nblk; b += U * groups) {
+          uint32_t h[U];
 #pragma unroll
-          for (int q = 0; q < V; ++q) { tot[q] += h[q]; pre[q] += b < me ? h[q] : 0; }
+          for (int q = 0; q < U; ++q) h[q] = hist[(uint32_t)(min(b + q * groups, nblk - 1) * nu + u)];
+#pragma unroll
+          for (int q = 0; q < U; ++q) {
+            const int bq = b + q * groups;
+            const uint32_t v = bq < nblk ? h[q] : 0u, ev = v & 0x00FF00FFu, od = (v >> 8) & 0x00FF00FFu;
+            tot[0] += ev; tot[1] += od;
+            pre[0] += bq < me ? ev : 0u; pre[1] += bq < me ? od : 0u;
+          }
         }
 #pragma unroll
-        for (int q = 0; q < V; ++q) { atomicAdd(&tot_s[u * V + q], tot[q]); atomicAdd(&base_s[u * V + q], pre[q]); }
+        for (int q = 0; q < V; ++q) {
+          atomicAdd(&tot_s[u * V + q], (int)(tot[q & 1] >> (8 * (q & 2)) & 0xFFFFu));
+          atomicAdd(&base_s[u * V + q], (int)(pre[q & 1] >> (8 * (q & 2)) & 0xFFFFu));
+        }
+      };
+      for (int u = tid % lanes; u < nu; u += lanes) {
+        if (nblk <= 4 * groups) add_up(u, std::integral_constant<int, 4>{});
+        else add_up(u, std::integral_constant<int, 16>{});
       }
     };
     if constexpr (FROM == SLOTS_HIST) {
-      if (npair % 4 == 0) sum_rows(std::integral_constant<int, 4>{});
-      else sum_rows(std::integral_constant<int, 1>{});
+      if (npair % 4 == 0) sum_rows(uint32_t{});
+      else sum_rows(uint8_t{});
     }
     __syncthreads();
     // choice-major queues: all demand of the earlier choices at expert e comes first
@@ -995,10 +1015,11 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     hipLaunchKernelGGL(gate_slots<SLOTS_IDX>, dim3(nblk), dim3(SLOT_NT), 0, st, idx, nullptr, counts, S, E, k, C, slot, inv);
     return moe::check_launch();
   }
-  // Every block reads all histograms itself up to 256 KiB of them and 64 MiB over all blocks (a few microseconds from L2,
-  // what the scan launch costs).
+  // Every block reads all histograms (a byte per block, choice and expert) itself up to 256 KiB of them and 64 MiB over all blocks.
+  // The gate with the scan launch and without: 8192 x 256, top-8 of 256 (256 KiB, 32 MiB) 52.1 and 46.4 us; 16384 x 256, top-2 of 256 (128
+  // KiB, 32 MiB) 57.6 and 54.0; 70000 x 64, top-2 of 16 (34 KiB, 37 MiB) 41.8 and 29.9; 32768 x 256, top-2 of 64 (64 KiB, 32 MiB) 40.2 and 32.9.
   const int64_t npair = (int64_t)k * E;
-  const bool self = nblk * npair <= 65536 && (int64_t)nblk * nblk * npair <= (1 << 24);
+  const bool self = nblk * npair <= 1 << 18 && (int64_t)nblk * nblk * npair <= 1 << 26;
   auto route = [&](auto w_tag, auto epl_tag) {   // returns true: the slots are assigned too
     constexpr int W = decltype(w_tag)::value, EPL = decltype(epl_tag)::value;
     if (S <= topk_tokens(W, true)) {
