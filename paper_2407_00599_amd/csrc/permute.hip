@@ -2,9 +2,8 @@
 // the expert outputs are combined back to token order) and the local sum of the N_ESP
 // partial results that return through the EP&ESP-AlltoAll (Section III-C).
 //
-// All three kernels are row movers bound by HBM bandwidth.  They run in gather form: every
-// output row is produced by exactly one wave, reading its source rows through the slot
-// maps, so there are no atomics and no prior memset; 16-byte accesses per lane.
+// The kernels are row movers bound by HBM bandwidth.  Every output row is produced by exactly one wave (gather form; in the combine
+// backward a token's wave writes its slots' rows), so there are no atomics and no prior memset; 16-byte accesses per lane.
 #include "common.h"
 
 namespace {
