@@ -1841,24 +1841,24 @@ extern "C" double moe_ffn_executed_flops(int dtype, int n_src, int G, int64_t C,
   GemmArgs a{};   // the problems as the calls below plan them
   a.G = G; a.n_src = n_src; a.Cc = (int)C; a.R = (int)(n_src * C);
   a.cnt = ignores_counts(dtype, tile) ? nullptr : row_counts_host;
-  auto gemm = [&](int Mdim, int Ndim, int Kdim) {
+  auto gemm = [&](int Mdim, int Ndim, int Kdim, int lda, int ldb) {
     GemmArgs p = a;
     p.Mdim = Mdim; p.Ndim = Ndim; p.Kdim = Kdim;
+    p.lda = lda; p.ldb = ldb;
     return p;
   };
   auto alone = [&](GemmArgs p) { return dtype == MOE_F32 ? plan_f32(p) : prepare_bf16(p, false, tile).tile_m; };
-  const GemmArgs to_h = gemm(a.R, Hl, M), to_m = gemm(a.R, M, Hl);
   double rows;
   if (!backward) {   // Z = X W1 (rows x Hl), Y = A W2 (rows x M)
-    rows = rows_multiplied(a, alone(to_h)) + rows_multiplied(a, alone(to_m));
+    rows = rows_multiplied(a, alone(gemm(a.R, Hl, M, M, H))) + rows_multiplied(a, alone(gemm(a.R, M, Hl, Hl, M)));
   } else {           // dA = dY W2^T (rows x Hl), dX = dZ W1^T (rows x M), dW2 (Hl x M) and dW1 (M x Hl) over the rows
-    GemmArgs w2 = gemm(Hl, M, a.R), w1 = gemm(M, Hl, a.R), dx = to_m;
+    GemmArgs w2 = gemm(Hl, M, a.R, Hl, M), w1 = gemm(M, Hl, a.R, M, Hl), dx = gemm(a.R, M, Hl, Hl, H);
     auto dx_tile = [&]() {
       const int merged = merged_backward(w2, w1, tile);
       return merged == 128 && !dx_alone(dx) ? Tile64x128::TM : prepare_bf16(dx, false, tile, merged == 256).tile_m;
     };
     const int dx_m = dtype == MOE_F32 ? plan_f32_trio(dx, w2, w1) : dx_tile();
-    rows = rows_multiplied(a, alone(to_h)) + rows_multiplied(a, dx_m) + 2.0 * rows_multiplied(a, 0);
+    rows = rows_multiplied(a, alone(gemm(a.R, Hl, M, M, M))) + rows_multiplied(a, dx_m) + 2.0 * rows_multiplied(a, 0);
   }
   return 2.0 * (double)M * (double)Hl * rows;
 }

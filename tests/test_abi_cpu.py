@@ -183,6 +183,12 @@ def test_executed_flops_accounting(L):
     for t in range(4):
         assert f(api.MOE_F32, n_src, G, C, M, H, 1, one, True, tile=t) == 2 * (2.0 * G * 64 * M * H) + 2 * (2.0 * G * 1 * M * H)
         assert f(api.MOE_F32, n_src, G, C, 64, 64, 1, one, tile=t) == 2 * (2.0 * G * 32 * 64 * 64)
+    # leading dimensions of 2^24 and more: 32-row tiles in the GEMMs that have one as lda or ldb, whatever their count
+    wide, C_ = 1 << 24, 64
+    n = np.ones((1, 1), np.int32)
+    for M_, H_, fwd, bwd in ((64, wide, 32 + 32, 64 + 32), (wide, 64, 32 + 32, 32 + 32), (64, wide - 8, 64 + 32, 64 + 64)):
+        assert f(api.MOE_F32, 1, 1, C_, M_, H_, 1, n) == 2.0 * fwd * M_ * H_, (M_, H_)        # Z, Y
+        assert f(api.MOE_F32, 1, 1, C_, M_, H_, 1, n, True) == 2.0 * (bwd + 2) * M_ * H_, (M_, H_)      # dA, dX, and a row in dW1, dW2
     # dX in the merged backward launch, which has no tiles of 64 columns, takes 64 rows; alone, as A W2 does, it would take 32
     assert f(api.MOE_BF16, n_src, G, 64, M, H, 1, one) == 2.0 * G * (64 + 32) * M * H
     assert f(api.MOE_BF16, n_src, G, 64, M, H, 1, one, True) == 2.0 * G * (64 + 64 + 2) * M * H
