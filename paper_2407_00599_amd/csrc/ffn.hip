@@ -1338,7 +1338,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* Bs, int
   constexpr int RW = TM / 16, KW = 4 / RW, NJ = TN / 16;            // row waves, k halves, blocks of 16 columns
   constexpr int SPL = 8 / KW;                                       // steps of a wave per chunk
   constexpr int PB = TN + 2, BUF = FK * PB, UB = TN * FK / 4 / 256; // 16-byte pieces of B per thread and chunk
-  static_assert(RW * KW == 4 && (KW == 1 || RW * 64 * (4 * NJ + 1) <= 2 * BUF), "the halves' sums fit in the buffers");
+  static_assert(RW * KW == 4 && NJ % KW == 0 && (KW == 1 || RW * 64 * (4 * NJ + 1) <= 2 * BUF), "the halves' sums fit in the buffers");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rw = wave % RW, kw = wave / RW;
   const int kb = kw * (FK / KW) + SPL * (lane >> 4);                // this lane's first k of a chunk
@@ -1540,19 +1540,18 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* Bs, int
   }
   if constexpr (KW == 2) {
     __syncthreads();
+    // Of two neighbouring blocks of columns the first half finishes one and the second the other: with the second idle here, the
+    // other's epilogue, eight values a lane, took 0.4 us more of every launch.
     double* red = Bs + (rw * 64 + lane) * (4 * NJ + 1);   // + 1: lanes on different banks
-    if (kw == 1) {
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < NJ; j += 2)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[4 * j + r] = acc[j][r];
-    }
+      for (int r = 0; r < 4; ++r) red[4 * (j + 1 - kw) + r] = kw == 0 ? acc[j + 1][r] : acc[j][r];
     __syncthreads();
-    if (kw == 1) return;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < NJ; j += 2)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[j][r] += red[4 * j + r];
+      for (int r = 0; r < 4; ++r) acc[j / 2][r] = (kw == 0 ? acc[j][r] : acc[j + 1][r]) + red[4 * (j + kw) + r];
   }
   float* __restrict__ C = reinterpret_cast<float*>(p.C);
   float* __restrict__ C2 = reinterpret_cast<float*>(p.C2);
@@ -1572,8 +1571,8 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* Bs, int
       crow = (int64_t)row * p.ldc;
     }
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int n = n0 + 16 * j + (lane & 15);
+    for (int j = 0; j < NJ / KW; ++j) {
+      const int n = n0 + 16 * (KW * j + kw) + (lane & 15);
       if (n >= p.Ndim) continue;
       const float v = zero ? 0.f : (float)acc[j][r];
       if (EPI == EPI_STORE) {
