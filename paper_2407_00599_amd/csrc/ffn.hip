@@ -1325,8 +1325,8 @@ __global__ __launch_bounds__(256) void ffn_add_parts(const GemmArgs pw2, const G
 // Bound by the fp64 matrix rate (77 TFLOP/s measured for the bare instruction) less the vector instructions between, of which
 // a conversion costs a tenth of a matrix instruction.  8192 rows x 2048 x 2048, forward and backward call, with both operands staged
 // and two barriers per chunk 2.31 and 4.63 ms (59 TFLOP/s) -> 2.06 and 4.07 ms (67); 8 experts of 256 x 512 x 2048 180 and
-// 324 -> 158 and 284 us; 8 of 51 x 1024 x 4096 213 and 399 -> 179 and 337; but 4 of 62 x 64 x 128, whose two chunks are latency,
-// 11.6 and 13.1 -> 12.5 and 13.9.
+// 324 -> 158 and 284 us; 8 of 51 x 1024 x 4096 204 and 409 -> 178 and 338; 4 of 62 x 64 x 128 8.5 and 9.9 -> 8.4 and 9.5; but one chunk
+// alone is latency and code that is fetched for the first time, 4 of 62 x 32 x 32 6.3 and 8.3 -> 6.6 and 8.5.
 // ------------------------------------------------------------------------------------------
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 constexpr int FK = 32;   // k chunk
@@ -1508,36 +1508,56 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& p, double* Bs, int
     stage_b(r0, 0, t0.lim);
     lim_b = t1.lim;
   }
+  auto zero_missing = [&](Piece& a) {
+    if (A_NC ? gathered || WIDE : a.keep != ALL) {
+#pragma unroll
+      for (int s = 0; s < SPL; ++s) a.v[s] = (a.keep >> s) & 1u ? a.v[s] : 0.f;
+    }
+  };
+  auto products = [&](const Piece& pc, const double* w, int s0, int s1) {
+#pragma unroll
+    for (int s = s0; s < s1; ++s) {
+      const double a = (double)pc.v[s];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, w[s * PB + 16 * j], acc[j], 0, 0, 0);
+    }
+  };
   auto step = [&](int c, auto set_tag) {
     constexpr int SET = decltype(set_tag)::value;
+    const double* wb = Bs + kb * PB + (lane & 15);
     __syncthreads();      // chunk c is staged, and the other buffer is consumed
-    if (A_NC ? gathered || WIDE : pa[SET].keep != ALL) {
-#pragma unroll
-      for (int s = 0; s < SPL; ++s) pa[SET].v[s] = (pa[SET].keep >> s) & 1u ? pa[SET].v[s] : 0.f;
-    }
-    const double* w = Bs + SET * BUF + kb * PB + (lane & 15);
-    auto products = [&](int s0) {
-#pragma unroll
-      for (int s = s0; s < s0 + SPL / 2; ++s) {
-        const double a = (double)pa[SET].v[s];
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, w[s * PB + 16 * j], acc[j], 0, 0, 0);
-      }
-    };
-    const bool live = KIND != KIND_TN || SET == 0 || c < nk;   // (the branch costs a row-tiled GEMM 1 %, more than it saves there)
-    if (live) products(0);
+    zero_missing(pa[SET]);
+    products(pa[SET], wb + SET * BUF, 0, SPL / 2);
     stage_b(rb, SET ^ 1, lim_b);
     fetch_b(rb, t2);
     lim_b = t2.lim;
-    if (live) products(SPL / 2);
+    products(pa[SET], wb + SET * BUF, SPL / 2, SPL);
     fetch_a(pa[SET], t2, slots);
     t2 = ktile(c + 3);
     if (gathered) fetch_map(slots, t2);
   };
-  for (int c = 0; c < nk; c += 2) {     // (a last step of its own would be a second copy of the code, with spills)
+  int c = 0;
+  for (; c + 2 < nk; c += 2) {
     step(c, std::integral_constant<int, 0>{});
     step(c + 1, std::integral_constant<int, 1>{});
   }
+  // The last chunk or two, behind which nothing is fetched or staged.  In the loop's steps the last one waited for a chunk that does
+  // not exist, and an odd number of chunks had one of zeros multiplied: 4 experts of 62 rows x 64 x 128, forward and backward call, 8.87 and
+  // 10.1 us, now 8.4 and 9.4; 8 of 2000 x 96 x 96 26.4 and 60, now 22.3 and 56; 12 of 100 x 200 x 328 23.3 and 36.4, now 21.5 and 34.1.
+  const double* w = Bs + kb * PB + (lane & 15);
+  auto last = [&]() {
+    __syncthreads();
+    zero_missing(pa[0]);
+    products(pa[0], w, 0, SPL);
+  };
+  if (c + 2 == nk) {
+    last();
+    stage_b(rb, 1, lim_b);
+    pa[0] = pa[1];
+    w += BUF;
+    ++c;
+  }
+  if (c < nk) last();
   if constexpr (KW == 2) {
     __syncthreads();
     // Of two neighbouring blocks of columns the first half finishes one and the second the other: with the second idle here, the
