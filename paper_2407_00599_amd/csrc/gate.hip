@@ -209,7 +209,7 @@ struct TokenPiece {
   }
 };
 
-// Many tokens.  A block owns 64 tokens x 64 experts (grid.y walks the expert blocks); KW groups of four waves take alternate
+// Many tokens.  A block owns 64 tokens x 64 experts (grid.y walks the expert blocks); KW = 1, 2 or 4 groups of four waves take alternate
 // chunks of M and add their sums through LDS at the end; a wave owns 16 tokens x 64 experts (four accumulator tiles).  The
 // weights are converted once per group on their way into LDS ([k][expert], pitch 66 doubles: the two k rows of a 32-lane read
 // fall into different halves of the banks), in two buffers: the next chunk is converted and stored between the current
@@ -997,13 +997,23 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     } else {
       // 16 x 16 tiles while 64 x 64 ones are at most 128 (half of the compute units).  The call, 64 x 64 and 16 x 16: 512 x 4096, 64
       // experts (8) 189 and 23 us; 4096 x 2048, 64 (64) 77 and 37; 128 (128) 82 and 71; 6144 x 2048, 128 (192) 80 and 93.
-      // Four groups over M while there is one block per compute unit, 16384 x 2048, 64 experts: 81 us, two 86.
+      // With two chunks of M at most a block is start and end only, and more than four 16 x 16 ones a compute unit are dearer: M = 64,
+      // 4096 tokens, 64 experts (1024 blocks of 16 x 16) 12.4 and 10.6; 8192, 32 (1024) 11.6 and 10.3; 8192, 64 (2048) 13.0 and 14.4;
+      // M = 16 11.3 and 10.7, 10.2 and 10.3, 11.8 and 14.2.
+      // Groups over M: a group costs its chunks, rounded up, and the exchange of the sums.  Four while there is one block per
+      // compute unit and M is long enough, 16384 x 2048, 64 experts: 81 us, two 86; one, two and four: 16384 tokens, 64 experts
+      // (256 blocks), M = 64 13.5, 13.7, 16.8; 128 16.3, 16.3, 16.8; 192 18.8, 18.3, 21.2; 224 19.8, 20.7, 21.1; 256 21.4, 20.7, 21.2; 320
+      // 24.1, 22.9, 25.3; 384 26.6, 25.2, 25.0; 1024 53.2, 48.1, 46.2; 9000 tokens, 128 (282) M = 96 19.9, 23.2, 26.9; 224 28.6, 31.0, 35.2;
+      // 256 30.8, 31.1, 35.4; 512 47.9, 47.0, 51.4.
       const dim3 grid((unsigned)((S + 63) / 64), (unsigned)((E + 63) / 64));
       const uint64_t tiles = (uint64_t)grid.x * grid.y;
 #define LAUNCH_WIDE(bf_, kw_) hipLaunchKernelGGL((gate_logits_mfma<bf_, kw_>), grid, dim3(256 * kw_), 0, st, xs, Wg, gate_bias, logits, S, M, E)
-      if (tiles <= 128 || M >= 1 << 24) {   // (the other kernel has 32-bit offsets within a block's tokens)
+      const bool few = M <= 2 * LM_KC ? ((S + 15) / 16) * ((E + 15) / 16) <= 1024 : tiles <= 128;
+      if (few || M >= 1 << 24) {   // (the other kernel has 32-bit offsets within a block's tokens)
         launch_few();
-      } else if (tiles <= 256) {
+      } else if (M < 8 * LM_KC) {
+        if (bf) LAUNCH_WIDE(true, 1); else LAUNCH_WIDE(false, 1);
+      } else if (tiles <= 256 && M >= 12 * LM_KC) {
         if (bf) LAUNCH_WIDE(true, 4); else LAUNCH_WIDE(false, 4);
       } else {
         if (bf) LAUNCH_WIDE(true, 2); else LAUNCH_WIDE(false, 2);

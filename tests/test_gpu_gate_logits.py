@@ -24,13 +24,16 @@ def gate(x, Wg, bias, k=1, C=None, norm=0, everything=False):
 
 
 # up to 16 experts: walks of a few waves (few tokens for their M), 16 x 16 tiles, the 4-block form (many bf16 tokens); beyond:
-# 16 x 16 tiles up to 128 tiles of 64 x 64, four groups over M up to 256, two beyond; M around whole chunks of 32 (tails of 8,
+# 16 x 16 tiles up to 128 tiles of 64 x 64, one, two or four groups over M beyond; M around whole chunks of 32 (tails of 8,
 # 16, 24), fewer chunks than waves or groups
 @pytest.mark.parametrize("S,M,E", [
     (1, 8, 1), (1023, 1024, 8), (1024, 1024, 8), (2049, 264, 3), (511, 520, 12), (513, 520, 12), (1003, 520, 16), (8191, 2048, 16),
     (8192, 136, 4), (8193, 40, 5), (16383, 72, 8), (16384, 72, 8), (16390, 1032, 9), (40000, 24, 16),
     (15, 64, 17), (17, 200, 33), (64, 2056, 256), (300, 8, 65), (8192, 96, 64), (8193, 40, 64), (8200, 264, 17), (16384, 24, 64),
     (4160, 104, 256), (17000, 8, 20), (16400, 232, 130),
+    # short M: 1024 blocks of 16 x 16 and more; one group up to 248, two from 256, four from 384 up to 256 blocks of 64 x 64
+    (8192, 64, 32), (8193, 64, 32), (8192, 64, 48), (8200, 16, 17), (8200, 72, 24), (8200, 248, 40), (8200, 256, 40), (8200, 376, 17),
+    (8200, 384, 17), (9000, 248, 128), (9000, 256, 128),
 ])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_logits(S, M, E, dtype):
