@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
     (2000, 17, 3, False), (65 * 64, 64, 8, False), (8192 + 1, 128, 4, True), (128 * 64, 256, 8, False), (128 * 64 + 1, 256, 8, False),
     (70000, 16, 2, True), (73280, 51, 1, True), (1024 * 64, 16, 4, False), (1024 * 64 + 3, 16, 4, True), (300, 255, 7, False), (12000, 2, 1, True),
     (30000, 257 // 3, 3, False), (131072, 4, 1, True),
+    # a wave's sums added across its lanes: one, four and eight pairs; more than 65535 of a pair to a wave; two and twelve pairs are not
+    (9000, 1, 1, False), (524288 - 5, 1, 1, False), (20000, 4, 1, False), (9001, 2, 2, False), (30000, 8, 1, True), (131072, 2, 1, True), (9000, 4, 3, False),
 ])
 def test_slots(S, E, k, hot):
     g = torch.Generator(device=DEV)
