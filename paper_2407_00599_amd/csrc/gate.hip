@@ -9,7 +9,7 @@
 //   gate_topk           : W lanes per token, k arg-max rounds (ties -> lower expert index); softmax weights;
 //                         per-block (choice, expert) histogram for the slot scan.  With a single token block it
 //                         assigns the slots as well.
-//                         (Up to 16 experts and three choices of few tokens the logits kernels do this.)
+//                         (Up to 16 experts and three choices of few tokens, though not the fewest, the logits kernels do this.)
 //   gate_scan           : one wave per expert; exclusive scan of the histograms over token blocks and
 //                         over choices (choice-major priority), per-expert demand counts.
 //   gate_slots          : rank of each (token, choice) inside its block via wave ballots,
@@ -954,9 +954,13 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     TopK tk{0, norm, idx, w};
     // Up to 16 experts and three choices the logits kernels select the experts as well (a thread per token, whose rounds are a chain), and
     // gate_slots counts the choices.  The call, three launches and two: 2048 x 768, 16 experts, top-2, 12.9 and 11.3 us; 4096 x 1024,
-    // 8, top-2, 13.6 and 12.4; 6000 x 512, 16, top-2 (12000 choices) 13.0 and 13.0; 2000 x 512, 12, top-4, 12.0 and 12.6.  With at most 64 tokens gate_topk assigns the slots as well: two
-    // launches either way (32 x 1024, 8, top-2, 9.6 and 9.6; 256 x 4096 12.5 and 11.9).
-    if (E <= 16 && k <= TOPK_MAX && S > 64 && S * k <= 8192) tk.k = k;
+    // 8, top-2, 13.6 and 12.4; 6000 x 512, 16, top-2 (12000 choices) 13.0 and 13.0; 2000 x 512, 12, top-4, 12.0 and 12.6.  Up to 256
+    // tokens gate_topk assigns the slots as well, two launches either way, and its one block is the faster for few tokens of few experts:
+    // 256 x 64, 2, top-1 5.8 and 6.4, 4, top-1 6.1 and 6.4, 4, top-3 7.4 and 7.5 (257 x 64, 4, top-1 10.6 and 6.4); 65 x 64, 8, top-1 6.2
+    // and 6.4, top-2 6.6 and 6.6; 100 x 64, 8, top-2 6.9 and 6.6; 65 x 64, 16, top-3 8.7 and 9.0; 100 x 64, 12, top-1 7.3 and 7.5, 16,
+    // top-2 7.8 and 7.7; 128 x 64, 16, top-2 7.9 and 7.75; 160 x 1024, 12, top-2 10.5 and 10.3.
+    const int64_t one_block = E <= 4 ? 256 : E <= 8 ? 64 : 112;
+    if (E <= 16 && k <= TOPK_MAX && S > one_block && S * k <= 8192) tk.k = k;
     auto launch_few = [&]() {
       selected = tk.k != 0;
       const dim3 grid((unsigned)((S + 15) / 16), (unsigned)((E + 15) / 16)), block(64 * std::min(LF_NW, (M + LM_KC - 1) / LM_KC));

@@ -69,6 +69,8 @@ def test_non_finite_values_stay_in_their_row_and_column(S, M, E):
     (1, 8, 1, 1, 1, 0), (63, 64, 16, 3, 5, 1), (65, 2048, 8, 2, 9, 0), (257, 40, 3, 3, 200, 1), (1023, 520, 12, 3, 250, 1),
     (2049, 72, 16, 2, 300, 0), (2730, 64, 9, 3, 1000, 1), (2731, 64, 9, 3, 900, 0), (4096, 1024, 8, 2, 1100, 1), (4097, 64, 8, 2, 1000, 1),
     (8191, 24, 2, 1, 4000, 0), (8192, 136, 12, 1, 600, 0), (300, 64, 16, 4, 70, 1),
+    # as many tokens as gate_topk's one block is left with, and one more
+    (256, 64, 4, 1, 70, 0), (257, 64, 4, 2, 100, 1), (64, 64, 8, 1, 9, 0), (65, 64, 5, 3, 20, 0), (112, 72, 9, 3, 30, 1), (113, 72, 9, 3, 30, 1),
 ])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_routing(S, M, E, k, C, norm, dtype):
