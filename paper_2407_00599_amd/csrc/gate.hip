@@ -967,15 +967,28 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
       if (bf) hipLaunchKernelGGL(gate_logits_few<true>, grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E, tk);
       else hipLaunchKernelGGL(gate_logits_few<false>, grid, block, 0, st, xs, Wg, gate_bias, logits, S, M, E, tk);
     };
-    // Up to 16 experts.  The 16 x 16 tiles cost the same whatever S, M and E: 8192 x 1024 17 us (the call), 16384 x 4096 61, fp32 29 at
-    // 16384 x 1024.  The others are faster
+    // Up to 16 experts.  What the 16 x 16 tiles cost does not depend on how many of the 16 columns are experts: 8192 x 1024 17 us (the
+    // call), 16384 x 4096 61, fp32 29 at 16384 x 1024.  The others are faster
     // - with few tokens for their M, where the walk along M is the time (split): 8 experts, 512 x 1024 13.5 and 14.0, 4096 x 4096 20 and
-    //   23, but 2048 x 1024 15.7 and 14.3; 16 experts, 512 x 1024 15.5 and 13.8, 1024 x 4096 20 and 22, 4096 x 4096 41 and 23;
+    //   23, but 2048 x 1024 15.7 and 14.3;
     // - with many tokens in bf16, where 8 or 4 columns are not multiplied (mfma4): 8 experts, 8192 x 1024 18.3 and 17.4, 16384 x 1024
     //   19 and 24, 32768 x 4096 69 and 114; 2 experts, 8192 x 1024 14 and 16; but 16 experts, 32768 x 4096 126 and 114.
+    // From 9 experts on split's time goes by its blocks, of 2 tokens or, from 1024 on, 4, per compute unit, split and 16 x 16 tiles:
+    //   one (512 tokens): 16 experts, 300 x 1024 11.5 and 10.0, 16 x 1536 10.7 and 11.0, 512 x 2048 13.6 and 13.3, 512 x 4096 18.4 and 20.1; 12,
+    //     64 x 1024 9.8 and 9.5, 64 x 1536 10.1 and 11.3; 9, 64 x 520 8.7 and 8.2, 64 x 1024 9.5 and 9.5, fp32 9.6 and 10.0, 512 x 2048 11.2
+    //     and 13.1;
+    //   two (1023 tokens), which the products of 14 or 16 columns fill: 700 x 4096, 16 experts 24.0 and 20.2, 12 18.7 and 20.0, 9 15.5 and
+    //     19.8; 1000 x 3072, 10 18.1 and 16.6, 9 16.5 and 16.7; 1000 x 8192, 14 36 and 33, 12 31 and 33;
+    //   some one and some two: 1400 x 4096, 9 25.7 and 20.1;
+    //   two of four waves, not the more that fewer blocks get (1641 to 2048 tokens): 2000 x 3072, 16 experts 21.9 and 17.4, 14 16.9 and 17.4,
+    //     2000 x 4096, 14 18.9 and 21.6; 2000 x 2048, 9 14.3 and 13.6;
+    //   more: 3000 x 4096, 9 23.5 and 22.0, 3000 x 8192, 12 40 and 36.
     const bool rows32 = (uint64_t)S * (uint64_t)M * 2 <= 0xFFFFFFF0ull;
     const int64_t m2 = (int64_t)M * M;
-    const bool split = S < (E <= 8 ? std::max<int64_t>(1024, m2 / 2048) : std::max<int64_t>(512, m2 / 4096)) && S < 8192;
+    const bool split = E <= 8       ? S < std::max<int64_t>(1024, m2 / 2048) && S < 8192
+                       : S <= 512   ? M > 90 * E
+                       : S < 1024   ? E <= 12 && M >= 341 * E
+                                    : S > 1640 && S <= 2048 && E <= 14 && M >= 3072;
     if (bf && E <= 8 && S >= (E <= 4 ? 8192 : 16384) && rows32) {
       // fp64 matrix cores; TW token waves (32 tokens each) per block so that the grid has about two blocks per
       // compute unit or more
