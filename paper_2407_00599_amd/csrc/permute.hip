@@ -4,6 +4,8 @@
 //
 // The kernels are row movers bound by HBM bandwidth.  Every output row is produced by exactly one wave (gather form; in the combine
 // backward a token's wave writes its slots' rows), so there are no atomics and no prior memset; 16-byte accesses per lane.
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
@@ -271,21 +273,26 @@ __global__ __launch_bounds__(256) void combine_dw(const void* __restrict__ dy, c
   }
 }
 
-// The whole combine backward in one launch.  A wave per token reads its row of dy once, writes it, times the weight, to the k
-// rows that its slots are (ROWS: dYret is wanted) and takes the dot products with the rows that came back.  The first nb_zero workgroups
-// store the rows of empty slots as zeros, a wave for zero_slots of them.
-// Bound by HBM.  With the rows of dYret gathered slot by slot, dy was read k times more, from beyond L2: 8192 tokens x 2048,
+// The whole combine backward in one launch: a wave per token takes the dot products of its row of dy with the rows that came back.
+// DY_ROWS_TOKEN: it writes that row, times the weight, to the k rows that its slots are as well, so that dy is read once, and the first nb_rows
+// workgroups store the rows of empty slots as zeros, a wave for zero_slots of them.
+// DY_ROWS_SLOT: the first nb_rows workgroups write dYret, a wave per row (the weighted dispatch of dy).
+// DY_ROWS_NONE: dYret is not wanted.
+// Many tokens are bound by HBM.  With the rows gathered slot by slot, dy was read k times more, from beyond L2: 8192 tokens x 2048,
 // top-4 of 128, 81 -> 68 us; 16384 x 2048, top-2, four partial sums, 68 -> 57; 32768 x 4096, top-2, two, 393 -> 361; 4096 x 1024, top-2
-// of 8, 14.0 -> 12.2.
-template <bool BF16, int K, int P, bool ROWS>
+// of 8, 14.0 -> 12.2.  Few are bound by the length of a wave's chain, and there the slots' own waves are faster.
+enum { DY_ROWS_NONE, DY_ROWS_TOKEN, DY_ROWS_SLOT };
+template <bool BF16, int K, int P, int ROWS>
 __global__ __launch_bounds__(256) void combine_bwd_kp(const void* __restrict__ dy, const void* __restrict__ Yret,
                                                       const int32_t* __restrict__ idx, const int32_t* __restrict__ slot,
                                                       const int32_t* __restrict__ inv, const float* __restrict__ w,
                                                       void* __restrict__ dYret, float* __restrict__ dw, int64_t S, int M,
-                                                      int64_t C, int64_t part_stride, int64_t rows, int64_t nb_zero, int zero_slots) {
+                                                      int64_t C, int64_t part_stride, int64_t rows, int64_t nb_rows, int zero_slots) {
   constexpr int NCH = (K * P >= 8) ? 1 : (K * P >= 4) ? 2 : 4;
   const int lane = threadIdx.x & 63;
-  if (ROWS && (int64_t)blockIdx.x < nb_zero) {
+  if (ROWS == DY_ROWS_SLOT && (int64_t)blockIdx.x < nb_rows)
+    return dispatch_rows_body<BF16>((int64_t)blockIdx.x, dy, inv, w, dYret, rows, M, K, C, (int64_t)0, C);
+  if (ROWS == DY_ROWS_TOKEN && (int64_t)blockIdx.x < nb_rows) {
     const int64_t r0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * zero_slots;
     unsigned long long empty = __ballot(lane < zero_slots && r0 + lane < rows && inv[min(r0 + lane, rows - 1)] < 0);
     const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -296,7 +303,7 @@ __global__ __launch_bounds__(256) void combine_bwd_kp(const void* __restrict__ d
     }
     return;
   }
-  const int64_t t = ((int64_t)blockIdx.x - nb_zero) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int64_t t = ((int64_t)blockIdx.x - nb_rows) * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (t >= S) return;
   int64_t src[K];
   float dot[K], wt[K];
@@ -304,7 +311,7 @@ __global__ __launch_bounds__(256) void combine_bwd_kp(const void* __restrict__ d
   for (int j = 0; j < K; ++j) {
     const int c = slot[t * K + j];
     src[j] = c >= 0 ? ((int64_t)idx[t * K + j] * C + c) * M : -1;
-    wt[j] = ROWS ? w[t * K + j] : 0.f;
+    wt[j] = ROWS == DY_ROWS_TOKEN ? w[t * K + j] : 0.f;
     dot[j] = 0.f;
   }
   for (int m0 = lane * 8; m0 < M; m0 += 512 * NCH) {
@@ -328,7 +335,7 @@ __global__ __launch_bounds__(256) void combine_bwd_kp(const void* __restrict__ d
 #pragma unroll
       for (int j = 0; j < K; ++j)
         if (src[j] >= 0) {
-          if (ROWS) {
+          if (ROWS == DY_ROWS_TOKEN) {
             float f[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) f[i] = g[i] * wt[j];
@@ -419,18 +426,33 @@ extern "C" int moe_combine_bwd(const void* dy, const void* Yret, int dtype, int 
   const int64_t ps = rows * M;
   const dim3 block(256), grid_r((unsigned)((rows + 3) / 4)), grid_t((unsigned)((S + 3) / 4));
   const bool bf = dtype == MOE_BF16;
-  // Slots that a wave looks through for empty ones.  Many cost fewer waves but, with few rows, are what the call waits for: 8 and 64,
-  // 40960 rows x 2048 63 and 57 us, 4096 x 768 5.1 and 8.8.
-  const int zero_slots = rows >= 32768 ? 64 : 8;
-  const int64_t nb_zero = dYret ? (rows + 4 * zero_slots - 1) / (4 * zero_slots) : 0;
-  const dim3 grid_b((unsigned)(nb_zero + grid_t.x));
+  // Rows by token or by slot, the call in bf16: 512 tokens top-2 of 1024 rows x 64 2.89 and 2.76 us, x 4096 6.4 and 6.5; 768 of 1536, 2.88 and 2.79,
+  // 7.4 and 8.5; 427 top-8 of 4096 x 520 7.5 and 6.8; 853 top-4 of 4096 x 2048 9.2 and 11.0; 853 top-1 of 1024 x 520 2.80 and 2.61, 1706 of
+  // 2048 2.97 and 2.93; fp32, 128 tokens top-2 of 320 rows x 2048 5.3 and 3.6.
+  const bool by_slot = S <= (k == 1 ? 1024 : 512);
+  // Slots that a wave looks through for empty ones.  Many cost fewer waves but are a chain that the call waits for, the longer the wider
+  // the rows: with 2, 4 and 8 of them 820 tokens top-2 of 2048 rows x 4096 bf16 8.4, 9.9 and 11.1 us, x 64 2.86, 2.77 and 2.74; with 4, 8 and 64
+  // 1640 of 4096 x 2048 7.6, 9.2; 4915 of 12288 x 2048 18.0, 17.9; fp32, 3277 of 8192 x 2048 28.9, 32.3; bf16, 12288 of 30720 x 2048 36.3 with 8 and
+  // 42.0 with 64.  From 32768 rows on it is 64 for the call that has mostly empty slots, 40960 x 2048, four parts, 51.1 and 47.6 (16: 49.4), though
+  // 65536 x 2048, a fifth of them empty, takes 90.8 and 100.
+  const int64_t row_bytes = (int64_t)M * (bf ? 2 : 4);
+  const int zero_slots = rows >= 32768 ? 64
+                         : rows >= (row_bytes <= 1024 ? 4096 : bf ? 8192 : 12288) ? 8
+                         : rows < 3072 && row_bytes >= 4096 ? 2 : 4;
+  const int64_t nb_rows = !dYret ? 0 : by_slot ? (int64_t)grid_r.x : (rows + 4 * zero_slots - 1) / (4 * zero_slots);
+  const dim3 grid_b((unsigned)(nb_rows + grid_t.x));
 #define COMBINE_DW_KP(K_, P_)                                                                                          \
   if (k == K_ && n_part == P_) {                                                                                       \
     auto go = [&](auto kernel) {                                                                                       \
-      hipLaunchKernelGGL(kernel, grid_b, block, 0, st, dy, Yret, idx, slot, inv, w, dYret, dw, S, M, C, ps, rows, nb_zero, zero_slots); \
+      hipLaunchKernelGGL(kernel, grid_b, block, 0, st, dy, Yret, idx, slot, inv, w, dYret, dw, S, M, C, ps, rows, nb_rows, zero_slots); \
     };                                                                                                                 \
-    if (dYret) { if (bf) go(combine_bwd_kp<true, K_, P_, true>); else go(combine_bwd_kp<false, K_, P_, true>); }       \
-    else { if (bf) go(combine_bwd_kp<true, K_, P_, false>); else go(combine_bwd_kp<false, K_, P_, false>); }           \
+    auto of_type = [&](auto how) {                                                                                     \
+      constexpr int ROWS = decltype(how)::value;                                                                       \
+      if (bf) go(combine_bwd_kp<true, K_, P_, ROWS>); else go(combine_bwd_kp<false, K_, P_, ROWS>);                    \
+    };                                                                                                                 \
+    if (!dYret) of_type(std::integral_constant<int, DY_ROWS_NONE>{});                                                  \
+    else if (by_slot) of_type(std::integral_constant<int, DY_ROWS_SLOT>{});                                            \
+    else of_type(std::integral_constant<int, DY_ROWS_TOKEN>{});                                                        \
     return moe::check_launch();                                                                                        \
   }
   COMBINE_DW_KP(1, 1) COMBINE_DW_KP(1, 2) COMBINE_DW_KP(1, 4) COMBINE_DW_KP(2, 1) COMBINE_DW_KP(2, 2) COMBINE_DW_KP(2, 4)

@@ -76,8 +76,7 @@ def test_identity_round_trip_on_device():
     assert np.array_equal(to_host(y), surv[:, None] * x.val.astype(np.float64))
 
 
-# the rows of empty slots: 8 or (from 32768 rows on) 64 slots to a wave, around whole waves; mostly empty, full, and no token at all for
-# some experts
+# the rows of empty slots, around whole waves and workgroups of them; mostly empty, full, and no token at all for some experts
 @pytest.mark.parametrize("S,M,E,k,C", [(5, 8, 3, 1, 11), (100, 264, 64, 2, 511), (100, 24, 64, 3, 512), (70, 8, 33, 2, 1001), (2000, 520, 9, 4, 800)])
 def test_combine_bwd_empty_slots(S, M, E, k, C):
     idx, slot, inv, w = routing(S, E, k, C, seed=S + E, skew=1.0)
@@ -88,3 +87,23 @@ def test_combine_bwd_empty_slots(S, M, E, k, C):
     rdY, rdw = O.combine_bwd(dy.val, Y.val, idx, slot, w)
     got = to_host(dY)
     assert np.all(got[inv < 0] == 0.0) and rel_err(got, rdY) <= 4e-3 and rel_err(to_host(dw), rdw) <= 2e-6 * np.sqrt(M)
+
+
+# every number of choices and parts on both sides of the line between rows by slot (up to 512 tokens, 1024 top-1) and by token, and with 2, 4, 8
+# and 64 slots to a wave that looks for empty ones
+@pytest.mark.parametrize("S,M,E,k,C", [
+    (1024, 264, 5, 1, 300), (1025, 264, 5, 1, 300), (512, 2056, 8, 2, 133), (513, 2056, 8, 2, 133), (514, 1032, 8, 2, 383), (520, 72, 9, 3, 300),
+    (600, 40, 33, 4, 150), (515, 520, 16, 8, 257), (513, 520, 64, 6, 191), (513, 24, 64, 6, 513), (700, 512, 32, 2, 385),
+])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_combine_bwd_rows_by_slot_and_by_token(S, M, E, k, C, dtype):
+    idx, slot, inv, w = routing(S, E, k, C, seed=S + E, skew=1.0)
+    rng = np.random.default_rng(E)
+    for n_part in (1, 2, 4):
+        dy, Y = (synth.store(rng.standard_normal(n).astype(np.float32), dtype) for n in ((S, M), (n_part, E, C, M)))
+        dY = torch.full((E, C, M), 7.0, dtype=torch_dtype(dtype), device=DEV); dw = torch.full((S, k), 7.0, device=DEV)
+        api.moe_combine_bwd(to_dev(dy), to_dev(Y), n_part, S, M, E, k, C, to_dev(idx), to_dev(slot), to_dev(inv), to_dev(w), dY, dw)
+        rdY, rdw = O.combine_bwd(dy.val, Y.val, idx, slot, w)
+        got = to_host(dY)
+        assert np.all(got[inv < 0] == 0.0) and rel_err(got, rdY) <= (1e-6 if dtype == "f32" else 4e-3)
+        assert rel_err(to_host(dw), rdw) <= 2e-6 * np.sqrt(M) and np.all(to_host(dw)[slot < 0] == 0.0)
