@@ -308,9 +308,18 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
           }
         }
       } else {
-        for (int i = tid; i < ms * E; i += NTHR) {
-          const int m = (int)((uint32_t)i * inv_e >> 16);
-          outs[(i - m * E) * PITCH + m] = slab[i];
+        // three values requested together (behind the end the last one again): 2000 x 2048, fp32, 6 experts 19.8 -> 19.3 us; 8192 x 4096, 13
+        // 118 -> 114, fp32 150 -> 136
+#pragma unroll 1
+        for (int i0 = tid; i0 < ms * E; i0 += 3 * NTHR) {
+          float v[3];
+#pragma unroll
+          for (int u = 0; u < 3; ++u) v[u] = slab[min(i0 + u * NTHR, ms * E - 1)];
+#pragma unroll
+          for (int u = 0; u < 3; ++u) {
+            const int i = min(i0 + u * NTHR, ms * E - 1), m = (int)((uint32_t)i * inv_e >> 16);
+            outs[(i - m * E) * PITCH + m] = v[u];
+          }
         }
 #pragma unroll
         for (int u = 0; u < FT; ++u) fetch(u, pos + u);

@@ -60,6 +60,9 @@ def test_gate_bwd(S, M, E, k, norm, dtype, acc):
 @pytest.mark.parametrize("S,M,E,k,norm,dtype,acc", [
     (19, 40, 12, 3, 1, "bf16", 0), (300, 280, 12, 8, 1, "f32", 1), (66003, 32, 12, 2, 0, "bf16", 1), (66003, 24, 6, 2, 1, "f32", 1),
     (2100, 264, 10, 4, 0, "bf16", 1),
+    # numbers of experts that are no multiple of 4: the slab in threes of values, whole and ragged columns
+    (50, 256, 2, 1, 0, "f32", 0), (40, 264, 3, 2, 1, "bf16", 1), (40, 8, 7, 3, 1, "f32", 1), (50, 520, 9, 2, 1, "bf16", 0), (40, 256, 11, 4, 0, "f32", 1),
+    (30, 504, 15, 8, 1, "f32", 0),
 ])
 def test_gate_bwd_slab_and_stages(S, M, E, k, norm, dtype, acc):
     test_gate_bwd(S, M, E, k, norm, dtype, acc)
