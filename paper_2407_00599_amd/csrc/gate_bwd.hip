@@ -600,12 +600,13 @@ template <bool BF16, int EP>   // E <= EP
 __global__ __launch_bounds__(SG_NT, 4) void gate_dx_sparse(const float* __restrict__ dw, const float* __restrict__ w,
                                                            const int32_t* __restrict__ idx, const float* __restrict__ Wg, int S,
                                                            int M, int E, int k, float* __restrict__ dl_out,
-                                                           void* __restrict__ dx, int accumulate, int chunk) {
+                                                           void* __restrict__ dx, int accumulate, int chunk, int ncb) {
   __shared__ __attribute__((aligned(16))) float wt[EP * SX_PITCH];
   __shared__ __attribute__((aligned(16))) uint2 ent[sx_tokens<EP>() * MOE_MAX_K];   // (expert, dl); what is missing is (0, 0)
   __shared__ int odd_s;
-  const int tid = threadIdx.x, k2 = (k + 1) & ~1, ncb = (int)gridDim.x, cx = (int)blockIdx.x, mb = cx * SX_C;
-  const int tb = (int)blockIdx.y * chunk, nt = min(chunk, S - tb);
+  const int tid = threadIdx.x, k2 = (k + 1) & ~1;
+  const int run = (int)blockIdx.x / ncb, cx = (int)blockIdx.x - run * ncb, mb = cx * SX_C;   // the column blocks of a run are neighbours
+  const int tb = run * chunk, nt = min(chunk, S - tb);
   const int c0 = 4 * (tid & 15), col = mb + c0, tq = tid >> 4;
   const bool cok = col < M;
   RawRow<BF16, 4> old[2][SX_U];
@@ -765,7 +766,7 @@ __global__ __launch_bounds__(SG_NT, EP > 128 ? 2 : 4) void gate_dwg_sparse(const
     }
     return v;
   };
-  const int cw = (int)blockIdx.x, mb = cw * SW_C, part = (int)blockIdx.y, tb = part * chunk, te = min(S, tb + chunk);
+  const int cw = (int)blockIdx.x, mb = cw * SW_C, part = (int)blockIdx.y, tb = part * chunk, te = tb + min(chunk, S - tb);
   constexpr int PPR = SW_C * ESZ / 16, UX = TT * PPR / SG_NT;         // 16-byte pieces per row; per thread
   constexpr int GW = NG / SG_NW;                                      // groups of 64 entries per wave
   static_assert(NG % SG_NW == 0, "groups are dealt evenly");
@@ -992,10 +993,10 @@ extern "C" int moe_gate_bwd(const float* dw, const float* w, const int32_t* idx,
     // 1024 40 + 12.
     const int64_t chunk_w = chunks(512, ncw, nchunk, tile_w), chunk_x = std::min<int64_t>(chunks(1024, ncx, S, SX_TPI), E > 128 ? 128 : 256);
     const int parts = (int)((S + chunk_w - 1) / chunk_w);
-    const dim3 gx((unsigned)ncx, (unsigned)((S + chunk_x - 1) / chunk_x)), gw((unsigned)ncw, (unsigned)parts);
+    const dim3 gx((unsigned)(ncx * ((S + chunk_x - 1) / chunk_x))), gw((unsigned)ncw, (unsigned)parts);   // (runs of 256 tokens may be more than y holds)
     const bool exact = (int64_t)chunk * k < (tile_w > chunk ? 6 : 4) * E;   // see gate_dwg_sparse
 #define MOE_SPARSE(BF, EP) do { \
-    hipLaunchKernelGGL((gate_dx_sparse<BF, EP>), gx, dim3(SG_NT), 0, st, dw, w, idx, Wg, (int)S, M, E, k, dlogits, dx, dx_accumulate, (int)chunk_x); \
+    hipLaunchKernelGGL((gate_dx_sparse<BF, EP>), gx, dim3(SG_NT), 0, st, dw, w, idx, Wg, (int)S, M, E, k, dlogits, dx, dx_accumulate, (int)chunk_x, (int)ncx); \
     if (exact) hipLaunchKernelGGL((gate_dwg_sparse<BF, EP, true>), gw, dim3(SG_NT), 0, st, dw, w, idx, x, (int)S, M, E, k, partial, (int)chunk_w); \
     else hipLaunchKernelGGL((gate_dwg_sparse<BF, EP, false>), gw, dim3(SG_NT), 0, st, dw, w, idx, x, (int)S, M, E, k, partial, (int)chunk_w); } while (0)
     if (bf) { if (E <= 64) MOE_SPARSE(true, 64); else if (E <= 128) MOE_SPARSE(true, 128); else MOE_SPARSE(true, 256); }

@@ -116,3 +116,33 @@ def test_non_finite(dtype, E, value):
         ok = np.isfinite(want)
         assert not ok.all() and rel_err(got[ok], want[ok]) <= (1e-5 if got is dWg or dtype == "f32" else 4e-3)
     assert np.isfinite(db).all()
+
+
+def test_more_runs_of_tokens_than_a_grid_dimension_holds():
+    """65537 runs of 256 tokens.  Every product and sum in float64 beside it, on the GPU; the entries of dl as in test_gate_bwd_selected."""
+    S, M, E, k = 65536 * 256 + 1, 8, 17, 2
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    x, dw = torch.randn(S, M, generator=g, device=DEV).to(torch.bfloat16), torch.randn(S, k, generator=g, device=DEV)
+    w0 = torch.rand(S, generator=g, device=DEV)
+    w = torch.stack([w0, 1 - w0], 1)
+    first = torch.randint(0, E, (S,), generator=g, device=DEV, dtype=torch.int32)
+    idx = torch.stack([first, (first + 5) % E], 1).contiguous()
+    Wg = torch.randn(M, E, generator=g, device=DEV) * 0.1
+    dl, dWg, db = torch.full((S, E), float("nan"), device=DEV), torch.empty(M, E, device=DEV), torch.empty(E, device=DEV)
+    dx = torch.full((S, M), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(api.moe_gate_bwd_workspace_bytes(S, M, E), dtype=torch.uint8, device=DEV)
+    api.moe_gate_bwd(dw, w, idx, torch.zeros(S, E, device=DEV), x, Wg, S, M, E, k, 1, dl, dWg, db, dx, 0, ws)
+    torch.cuda.synchronize()
+    entry = w.double() * (dw.double() - (w.double() * dw.double()).sum(1, keepdim=True))
+    got = torch.gather(dl, 1, idx.long())
+    assert bool(((got - entry).abs() <= (k + 2) * 2.0 ** -23 * dw.abs().max()).all())
+    assert torch.equal(dl.scatter(1, idx.long(), 0.0), torch.zeros_like(dl))
+    for part in range(0, S, 1 << 22):
+        want = dl[part:part + (1 << 22)].double() @ Wg.double().T
+        # k fp32 products and sums, rounded to 8 bits
+        assert bool(((dx[part:part + (1 << 22)].double() - want).abs() <= want.abs() * 2.0 ** -8 + 1e-6 * want.abs().max()).all())
+    l64, x64 = dl.double(), x.double()
+    # partial sums rounded to fp32, at most dwg chunks of 64: 64 2^-24 of the magnitudes is a bound with room
+    for out, A in ((dWg, x64.T), (db[None], torch.ones(1, S, dtype=torch.float64, device=DEV))):
+        assert bool(((out.double() - A @ l64).abs() <= 64 * 2.0 ** -24 * (A.abs() @ l64.abs())).all())
