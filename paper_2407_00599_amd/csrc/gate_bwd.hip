@@ -31,19 +31,12 @@ struct Picks {
   float w[MOE_MAX_K], g[MOE_MAX_K];
   int e[MOE_MAX_K];
   float inner;   // sum_j w_j dw_j
-  Picks() = default;
   __device__ __forceinline__ Picks(const float* dw, const float* wt, const int32_t* idx, int64_t t, int k) {
-    fetch(dw, wt, idx, t, k);
-    add_up(k);
-  }
-  __device__ __forceinline__ void fetch(const float* dw, const float* wt, const int32_t* idx, int64_t t, int k) {
 #pragma unroll
     for (int j = 0; j < MOE_MAX_K; ++j) {
       const int64_t at = t * k + (j < k ? j : k - 1);
       w[j] = wt[at]; g[j] = dw[at]; e[j] = idx[at];
     }
-  }
-  __device__ __forceinline__ void add_up(int k) {
     inner = 0.f;
 #pragma unroll
     for (int j = 0; j < MOE_MAX_K; ++j)
