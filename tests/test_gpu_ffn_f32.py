@@ -1,5 +1,5 @@
 """GPU parity of the fp32 expert FFN at the edges of its tiles (32 and 64 rows and columns, k chunks of 32 in pairs): every product
-against the float64 product of the operands that the call was given or returned."""
+against the float64 product of the operands that the call was given or returned, the activation and its gradient against erf's."""
 import pytest
 import torch
 
@@ -16,18 +16,31 @@ def close(got, A, B, name):
     assert bool(((got.double() - exact).abs() <= exact.abs() * 2.0 ** -24 + (A.shape[-1] + 2) * 2.0 ** -53 * size).all()), name
 
 
-def run(n_src, G, C, M, H, occ, gather):
+def close_gelu(z, a, dA, dA_size, dz):
+    """a = gelu(z) and dz = dA gelu'(z), dA being the exact product, summed in float64 and rounded once.  In fp32 the normal CDF of z, 0.5 (1 + erf),
+    is off by at most 4 2^-24: erf and the sum by 2^-22 of one and half a place, its argument's rounding by as much again.  z times it,
+    rounded twice, is within 6 2^-24 |z| (a <= |z|), and gelu' = cdf + z phi(z), whose exponential's argument and result are rounded
+    (z^3 phi <= 0.47 and z phi <= 0.25 times 2^-22), within 12 2^-24; the product with dA adds 2 2^-24 of it, |gelu'| <= 1.13."""
+    z, u = z.double(), 2.0 ** -24
+    cdf, phi = 0.5 * torch.special.erfc(-z * 0.5 ** 0.5), torch.exp(-0.5 * z * z) * (0.5 / torch.pi) ** 0.5
+    assert bool(((a.double() - z * cdf).abs() <= 6 * u * z.abs()).all()), "A"
+    assert bool(((dz.double() - dA * (cdf + z * phi)).abs() <= 15 * u * dA.abs() + 1.2 * dA_size).all()), "dZ"
+
+
+def run(n_src, G, C, M, H, occ, gather, n_esp=1, esp_idx=0):
+    full, H = H, H // n_esp
+    h = slice(esp_idx * H, (esp_idx + 1) * H)
     g = torch.Generator(device=DEV)
     g.manual_seed(C + M + H)
     rn = lambda *s: torch.randn(*s, generator=g, device=DEV)      # noqa: E731
-    W1, W2, dY = rn(G, M, H) / M ** 0.5, rn(G, H, M) / H ** 0.5, rn(n_src, G, C, M)
+    W1, W2, dY = rn(G, M, full) / M ** 0.5, rn(G, full, M) / H ** 0.5, rn(n_src, G, C, M)
     counts = None if occ is None else torch.tensor(occ, dtype=torch.int32, device=DEV).expand(n_src, G).contiguous()
     pad = torch.zeros(n_src, G, C, dtype=torch.bool, device=DEV)
     if counts is not None:
         pad = torch.arange(C, device=DEV) >= counts[:, :, None]
     nan = lambda *s: torch.full(s, float("nan"), device=DEV)      # noqa: E731
-    Z, A, Y, dX, dW1, dW2 = nan(n_src, G, C, H), nan(n_src, G, C, H), nan(n_src, G, C, M), nan(n_src, G, C, M), nan(G, M, H), nan(G, H, M)
-    nbytes = api.moe_ffn_workspace_bytes(api.MOE_F32, n_src, G, C, M, H, 1)
+    Z, A, Y, dX, dW1, dW2 = nan(n_src, G, C, H), nan(n_src, G, C, H), nan(n_src, G, C, M), nan(n_src, G, C, M), nan(G, M, full), nan(G, full, M)
+    nbytes = api.moe_ffn_workspace_bytes(api.MOE_F32, n_src, G, C, M, full, n_esp)
     ws = torch.full((nbytes,), 255, dtype=torch.uint8, device=DEV)
     if gather:
         S, k = G * C, 2
@@ -37,14 +50,14 @@ def run(n_src, G, C, M, H, occ, gather):
         inv[:, ::7] = -1
         X = torch.where(inv[..., None] >= 0, x[inv.clamp(min=0) // k], 0)[None]
         dY[(inv < 0)[None]] = 0
-        api.moe_expert_ffn_fwd_gather(x, inv, S, k, W1, W2, G, C, M, H, 0, 1, Z, A, Y, counts)
-        api.moe_expert_ffn_bwd_gather(dY, x, inv, S, k, Z, A, W1, W2, G, C, M, H, 0, 1, dX, dW1, dW2, ws, counts)
+        api.moe_expert_ffn_fwd_gather(x, inv, S, k, W1, W2, G, C, M, full, esp_idx, n_esp, Z, A, Y, counts)
+        api.moe_expert_ffn_bwd_gather(dY, x, inv, S, k, Z, A, W1, W2, G, C, M, full, esp_idx, n_esp, dX, dW1, dW2, ws, counts)
     else:
         X = rn(n_src, G, C, M)
         X[pad] = 0
         dY[pad] = 0
-        api.moe_expert_ffn_fwd(X, W1, W2, n_src, G, C, M, H, 0, 1, Z, A, Y, counts)
-        api.moe_expert_ffn_bwd(dY, X, Z, A, W1, W2, n_src, G, C, M, H, 0, 1, dX, dW1, dW2, ws, counts)
+        api.moe_expert_ffn_fwd(X, W1, W2, n_src, G, C, M, full, esp_idx, n_esp, Z, A, Y, counts)
+        api.moe_expert_ffn_bwd(dY, X, Z, A, W1, W2, n_src, G, C, M, full, esp_idx, n_esp, dX, dW1, dW2, ws, counts)
     torch.cuda.synchronize()
     dZ = ws[:n_src * G * C * H * 4].view(torch.float32).view(n_src, G, C, H).clone()
     dZ[pad] = 0                                                    # (not written, not read)
@@ -52,9 +65,15 @@ def run(n_src, G, C, M, H, occ, gather):
         assert not bool(t[pad].any())
     rows = lambda t, e: t[:, e].reshape(n_src * C, -1)             # noqa: E731
     for e in range(G):
-        close(rows(Z, e), rows(X, e), W1[e], "Z"), close(rows(Y, e), rows(A, e), W2[e], "Y")
-        close(dW2[e], rows(A, e).T, rows(dY, e), "dW2"), close(dW1[e], rows(X, e).T, rows(dZ, e), "dW1")
-        close(rows(dX, e), rows(dZ, e), W1[e].T, "dX")
+        w1, w2 = W1[e][:, h], W2[e][h]
+        close(rows(Z, e), rows(X, e), w1, "Z"), close(rows(Y, e), rows(A, e), w2, "Y")
+        dA, size = rows(dY, e).double() @ w2.double().T, rows(dY, e).double().abs() @ w2.double().abs().T
+        close_gelu(rows(Z, e), rows(A, e), dA, (M + 2) * 2.0 ** -53 * size, rows(dZ, e))
+        close(dW2[e][h], rows(A, e).T, rows(dY, e), "dW2"), close(dW1[e][:, h], rows(X, e).T, rows(dZ, e), "dW1")
+        close(rows(dX, e), rows(dZ, e), w1.T, "dX")
+    if n_esp > 1:                                                  # the other shards' gradients are not touched
+        dW1[:, :, h], dW2[:, h] = float("nan"), float("nan")
+        assert bool(dW1.isnan().all()) and bool(dW2.isnan().all())
 
 
 @pytest.mark.parametrize("n_src,G,C,M,H,occ", [
@@ -74,3 +93,11 @@ def test_products(n_src, G, C, M, H, occ, gather):
 
 def test_leading_dimension_beyond_32_bit_offsets():
     run(1, 1, 3, 1 << 24, 8, [2], False)
+
+
+# a shard's columns of W1 and rows of W2, in 32 x 32 tiles and, ragged, in 64 x 64 ones (Z and the gradients; Y as well)
+@pytest.mark.parametrize("n_src,G,C,M,H,occ,n_esp,esp_idx", [
+    (2, 3, 40, 72, 144, [40, 7, 0], 2, 0), (1, 8, 64, 72, 2 * 6208, None, 2, 1), (1, 16, 256, 760, 3 * 712, [256, 200, 0, 31] * 4, 3, 1),
+])
+def test_shards(n_src, G, C, M, H, occ, n_esp, esp_idx):
+    run(n_src, G, C, M, H, occ, False, n_esp, esp_idx)
