@@ -969,10 +969,17 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     };
     // Up to 16 experts.  What the 16 x 16 tiles cost does not depend on how many of the 16 columns are experts: 8192 x 1024 17 us (the
     // call), 16384 x 4096 61, fp32 29 at 16384 x 1024.  The others are faster
-    // - with few tokens for their M, where the walk along M is the time (split): 8 experts, 512 x 1024 13.5 and 14.0, 4096 x 4096 20 and
-    //   23, but 2048 x 1024 15.7 and 14.3;
-    // - with many tokens in bf16, where 8 or 4 columns are not multiplied (mfma4): 8 experts, 8192 x 1024 18.3 and 17.4, 16384 x 1024
-    //   19 and 24, 32768 x 4096 69 and 114; 2 experts, 8192 x 1024 14 and 16; but 16 experts, 32768 x 4096 126 and 114.
+    // - with many tokens in bf16, where 8 or 4 columns are not multiplied (mfma4): 8 experts, 8192 x 1024 17.7 and 15.2, 9000 x 1024 18.0 and
+    //   19.1, 14000 x 2048 27.8 and 36.1, 32768 x 4096 69 and 114, but 14000 x 256 14.1 and 12.7; 4 experts, 7000 x 2048 19.7 and 22.2, 8192 x 2048
+    //   19.8 and 22.4; but 16 experts, 32768 x 4096 126 and 114;
+    // - with few tokens for their M, where the walk along M is the time (split): it goes by its blocks per compute unit.
+    // Up to 8 experts a block has 4 tokens or, from 1024 on, 8, and 2048 / blocks waves.  Split and 16 x 16 tiles, 8 experts, bf16 where not said:
+    //   up to 1024 tokens 512 x 1024 13.5 and 14.0, 1000 x 512 7.7 and 8.1;
+    //   one block a compute unit (2048 tokens): 2000 x 1024 11.4 and 9.9, x 1536 12.0 and 11.7, x 2048 11.7 and 13.1, x 4096 13.7 and 21.0;
+    //   some one and some two: 2500 x 2048 18.6 and 13.6, x 4096 23.1 and 21.4;
+    //   two (4096): 4096 x 1536 12.8 and 12.3, x 2048 13.6 and 14.4, x 4096 17.7 and 21.6, fp32 x 2048 16.5 and 15.3, x 4096 24.2 and 24.6;
+    //   two waves a block: 6000 x 1024 13.8 and 14.3, 5000 x 1536 15.4 and 17.3, 8000 x 2048 19.9 and 22.7, x 4096 26.8 and 35.1; fp32 5000 x 2048
+    //     26.5 and 22.6, 6000 x 2048 21.9 and 22.8, 5000 x 4096 35.6 and 36.4.
     // From 9 experts on split's time goes by its blocks, of 2 tokens or, from 1024 on, 4, per compute unit, split and 16 x 16 tiles:
     //   one (512 tokens): 16 experts, 300 x 1024 11.5 and 10.0, 16 x 1536 10.7 and 11.0, 512 x 2048 13.6 and 13.3, 512 x 4096 18.4 and 20.1; 12,
     //     64 x 1024 9.8 and 9.5, 64 x 1536 10.1 and 11.3; 9, 64 x 520 8.7 and 8.2, 64 x 1024 9.5 and 9.5, fp32 9.6 and 10.0, 512 x 2048 11.2
@@ -984,12 +991,10 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     //     2000 x 4096, 14 18.9 and 21.6; 2000 x 2048, 9 14.3 and 13.6;
     //   more: 3000 x 4096, 9 23.5 and 22.0, 3000 x 8192, 12 40 and 36.
     const bool rows32 = (uint64_t)S * (uint64_t)M * 2 <= 0xFFFFFFF0ull;
-    const int64_t m2 = (int64_t)M * M;
-    const bool split = E <= 8       ? S < std::max<int64_t>(1024, m2 / 2048) && S < 8192
-                       : S <= 512   ? M > 90 * E
-                       : S < 1024   ? E <= 12 && M >= 341 * E
-                                    : S > 1640 && S <= 2048 && E <= 14 && M >= 3072;
-    if (bf && E <= 8 && S >= (E <= 4 ? 8192 : 16384) && rows32) {
+    bool split;
+    if (E <= 8) split = S < 1024 || (S <= 2048 ? M >= 2048 : S <= 3400 ? false : S <= 4096 ? M >= (bf ? 2048 : 3072) : S < 8192 && M >= (bf || S > 5400 ? 1536 : 3072));
+    else split = S <= 512 ? M > 90 * E : S < 1024 ? E <= 12 && M >= 341 * E : S > 1640 && S <= 2048 && E <= 14 && M >= 3072;
+    if (bf && E <= 8 && rows32 && (E <= 4 ? S >= 8192 : M >= 512 ? S > 8192 : S >= 16384)) {
       // fp64 matrix cores; TW token waves (32 tokens each) per block so that the grid has about two blocks per
       // compute unit or more
       const int tw = S >= 512 * 4 * 32 ? 4 : S >= 512 * 2 * 32 ? 2 : 1;

@@ -30,6 +30,8 @@ def gate(x, Wg, bias, k=1, C=None, norm=0, everything=False):
     (1, 8, 1), (1023, 1024, 8), (1024, 1024, 8), (2049, 264, 3), (511, 520, 12), (513, 520, 12), (1003, 520, 16), (8191, 2048, 16),
     (1, 1440, 16), (1, 1448, 16), (512, 1176, 13), (513, 2048, 16), (1023, 4096, 12), (1000, 3072, 9), (1000, 3072, 10), (1640, 3072, 14), (1641, 3080, 14),
     (2048, 3072, 9), (2049, 3072, 9),
+    (2048, 2048, 8), (2049, 2048, 8), (3400, 2056, 5), (3401, 2056, 5), (4096, 2048, 2), (4097, 1536, 7), (5400, 1544, 3), (5401, 1544, 3), (8191, 1536, 1),
+    (8192, 512, 8), (8193, 512, 8), (8193, 504, 8), (8200, 1032, 5),
     (8192, 136, 4), (8193, 40, 5), (16383, 72, 8), (16384, 72, 8), (16390, 1032, 9), (40000, 24, 16),
     (15, 64, 17), (17, 200, 33), (64, 2056, 256), (300, 8, 65), (8192, 96, 64), (8193, 40, 64), (8200, 264, 17), (16384, 24, 64),
     (4160, 104, 256), (17000, 8, 20), (16400, 232, 130),
