@@ -953,14 +953,16 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     const void* xs = (const char*)x + (size_t)mp_idx * S * M * esz;
     TopK tk{0, norm, idx, w};
     // Up to 16 experts and three choices the logits kernels select the experts as well (a thread per token, whose rounds are a chain), and
-    // gate_slots counts the choices.  The call, three launches and two: 2048 x 768, 16 experts, top-2, 12.9 and 11.3 us; 4096 x 1024,
-    // 8, top-2, 13.6 and 12.4; 6000 x 512, 16, top-2 (12000 choices) 13.0 and 13.0; 2000 x 512, 12, top-4, 12.0 and 12.6.  Up to 256
+    // gate_slots counts the choices, 2048 of them in a step of each block.  The call, three launches and two: 2048 x 768, 16 experts, top-2, 12.9
+    // and 11.3 us; 4096 x 1024, 8, top-2, 13.6 and 12.4; x 256, three steps: 6000 choices, 2, top-1 8.9 and 9.3, 4, top-2 9.2 and 8.1, 8, top-3 9.4
+    // and 9.2, 16, top-1 10.6 and 9.5; four steps: 8000, 2, top-1 9.1 and 10.3, top-2 9.2 and 9.0, 8, top-2 9.3 and 9.3, top-3 9.5 and 10.4, 12, top-1 11.0 and 10.6,
+    // top-3 10.5 and 10.9, 16, top-2 9.9 and 9.8; 2000 x 512, 12, top-4, 12.0 and 12.6.  Up to 256
     // tokens gate_topk assigns the slots as well, two launches either way, and its one block is the faster for few tokens of few experts:
     // 256 x 64, 2, top-1 5.8 and 6.4, 4, top-1 6.1 and 6.4, 4, top-3 7.4 and 7.5 (257 x 64, 4, top-1 10.6 and 6.4); 65 x 64, 8, top-1 6.2
     // and 6.4, top-2 6.6 and 6.6; 100 x 64, 8, top-2 6.9 and 6.6; 65 x 64, 16, top-3 8.7 and 9.0; 100 x 64, 12, top-1 7.3 and 7.5, 16,
     // top-2 7.8 and 7.7; 128 x 64, 16, top-2 7.9 and 7.75; 160 x 1024, 12, top-2 10.5 and 10.3.
     const int64_t one_block = E <= 4 ? 256 : E <= 8 ? 64 : 112;
-    if (E <= 16 && k <= TOPK_MAX && S > one_block && S * k <= 8192) tk.k = k;
+    if (E <= 16 && k <= TOPK_MAX && S > one_block && S * k <= (k == 2 || (k == 1 && E >= 8) ? 8192 : 6144)) tk.k = k;
     auto launch_few = [&]() {
       selected = tk.k != 0;
       const dim3 grid((unsigned)((S + 15) / 16), (unsigned)((E + 15) / 16)), block(64 * std::min(LF_NW, (M + LM_KC - 1) / LM_KC));
@@ -979,7 +981,7 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     //   some one and some two: 2500 x 2048 18.6 and 13.6, x 4096 23.1 and 21.4;
     //   two (4096): 4096 x 1536 12.8 and 12.3, x 2048 13.6 and 14.4, x 4096 17.7 and 21.6, fp32 x 2048 16.5 and 15.3, x 4096 24.2 and 24.6;
     //   two waves a block: 6000 x 1024 13.8 and 14.3, 5000 x 1536 15.4 and 17.3, 8000 x 2048 19.9 and 22.7, x 4096 26.8 and 35.1; fp32 5000 x 2048
-    //     26.5 and 22.6, 6000 x 2048 21.9 and 22.8, 5000 x 4096 35.6 and 36.4.
+    //     26.5 and 22.6, 6000 x 2048 21.9 and 22.8, 8000 x 2048 25.8 and 24.7, 5000 x 4096 35.6 and 36.4.
     // From 9 experts on split's time goes by its blocks, of 2 tokens or, from 1024 on, 4, per compute unit, split and 16 x 16 tiles:
     //   one (512 tokens): 16 experts, 300 x 1024 11.5 and 10.0, 16 x 1536 10.7 and 11.0, 512 x 2048 13.6 and 13.3, 512 x 4096 18.4 and 20.1; 12,
     //     64 x 1024 9.8 and 9.5, 64 x 1536 10.1 and 11.3; 9, 64 x 520 8.7 and 8.2, 64 x 1024 9.5 and 9.5, fp32 9.6 and 10.0, 512 x 2048 11.2
@@ -992,7 +994,7 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     //   more: 3000 x 4096, 9 23.5 and 22.0, 3000 x 8192, 12 40 and 36.
     const bool rows32 = (uint64_t)S * (uint64_t)M * 2 <= 0xFFFFFFF0ull;
     bool split;
-    if (E <= 8) split = S < 1024 || (S <= 2048 ? M >= 2048 : S <= 3400 ? false : S <= 4096 ? M >= (bf ? 2048 : 3072) : S < 8192 && M >= (bf || S > 5400 ? 1536 : 3072));
+    if (E <= 8) split = S < 1024 || (S <= 2048 ? M >= 2048 : S <= 3400 ? false : S <= 4096 ? M >= (bf ? 2048 : 3072) : S < 8192 && M >= (bf || (S > 5400 && S <= 7000) ? 1536 : 3072));
     else split = S <= 512 ? M > 90 * E : S < 1024 ? E <= 12 && M >= 341 * E : S > 1640 && S <= 2048 && E <= 14 && M >= 3072;
     if (bf && E <= 8 && rows32 && (E <= 4 ? S >= 8192 : M >= 512 ? S > 8192 : S >= 16384)) {
       // fp64 matrix cores; TW token waves (32 tokens each) per block so that the grid has about two blocks per

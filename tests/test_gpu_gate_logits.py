@@ -30,7 +30,7 @@ def gate(x, Wg, bias, k=1, C=None, norm=0, everything=False):
     (1, 8, 1), (1023, 1024, 8), (1024, 1024, 8), (2049, 264, 3), (511, 520, 12), (513, 520, 12), (1003, 520, 16), (8191, 2048, 16),
     (1, 1440, 16), (1, 1448, 16), (512, 1176, 13), (513, 2048, 16), (1023, 4096, 12), (1000, 3072, 9), (1000, 3072, 10), (1640, 3072, 14), (1641, 3080, 14),
     (2048, 3072, 9), (2049, 3072, 9),
-    (2048, 2048, 8), (2049, 2048, 8), (3400, 2056, 5), (3401, 2056, 5), (4096, 2048, 2), (4097, 1536, 7), (5400, 1544, 3), (5401, 1544, 3), (8191, 1536, 1),
+    (2048, 2048, 8), (2049, 2048, 8), (3400, 2056, 5), (3401, 2056, 5), (4096, 2048, 2), (4097, 1536, 7), (5400, 1544, 3), (5401, 1544, 3), (7000, 1536, 4), (7001, 1536, 4), (8191, 3072, 1),
     (8192, 512, 8), (8193, 512, 8), (8193, 504, 8), (8200, 1032, 5),
     (8192, 136, 4), (8193, 40, 5), (16383, 72, 8), (16384, 72, 8), (16390, 1032, 9), (40000, 24, 16),
     (15, 64, 17), (17, 200, 33), (64, 2056, 256), (300, 8, 65), (8192, 96, 64), (8193, 40, 64), (8200, 264, 17), (16384, 24, 64),
@@ -68,11 +68,12 @@ def test_non_finite_values_stay_in_their_row_and_column(S, M, E):
     assert not bool(torch.isfinite(got[~rows]).any()) and not bool(torch.isfinite(got[:, E - 1]).any())
 
 
-# the experts selected by the logits kernel (up to 16 experts, k <= 3, S k <= 8192), and one step beyond each line; ties by equal columns
+# the experts selected by the logits kernel (up to 16 experts, k <= 3, S k <= 6144 or 8192), and one step beyond each line; ties by equal columns
 @pytest.mark.parametrize("S,M,E,k,C,norm", [
     (1, 8, 1, 1, 1, 0), (63, 64, 16, 3, 5, 1), (65, 2048, 8, 2, 9, 0), (257, 40, 3, 3, 200, 1), (1023, 520, 12, 3, 250, 1),
     (2049, 72, 16, 2, 300, 0), (2730, 64, 9, 3, 1000, 1), (2731, 64, 9, 3, 900, 0), (4096, 1024, 8, 2, 1100, 1), (4097, 64, 8, 2, 1000, 1),
     (8191, 24, 2, 1, 4000, 0), (8192, 136, 12, 1, 600, 0), (300, 64, 16, 4, 70, 1),
+    (6144, 24, 5, 1, 900, 0), (6145, 24, 5, 1, 900, 0), (2048, 64, 9, 3, 700, 1), (2049, 64, 9, 3, 700, 1), (4096, 24, 9, 2, 900, 1),
     # as many tokens as gate_topk's one block is left with, and one more
     (256, 64, 4, 1, 70, 0), (257, 64, 4, 2, 100, 1), (64, 64, 8, 1, 9, 0), (65, 64, 5, 3, 20, 0), (112, 72, 9, 3, 30, 1), (113, 72, 9, 3, 30, 1),
 ])
