@@ -1766,9 +1766,24 @@ int plan_f32(const GemmArgs& a) {   // of a row-tiled GEMM
   const int64_t rows = priced_rows(a, false), rows64 = (rows + 63) / 64 * 64, rows32 = (rows + 31) / 32 * 32;
   return tiles_f32(a, false, 64) >= 3 * (int64_t)num_cus() && 8 * rows64 <= 9 * rows32 ? 64 : 32;
 }
-int plan_f32_trio(const GemmArgs& dx, const GemmArgs& w2, const GemmArgs& w1) {   // of the merged backward launch
+// Of the merged backward launch, whose reductions differ in length: where the longest, a chain of k chunks in one workgroup, has more
+// of them than a compute unit's share of all, the launch waits for it, and the chunks of 32 x 32 tiles are half as long.  Backward call
+// in tiles of 64 and of 32 (tiles of 64; chunks: the chain, a compute unit's share): 4 experts of 11 x 104 x 3032 (776; 95, 5) 137 and 75 us, 8 of
+// 30 x 144 x 8040 (6072; 252, 47) 356 and 166, 2 of 41 x 1160 x 1392 (1710; 44, 20) 90 and 64, 4 of 71 x 704 x 864 (1320; 27, 24) 69 and 62, 4 of
+// 93 x 768 x 4944 (7584; 155, 146) 309 and 276; 8 of 12 x 1024 x 704 (2944; 22, 22) 58 and 69, 4 of 55 x 1432 x 3432 (10028; 108, 116) 246 and
+// 275, 16 of 32 x 576 x 2504 (11664; 79, 89) 177 and 218, 8 of 62 x 1024 x 808 (3456; 26, 39) 85 and 104; but 4 of 643 x 152 x 3376 (1404; 106, 159)
+// 283 and 238.
+int plan_f32_trio(const GemmArgs& dx, const GemmArgs& w2, const GemmArgs& w1) {
   if (wide_f32(dx) || wide_f32(w2) || wide_f32(w1)) return 32;
-  return tiles_f32(dx, false, 64) + tiles_f32(w2, true, 64) + tiles_f32(w1, true, 64) >= 3 * (int64_t)num_cus() ? 64 : 32;
+  int64_t tiles = 0, work = 0, chain = 0;
+  auto add = [&](const GemmArgs& a, bool tn) {
+    const int64_t n = tiles_f32(a, tn, 64), chunks = (a.Kdim + FK - 1) / FK;
+    tiles += n;
+    work += n * chunks;
+    chain = std::max(chain, chunks);
+  };
+  add(dx, false); add(w2, true); add(w1, true);
+  return tiles >= 3 * (int64_t)num_cus() && chain * num_cus() <= work ? 64 : 32;
 }
 void prepare_f32(GemmArgs& a, bool tn, int tile) {
   a.tiles_m = (a.Mdim + tile - 1) / tile;

@@ -186,9 +186,14 @@ def test_executed_flops_accounting(L):
     # leading dimensions of 2^24 and more: 32-row tiles in the GEMMs that have one as lda or ldb, whatever their count
     wide, C_ = 1 << 24, 64
     n = np.ones((1, 1), np.int32)
-    for M_, H_, fwd, bwd in ((64, wide, 32 + 32, 64 + 32), (wide, 64, 32 + 32, 32 + 32), (64, wide - 8, 64 + 32, 64 + 64)):
+    for M_, H_, fwd, bwd in ((64, wide, 32 + 32, 64 + 32), (wide, 64, 32 + 32, 32 + 32), (64, wide - 8, 64 + 32, 64 + 32)):
         assert f(api.MOE_F32, 1, 1, C_, M_, H_, 1, n) == 2.0 * fwd * M_ * H_, (M_, H_)        # Z, Y
         assert f(api.MOE_F32, 1, 1, C_, M_, H_, 1, n, True) == 2.0 * (bwd + 2) * M_ * H_, (M_, H_)      # dA, dX, and a row in dW1, dW2
+    # the merged fp32 backward launch: 32-row tiles in dX where its reduction, or the weight gradients', is longer than a compute unit's share
+    for C_, M_, H_, rows in ((11, 104, 3032, 32), (512, 2048, 2048, 64), (64000, 64, 64, 32)):
+        bwd = f(api.MOE_F32, 1, 4, C_, M_, H_, 1, np.ones((1, 4), np.int32), True)
+        dA = f(api.MOE_F32, 1, 4, C_, M_, H_, 1, np.ones((1, 4), np.int32)) / 2 if M_ == H_ else 2.0 * 4 * min(C_, 32) * M_ * H_
+        assert bwd - dA - 2 * (2.0 * 4 * M_ * H_) == 2.0 * 4 * min(C_, rows) * M_ * H_, (C_, M_, H_)
     # dX in the merged backward launch, which has no tiles of 64 columns, takes 64 rows; alone, as A W2 does, it would take 32
     assert f(api.MOE_BF16, n_src, G, 64, M, H, 1, one) == 2.0 * G * (64 + 32) * M * H
     assert f(api.MOE_BF16, n_src, G, 64, M, H, 1, one, True) == 2.0 * G * (64 + 64 + 2) * M * H

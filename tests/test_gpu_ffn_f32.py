@@ -81,8 +81,10 @@ def run(n_src, G, C, M, H, occ, gather, n_esp=1, esp_idx=0):
     (3, 2, 50, 104, 64, [17, 50]), (1, 2, 97, 96, 136, [97, 33]), (70, 1, 9, 64, 40, [5]),
     # enough tiles for 64 x 64: whole and ragged rows and columns, odd and even numbers of chunks
     (1, 8, 64, 72, 6208, None), (1, 5, 300, 2056, 2088, [300, 257, 64, 0, 130]), (2, 4, 400, 1024, 264, [400, 1, 333, 64]),
-    # 64 x 64: one, two and three chunks of k; weight gradients over none to four
+    # 64 x 64: one, two and three chunks of k, in Z and in dX; weight gradients over none to four; backward in 32 x 32 for a long dX or dW
     (1, 8, 128, 32, 3200, [128, 0, 20, 33, 64, 65, 96, 97]), (1, 8, 128, 64, 3168, None), (1, 8, 128, 96, 3104, [128] * 7 + [1]),
+    (1, 8, 128, 3200, 32, [128, 0, 20, 33, 64, 65, 96, 97]), (1, 8, 128, 3168, 64, None), (1, 8, 128, 3104, 96, [1] + [128] * 7),
+    (1, 8, 128, 520, 520, [128, 0, 20, 33, 64, 65, 96, 97]), (1, 2, 25000, 40, 72, [25000, 24999]),
 ])
 @pytest.mark.parametrize("gather", [False, True])
 def test_products(n_src, G, C, M, H, occ, gather):
