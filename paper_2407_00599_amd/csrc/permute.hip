@@ -426,10 +426,11 @@ extern "C" int moe_combine_bwd(const void* dy, const void* Yret, int dtype, int 
   const int64_t ps = rows * M;
   const dim3 block(256), grid_r((unsigned)((rows + 3) / 4)), grid_t((unsigned)((S + 3) / 4));
   const bool bf = dtype == MOE_BF16;
-  // Rows by token or by slot, the call in bf16: 512 tokens top-2 of 1024 rows x 64 2.89 and 2.76 us, x 4096 6.4 and 6.5; 768 of 1536, 2.88 and 2.79,
-  // 7.4 and 8.5; 427 top-8 of 4096 x 520 7.5 and 6.8; 853 top-4 of 4096 x 2048 9.2 and 11.0; 853 top-1 of 1024 x 520 2.80 and 2.61, 1706 of
-  // 2048 2.97 and 2.93; fp32, 128 tokens top-2 of 320 rows x 2048 5.3 and 3.6.
-  const bool by_slot = S <= (k == 1 ? 1024 : 512);
+  // Rows by token or by slot, the call in bf16: 256 tokens x 512, top-2 2.80 and 2.69 us, top-8 5.45 and 5.24; 256 x 2048, top-4 5.31 and 5.26,
+  // top-2, two parts, 4.54 and 4.39; 481 x 1344, top-2 3.48 and 3.48, fp32 5.2 and 5.6, top-4 5.4 and 6.2; 481 top-1, two parts, x 1344 3.14 and
+  // 2.94, x 3456 5.4 and 6.2; 1024 x 2048, top-2 4.95 and 5.5; top-1, one part, 1024 x 2048 3.7 and 3.3, 2000 x 2048 5.05 and 5.3; fp32, 128 x
+  // 2048, top-2 4.9 and 3.7.
+  const bool by_slot = S <= (k == 1 && n_part == 1 ? 1024 : 384);
   // Slots that a wave looks through for empty ones.  Many cost fewer waves but are a chain that the call waits for, the longer the wider
   // the rows: with 2, 4 and 8 of them 820 tokens top-2 of 2048 rows x 4096 bf16 8.4, 9.9 and 11.1 us, x 64 2.86, 2.77 and 2.74; with 4, 8 and 64
   // 1640 of 4096 x 2048 7.6, 9.2; 4915 of 12288 x 2048 18.0, 17.9; fp32, 3277 of 8192 x 2048 28.9, 32.3; bf16, 12288 of 30720 x 2048 36.3 with 8 and

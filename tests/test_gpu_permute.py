@@ -89,10 +89,10 @@ def test_combine_bwd_empty_slots(S, M, E, k, C):
     assert np.all(got[inv < 0] == 0.0) and rel_err(got, rdY) <= 4e-3 and rel_err(to_host(dw), rdw) <= 2e-6 * np.sqrt(M)
 
 
-# every number of choices and parts on both sides of the line between rows by slot (up to 512 tokens, 1024 top-1) and by token, and with 2, 4, 8
+# every number of choices and parts on both sides of the line between rows by slot (up to 384 tokens, 1024 top-1 with one part) and by token, and with 2, 4, 8
 # and 64 slots to a wave that looks for empty ones
 @pytest.mark.parametrize("S,M,E,k,C", [
-    (1024, 264, 5, 1, 300), (1025, 264, 5, 1, 300), (512, 2056, 8, 2, 133), (513, 2056, 8, 2, 133), (514, 1032, 8, 2, 383), (520, 72, 9, 3, 300),
+    (384, 264, 8, 2, 110), (385, 264, 8, 2, 110), (390, 72, 33, 4, 60), (1024, 264, 5, 1, 300), (1025, 264, 5, 1, 300), (512, 2056, 8, 2, 133), (513, 2056, 8, 2, 133), (514, 1032, 8, 2, 383), (520, 72, 9, 3, 300),
     (600, 40, 33, 4, 150), (515, 520, 16, 8, 257), (513, 520, 64, 6, 191), (513, 24, 64, 6, 513), (700, 512, 32, 2, 385),
 ])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
