@@ -301,15 +301,16 @@ __global__ __launch_bounds__(64 * FW, EC > 8 ? 2 : BF16 ? 4 : 3) void gate_bwd_f
           }
         }
       } else {
-        // three values requested together (behind the end the last one again): 2000 x 2048, fp32, 6 experts 19.8 -> 19.3 us; 8192 x 4096, 13
-        // 118 -> 114, fp32 150 -> 136
+        // NS values requested together (behind the end the last one again): 2000 x 2048, fp32, 6 experts 19.8 -> 19.3 us; 8192 x 4096, 13 118 ->
+        // 114, fp32 150 -> 136.  Two in bf16 with up to 8 experts, whose code for whole fours, beside this, takes 1 % longer with three.
+        constexpr int NS = BF16 && EC == 8 ? 2 : 3;
 #pragma unroll 1
-        for (int i0 = tid; i0 < ms * E; i0 += 3 * NTHR) {
-          float v[3];
+        for (int i0 = tid; i0 < ms * E; i0 += NS * NTHR) {
+          float v[NS];
 #pragma unroll
-          for (int u = 0; u < 3; ++u) v[u] = slab[min(i0 + u * NTHR, ms * E - 1)];
+          for (int u = 0; u < NS; ++u) v[u] = slab[min(i0 + u * NTHR, ms * E - 1)];
 #pragma unroll
-          for (int u = 0; u < 3; ++u) {
+          for (int u = 0; u < NS; ++u) {
             const int i = min(i0 + u * NTHR, ms * E - 1), m = (int)((uint32_t)i * inv_e >> 16);
             outs[(i - m * E) * PITCH + m] = v[u];
           }

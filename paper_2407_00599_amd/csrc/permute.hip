@@ -438,7 +438,7 @@ extern "C" int moe_combine_bwd(const void* dy, const void* Yret, int dtype, int 
   // 65536 x 2048, a fifth of them empty, takes 90.8 and 100.
   const int64_t row_bytes = (int64_t)M * (bf ? 2 : 4);
   const int zero_slots = rows >= 32768 ? 64
-                         : rows >= (row_bytes <= 1024 ? 4096 : bf ? 8192 : 12288) ? 8
+                         : rows >= (row_bytes < 2048 ? 2048 : bf ? 8192 : 12288) ? 8
                          : rows < 3072 && row_bytes >= 4096 ? 2 : 4;
   const int64_t nb_rows = !dYret ? 0 : by_slot ? (int64_t)grid_r.x : (rows + 4 * zero_slots - 1) / (4 * zero_slots);
   const dim3 grid_b((unsigned)(nb_rows + grid_t.x));
