@@ -8,8 +8,8 @@
 //   gate_logits_mfma    : E > 16, many tokens.  64 tokens x 64 experts per block.
 //   gate_topk           : W lanes per token, k arg-max rounds (ties -> lower expert index); softmax weights;
 //                         per-block (choice, expert) histogram for the slot scan.  With a single token block it
-//                         assigns the slots as well.
-//                         (Up to 16 experts and three choices of few tokens, though not the fewest, the logits kernels do this.)
+//                         assigns the slots as well.  (The logits kernels for up to 16 experts select them
+//                         themselves, up to three choices of a few hundred to a few thousand tokens.)
 //   gate_scan           : one wave per expert; exclusive scan of the histograms over token blocks and
 //                         over choices (choice-major priority), per-expert demand counts.
 //   gate_slots          : rank of each (token, choice) inside its block via wave ballots,
@@ -80,8 +80,8 @@ __device__ __forceinline__ void pick_experts(const float (&v)[EPL], int E, int k
 // read from L2 (with E = EC as 16-byte pieces) and converted once for the T tokens; the waves' sums are added through
 // LDS.  Pieces of 4 m per lane need fewer requests, but a request then touches twice the lines, which several waves'
 // requests push out of L1 before their other halves are read.  256 tokens x 4096, 8 experts: 13 us, where a walk in
-// chunks staged through LDS with a barrier each took 49; 4096 x 1024, 8 experts: 14 -> 10 us; 2048 x 768, 16
-// experts: 23 -> 10 us.
+// chunks staged through LDS with a barrier each took 49.  The 16 x 16 tiles took over many products that this kernel
+// had; against them, the call: 2000 x 4096, 8 experts 13.7 and 21.0 us; 700 x 4096, 9 experts 15.5 and 19.8.
 constexpr int LS_MAXW = 8;
 template <int EC, bool BF16, int T, bool FULL>   // FULL: E = EC
 __global__ __launch_bounds__(64 * LS_MAXW) void gate_logits_split(const void* __restrict__ x, const float* __restrict__ Wg,
@@ -954,10 +954,10 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     TopK tk{0, norm, idx, w};
     // Up to 16 experts and three choices the logits kernels select the experts as well (a thread per token, whose rounds are a chain), and
     // gate_slots counts the choices, 2048 of them in a step of each block.  The call, three launches and two: 2048 x 768, 16 experts, top-2, 12.9
-    // and 11.3 us; 4096 x 1024, 8, top-2, 13.6 and 12.4; x 256, three steps: 6000 choices, 2, top-1 8.9 and 9.3, 4, top-2 9.2 and 8.1, 8, top-3 9.4
-    // and 9.2, 16, top-1 10.6 and 9.5; four steps: 8000, 2, top-1 9.1 and 10.3, top-2 9.2 and 9.0, 8, top-2 9.3 and 9.3, top-3 9.5 and 10.4, 12, top-1 11.0 and 10.6,
-    // top-3 10.5 and 10.9, 16, top-2 9.9 and 9.8; 2000 x 512, 12, top-4, 12.0 and 12.6.  Up to 256
-    // tokens gate_topk assigns the slots as well, two launches either way, and its one block is the faster for few tokens of few experts:
+    // and 11.3 us; 4096 x 1024, 8, top-2, 13.6 and 12.4; x 256, three steps: 6000 choices, 2, top-1 8.9 and 9.3, 4, top-2 9.2 and 8.1, 8,
+    // top-3 9.4 and 9.2, 16, top-1 10.6 and 9.5; four steps: 8000, 2, top-1 9.1 and 10.3, top-2 9.2 and 9.0, 8, top-2 9.3 and 9.3, top-3 9.5
+    // and 10.4, 12, top-1 11.0 and 10.6, top-3 10.5 and 10.9, 16, top-2 9.9 and 9.8; 2000 x 512, 12, top-4, 12.0 and 12.6.  Up to 256 tokens
+    // gate_topk assigns the slots as well, two launches either way, and its one block is the faster for few tokens of few experts:
     // 256 x 64, 2, top-1 5.8 and 6.4, 4, top-1 6.1 and 6.4, 4, top-3 7.4 and 7.5 (257 x 64, 4, top-1 10.6 and 6.4); 65 x 64, 8, top-1 6.2
     // and 6.4, top-2 6.6 and 6.6; 100 x 64, 8, top-2 6.9 and 6.6; 65 x 64, 16, top-3 8.7 and 9.0; 100 x 64, 12, top-1 7.3 and 7.5, 16,
     // top-2 7.8 and 7.7; 128 x 64, 16, top-2 7.9 and 7.75; 160 x 1024, 12, top-2 10.5 and 10.3.
@@ -994,7 +994,10 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     //   more: 3000 x 4096, 9 23.5 and 22.0, 3000 x 8192, 12 40 and 36.
     const bool rows32 = (uint64_t)S * (uint64_t)M * 2 <= 0xFFFFFFF0ull;
     bool split;
-    if (E <= 8) split = S < 1024 || (S <= 2048 ? M >= 2048 : S <= 3400 ? false : S <= 4096 ? M >= (bf ? 2048 : 3072) : S < 8192 && M >= (bf || (S > 5400 && S <= 7000) ? 1536 : 3072));
+    if (E <= 8) {
+      const int least = S <= 2048 ? 2048 : S <= 4096 ? (bf ? 2048 : 3072) : bf || (S > 5400 && S <= 7000) ? 1536 : 3072;
+      split = S < 1024 || ((S <= 2048 || (S > 3400 && S < 8192)) && M >= least);
+    }
     else split = S <= 512 ? M > 90 * E : S < 1024 ? E <= 12 && M >= 341 * E : S > 1640 && S <= 2048 && E <= 14 && M >= 3072;
     if (bf && E <= 8 && rows32 && (E <= 4 ? S >= 8192 : M >= 512 ? S > 8192 : S >= 16384)) {
       // fp64 matrix cores; TW token waves (32 tokens each) per block so that the grid has about two blocks per

@@ -726,11 +726,15 @@ __global__ __launch_bounds__(SG_NT, 4) void gate_dx_sparse(const float* __restri
 // Rounding.  The entries of a tile are added in two fp32 chains of at most four, these in fp64, the chunk's sum is rounded.  In
 // units of the last place of one entry, the variance that an entry adds is then (n + 1) / 2 for chains of n, and 1; for the one
 // chain per expert and dwg_chunk tokens that all experts are summed in, with n entries in it, (n + 1) / 2 alone.  So these sums are
-// no farther off from n = 4 there, or from 6 where the tile is longer than that chunk.  Below that (EXACT) the products are added in
+// no farther off from n = 4 there, or from 6 where the tile is longer than that chunk; n is the average expert's, and columns of
+// the rarest ones under skewed routing are up to 1.3 times as far off (4e-8 and 3.5e-8).  Below that (EXACT) the products are added in
 // fp64, which costs a fifth of the kernel.  Relative error of dWg, all experts and this: 8192 x 2048, top-4 of 128 (n = 4) 5.1e-8
 // and 4.9e-8, top-4 of 24 9.1e-8 and 5.3e-8; 4096 x 512, top-2 of 160 3.9e-8 and, EXACT, 3.6e-8 (4.5e-8 in fp32 chains).
-// Bound by the chain of LDS reads (entry, row of x) per four entries and by the sort's barriers: 8192 x 2048, top-4 of 128, 31 us
-// where reading x takes 6, against 54 us on the fp32 matrix cores; 16384 x 2048, top-2 of 64, 35 against 61.
+// 8192 x 2048, top-4 of 128, 31 us where reading x takes 6, against 54 us on the fp32 matrix cores; 16384 x 2048, top-2 of 64, 35
+// against 61.  What the 31 us go into was not taken apart; in question are the chain of LDS reads (entry, row of x) per four entries,
+// the sort, which every column block does again with six barriers a tile, and the fetch of the code: the sums of all of a wave's
+// experts are in registers, so the loop over them is unrolled, 14 to 18 KB of it at EP = 64, 25 to 33 at 128, 46 to 59 at 256, walked
+// once a tile.  EP = 128 spills 8 to 14 loop invariants, reloaded once a tile.
 constexpr int SW_C = 128;
 template <bool BF16> constexpr int sw_tile() { return BF16 ? 128 : 64; }   // tokens
 template <bool BF16, int EP, bool EXACT>   // E <= EP
@@ -990,9 +994,12 @@ extern "C" int moe_gate_bwd(const float* dw, const float* w, const int32_t* idx,
     const dim3 gx((unsigned)(ncx * ((S + chunk_x - 1) / chunk_x))), gw((unsigned)ncw, (unsigned)parts);   // (runs of 256 tokens may be more than y holds)
     const bool exact = (int64_t)chunk * k < (tile_w > chunk ? 6 : 4) * E;   // see gate_dwg_sparse
 #define MOE_SPARSE(BF, EP) do { \
-    hipLaunchKernelGGL((gate_dx_sparse<BF, EP>), gx, dim3(SG_NT), 0, st, dw, w, idx, Wg, (int)S, M, E, k, dlogits, dx, dx_accumulate, (int)chunk_x, (int)ncx); \
-    if (exact) hipLaunchKernelGGL((gate_dwg_sparse<BF, EP, true>), gw, dim3(SG_NT), 0, st, dw, w, idx, x, (int)S, M, E, k, partial, (int)chunk_w); \
-    else hipLaunchKernelGGL((gate_dwg_sparse<BF, EP, false>), gw, dim3(SG_NT), 0, st, dw, w, idx, x, (int)S, M, E, k, partial, (int)chunk_w); } while (0)
+    hipLaunchKernelGGL((gate_dx_sparse<BF, EP>), gx, dim3(SG_NT), 0, st, dw, w, idx, Wg, (int)S, M, E, k, dlogits, dx, dx_accumulate, \
+                       (int)chunk_x, (int)ncx); \
+    if (exact) hipLaunchKernelGGL((gate_dwg_sparse<BF, EP, true>), gw, dim3(SG_NT), 0, st, dw, w, idx, x, (int)S, M, E, k, partial, \
+                                  (int)chunk_w); \
+    else hipLaunchKernelGGL((gate_dwg_sparse<BF, EP, false>), gw, dim3(SG_NT), 0, st, dw, w, idx, x, (int)S, M, E, k, partial, \
+                            (int)chunk_w); } while (0)
     if (bf) { if (E <= 64) MOE_SPARSE(true, 64); else if (E <= 128) MOE_SPARSE(true, 128); else MOE_SPARSE(true, 256); }
     else { if (E <= 64) MOE_SPARSE(false, 64); else if (E <= 128) MOE_SPARSE(false, 128); else MOE_SPARSE(false, 256); }
 #undef MOE_SPARSE
