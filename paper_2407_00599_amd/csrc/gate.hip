@@ -997,8 +997,9 @@ static int gate_topk_impl(const void* x, int x_dtype, const float* Wg, const flo
     if (E <= 8) {
       const int least = S <= 2048 ? 2048 : S <= 4096 ? (bf ? 2048 : 3072) : bf || (S > 5400 && S <= 7000) ? 1536 : 3072;
       split = S < 1024 || ((S <= 2048 || (S > 3400 && S < 8192)) && M >= least);
+    } else {
+      split = S <= 512 ? M > 90 * E : S < 1024 ? E <= 12 && M >= 341 * E : S > 1640 && S <= 2048 && E <= 14 && M >= 3072;
     }
-    else split = S <= 512 ? M > 90 * E : S < 1024 ? E <= 12 && M >= 341 * E : S > 1640 && S <= 2048 && E <= 14 && M >= 3072;
     if (bf && E <= 8 && rows32 && (E <= 4 ? S >= 8192 : M >= 512 ? S > 8192 : S >= 16384)) {
       // fp64 matrix cores; TW token waves (32 tokens each) per block so that the grid has about two blocks per
       // compute unit or more
